@@ -161,6 +161,17 @@ const char *check_config(const poss_config &c) {
 
 size_t esize(const poss_config &c) { return dtype_size(c.dtype); }
 
+// Rows that one pass over a prompt carries: LAUNCH_ROWS of the weight-streaming kernels, or, 16-bit types, up to PREFILL_ROWS
+// of the many-row kernels (a chunk of 4096 rows divides the 4096-column products of the 8B shape into 256 tiles of 256 x 256,
+// one per CU).  Operands stay below 4 GiB.
+int prefill_rows(const poss_config &c) {
+    if (c.dtype == POSS_DTYPE_F32 || c.max_seq <= LAUNCH_ROWS) return LAUNCH_ROWS;
+    const size_t widest = (size_t)(c.d_ffn > 2 * c.d_model ? c.d_ffn : 2 * c.d_model) + (size_t)c.n_q_heads * c.head_dim;
+    int rows = c.max_seq < PREFILL_ROWS ? round_up(c.max_seq, LAUNCH_ROWS) : PREFILL_ROWS;
+    while (rows > LAUNCH_ROWS && (size_t)rows * widest * 2 > 0xffffffffull) rows = round_up(rows / 2, LAUNCH_ROWS);
+    return rows;
+}
+
 // Lays every buffer out in the arena (measuring when it has no base) and, if ctx != nullptr,
 // records the addresses.  Weight destinations are returned through ctx as well.
 struct WeightSlots {
@@ -213,8 +224,9 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
         if (f > part_floats) part_floats = f;
     }
     const int QR = B * 16 < R ? B * 16 : R;                  // full rows of a draft pass: at most k <= 16 per sequence
-    float *h = a.take_n<float>((size_t)R * d);
-    float2 *cs = a.take_n<float2>((size_t)R * (c.head_dim / 2));
+    const int PR = prefill_rows(c);                          // rows of the passes over a prompt
+    float *h = a.take_n<float>((size_t)PR * d);
+    float2 *cs = a.take_n<float2>((size_t)PR * (c.head_dim / 2));
     float *part = a.take_n<float>(part_floats);
     float *logits = a.take_n<float>((size_t)R * gemm_npad(V));
     float *feats = a.take_n<float>((size_t)RA * d);
@@ -223,15 +235,15 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
     if (argmax_scratch_floats(R, V) > scr_floats) scr_floats = argmax_scratch_floats(R, V);
     if (sample_scratch_floats(R, V) > scr_floats) scr_floats = sample_scratch_floats(R, V);
     float *topk_scr = a.take_n<float>(scr_floats);      // shared by top-k (draft) and argmax (verify)
-    void *u = a.take((size_t)R * d * es), *xin = a.take((size_t)R * 2 * d * es);
-    void *q = a.take((size_t)R * qd * es), *ao = a.take((size_t)R * qd * es), *act = a.take((size_t)R * F * es);
+    void *u = a.take((size_t)PR * d * es), *xin = a.take((size_t)PR * 2 * d * es);
+    void *q = a.take((size_t)PR * qd * es), *ao = a.take((size_t)PR * qd * es), *act = a.take((size_t)PR * F * es);
     const int G = c.n_q_heads / c.n_kv_heads;
     const int rho_pad = round_up(R * G, 16) + 16 * 8;          // every sequence of a batch pads its row tiles
     const int max_splits = attention_splits(slots, 64);
     float *ao_part = a.take_n<float>((size_t)max_splits * c.n_kv_heads * rho_pad * c.head_dim);
     float *ml_part = a.take_n<float>((size_t)max_splits * c.n_kv_heads * rho_pad * 2);
-    int32_t *row_pos = a.take_n<int32_t>(R), *row_slot = a.take_n<int32_t>(R);
-    uint64_t *row_mask = a.take_n<uint64_t>((size_t)R * MASK_WORDS);
+    int32_t *row_pos = a.take_n<int32_t>(PR), *row_slot = a.take_n<int32_t>(PR);
+    uint64_t *row_mask = a.take_n<uint64_t>((size_t)PR * MASK_WORDS);
     // rows of the verification pass (sequence b owns rows [b * (total_tokens + 1), ...)) and of the top-k
     int32_t *token_all = a.take_n<int32_t>(RA), *pos_all = a.take_n<int32_t>(RA), *slot_all = a.take_n<int32_t>(RA);
     int32_t *depth_all = a.take_n<int32_t>(RA), *parent_all = a.take_n<int32_t>(RA);
@@ -421,8 +433,16 @@ void run_head_topk(poss_ctx *c, int rows, int depth) {
         launch_topk_logsoftmax(c->logits, g.Npad, rows, c->cfg.vocab, c->cfg.top_k, c->topk_scratch, c->topk_id_all, c->topk_logp_all, c->st);
 }
 
+// The next chunk of `left` rows of a prompt, at most `most` a pass: chunks of equal size, whole LAUNCH_ROWS.
+int prompt_chunk(int left, int most) {
+    if (left <= most) return left;
+    const int n = (left + most - 1) / most;
+    const int each = round_up((left + n - 1) / n, LAUNCH_ROWS);
+    return each < most ? each : most;
+}
+
 __global__ void causal_meta_kernel(int n, int c0, int32_t *pos, int32_t *slot, uint64_t *mask) {
-    const int i = threadIdx.x;
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     pos[i] = c0 + i; slot[i] = c0 + i;
     const int bits = i % MAX_ROWS + 1;                     // within the row's range of MAX_ROWS rows
@@ -482,9 +502,76 @@ void spec_pass(poss_ctx *c, int s, std::vector<SeqPlan> &plans, int depth_index,
     run_layer(c, w.layer, segs, rows_all, rows_q, rm, c->final_norm, fhat_out, true);
 }
 
-// Keys/values of committed pairs [spec_len[s], upto) of one sequence for specialist s, in chunks of MAX_ROWS rows.
+void run_block(poss_ctx *c, const void *Wp, int N, int K, int col0, const void *X, int M, const EpiArgs &e) {
+    if (!launch_gemm_block(c->md.dt, M, N, K, col0, Wp, X, K, e, c->st)) c->launch_refused = true;
+}
+
+EpiArgs epi_rope(poss_ctx *c, const KVCache &kv, int rows_q) {
+    EpiArgs e{};
+    e.mode = EPI_ROPE_KV; e.rows_q = rows_q; e.cs = c->cs; e.slot = c->row_slot; e.q = c->q; e.kv = kv;
+    e.hq = c->md.hq; e.hkv = c->md.hkv; e.dh = c->md.dh;
+    return e;
+}
+
+// More than LAUNCH_ROWS rows of a prompt, [c0, c0 + rows), through the target: the many-row kernels.  The rows' tokens are on
+// the device; their metadata is in c->row_*.  Features go to the sequence's stash, T(rmsnorm_final(features)) to c->u.
+void prefill_pass(poss_ctx *c, int b, int rows, int c0) {
+    const ModelDims &md = c->md;
+    Seq &sq = c->seq[b];
+    const int qd = md.hq * md.dh, kd = md.hkv * md.dh, nl = c->cfg.n_layers;
+    const size_t es = dtype_size(md.dt);
+    launch_embed_norm(md, c->embed, sq.tokens_dev + c0, rows, c->layers[0].attn_norm, c->h, c->u, c->row_pos, c->inv_freq, c->cs, c->st);
+    for (int l = 0; l < nl; ++l) {
+        const LayerW &w = c->layers[l];
+        run_block(c, w.wqkv, qd + 2 * kd, md.d, 0, c->u, rows, epi_rope(c, sq.target_kv[l], rows));
+        // ranges of MAX_ROWS rows (the width of a row's mask), two per launch: a range finds the keys of those before it,
+        // written by the launch above, in its committed prefix
+        for (int r = 0; r < rows; r += LAUNCH_ROWS) {
+            AttnSeg as[2];
+            int na = 0;
+            for (int r0 = 0; r0 < LAUNCH_ROWS && r + r0 < rows; r0 += MAX_ROWS) {
+                const int n = rows - r - r0 < MAX_ROWS ? rows - r - r0 : MAX_ROWS;
+                as[na++] = AttnSeg{r0, n, c0 + r + r0, n, &sq.target_kv[l]};
+            }
+            const RowMeta rm{c->row_pos + r, c->row_slot + r, c->row_mask + (size_t)r * MASK_WORDS};
+            launch_attention_batch(md, static_cast<char *>(c->q) + (size_t)r * qd * es, rm, as, na, c->attn_keys_per_split, c->attn_sc,
+                                   static_cast<char *>(c->attn_out) + (size_t)r * qd * es, c->st);
+        }
+        run_block(c, w.wo, md.d, qd, 0, c->attn_out, rows, epi_residual(c, true, nullptr, nullptr, nullptr));
+        launch_norm_rows(md, c->h, rows, w.mlp_norm, c->u, nullptr, c->st);
+        EpiArgs e{};
+        e.mode = EPI_SILU; e.act = c->act; e.F = md.ffn;
+        run_block(c, w.wgu, gate_up_rows(md.ffn), md.d, 0, c->u, rows, e);
+        run_block(c, w.wdown, md.d, md.ffn, 0, c->act, rows, epi_residual(c, true, nullptr, nullptr, nullptr));
+        const bool last = l + 1 == nl;
+        launch_norm_rows(md, c->h, rows, last ? c->final_norm : c->layers[l + 1].attn_norm, c->u,
+                         last ? static_cast<char *>(sq.feat_stash) + (size_t)c0 * md.d * es : nullptr, c->st);
+    }
+}
+
+// The same for the keys and values (alone: no queries are formed) of the pairs [i0, i0 + n) in specialist s.
+void catchup_pass(poss_ctx *c, int b, int s, int i0, int n) {
+    const ModelDims &md = c->md;
+    const SpecW &w = c->specs[s];
+    Seq &sq = c->seq[b];
+    const int qd = md.hq * md.dh, kd = md.hkv * md.dh;
+    launch_assemble_pairs(md, i0, n, c->embed, sq.tokens_dev, sq.feat_stash, c->xin, c->row_slot, c->inv_freq, c->cs, c->st);
+    run_block(c, w.fc_w, md.d, 2 * md.d, 0, c->xin, n, epi_residual(c, false, c->cfg.fc_bias ? w.fc_b : nullptr, nullptr, nullptr));
+    launch_norm_rows(md, c->h, n, w.layer.attn_norm, c->u, nullptr, c->st);
+    run_block(c, w.layer.wqkv, qd + 2 * kd, md.d, qd, c->u, n, epi_rope(c, sq.spec_kv[s], 0));
+}
+
+// Keys/values of committed pairs [spec_len[s], upto) of one sequence for specialist s: more than LAUNCH_ROWS of them by the
+// many-row kernels, otherwise in chunks of MAX_ROWS rows.
 void spec_catchup(poss_ctx *c, int b, int s, int upto) {
     Seq &sq = c->seq[b];
+    const int most = prefill_rows(c->cfg);
+    while (most > LAUNCH_ROWS && upto - sq.spec_len[s] > LAUNCH_ROWS) {
+        const int n = prompt_chunk(upto - sq.spec_len[s], most);
+        if (n <= LAUNCH_ROWS) break;
+        catchup_pass(c, b, s, sq.spec_len[s], n);
+        sq.spec_len[s] += n;
+    }
     while (sq.spec_len[s] < upto) {
         const int i0 = sq.spec_len[s], n = upto - i0 < MAX_ROWS ? upto - i0 : MAX_ROWS;
         std::vector<SeqPlan> plans(1);
@@ -757,20 +844,26 @@ int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_
         if (prompt[i] < 0 || prompt[i] >= c->cfg.vocab) return fail(c, POSS_E_INVALID_ARG, "poss_prefill: token id %d out of range at %d", prompt[i], i);
     const ModelDims &md = c->md;
     int32_t *stage = static_cast<int32_t *>(c->pinned);
-    // A launch carries LAUNCH_ROWS prompt tokens as two row ranges of at most MAX_ROWS (the width of a row's mask): the
-    // second range finds the keys of the first, written by the same layer's QKV epilogue, in its committed prefix.
-    for (int c0 = 0; c0 < n_prompt; c0 += LAUNCH_ROWS) {
-        const int rows = n_prompt - c0 < LAUNCH_ROWS ? n_prompt - c0 : LAUNCH_ROWS;
+    // A pass carries up to prefill_rows tokens through the many-row kernels.  With taps on, and for what is left of a prompt
+    // when it is LAUNCH_ROWS or fewer, it is the weight-streaming kernels on two row ranges of at most MAX_ROWS (the width of
+    // a row's mask): the second range finds the keys of the first, written by the same layer's QKV epilogue, in its prefix.
+    const int most = c->taps_user ? LAUNCH_ROWS : prefill_rows(c->cfg);
+    for (int c0 = 0, rows; c0 < n_prompt; c0 += rows) {
+        rows = prompt_chunk(n_prompt - c0, most);
         memcpy(stage, prompt + c0, rows * sizeof(int32_t));
         HIP_TRY(c, hipMemcpyAsync(sq.tokens_dev + c0, stage, rows * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
-        hipLaunchKernelGGL(causal_meta_kernel, dim3(1), dim3(LAUNCH_ROWS), 0, c->st, rows, c0, c->row_pos, c->row_slot, c->row_mask);
-        RowMeta rm{c->row_pos, c->row_slot, c->row_mask};
-        std::vector<Seg> segs;
-        const int ra = rows < MAX_ROWS ? rows : MAX_ROWS;
-        segs.push_back(Seg{seq, nullptr, 0, ra, rows, 0, c0, ra});
-        if (rows > ra) segs.push_back(Seg{seq, nullptr, ra, rows - ra, rows, 0, c0 + ra, rows - ra});
-        target_forward(c, rows, sq.tokens_dev + c0, rm, segs, c->feats);
-        stash_rows(c, sq, rows, c0);
+        hipLaunchKernelGGL(causal_meta_kernel, dim3((rows + 255) / 256), dim3(256), 0, c->st, rows, c0, c->row_pos, c->row_slot, c->row_mask);
+        if (rows > LAUNCH_ROWS) {
+            prefill_pass(c, seq, rows, c0);
+        } else {
+            RowMeta rm{c->row_pos, c->row_slot, c->row_mask};
+            std::vector<Seg> segs;
+            const int ra = rows < MAX_ROWS ? rows : MAX_ROWS;
+            segs.push_back(Seg{seq, nullptr, 0, ra, rows, 0, c0, ra});
+            if (rows > ra) segs.push_back(Seg{seq, nullptr, ra, rows - ra, rows, 0, c0 + ra, rows - ra});
+            target_forward(c, rows, sq.tokens_dev + c0, rm, segs, c->feats);
+            stash_rows(c, sq, rows, c0);
+        }
         if (c0 + rows == n_prompt) {
             // Head on the last row only: its normed activations sit at row rows-1 of c->u
             const char *last = static_cast<const char *>(c->u) + (size_t)(rows - 1) * md.d * dtype_size(md.dt);

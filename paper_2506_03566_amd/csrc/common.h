@@ -127,7 +127,16 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
 int gemm_head_segments(const GemmShape &g);
 static inline int head_segments_max(int vocab) { return gemm_npad(vocab) / GEMM_BLOCK_N; }
 
+// The same product for many rows (gemm_block.hip): 16-bit types, one range of rows and one cache, the epilogues EPI_ROPE_KV,
+// EPI_RESIDUAL (h alone: the norm is launch_norm_rows) and EPI_SILU; columns [col0, N) are formed (col0 > 0: EPI_ROPE_KV
+// without its queries).  tile < 0: chosen by the shape.  Returns false, launching nothing, on arguments it does not take.
+constexpr int PREFILL_ROWS = 4096;             // rows of a prompt that one pass of such launches carries at most
+bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &epi,
+                       hipStream_t st, int tile = -1);
+
 // ---------------------------------------------------------------- launchers: elementwise
+// u[m] = T(rmsnorm(h[m]) * gain) and, if stash != nullptr, stash[m] = T(h[m]); d a multiple of 4, at most 16384
+void launch_norm_rows(const ModelDims &md, const float *h, int rows, const void *gain, void *u, void *stash, hipStream_t st);
 // also writes the rotary table of the rows: cs[m][i] = (cos, sin)(pos[m] * theta^(-2i/dh)), angle formed in float64
 void launch_embed_norm(const ModelDims &md, const void *embed, const int32_t *tokens, int rows,
                        const void *gain, float *h, void *u, const int32_t *pos, const double *inv_freq,
@@ -214,6 +223,9 @@ void launch_draft_assemble(const ModelDims &md, const DraftRowPlan &plan, int de
                            const TreeDev &td, const float *fhat_prev, void *xin_tmp, void *x_out,
                            int32_t *pos_out, int32_t *slot_out, uint64_t *mask_out, const double *inv_freq,
                            float2 *cs, hipStream_t st);     // also writes the rows' rotary table cs
+// the committed pairs [x_{i+1} ; f_i], i = i0 .. i0 + n - 1, in order: rows of x_out, their positions' rotary table, their slots
+void launch_assemble_pairs(const ModelDims &md, int i0, int n, const void *embed, const int32_t *tokens_dev, const void *feat_stash,
+                           void *x_out, int32_t *slot_out, const double *inv_freq, float2 *cs, hipStream_t st);
 
 // ---------------------------------------------------------------- accept + commit
 void launch_tree_upload_finish(int n, int t, const int32_t *token, const int32_t *parent, int32_t *depth,

@@ -37,6 +37,10 @@ __device__ __forceinline__ float block_sum(float v, float *red /* >= 17 floats o
 __device__ __forceinline__ void lds_dma16(unsigned lds_base, const void *g) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(g) : "memory");
 }
+// The same with a scalar base and a byte offset per lane.
+__device__ __forceinline__ void lds_dma16_s(unsigned lds_base, const void *g, unsigned off) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(off), "s"(g) : "memory");
+}
 // Wait until at most N of this wave's vector-memory loads are outstanding (they complete in order).
 template <int N>
 __device__ __forceinline__ void dma_wait() {
@@ -105,6 +109,15 @@ __device__ __forceinline__ void rope_table_row(int pos, const double *__restrict
     double s, c;
     sincos((double)pos * inv_freq[i], &s, &c);
     cs_row[i] = make_float2((float)c, (float)s);
+}
+
+// Rotation of one rotary pair, spelt out operation by operation (two products, two fused multiply-adds): the kernels
+// that apply it must round alike, so nothing is left to the compiler's choice of what to contract.
+__device__ __forceinline__ void rope_pair(float x1, float x2, float2 cs, float &o1, float &o2) {
+#pragma clang fp contract(off)
+    const float p = x2 * cs.y, q = x1 * cs.y;
+    o1 = __builtin_fmaf(x1, cs.x, -p);
+    o2 = __builtin_fmaf(x2, cs.x, q);
 }
 
 // Element offsets into the paged caches.

@@ -88,6 +88,52 @@ void launch_embed_norm(const ModelDims &md, const void *embed, const int32_t *to
                                             md.dh / 2, cs));
 }
 
+// ------------------------------------------------------------------ u = T(rmsnorm(h) g), stash = T(h), many rows
+// Bound by memory: a row is read once, in 16-byte pieces kept in registers, and its 16-bit rows are written 8 bytes at a time.
+template <typename T>
+__global__ __launch_bounds__(1024) void norm_rows_kernel(const float *__restrict__ h, int d, float eps, const T *__restrict__ gain,
+                                                         T *__restrict__ u, T *__restrict__ stash) {
+    __shared__ float red[17];
+    constexpr int MAXV = 4;                                // four columns each: d <= 16 * blockDim.x
+    struct __attribute__((aligned(4 * sizeof(T)))) Quad { T t[4]; };
+    const size_t row = blockIdx.x;
+    const float4 *src = reinterpret_cast<const float4 *>(h + row * d);
+    const int nv = d / 4;
+    float4 v[MAXV];
+    Quad gv[MAXV];
+    float ss = 0.f;
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+        const int p = threadIdx.x + j * blockDim.x;
+        v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (p < nv) { v[j] = src[p]; gv[j] = reinterpret_cast<const Quad *>(gain)[p]; }
+        ss += v[j].x * v[j].x; ss += v[j].y * v[j].y; ss += v[j].z * v[j].z; ss += v[j].w * v[j].w;
+    }
+    ss = block_sum(ss, red);
+    const float rs = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+    for (int j = 0; j < MAXV; ++j) {
+        const int p = threadIdx.x + j * blockDim.x;
+        if (p >= nv) continue;
+        const float x[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+        Quad o;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o.t[i] = from_f<T>(x[i] * rs * to_f(gv[j].t[i]));
+        reinterpret_cast<Quad *>(u + row * d)[p] = o;
+        if (stash) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o.t[i] = from_f<T>(x[i]);
+            reinterpret_cast<Quad *>(stash + row * d)[p] = o;
+        }
+    }
+}
+
+void launch_norm_rows(const ModelDims &md, const float *h, int rows, const void *gain, void *u, void *stash, hipStream_t st) {
+    const int threads = md.d <= 4096 ? 256 : md.d <= 8192 ? 512 : 1024;
+    POSS_DISPATCH(md.dt, hipLaunchKernelGGL((norm_rows_kernel<T>), dim3(rows), dim3(threads), 0, st, h, md.d, md.eps,
+                                            static_cast<const T *>(gain), static_cast<T *>(u), static_cast<T *>(stash)));
+}
+
 // ------------------------------------------------------------------ argmax per row (lowest index on ties)
 // Two stages so that a 128K-entry row is not one workgroup's serial scan: (segment, row) partial
 // winners, then one small workgroup per row over the partials.

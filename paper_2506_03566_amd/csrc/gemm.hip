@@ -49,15 +49,6 @@ template <> struct Mfma<f16_t> {
     }
 };
 
-// Rotation of one rotary pair, spelt out operation by operation (two products, two fused multiply-adds): the two kernels
-// that apply it must round alike, so nothing is left to the compiler's choice of what to contract.
-__device__ __forceinline__ void rope_pair(float x1, float x2, float2 cs, float &o1, float &o2) {
-#pragma clang fp contract(off)
-    const float p = x2 * cs.y, q = x1 * cs.y;
-    o1 = __builtin_fmaf(x1, cs.x, -p);
-    o2 = __builtin_fmaf(x2, cs.x, q);
-}
-
 constexpr int KCS = GEMM_KCHUNK / GEMM_KSTEP;   // k-steps per LDS chunk (8)
 // PF = weight k-steps in flight per wave (template parameter of the stream kernel): 4, or 8 for launches
 // with fewer workgroups than CUs, where each CU has to keep more bytes in flight to fill the memory system.

@@ -552,6 +552,33 @@ void launch_draft_assemble(const ModelDims &md, const DraftRowPlan &plan, int de
 #undef POSS_ASM
 }
 
+// Committed pairs alone, any number of them (a prompt's): no plan, the row is the pair's index.
+template <typename T>
+__global__ __launch_bounds__(256) void assemble_pairs_kernel(int i0, int d_model, int vocab, const T *__restrict__ embed,
+                                                             const int32_t *__restrict__ tokens_dev, const T *__restrict__ feat_stash,
+                                                             T *__restrict__ x_out, int32_t *__restrict__ slot_out,
+                                                             const double *__restrict__ inv_freq, int half, float2 *__restrict__ cs) {
+    const int row = blockIdx.x, i = i0 + row;
+    rope_table_row(i, inv_freq, half, cs + (size_t)row * half, half <= 64 ? (int)blockDim.x - 64 : 0);
+    if (threadIdx.x == 0) slot_out[row] = i;
+    T *dst = x_out + (size_t)row * 2 * d_model;
+    const T *e = embed + (size_t)embedding_row(tokens_dev[i + 1], vocab) * d_model, *f = feat_stash + (size_t)i * d_model;
+    constexpr int VE = 16 / (int)sizeof(T);
+    const int nv = d_model / VE;                         // (16-bit types: d_model is a multiple of 8)
+    const uint4 *e4 = reinterpret_cast<const uint4 *>(e), *f4 = reinterpret_cast<const uint4 *>(f);
+    uint4 *d4 = reinterpret_cast<uint4 *>(dst);
+    for (int p = threadIdx.x; p < nv; p += blockDim.x) { d4[p] = e4[p]; d4[nv + p] = f4[p]; }
+}
+
+void launch_assemble_pairs(const ModelDims &md, int i0, int n, const void *embed, const int32_t *tokens_dev, const void *feat_stash,
+                           void *x_out, int32_t *slot_out, const double *inv_freq, float2 *cs, hipStream_t st) {
+#define POSS_PAIRS(T)                                                                                                  \
+    hipLaunchKernelGGL((assemble_pairs_kernel<T>), dim3(n), dim3(256), 0, st, i0, md.d, md.vocab, static_cast<const T *>(embed), \
+                       tokens_dev, static_cast<const T *>(feat_stash), static_cast<T *>(x_out), slot_out, inv_freq, md.dh / 2, cs)
+    if (md.dt == DT_BF16) POSS_PAIRS(bf16_t); else POSS_PAIRS(f16_t);
+#undef POSS_PAIRS
+}
+
 // ------------------------------------------------------------------ caller-supplied tree -> depth/pos/slot/mask
 __global__ void tree_upload_finish_kernel(int n, int t, const int32_t *__restrict__ parent, int32_t *__restrict__ depth,
                                           int32_t *__restrict__ pos, int32_t *__restrict__ slot,

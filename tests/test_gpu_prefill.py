@@ -1,0 +1,52 @@
+"""Prompts that are longer than one weight-streaming launch carries go through the many-row kernels (gemm_block_kernel and what
+surrounds it).  The caches they leave, the target's and every specialist's, against the oracle's, at prompt lengths around the
+edges of tiles and chunks and at widths that select each tile shape.  Tolerances: those of the other cache comparisons, 2e-2
+for 16-bit storage (rounding points are the oracle's; float32 against float64 sums flip a few of them)."""
+import numpy as np
+import pytest
+
+from gpu_util import have_gpu, Pair, tol_for
+
+pytestmark = pytest.mark.gpu
+
+if have_gpu():
+    from oracle.model import specialist_kv
+    from synth import make_prompt
+
+
+# (shape, prompt, layers, overrides): tiles of 128 x 128 (few columns), 256 x 256 (gate/up of 14336 units), 256 x 128 (gate/up of
+# 3072 units, 1001 rows); K not a multiple of 32 in the down projection (1416, 1736) and odd k-step counts; the rows of a
+# specialist's catch-up one short of a launch, exactly one and more
+@pytest.mark.parametrize("name,n_prompt,over", [
+    ("t_mid_bf16", 257, {}),
+    ("t_mid_bf16", 258, dict(d_ffn=1416, kv_page_tokens=32, kv_page_order=1)),
+    ("t_mid_f16", 385, dict(d_ffn=1736)),
+    ("t_mid_f16", 513, dict(kv_page_tokens=128)),
+    ("t_mid_bf16", 300, dict(d_ffn=14336)),
+    ("t_mid_bf16", 1001, dict(d_ffn=3072)),
+    ("t_mid_f16", 1100, dict(fc_bias=0)),
+])
+def test_long_prompt_leaves_the_oracles_caches(name, n_prompt, over):
+    print(f"prefill {name} prompt={n_prompt} {over}", flush=True)
+    pair = Pair(name, n_layers=2, max_seq=1280, n_specialists=2, positions_per_specialist=3, **over)
+    cfg, tol = pair.cfg, tol_for(pair.cfg)
+    prompt = make_prompt(cfg, n=n_prompt)
+    o = pair.oracle()
+    o.prefill(prompt)
+    first = pair.ctx.prefill(prompt)
+    for layer in range(cfg.n_layers):
+        k, v = pair.ctx.debug_read_kv(-1, layer, 0, n_prompt)
+        err = max(np.abs(k - o.kv[layer][0]).max(), np.abs(v - o.kv[layer][1]).max())
+        print(f"  layer {layer}: {err:.2e}", flush=True)
+        assert err <= tol
+    for s in range(cfg.n_specialists):
+        wk, wv = specialist_kv(pair.W, cfg, s, prompt[1:], np.stack(o.feats[:n_prompt - 1]), np.arange(n_prompt - 1), pair.act)
+        k, v = pair.ctx.debug_read_kv(s, 0, 0, n_prompt - 1)
+        err = max(np.abs(k - wk).max(), np.abs(v - wv).max())
+        print(f"  specialist {s}: {err:.2e}", flush=True)
+        assert err <= tol
+    o.tokens[-1] = first                                   # (a near-tie may go either way; the round below has its own checks)
+    assert pair.ctx.draft_tree().n == cfg.total_tokens + 1
+    pair.ctx.verify_tree()
+    assert len(pair.ctx.accept_and_commit()[2]) >= 1
+    pair.close()
