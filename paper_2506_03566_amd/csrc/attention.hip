@@ -600,41 +600,73 @@ __global__ void attn_merge_batch_kernel(AttnSeqs seqs, int hq, int hkv, int dh, 
     attn_merge_body<T>(m, a.o_part, a.ml_part, a.n_splits, hq, hkv, dh, a.rho_pad, out + (size_t)a.row0 * hq * dh);
 }
 
-// float32 storage: one wave per (row, query head); exact two-pass softmax.
-__global__ __launch_bounds__(64) void attn_f32_kernel(const float *__restrict__ q, int hq, int hkv, int dh,
-                                                      const uint64_t *__restrict__ mask, int n_prefix, int region_len,
-                                                      KVCache kv, float scale, float *__restrict__ out) {
-    extern __shared__ float sc[];
-    const int m = blockIdx.x, qh = blockIdx.y, kvh = qh / (hq / hkv), lane = threadIdx.x;
+// float32 storage: one workgroup per (row, query head); exact two-pass softmax.  A thread takes whole keys for the scores
+// (16 bytes at a time), then the threads split into 256 / dh2 groups over the keys for P V (dh2: dh rounded up to a power of two),
+// whose partial sums are added in group order.  4 rows of four heads over 89 keys: 19.3 -> 6.5 us (before: one wave, dh
+// scalar loads per key and one dependent load per key in P V).
+constexpr int AF32_THREADS = 256;
+template <bool VEC>
+__global__ __launch_bounds__(AF32_THREADS) void attn_f32_kernel(const float *__restrict__ q, int hq, int hkv, int dh, int dh2,
+                                                                const uint64_t *__restrict__ mask, int n_prefix, int region_len,
+                                                                KVCache kv, float scale, float *__restrict__ out) {
+    extern __shared__ float sc[];                         // max(keys, AF32_THREADS) floats
+    __shared__ float red[17];
+    const int m = blockIdx.x, qh = blockIdx.y, kvh = qh / (hq / hkv), tid = threadIdx.x;
     const float *qr = q + ((size_t)m * hq + qh) * dh;
     const uint64_t m0 = mask[(size_t)m * MASK_WORDS], m1 = mask[(size_t)m * MASK_WORDS + 1];
     const int total = n_prefix + region_len;
     const float *kc = static_cast<const float *>(kv.k), *vc = static_cast<const float *>(kv.vt);
     float mx = -INFINITY;
-    for (int sl = lane; sl < total; sl += 64) {
+    for (int sl = tid; sl < total; sl += AF32_THREADS) {
         float x = -INFINITY;
         if (slot_visible(sl, n_prefix, region_len, m0, m1)) {
             const float *kr = kc + k_offset(kv, sl, kvh, hkv, dh);
             float a = 0.f;
-            for (int i = 0; i < dh; ++i) a = fmaf(qr[i], kr[i], a);
+            if constexpr (VEC) {
+#pragma unroll 8
+                for (int i = 0; i < dh; i += 4) {
+                    const f32x4 k4 = *reinterpret_cast<const f32x4 *>(kr + i), q4 = *reinterpret_cast<const f32x4 *>(qr + i);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) a = fmaf(q4[j], k4[j], a);
+                }
+            } else {
+                for (int i = 0; i < dh; ++i) a = fmaf(qr[i], kr[i], a);
+            }
             x = a * scale;
         }
         sc[sl] = x;
         mx = fmaxf(mx, x);
     }
     mx = wave_max(mx);
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     float sum = 0.f;
-    for (int sl = lane; sl < total; sl += 64) {
+    for (int sl = tid; sl < total; sl += AF32_THREADS) {
         const float p = expf(sc[sl] - mx);
         sc[sl] = p;
         sum += p;
     }
-    sum = wave_sum(sum);
+    sum = block_sum(sum, red);                            // (its barriers also publish sc)
+    const int groups = AF32_THREADS / dh2, i = tid & (dh2 - 1), gi = tid / dh2;
+    const int per = ((total + groups - 1) / groups + 3) & ~3, s0 = min(total, gi * per), s1 = min(total, s0 + per);
+    float a = 0.f;
+    if (i < dh) {
+        int sl = s0;
+        for (; sl + 4 <= s1; sl += 4) {                   // four consecutive slots, s0 a multiple of 4: one page
+            const f32x4 v = *reinterpret_cast<const f32x4 *>(vc + vt_offset(kv, sl, kvh, hkv, dh, i));
+#pragma unroll
+            for (int j = 0; j < 4; ++j) a = fmaf(sc[sl + j], v[j], a);
+        }
+        for (; sl < s1; ++sl) a = fmaf(sc[sl], vc[vt_offset(kv, sl, kvh, hkv, dh, i)], a);
+    }
+    __syncthreads();                                      // every score has been read
+    sc[tid] = a;
     __syncthreads();
-    for (int i = lane; i < dh; i += 64) {
-        float a = 0.f;
-        for (int sl = 0; sl < total; ++sl) a = fmaf(sc[sl], vc[vt_offset(kv, sl, kvh, hkv, dh, i)], a);
-        out[((size_t)m * hq + qh) * dh + i] = a / sum;
+    if (tid < dh) {
+        float o = 0.f;
+        for (int g = 0; g < groups; ++g) o += sc[g * dh2 + tid];
+        out[((size_t)m * hq + qh) * dh + tid] = o / sum;
     }
 }
 
@@ -797,10 +829,19 @@ void launch_attention(const ModelDims &md, const void *q, int rows, const RowMet
                       int region_len, const KVCache &kv, int keys_per_split, const AttnScratch &sc,
                       void *out, hipStream_t st) {
     if (md.dt == DT_F32) {
-        const size_t lds = (size_t)(n_prefix + region_len) * sizeof(float);
-        hipLaunchKernelGGL(attn_f32_kernel, dim3(rows, md.hq), dim3(64), lds, st, static_cast<const float *>(q),
-                           md.hq, md.hkv, md.dh, rm.mask, n_prefix, region_len, kv, 1.0f / sqrtf((float)md.dh),
-                           static_cast<float *>(out));
+        const int keys = n_prefix + region_len;
+        const size_t lds = (size_t)(keys < AF32_THREADS ? AF32_THREADS : keys) * sizeof(float);
+        int dh2 = 2;
+        while (dh2 < md.dh) dh2 *= 2;                     // (dh is at most 256)
+        const float scale = 1.0f / sqrtf((float)md.dh);
+        const float *qf = static_cast<const float *>(q);
+        float *of = static_cast<float *>(out);
+        if (md.dh % 4 == 0)
+            hipLaunchKernelGGL((attn_f32_kernel<true>), dim3(rows, md.hq), dim3(AF32_THREADS), lds, st, qf, md.hq, md.hkv, md.dh, dh2,
+                               rm.mask, n_prefix, region_len, kv, scale, of);
+        else
+            hipLaunchKernelGGL((attn_f32_kernel<false>), dim3(rows, md.hq), dim3(AF32_THREADS), lds, st, qf, md.hq, md.hkv, md.dh, dh2,
+                               rm.mask, n_prefix, region_len, kv, scale, of);
     } else if (md.dt == DT_BF16) {
         launch_attention_t<bf16_t>(md, q, rows, rm, n_prefix, region_len, kv, keys_per_split, sc, out, st);
     } else {
