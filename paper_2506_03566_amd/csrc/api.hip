@@ -1505,14 +1505,21 @@ extern "C" int poss_gemm_static(int32_t dtype, const void *x, const void *w, voi
     unsigned char *base = static_cast<unsigned char *>(static_scratch_address());
     if (!base) return POSS_E_HIP;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    void *wp = base;
-    float *part = reinterpret_cast<float *>(base + w_bytes);
     EpiArgs epi{};
     epi.mode = EPI_PLAIN; epi.out = static_cast<float *>(y); epi.ld_out = N;
-    // every byte the kernels read is written first by this call: the packed matrix including its zero
-    // padding by the pack kernel, every row of every plane by the stream kernel
-    launch_pack(dtype, PackSrc{{w, nullptr, nullptr}, {N, 0, 0}}, K, wp, st);
-    if (!launch_gemm(dtype, g, wp, x, K, part, epi, 0.f, st)) return fail(nullptr, POSS_E_INVALID_ARG, "poss_gemm_static: launch refused");
+    // One launch on the row-major matrix where there is such a kernel: float32 (it is the packed layout) and 16-bit types up
+    // to 16 splits.  Otherwise (a caller's workgroup target, or few columns and K in the thousands) pack, stream, sum: every byte those
+    // kernels read is written first by this call, the packed matrix including its zero padding by the pack kernel, every row
+    // of every plane by the stream kernel.
+    float *part = reinterpret_cast<float *>(base + w_bytes);
+    bool ok = true;
+    if (dtype == DT_F32) {
+        ok = launch_gemm(dtype, g, w, x, K, part, epi, 0.f, st);
+    } else if (!launch_gemm_direct(dtype, g, w, x, static_cast<float *>(y), st)) {
+        launch_pack(dtype, PackSrc{{w, nullptr, nullptr}, {N, 0, 0}}, K, base, st);
+        ok = launch_gemm(dtype, g, base, x, K, part, epi, 0.f, st);
+    }
+    if (!ok) return fail(nullptr, POSS_E_INVALID_ARG, "poss_gemm_static: launch refused");
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(nullptr, POSS_E_HIP, "poss_gemm_static: %s", hipGetErrorString(e));
     return POSS_OK;

@@ -122,6 +122,9 @@ struct RopeRanges { int n; int r0[ROPE_MAX_RANGES], r1[ROPE_MAX_RANGES], rows_q[
 bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int ldx, float *part,
                  const EpiArgs &epi, float rms_eps, hipStream_t st, hipEvent_t ev_start = nullptr,
                  hipEvent_t ev_stop = nullptr, const RopeRanges *ranges = nullptr);
+// The same product (EPI_PLAIN, y[m * N + n]) from a row-major matrix of a 16-bit type, at most 128 rows and 16 splits, in one
+// launch: bit for bit what packing it and launch_gemm give.  Returns false, launching nothing, for what it does not take.
+bool launch_gemm_direct(int dt, const GemmShape &g, const void *W, const void *X, float *y, hipStream_t st);
 // Column tiles ("segments") of an unsplit launch of this shape, i.e. records per row an EPI_HEAD launch writes;
 // head_segments_max bounds it for any row count.
 int gemm_head_segments(const GemmShape &g);

@@ -744,6 +744,115 @@ __global__ __launch_bounds__(256) void gemm_qkv_rope_kernel(const u32x4 *__restr
 }
 
 // ------------------------------------------------------------------------------------------
+// One product with a ROW-MAJOR matrix (a caller that has no packed weights and calls once): no repacking, no partial planes,
+// one launch.  A workgroup takes 16 columns x 16 MT rows; wave s computes K split s - the very splits, and inside them the
+// very order, of the streaming kernels - and the splits' tiles are added in split order, so the result is bit for bit that of
+// packing, streaming and summing.  A wave brings its own operands into its own corner of LDS (no barrier), two k-steps and
+// whole 128-byte lines at a time, in the swizzled order of gemm_tall_kernel: fetched as operands, 64 bytes of 16 rows per
+// instruction, the same bytes took the CU's memory pipe twice as long.  NST stages in a ring: four where LDS holds them (few
+// splits: few waves to hide the latency), otherwise two.
+// 61 x 1720 x 5000: pack 9.6 + stream 6.1 + sum 3.6 us -> 8.9 us (14.5 fetched as operands into registers); 1 x 512 x 512:
+// three launches of 8.0 us -> 2.9 us.
+constexpr int DIRECT_MAX_SPLITS = 16;
+__device__ const u32x4 direct_zero = {0u, 0u, 0u, 0u};    // what a lane fetches where its k lies beyond K
+
+template <typename T, int MT, int NST>
+__global__ __launch_bounds__(DIRECT_MAX_SPLITS * 64) void gemm_direct_kernel(const T *__restrict__ W, const T *__restrict__ X,
+                                                                            float *__restrict__ y, int M, int N, int K, int n_chunks, int mparts) {
+    typedef __attribute__((address_space(3))) void *LdsPtr;
+    constexpr int TILES = MT + 1, STAGE = TILES * 128;    // 16-row operand tiles of a stage (the last: weights), 16-byte units
+    extern __shared__ __attribute__((aligned(1024))) u32x4 dlds[];   // [wave][NST][STAGE]; at the end [wave][MT][64] partial tiles
+    const int S = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
+    // the row parts of a column tile read the same weights: ids equal modulo 8 (one XCD), one after the other
+    const int xcd = blockIdx.x & 7, qid = blockIdx.x >> 3;
+    const int n0 = ((qid / mparts) * 8 + xcd) * 16, m0 = (qid % mparts) * (16 * MT);
+    if (n0 >= N) return;
+    const int k0 = wave * n_chunks / S * KCS, k1 = min((wave + 1) * n_chunks / S * KCS, (K + GEMM_KSTEP - 1) / GEMM_KSTEP);
+    const int n_st = (k1 - k0 + 1) / 2;                   // stages of two k-steps (what lies beyond K is zero)
+    const T *src[TILES][2];                               // load i of a tile: its rows 8 i + lane / 8, eight lanes per row
+    int kk[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int r = i * 8 + (lane >> 3);
+        kk[i] = ((lane & 7) ^ tall_x_swizzle(r)) * 8;
+#pragma unroll
+        for (int t = 0; t < MT; ++t) src[t][i] = X + (size_t)min(m0 + t * 16 + r, M - 1) * K + kk[i];   // rows and columns beyond the
+        src[MT][i] = W + (size_t)min(n0 + r, N - 1) * K + kk[i];                                        // matrix repeat the last (never stored)
+    }
+    const unsigned lds0 = (unsigned)(uintptr_t)(LdsPtr)dlds + (unsigned)(wave * NST * STAGE * 16);
+    auto fetch = [&](int st) {
+#pragma unroll
+        for (int t = 0; t < TILES; ++t)
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int k = (k0 + 2 * st) * GEMM_KSTEP;
+                const void *p = k + kk[i] < K ? static_cast<const void *>(src[t][i] + k) : static_cast<const void *>(&direct_zero);
+                lds_dma16(lds0 + (unsigned)(((st % NST) * STAGE + t * 128 + i * 64) * 16), p);
+            }
+    };
+    f32x4 acc[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const u32x4 *mine = dlds + wave * NST * STAGE + lr * 8;
+    const int swz = tall_x_swizzle(lr);
+#pragma unroll
+    for (int st = 0; st < NST; ++st) if (st < n_st) fetch(st);
+    for (int st = 0; st < n_st; ++st) {
+        if (st + NST <= n_st) dma_wait<(NST - 1) * TILES * 2>(); else dma_wait<0>();
+        const u32x4 *base = mine + (st % NST) * STAGE;
+        u32x4 f[2][TILES];
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int t = 0; t < TILES; ++t) f[ks][t] = base[t * 128 + ((ks * 4 + lg) ^ swz)];
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this stage has been read: its place may be filled again
+        if (st + NST < n_st) fetch(st + NST);
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) acc[mt] = Mfma<T>::run(f[ks][mt], f[ks][MT], acc[mt]);
+    }
+    __syncthreads();                                      // every wave is done with its stages
+    f32x4 *red = reinterpret_cast<f32x4 *>(dlds);
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) red[(wave * MT + mt) * 64 + lane] = acc[mt];
+    __syncthreads();
+    for (int mt = wave; mt < MT; mt += S) {
+        f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int s = 0; s < S; ++s) v += red[(s * MT + mt) * 64 + lane];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + mt * 16 + lg * 4 + r;
+            if (m < M && n0 + lr < N) y[(size_t)m * N + n0 + lr] = v[r];
+        }
+    }
+}
+
+bool launch_gemm_direct(int dt, const GemmShape &g, const void *W, const void *X, float *y, hipStream_t st) {
+    if (dt == DT_F32 || !W || !X || !y || g.M < 1 || g.M > MAX_ROWS || g.N < 1 || g.K < 8 || g.K % 8 || g.S < 1 || g.S > DIRECT_MAX_SPLITS) return false;
+    if ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(X)) % 16) return false;      // 16-byte loads to LDS
+    // two row tiles per workgroup where there are two and the stages fit; the stages of S waves within 160 KB (64 KB asked for
+    // with one or two splits leaves room for more than one workgroup per CU)
+    const int row_tiles = (g.M + 15) / 16, mt = row_tiles == 1 || g.S > 13 ? 1 : 2, mparts = (row_tiles + mt - 1) / mt, ctiles = (g.N + 15) / 16;
+    const size_t stage = (size_t)g.S * (mt + 1) * 128 * 16;
+    const int nst = stage * 4 <= 160 * 1024 ? 4 : 2;
+    dim3 grid(8 * mparts * ((ctiles + 7) / 8)), block(g.S * 64);
+    const int n_chunks = g.Kpad / GEMM_KCHUNK;
+#define POSS_DIRECT(T, MT, NST)                                                                                              \
+    hipLaunchKernelGGL((gemm_direct_kernel<T, MT, NST>), grid, block, stage * NST, st, static_cast<const T *>(W), static_cast<const T *>(X), y, \
+                       g.M, g.N, g.K, n_chunks, mparts)
+#define POSS_DIRECT_T(T)                                                                                                     \
+    do {                                                                                                                     \
+        if (mt == 1) { if (nst == 4) POSS_DIRECT(T, 1, 4); else POSS_DIRECT(T, 1, 2); }                                       \
+        else         { if (nst == 4) POSS_DIRECT(T, 2, 4); else POSS_DIRECT(T, 2, 2); }                                       \
+    } while (0)
+    if (dt == DT_BF16) POSS_DIRECT_T(bf16_t); else POSS_DIRECT_T(f16_t);
+#undef POSS_DIRECT_T
+#undef POSS_DIRECT
+    return true;
+}
+
+// ------------------------------------------------------------------------------------------
 // Residual epilogue, one workgroup per row: h = sum of planes (+ bias) (+ h); then, because the
 // whole row is in this workgroup, the RMSNorm that feeds the next GEMM right away:
 // u = T(h / sqrt(mean(h^2) + eps) * gain).  Saves a kernel per norm.

@@ -40,6 +40,27 @@ def test_static_scratch_gemm_matches_the_scratch_argument_gemm_twice_in_a_row(dt
         assert err < 2e-5 * np.sqrt(max(K, 256) / 256.0), err
 
 
+# 16-bit types: one row tile, two and an odd number of them; column tiles that end inside the matrix; K below a k-step, not a
+# multiple of two k-steps; one split, seven (four stages no longer fit), thirteen and fourteen (one row tile per workgroup),
+# sixteen and seventeen (packed instead), and pointers that are not aligned to 16 bytes (packed as well)
+@pytest.mark.parametrize("dtype,M,N,K", [(1, 1, 512, 512), (2, 17, 130, 8), (1, 16, 8, 40), (2, 48, 1000, 1000), (1, 128, 16000, 504),
+                                         (2, 61, 4000, 3608), (1, 61, 128, 6656), (1, 40, 120, 7160), (2, 61, 128, 8192),
+                                         (1, 33, 128, 8448)])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_static_gemm_is_the_packed_gemm_bit_for_bit(dtype, M, N, K, shift):
+    print(f"gemm_static dtype={dtype} M={M} N={N} K={K} shift={shift}", flush=True)
+    x, w, _ = _case(dtype, M, N, K, M + N + K)
+    xd, wd = to_device(x, dtype), to_device(w, dtype)
+    want, _ = P.debug_gemm(dtype, xd, wd)
+    if shift:
+        buf = torch.empty(M * K + 4, dtype=xd.dtype, device="cuda")
+        buf[4:] = xd.reshape(-1)
+        xd = buf[4:].view(M, K)
+    y = torch.full((M, N), float("nan"), dtype=torch.float32, device="cuda")
+    P.gemm_static(dtype, xd, wd, y)
+    assert torch.equal(y, want)
+
+
 def test_static_scratch_gemm_refuses_what_does_not_fit():
     lib = P.load_library()
     x = torch.zeros(8, 8192, dtype=torch.bfloat16, device="cuda")
