@@ -524,19 +524,7 @@ void prefill_pass(poss_ctx *c, int b, int rows, int c0) {
     for (int l = 0; l < nl; ++l) {
         const LayerW &w = c->layers[l];
         run_block(c, w.wqkv, qd + 2 * kd, md.d, 0, c->u, rows, epi_rope(c, sq.target_kv[l], rows));
-        // ranges of MAX_ROWS rows (the width of a row's mask), two per launch: a range finds the keys of those before it,
-        // written by the launch above, in its committed prefix
-        for (int r = 0; r < rows; r += LAUNCH_ROWS) {
-            AttnSeg as[2];
-            int na = 0;
-            for (int r0 = 0; r0 < LAUNCH_ROWS && r + r0 < rows; r0 += MAX_ROWS) {
-                const int n = rows - r - r0 < MAX_ROWS ? rows - r - r0 : MAX_ROWS;
-                as[na++] = AttnSeg{r0, n, c0 + r + r0, n, &sq.target_kv[l]};
-            }
-            const RowMeta rm{c->row_pos + r, c->row_slot + r, c->row_mask + (size_t)r * MASK_WORDS};
-            launch_attention_batch(md, static_cast<char *>(c->q) + (size_t)r * qd * es, rm, as, na, c->attn_keys_per_split, c->attn_sc,
-                                   static_cast<char *>(c->attn_out) + (size_t)r * qd * es, c->st);
-        }
+        launch_attention_prompt(md, c->q, rows, c->row_mask, c0, sq.target_kv[l], c->attn_out, c->st);
         run_block(c, w.wo, md.d, qd, 0, c->attn_out, rows, epi_residual(c, true, nullptr, nullptr, nullptr));
         launch_norm_rows(md, c->h, rows, w.mlp_norm, c->u, nullptr, c->st);
         EpiArgs e{};

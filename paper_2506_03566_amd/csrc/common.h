@@ -169,6 +169,11 @@ struct AttnSeg { int row0, rows, n_prefix, region_len; const KVCache *kv; };
 void launch_attention_batch(const ModelDims &md, const void *q, const RowMeta &rm, const AttnSeg *segs, int n,
                             int keys_per_split, const AttnScratch &sc, void *out, hipStream_t st);
 
+// A prompt's rows [0, rows) at slots c0 .., 16-bit types: row r sees the slots before its range of MAX_ROWS rows and, of the
+// range, those in its mask.  One launch, no scratch.
+void launch_attention_prompt(const ModelDims &md, const void *q, int rows, const uint64_t *mask, int c0, const KVCache &kv, void *out,
+                             hipStream_t st);
+
 // ---------------------------------------------------------------- draft-tree kernels
 struct TreeDev {            // device-resident tree state of one round
     // candidate pool

@@ -25,10 +25,12 @@ if have_gpu():
     ("t_mid_bf16", 300, dict(d_ffn=14336)),
     ("t_mid_bf16", 1001, dict(d_ffn=3072)),
     ("t_mid_f16", 1100, dict(fc_bias=0)),
+    ("t_mid_f16", 2305, dict(max_seq=2560)),                                         # a walk of more than 64 key blocks
+    ("t_mid_bf16", 4400, dict(max_seq=4480, d_model=128, n_q_heads=2, n_kv_heads=1)),   # two passes; more than 128 blocks
 ])
 def test_long_prompt_leaves_the_oracles_caches(name, n_prompt, over):
     print(f"prefill {name} prompt={n_prompt} {over}", flush=True)
-    pair = Pair(name, n_layers=2, max_seq=1280, n_specialists=2, positions_per_specialist=3, **over)
+    pair = Pair(name, **dict(dict(n_layers=2, max_seq=1280, n_specialists=2, positions_per_specialist=3), **over))
     cfg, tol = pair.cfg, tol_for(pair.cfg)
     prompt = make_prompt(cfg, n=n_prompt)
     o = pair.oracle()
