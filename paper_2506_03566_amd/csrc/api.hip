@@ -161,11 +161,17 @@ const char *check_config(const poss_config &c) {
 
 size_t esize(const poss_config &c) { return dtype_size(c.dtype); }
 
+// Prompts up to this many tokens stay with the weight-streaming kernels, two launches of 256 rows: their sums are those of every
+// other pass bit for bit, on which the children that a short request draws at a temperature hang, and the gain would be small
+// (prompt and catch-up of one specialist, four layers of the 8B shape: 260 tokens 1.50 ms streamed, 1.57 ms by the many-row
+// kernels; 384: 1.72, 1.78; 512: 2.02, 1.80).
+constexpr int STREAMED_PROMPT = 2 * LAUNCH_ROWS;
+
 // Rows that one pass over a prompt carries: LAUNCH_ROWS of the weight-streaming kernels, or, 16-bit types, up to PREFILL_ROWS
 // of the many-row kernels (a chunk of 4096 rows divides the 4096-column products of the 8B shape into 256 tiles of 256 x 256,
 // one per CU).  Operands stay below 4 GiB.
 int prefill_rows(const poss_config &c) {
-    if (c.dtype == POSS_DTYPE_F32 || c.max_seq <= LAUNCH_ROWS) return LAUNCH_ROWS;
+    if (c.dtype == POSS_DTYPE_F32 || c.max_seq <= STREAMED_PROMPT) return LAUNCH_ROWS;
     const size_t widest = (size_t)(c.d_ffn > 2 * c.d_model ? c.d_ffn : 2 * c.d_model) + (size_t)c.n_q_heads * c.head_dim;
     int rows = c.max_seq < PREFILL_ROWS ? round_up(c.max_seq, LAUNCH_ROWS) : PREFILL_ROWS;
     while (rows > LAUNCH_ROWS && (size_t)rows * widest * 2 > 0xffffffffull) rows = round_up(rows / 2, LAUNCH_ROWS);
@@ -549,14 +555,13 @@ void catchup_pass(poss_ctx *c, int b, int s, int i0, int n) {
     run_block(c, w.layer.wqkv, qd + 2 * kd, md.d, qd, c->u, n, epi_rope(c, sq.spec_kv[s], 0));
 }
 
-// Keys/values of committed pairs [spec_len[s], upto) of one sequence for specialist s: more than LAUNCH_ROWS of them by the
+// Keys/values of committed pairs [spec_len[s], upto) of one sequence for specialist s: more than STREAMED_PROMPT of them by the
 // many-row kernels, otherwise in chunks of MAX_ROWS rows.
 void spec_catchup(poss_ctx *c, int b, int s, int upto) {
     Seq &sq = c->seq[b];
     const int most = prefill_rows(c->cfg);
-    while (most > LAUNCH_ROWS && upto - sq.spec_len[s] > LAUNCH_ROWS) {
+    while (most > LAUNCH_ROWS && upto - sq.spec_len[s] > STREAMED_PROMPT) {
         const int n = prompt_chunk(upto - sq.spec_len[s], most);
-        if (n <= LAUNCH_ROWS) break;
         catchup_pass(c, b, s, sq.spec_len[s], n);
         sq.spec_len[s] += n;
     }
@@ -832,10 +837,10 @@ int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_
         if (prompt[i] < 0 || prompt[i] >= c->cfg.vocab) return fail(c, POSS_E_INVALID_ARG, "poss_prefill: token id %d out of range at %d", prompt[i], i);
     const ModelDims &md = c->md;
     int32_t *stage = static_cast<int32_t *>(c->pinned);
-    // A pass carries up to prefill_rows tokens through the many-row kernels.  With taps on, and for what is left of a prompt
-    // when it is LAUNCH_ROWS or fewer, it is the weight-streaming kernels on two row ranges of at most MAX_ROWS (the width of
-    // a row's mask): the second range finds the keys of the first, written by the same layer's QKV epilogue, in its prefix.
-    const int most = c->taps_user ? LAUNCH_ROWS : prefill_rows(c->cfg);
+    // A long prompt goes through the many-row kernels, up to prefill_rows tokens a pass.  Up to STREAMED_PROMPT tokens (and with
+    // taps on) it is the weight-streaming kernels, LAUNCH_ROWS a pass, on two row ranges of at most MAX_ROWS (the width of a
+    // row's mask): the second range finds the keys of the first, written by the same layer's QKV epilogue, in its prefix.
+    const int most = c->taps_user || n_prompt <= STREAMED_PROMPT ? LAUNCH_ROWS : prefill_rows(c->cfg);
     for (int c0 = 0, rows; c0 < n_prompt; c0 += rows) {
         rows = prompt_chunk(n_prompt - c0, most);
         memcpy(stage, prompt + c0, rows * sizeof(int32_t));

@@ -1,4 +1,4 @@
-"""Prompts that are longer than one weight-streaming launch carries go through the many-row kernels (gemm_block_kernel and what
+"""Prompts of more than 512 tokens go through the many-row kernels (gemm_block_kernel and what
 surrounds it).  The caches they leave, the target's and every specialist's, against the oracle's, at prompt lengths around the
 edges of tiles and chunks and at widths that select each tile shape.  Tolerances: those of the other cache comparisons, 2e-2
 for 16-bit storage (rounding points are the oracle's; float32 against float64 sums flip a few of them)."""
@@ -15,14 +15,14 @@ if have_gpu():
 
 
 # (shape, prompt, layers, overrides): tiles of 128 x 128 (few columns), 256 x 256 (gate/up of 14336 units), 256 x 128 (gate/up of
-# 3072 units, 1001 rows); K not a multiple of 32 in the down projection (1416, 1736) and odd k-step counts; the rows of a
-# specialist's catch-up one short of a launch, exactly one and more
+# 3072 units, 1001 rows); K not a multiple of 32 in the down projection (1416, 1736) and odd k-step counts; a specialist's catch-up of 512
+# rows (the weight-streaming kernels) and of more
 @pytest.mark.parametrize("name,n_prompt,over", [
-    ("t_mid_bf16", 257, {}),
-    ("t_mid_bf16", 258, dict(d_ffn=1416, kv_page_tokens=32, kv_page_order=1)),
-    ("t_mid_f16", 385, dict(d_ffn=1736)),
-    ("t_mid_f16", 513, dict(kv_page_tokens=128)),
-    ("t_mid_bf16", 300, dict(d_ffn=14336)),
+    ("t_mid_bf16", 513, {}),
+    ("t_mid_bf16", 514, dict(d_ffn=1416, kv_page_tokens=32, kv_page_order=1)),
+    ("t_mid_f16", 641, dict(d_ffn=1736)),
+    ("t_mid_f16", 769, dict(kv_page_tokens=128)),
+    ("t_mid_bf16", 600, dict(d_ffn=14336)),
     ("t_mid_bf16", 1001, dict(d_ffn=3072)),
     ("t_mid_f16", 1100, dict(fc_bias=0)),
     ("t_mid_f16", 2305, dict(max_seq=2560)),                                         # a walk of more than 64 key blocks
