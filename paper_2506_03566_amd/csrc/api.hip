@@ -98,9 +98,12 @@ struct poss_ctx {
     float temperature;                 // 0: greedy verification; > 0: the target's tokens are drawn (poss_set_sampling)
     float *u_pinned, *u_dev;           // per sequence, one uniform number per tree depth: host staging and device copy
     // drawn children (poss_set_draft_sampling): uniform numbers of the draws [depth][k][k] and of the tests [depth + 1][k + 1]
-    // (host staging, device copies), the drafter's logits of every expanded node, the residual vector of the walk
+    // (host staging, device copies), the drafter's logits of every expanded node, the masses of
+    // those rows and of the verified tree's, the residual vector of the walk
     int draft_sampling;
     float *ud_pinned, *ua_pinned, *ud_dev, *ua_dev, *dlogits, *resid;
+    DrawMasses draft_m, target_m;
+    float draft_m_temperature;         // at which draft_m was formed
     int gemm_target_wgs, attn_keys_per_split;
     int launch_rows;                   // rows one launch of a batch's pass carries (POSS_LAUNCH_ROWS unless lowered for a sweep)
     // gemm profiling
@@ -262,7 +265,16 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
     float *ud_dev = a.take_n<float>((size_t)c.depth * c.top_k * c.top_k), *ua_dev = a.take_n<float>((size_t)(c.depth + 1) * (c.top_k + 1));
     // one row per expanded node; a pass's Head launch writes whole 16-row tiles, so the last pass needs room beyond its rows
     float *dlogits = a.take_n<float>((size_t)(1 + (c.depth - 1) * c.top_k + 16) * gemm_npad(V));
+    // masses of those rows and of a verified tree's (drawn children are built for one sequence)
+    const int dr = 1 + (c.depth - 1) * c.top_k, tr = B == 1 ? c.total_tokens + 1 : 0;
+    auto masses = [&](int rows) {
+        DrawMasses m;
+        m.mass = a.take_n<float>((size_t)rows * gemm_npad(V)); m.bsum = a.take_n<float>(draw_bsum_floats(rows, V));
+        m.mx = a.take_n<float>(rows); m.z = a.take_n<float>(rows); m.pm = a.take_n<float>(draw_pm_floats(rows, V));
+        return m;
+    };
     float *resid = a.take_n<float>(gemm_npad(V));
+    const DrawMasses draft_m = masses(B == 1 ? dr : 0), target_m = masses(tr);
     // per sequence: tree state, token stream, feature stash, stored frontier rows
     const int k = c.top_k, L = c.depth, pool = k + (L - 1) * k * k, stride = c.total_tokens + 1;
     std::vector<Seq> seqs(B);
@@ -306,7 +318,7 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
         ctx->topk_id_all = topk_id_all; ctx->topk_logp_all = topk_logp_all;
         ctx->argmax_dev = argmax_dev;
         ctx->inv_freq = inv_freq; ctx->u_dev = u_dev;
-        ctx->ud_dev = ud_dev; ctx->ua_dev = ua_dev; ctx->dlogits = dlogits; ctx->resid = resid;
+        ctx->ud_dev = ud_dev; ctx->ua_dev = ua_dev; ctx->dlogits = dlogits; ctx->resid = resid; ctx->draft_m = draft_m; ctx->target_m = target_m;
     }
     return a.off + 256;
 }
@@ -425,9 +437,14 @@ void run_head_topk(poss_ctx *c, int rows, int depth) {
         // drawn children: the logits of the pass's rows are kept (the walk needs the distribution each child came from),
         // k children per row drawn without replacement with the caller's numbers
         const int k = c->cfg.top_k;
-        float *dst = c->dlogits + (size_t)(depth == 1 ? 0 : 1 + (depth - 2) * k) * gemm_npad(c->cfg.vocab);
+        const int V = c->cfg.vocab;
+        const size_t row0 = depth == 1 ? 0 : 1 + (size_t)(depth - 2) * k;
+        float *dst = c->dlogits + row0 * gemm_npad(V);
         const GemmShape g = run_head(c, rows, 0, true, nullptr, nullptr, dst);
-        launch_sample_children(dst, g.Npad, rows, c->cfg.vocab, k, c->temperature, c->ud_dev + (size_t)(depth - 1) * k * k,
+        const DrawMasses m{c->draft_m.mass + row0 * gemm_npad(V), c->draft_m.bsum + row0 * draw_bsum_floats(1, V), c->draft_m.mx + row0,
+                           c->draft_m.pm + row0 * draw_pm_floats(1, V), c->draft_m.z + row0};
+        c->draft_m_temperature = c->temperature;
+        launch_sample_children(dst, g.Npad, rows, V, k, c->temperature, m, c->ud_dev + (size_t)(depth - 1) * k * k,
                                c->topk_id_all, c->topk_logp_all, c->st);
         return;
     }
@@ -741,7 +758,7 @@ int poss_load(const poss_config *cfg, const poss_weights *w, void *workspace, si
         LOAD_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&dev), c->result_pinned_all, 0));
         for (int b = 0; b < c->B; ++b) { c->seq[b].result_pinned = c->result_pinned_all + b * 64; c->seq[b].result_dev = dev + b * 64; }
     }
-    c->temperature = 0.f;
+    c->temperature = 0.f; c->draft_m_temperature = 0.f;
     {
         char *p = static_cast<char *>(c->pinned);
         int32_t *pt = reinterpret_cast<int32_t *>(p);
@@ -898,8 +915,13 @@ static int head_and_choose(poss_ctx *c, const void *x, int rows, bool want_logit
         if (ld_out) *ld_out = g.Npad;
         const poss_config &cf = c->cfg;
         HIP_TRY(c, hipMemcpyAsync(c->ua_dev, c->ua_pinned, (size_t)(cf.depth + 1) * (cf.top_k + 1) * sizeof(float), hipMemcpyHostToDevice, c->st));
-        launch_rejection_walk(c->seq[seq_ids[0]].td, cf.top_k, cf.depth, cf.vocab, c->logits, c->dlogits, g.Npad, c->temperature,
-                              c->ua_dev, c->resid, c->argmax_dev + base, c->st);
+        if (c->draft_m_temperature != c->temperature) {   // changed since the children were drawn: both sides at the present one
+            launch_draft_masses(c->dlogits, g.Npad, 1 + (cf.depth - 1) * cf.top_k, cf.vocab, c->temperature, c->draft_m, c->st);
+            c->draft_m_temperature = c->temperature;
+        }
+        launch_draw_masses(c->logits, g.Npad, rows, cf.vocab, c->temperature, c->target_m, c->st);
+        launch_rejection_walk(c->seq[seq_ids[0]].td, cf.top_k, cf.depth, cf.vocab, c->target_m, c->draft_m, g.Npad, c->ua_dev, c->resid,
+                              c->argmax_dev + base, c->st);
         return POSS_OK;
     }
     if (c->temperature > 0.f) {

@@ -7,15 +7,43 @@ namespace poss {
 template <typename T> __device__ __forceinline__ float to_f(T v) { return (float)v; }
 template <typename T> __device__ __forceinline__ T from_f(float v) { return (T)v; }   // round to nearest even
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+// x of lane l ^ OFF as a second operand: bits 5 and 4 by the row-swap instructions of gfx950 (see rows_max below), the
+// others by DPP.  Nothing goes through the LDS crossbar, as a shuffle would (about 100 cycles a step).  Every lane of the wave
+// must be active.
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ float dpp(float old, float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, x), CTRL, 0xf, BANKS, false));
+}
+// the pairs (x[l], x[l ^ 32]) resp. (x[l], x[l ^ 16]) of a lane, in the order (lower, upper)
+__device__ __forceinline__ void swap32(float x, float &a, float &b) {
+    a = x; b = x;
+    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ void swap16(float x, float &a, float &b) {
+    a = x; b = x;
+    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+}
+__device__ __forceinline__ float xor8(float x) { return dpp<0x128>(x, x); }                          // row_ror:8
+__device__ __forceinline__ float xor4(float x) { return dpp<0x114, 0xa>(dpp<0x104, 0x5>(x, x), x); } // row_shl:4 | row_shr:4
+__device__ __forceinline__ float xor2(float x) { return dpp<0x4e>(x, x); }                           // quad_perm 2 3 0 1
+__device__ __forceinline__ float xor1(float x) { return dpp<0xb1>(x, x); }                           // quad_perm 1 0 3 2
+
+__device__ __forceinline__ float wave_sum(float v) {      // butterfly over 32, 16, .. 1
+    float a, b;
+    swap32(v, a, b); v = a + b;
+    swap16(v, a, b); v = a + b;
+    v += xor8(v); v += xor4(v); v += xor2(v); v += xor1(v);
     return v;
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
+    float a, b;
+    swap32(v, a, b); v = fmaxf(a, b);
+    swap16(v, a, b); v = fmaxf(a, b);
+    v = fmaxf(v, xor8(v)); v = fmaxf(v, xor4(v)); v = fmaxf(v, xor2(v)); v = fmaxf(v, xor1(v));
     return v;
+}
+__device__ __forceinline__ float lane_value(float v, int lane) {       // lane wave-uniform
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
 // Sum over a workgroup of up to 1024 threads, identical in every thread; fixed order.
@@ -91,11 +119,10 @@ __device__ __forceinline__ void block_argmax(float &v, int &i, float *red_v, int
 // register.  (The s_nop covers the wait states a swap needs behind the VALU write of its operands.)
 // Every lane of the wave must be active.
 __device__ __forceinline__ float rows_max(float x) {
-    float a = x, b = x;
-    asm volatile("s_nop 1\n\tv_permlane16_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    float a, b;
+    swap16(x, a, b);
     x = fmaxf(a, b);
-    a = x; b = x;
-    asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
+    swap32(x, a, b);
     return fmaxf(a, b);
 }
 

@@ -292,11 +292,78 @@ bool launch_sample(const float *logits, int ld, int rows, int vocab, float tempe
 }
 
 // ------------------------------------------------------------------ drawn children and the rejection rule
-// Both kernels cut the vocabulary into blocks of 256 ids (one float4 per lane of a wave: coalesced) and find "the first id
-// whose cumulative mass exceeds the target" in two steps: the block (a scan over the block sums), then the id inside it (a
-// scan over the lanes of one wave).  Every sum is formed in one fixed order, so a run is repeatable.
-constexpr int DRAW_THREADS = 1024, DRAW_BLOCK = 256, DRAW_MAX_BLOCKS = 8192;
+// A draw is "the first id whose cumulative mass exceeds u times the total", masses exp((l - max) / T).  The vocabulary is cut
+// into blocks of 256 ids (one float4 per lane of a wave: coalesced); a draw finds the block (a scan over the block sums), then
+// the id inside it (a scan over the lanes of one wave).  Every sum is formed in one fixed order, so a run is repeatable - and the
+// order decides draws (an id of a 128K-entry vocabulary owns 8e-6 of the mass, the rounding of a prefix sum is a tenth of that),
+// so all that follows keeps it: block sums by wave_sum; a scan over the shares of 1024 "threads" (ceil(blocks / 1024) blocks each),
+// 64 at a time, the sixteen totals added one after the other; the drafter's total over its row by the same 1024 threads.
+// Two launches over the whole chip (draw_max_kernel, draw_mass_kernel) leave, per row, the maximum, the masses and the block
+// sums; a draw is one wave's work, with the sixteen scans in registers: no barriers, one trip to memory, and a drawn id changes
+// one scan.  Ten children of ten rows of 128256: 79.5 -> 41.6 us, the two launches of 10 us included (before: one workgroup per row made every pass over it and
+// every step of a draw was a workgroup's).
+constexpr int DRAW_THREADS = 1024, DRAW_BLOCK = 256, DRAW_MAX_BLOCKS = 8192, DRAW_SEG = 4096;
+constexpr int DRAW_UNROLL = 4, DRAW_WAVES = DRAW_THREADS / 64;
 typedef float f32x4e __attribute__((ext_vector_type(4)));
+
+static inline int draw_blocks(int vocab) { return (vocab + DRAW_BLOCK - 1) / DRAW_BLOCK; }
+static inline int draw_segs(int vocab) { return (vocab + DRAW_SEG - 1) / DRAW_SEG; }
+
+// pm[row][seg] = the largest of row[seg * DRAW_SEG ..]
+__global__ __launch_bounds__(256) void draw_max_kernel(const float *__restrict__ logits, int ld, int vocab, int n_seg, float *__restrict__ pm) {
+    __shared__ float red[4];
+    const int seg = blockIdx.x, rowi = blockIdx.y, tid = threadIdx.x;
+    const float *row = logits + (size_t)rowi * ld;
+    float v[DRAW_SEG / 256], mx = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < DRAW_SEG / 256; ++j) {            // requested together, never predicated (a repeated id changes no maximum)
+        const int i = seg * DRAW_SEG + j * 256 + tid;
+        v[j] = row[i < vocab ? i : vocab - 1];
+    }
+#pragma unroll
+    for (int j = 0; j < DRAW_SEG / 256; ++j) mx = fmaxf(mx, v[j]);
+    mx = wave_max(mx);
+    if ((tid & 63) == 0) red[tid >> 6] = mx;
+    __syncthreads();
+    if (tid == 0) pm[(size_t)rowi * n_seg + seg] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+}
+
+// mass[row][id] = exp((l - max) / T) (0 from the vocabulary's end to the row's), bsum[row][block], mx[row]; a wave takes four blocks
+__global__ __launch_bounds__(256) void draw_mass_kernel(const float *__restrict__ logits, int ld, int vocab, int n_seg, int nblk, float inv_t,
+                                                        const float *__restrict__ pm, float *__restrict__ mass, float *__restrict__ bsum,
+                                                        float *__restrict__ mx_out) {
+    const int rowi = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63, b0 = (blockIdx.x * 4 + wave) * 4;
+    const float *row = logits + (size_t)rowi * ld;
+    f32x4e v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int id0 = (b0 + u) * DRAW_BLOCK + lane * 4;
+        v[u] = *reinterpret_cast<const f32x4e *>(row + (id0 + 3 < ld ? id0 : 0));
+    }
+    float mx = -INFINITY;
+    for (int s = lane; s < n_seg; s += 64) mx = fmaxf(mx, pm[(size_t)rowi * n_seg + s]);
+    mx = wave_max(mx);
+    if (b0 == 0 && lane == 0) mx_out[rowi] = mx;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int id0 = (b0 + u) * DRAW_BLOCK + lane * 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[u][j] = id0 + j < vocab ? expf((v[u][j] - mx) * inv_t) : 0.f;
+        if (id0 + 3 < ld) *reinterpret_cast<f32x4e *>(mass + (size_t)rowi * ld + id0) = v[u];
+        const float s = wave_sum(((v[u][0] + v[u][1]) + v[u][2]) + v[u][3]);
+        if (lane == 0 && b0 + u < nblk) bsum[(size_t)rowi * nblk + b0 + u] = s;
+    }
+}
+
+void launch_draw_masses(const float *logits, int ld, int rows, int vocab, float temperature, const DrawMasses &m, hipStream_t st) {
+    const int n_seg = draw_segs(vocab), nblk = draw_blocks(vocab);
+    hipLaunchKernelGGL(draw_max_kernel, dim3(n_seg, rows), dim3(256), 0, st, logits, ld, vocab, n_seg, m.pm);
+    hipLaunchKernelGGL(draw_mass_kernel, dim3((nblk + 15) / 16, rows), dim3(256), 0, st, logits, ld, vocab, n_seg, nblk, 1.0f / temperature,
+                       m.pm, m.mass, m.bsum, m.mx);
+}
+
+size_t draw_pm_floats(int rows, int vocab) { return (size_t)rows * draw_segs(vocab); }
+size_t draw_bsum_floats(int rows, int vocab) { return (size_t)rows * draw_blocks(vocab); }
 
 struct DrawLds {
     float bsum[DRAW_MAX_BLOCKS];       // mass of every block
@@ -360,13 +427,10 @@ __device__ __forceinline__ int find_block(DrawLds &L, int nblk, float u, float *
     return L.i[1] < 0 ? 0 : L.i[1];
 }
 
-// By wave 0: the id inside block b at which the cumulative mass (mass(id), in id order) exceeds `rest`; with rest = +inf or
-// nothing crossing, the last id with mass.  The result goes to L.i[2] (every thread reads it after the barrier that follows).
-template <class Mass>
-__device__ __forceinline__ void pick_in_block(DrawLds &L, int b, float rest, bool take_last, Mass mass) {
-    if (threadIdx.x >= 64) return;
-    const int lane = threadIdx.x;
-    const f32x4e m = mass(b, lane);
+// By one wave: the id inside block b at which the cumulative mass (m: the lane's four ids, in id order) exceeds `rest`; with
+// take_last or nothing crossing, the last id with mass (the block's first if none has any).
+__device__ __forceinline__ int pick_in_block(int b, float rest, bool take_last, f32x4e m) {
+    const int lane = threadIdx.x & 63;
     const float ls = ((m[0] + m[1]) + m[2]) + m[3];
     float incl = ls;
 #pragma unroll
@@ -393,152 +457,192 @@ __device__ __forceinline__ void pick_in_block(DrawLds &L, int b, float rest, boo
     int pick;
     if (crossed) {
         const int src = __ffsll((long long)crossed) - 1;
-        pick = __shfl(mine, src, 64);
+        pick = __builtin_amdgcn_readlane(mine, src);
     } else {
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
         pick = last;
     }
-    if (lane == 0) L.i[2] = pick;
+    return pick < 0 ? b * DRAW_BLOCK : pick;
 }
 
-// the four values row[id] of lane's ids in block b (0 where the row ends)
-__device__ __forceinline__ f32x4e load_ids(const float *row, int ld, int b, int lane) {
+// the masses of lane's four ids of block b, of a row of masses (0 where the row ends)
+__device__ __forceinline__ f32x4e load_masses(const float *mass, int ld, int b, int lane) {
     const int id0 = b * DRAW_BLOCK + lane * 4;
     f32x4e v = f32x4e{0.f, 0.f, 0.f, 0.f};
-    if (id0 + 3 < ld) v = *reinterpret_cast<const f32x4e *>(row + id0);
+    if (id0 + 3 < ld) v = *reinterpret_cast<const f32x4e *>(mass + id0);
     return v;
 }
-// their masses exp((l - mx) * inv_t) (0 beyond the vocabulary)
-__device__ __forceinline__ f32x4e masses_of(f32x4e v, int vocab, int b, int lane, float mx, float inv_t) {
-    const int id0 = b * DRAW_BLOCK + lane * 4;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) v[j] = id0 + j < vocab ? expf((v[j] - mx) * inv_t) : 0.f;
-    return v;
-}
-// the four masses exp((row[id] - mx) * inv_t) of lane's ids in block b
-__device__ __forceinline__ f32x4e exp_masses(const float *row, int ld, int vocab, int b, int lane, float mx, float inv_t) {
-    return masses_of(load_ids(row, ld, b, lane), vocab, b, lane, mx, inv_t);
-}
-// A wave walks the blocks wave, wave + 16, ...: DRAW_UNROLL of them at a time, their loads asked for together (one block
-// after the other, each load waited for, the walk over a 128K-entry row is 31 trips to memory in a row).
-constexpr int DRAW_UNROLL = 4, DRAW_WAVES = DRAW_THREADS / 64;
 
-__device__ __forceinline__ float draw_block_max(float v, DrawLds &L) {
-    v = wave_max(v);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) L.red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    float m = L.red[0];
-    for (int w = 1; w < DRAW_THREADS / 64; ++w) m = fmaxf(m, L.red[w]);
-    return m;
-}
-
-// the largest of row[0 .. vocab)
-__device__ __forceinline__ float row_max(const float *row, int ld, int vocab, int nblk, DrawLds &L) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    float mx = -INFINITY;
-    for (int b0 = wave; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
-        f32x4e v[DRAW_UNROLL];
+// One workgroup per row: wave 0 draws k ids without replacement; the others sum the row meanwhile (z: the total the rejection
+// walk divides by), as block_sum over all sixteen would: wave 1 takes the share of wave 0 besides its own.
+__global__ __launch_bounds__(DRAW_THREADS) void sample_children_kernel(const float *__restrict__ logits, int ld, int vocab, int nblk, int k,
+                                                                       float inv_t, DrawMasses dm, const float *__restrict__ u,
+                                                                       int32_t *__restrict__ out_id, float *__restrict__ out_logp) {
+    __shared__ float bsum[DRAW_MAX_BLOCKS];
+    __shared__ float red[17];
+    const int rowi = blockIdx.x, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    const float *mass = dm.mass + (size_t)rowi * ld;
+    const int per = (nblk + DRAW_THREADS - 1) / DRAW_THREADS;
+    if (wave == 0) {
+        const float uu = lane < k ? u[rowi * k + lane] : 0.f, mx = dm.mx[rowi];
+        for (int b = lane; b < nblk; b += 64) bsum[b] = dm.bsum[(size_t)rowi * nblk + b];
+        __builtin_amdgcn_wave_barrier();
+        // share t = blocks [t per, (t + 1) per); lane l of scan w has share 64 w + l: sh its sum, sc the inclusive scan over the 64
+        auto share = [&](int t) {
+            float s = 0.f;
+            for (int b = t * per; b < min(nblk, (t + 1) * per); ++b) s += bsum[b];
+            return s;
+        };
+        auto scan = [&](float v) {
 #pragma unroll
-        for (int u = 0; u < DRAW_UNROLL; ++u) v[u] = load_ids(row, ld, min(b0 + u * DRAW_WAVES, nblk - 1), lane);
+            for (int o = 1; o < 64; o <<= 1) {
+                const float t = __shfl_up(v, o, 64);
+                if (lane >= o) v += t;
+            }
+            return v;
+        };
+        float sh[DRAW_WAVES], sc[DRAW_WAVES];
 #pragma unroll
-        for (int u = 0; u < DRAW_UNROLL; ++u) {
-            const int b = b0 + u * DRAW_WAVES, id0 = b * DRAW_BLOCK + lane * 4;
-            if (b < nblk && id0 + 3 < ld) {
+        for (int w = 0; w < DRAW_WAVES; ++w) { sh[w] = share(w * 64 + lane); sc[w] = scan(sh[w]); }
+        int mine = 0;                                     // lane j < k: the j-th id drawn
+        float log_z = 0.f;
+        for (int d = 0; d < k; ++d) {
+            float off[DRAW_WAVES + 1];
+            off[0] = 0.f;
 #pragma unroll
-                for (int j = 0; j < 4; ++j) if (id0 + j < vocab) mx = fmaxf(mx, v[u][j]);
+            for (int w = 0; w < DRAW_WAVES; ++w) off[w + 1] = off[w] + lane_value(sc[w], 63);
+            const float total = off[DRAW_WAVES], target = lane_value(uu, d) * total;
+            if (d == 0) log_z = logf(total);              // the normaliser of the full distribution
+            // the scan that holds the target, the share inside it, the block inside the share
+            int b = -1, w_hit = -1;
+            float before = -INFINITY;
+#pragma unroll
+            for (int w = 0; w < DRAW_WAVES; ++w) {
+                if (w_hit >= 0 || !(off[w] <= target && target < off[w + 1])) continue;      // (wave-uniform)
+                const float incl = sc[w] + off[w];
+                float prev = __shfl_up(incl, 1, 64);
+                if (lane == 0) prev = off[w];
+                const unsigned long long hit = __ballot(sh[w] > 0.f && prev <= target && target < incl);
+                if (!hit) continue;
+                w_hit = w;
+                const int l = __ffsll((long long)hit) - 1, t = w * 64 + l;
+                before = lane_value(prev, l);
+                int last_mass = -1;
+                for (int x = t * per; x < min(nblk, (t + 1) * per); ++x) if (bsum[x] > 0.f) last_mass = x;
+                for (int x = t * per; x < min(nblk, (t + 1) * per); ++x) {
+                    const float m = bsum[x];
+                    if (m > 0.f && (before + m > target || x == last_mass)) { b = x; break; }
+                    before += m;
+                }
+            }
+            if (b < 0) {                                  // rounding pushed the target past the total: the last block with mass
+                before = -INFINITY;
+                int last = 0;
+                for (int x = lane; x < nblk; x += 64) if (bsum[x] > 0.f) last = x;
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
+                b = last;
+            }
+            f32x4e m = load_masses(mass, ld, b, lane);    // without the ids already drawn
+            const int id0 = b * DRAW_BLOCK + lane * 4;
+            for (int j = 0; j < d; ++j) {
+                const int r = __builtin_amdgcn_readlane(mine, j) - id0;
+#pragma unroll
+                for (int x = 0; x < 4; ++x) if (r == x) m[x] = 0.f;
+            }
+            const int c = pick_in_block(b, target - before, before == -INFINITY, m);
+            if (lane == d) mine = c;
+#pragma unroll
+            for (int x = 0; x < 4; ++x) if (c - id0 == x) m[x] = 0.f;
+            const float s = wave_sum(((m[0] + m[1]) + m[2]) + m[3]);      // the block's mass without the id just drawn, formed afresh
+            if (lane == 0) bsum[b] = s;
+            __builtin_amdgcn_wave_barrier();
+            const int t = b / per;
+#pragma unroll
+            for (int w = 0; w < DRAW_WAVES; ++w)
+                if (t >> 6 == w) {                        // (wave-uniform)
+                    if (lane == (t & 63)) sh[w] = share(t);
+                    sc[w] = scan(sh[w]);
+                }
+        }
+        if (lane < k) {
+            out_id[rowi * k + lane] = mine;
+            out_logp[rowi * k + lane] = (logits[(size_t)rowi * ld + mine] - mx) * inv_t - log_z;
+        }
+    }
+    auto share_of = [&](int w) {
+        float sq = 0.f;
+        for (int b0 = w; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
+            f32x4e v[DRAW_UNROLL];
+#pragma unroll
+            for (int x = 0; x < DRAW_UNROLL; ++x) v[x] = load_masses(mass, ld, min(b0 + x * DRAW_WAVES, nblk - 1), lane);
+#pragma unroll
+            for (int x = 0; x < DRAW_UNROLL; ++x) {
+                if (b0 + x * DRAW_WAVES >= nblk) break;   // wave-uniform
+                sq += ((v[x][0] + v[x][1]) + v[x][2]) + v[x][3];
             }
         }
-    }
-    return draw_block_max(mx, L);
-}
-
-__global__ __launch_bounds__(DRAW_THREADS) void sample_children_kernel(const float *__restrict__ logits, int ld, int vocab, int k,
-                                                                       float inv_t, const float *__restrict__ u,
-                                                                       int32_t *__restrict__ out_id, float *__restrict__ out_logp) {
-    __shared__ DrawLds L;
-    const int rowi = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const float *row = logits + (size_t)rowi * ld;
-    const int nblk = (vocab + DRAW_BLOCK - 1) / DRAW_BLOCK;
-    const float mx = row_max(row, ld, vocab, nblk, L);
-    // masses of a block without the ids already drawn (n_removed of them)
-    auto masses = [&](int b, int ln, int n_removed) {
-        f32x4e m = exp_masses(row, ld, vocab, b, ln, mx, inv_t);
-        const int id0 = b * DRAW_BLOCK + ln * 4;
-        for (int j = 0; j < n_removed; ++j) {
-            const int r = L.removed[j] - id0;
-            if (r >= 0 && r < 4) m[r] = 0.f;
-        }
-        return m;
+        sq = wave_sum(sq);
+        if (lane == 0) red[w] = sq;
     };
-    for (int b0 = wave; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
-        f32x4e v[DRAW_UNROLL];
-#pragma unroll
-        for (int u = 0; u < DRAW_UNROLL; ++u) v[u] = load_ids(row, ld, min(b0 + u * DRAW_WAVES, nblk - 1), lane);
-#pragma unroll
-        for (int u = 0; u < DRAW_UNROLL; ++u) {
-            const int b = b0 + u * DRAW_WAVES;
-            if (b >= nblk) break;                         // wave-uniform
-            const f32x4e m = masses_of(v[u], vocab, b, lane, mx, inv_t);
-            const float s = wave_sum(((m[0] + m[1]) + m[2]) + m[3]);
-            if (lane == 0) L.bsum[b] = s;
-        }
-    }
+    if (wave > 0) share_of(wave);
+    if (wave == 1) share_of(0);
     __syncthreads();
-    float log_z = 0.f;
-    for (int d = 0; d < k; ++d) {
-        float before, total;
-        const int b = find_block(L, nblk, u[rowi * k + d], &before, &total);
-        if (d == 0) log_z = logf(total);                  // the normaliser of the full distribution
-        const float target = u[rowi * k + d] * total;
-        pick_in_block(L, b, target - before, before == -INFINITY, [&](int bb, int ln) { return masses(bb, ln, d); });
-        __syncthreads();
-        const int c = L.i[2];
-        if (tid == 0) {
-            L.removed[d] = c;
-            out_id[rowi * k + d] = c;
-            out_logp[rowi * k + d] = (row[c] - mx) * inv_t - log_z;
-        }
-        __syncthreads();
-        if (wave == 0) {                                  // the block's mass without the id just drawn, formed afresh
-            const f32x4e m = masses(b, lane, d + 1);
-            const float s = wave_sum(((m[0] + m[1]) + m[2]) + m[3]);
-            if (lane == 0) L.bsum[b] = s;
-        }
-        __syncthreads();
+    if (tid == 0) {
+        float z = 0.f;
+        for (int w = 0; w < DRAW_WAVES; ++w) z += red[w];
+        dm.z[rowi] = z;
     }
 }
 
-void launch_sample_children(const float *logits, int ld, int rows, int vocab, int k, float temperature, const float *u,
+void launch_sample_children(const float *logits, int ld, int rows, int vocab, int k, float temperature, const DrawMasses &m, const float *u,
                             int32_t *out_id, float *out_logp, hipStream_t st) {
-    hipLaunchKernelGGL(sample_children_kernel, dim3(rows), dim3(DRAW_THREADS), 0, st, logits, ld, vocab, k, 1.0f / temperature, u,
-                       out_id, out_logp);
+    launch_draw_masses(logits, ld, rows, vocab, temperature, m, st);
+    hipLaunchKernelGGL(sample_children_kernel, dim3(rows), dim3(DRAW_THREADS), 0, st, logits, ld, vocab, draw_blocks(vocab), k, 1.0f / temperature,
+                       m, u, out_id, out_logp);
 }
 
-__global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td, int k, int L_depth, int vocab,
-                                                                      const float *__restrict__ target_logits,
-                                                                      const float *__restrict__ draft_logits, int ld, float inv_t,
-                                                                      const float *__restrict__ ua, float *__restrict__ resid,
-                                                                      int32_t *__restrict__ g) {
+// the masses and totals alone (no draws)
+void launch_draft_masses(const float *logits, int ld, int rows, int vocab, float temperature, const DrawMasses &m, hipStream_t st) {
+    launch_sample_children(logits, ld, rows, vocab, 0, temperature, m, nullptr, nullptr, nullptr, st);
+}
+
+// x / z with y = 1 / z (rounded to nearest), rounded to nearest as the division is: one correction makes the quotient faithful,
+// the second, its remainder exact, rounds it (Markstein).  Five operations where the compiler's division takes about ten; below
+// 2.4e-38, where the remainders underflow, the last bit may differ.
+__device__ __forceinline__ float quotient(float x, float z, float y) {
+    float q = x * y;
+    q = fmaf(fmaf(-q, z, x), y, q);
+    return fmaf(fmaf(-q, z, x), y, q);
+}
+
+// The walk, one workgroup.  The masses of the target's rows and the drafter's are there (draw_mass_kernel), so a rejection is one
+// pass that reads two rows, P and Q, and writes the residual with its block sums (before: two exponentials and two divisions per
+// id as well, and four passes per node for maxima and totals).  One round over 128256 ids: 401 -> 41 us, and 16 for the masses of
+// the tree's 61 rows.
+__global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td, int k, int L_depth, int vocab, int nblk, DrawMasses target,
+                                                                      DrawMasses draft, int ld, const float *__restrict__ ua,
+                                                                      float *__restrict__ resid, int32_t *__restrict__ g) {
     __shared__ DrawLds L;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    const int nblk = (vocab + DRAW_BLOCK - 1) / DRAW_BLOCK;
-    auto resid_masses = [&](int b, int ln) {
-        const int id0 = b * DRAW_BLOCK + ln * 4;
-        f32x4e v = f32x4e{0.f, 0.f, 0.f, 0.f};
-        if (id0 + 3 < ld) v = *reinterpret_cast<const f32x4e *>(resid + id0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) if (id0 + j >= vocab) v[j] = 0.f;
-        return v;
+    // a token from the block sums in L.bsum: found by all threads, picked by wave 0, given to every thread
+    auto draw_token = [&](float un, const float *mass) {
+        float before, total;
+        const int b = find_block(L, nblk, un, &before, &total);
+        if (wave == 0) {
+            const int c = pick_in_block(b, un * total - before, before == -INFINITY, load_masses(mass, ld, b, lane));
+            if (lane == 0) L.i[2] = c;
+        }
+        __syncthreads();
+        return L.i[2];
     };
     const int n_nodes = td.n_nodes[0];
     for (int i = tid; i < n_nodes; i += DRAW_THREADS) g[i] = -1;
     int cur = 0;
     for (int step = 0; step <= L_depth; ++step) {         // at most L accepted children, then the last token
         const int d = td.depth[cur];
-        const float *prow = target_logits + (size_t)cur * ld;
-        const float mp = row_max(prow, ld, vocab, nblk, L);
+        const float *P = target.mass + (size_t)cur * ld;
         // which drafter row expanded this node, and where its drawn children sit in the pool
         int e = -1, cbase = 0;
         if (cur == 0) { e = 0; cbase = 0; }
@@ -547,55 +651,23 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
             for (int r = 0; r < k; ++r)
                 if (td.fr_pool[d * k + r] == pv) { e = 1 + (d - 1) * k + r; cbase = k + (d - 1) * k * k + r * k; }
         }
-        // block sums of the target's masses P = exp((l - max) / T); zp = their total (p = P / zp)
-        for (int b0 = wave; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
-            f32x4e v[DRAW_UNROLL];
-#pragma unroll
-            for (int u = 0; u < DRAW_UNROLL; ++u) v[u] = load_ids(prow, ld, min(b0 + u * DRAW_WAVES, nblk - 1), lane);
-#pragma unroll
-            for (int u = 0; u < DRAW_UNROLL; ++u) {
-                const int b = b0 + u * DRAW_WAVES;
-                if (b >= nblk) break;                     // wave-uniform
-                const f32x4e m = masses_of(v[u], vocab, b, lane, mp, inv_t);
-                const float s = wave_sum(((m[0] + m[1]) + m[2]) + m[3]);
-                if (lane == 0) L.bsum[b] = s;
-            }
-        }
+        for (int b = tid; b < nblk; b += DRAW_THREADS) L.bsum[b] = target.bsum[(size_t)cur * nblk + b];
         __syncthreads();
         if (e < 0) {                                      // no drawn children: the target's own token ends the walk
-            float before, total;
-            const float un = ua[d * (k + 1) + k];
-            const int b = find_block(L, nblk, un, &before, &total);
-            pick_in_block(L, b, un * total - before, before == -INFINITY,
-                          [&](int bb, int ln) { return exp_masses(prow, ld, vocab, bb, ln, mp, inv_t); });
-            __syncthreads();
-            if (tid == 0) g[cur] = L.i[2];
+            const int c = draw_token(ua[d * (k + 1) + k], P);
+            if (tid == 0) g[cur] = c;
             return;
         }
-        float before_unused, zp;
+        float before_unused, zp;                          // zp: the total of P (p = P / zp)
         (void)find_block(L, nblk, 0.f, &before_unused, &zp);
-        const float *qrow = draft_logits + (size_t)e * ld;
-        const float mq = row_max(qrow, ld, vocab, nblk, L);
-        float sq = 0.f;                                   // zq: total of the drafter's masses, same block order
-        for (int b0 = wave; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
-            f32x4e v[DRAW_UNROLL];
-#pragma unroll
-            for (int u = 0; u < DRAW_UNROLL; ++u) v[u] = load_ids(qrow, ld, min(b0 + u * DRAW_WAVES, nblk - 1), lane);
-#pragma unroll
-            for (int u = 0; u < DRAW_UNROLL; ++u) {
-                const int b = b0 + u * DRAW_WAVES;
-                if (b >= nblk) break;                     // wave-uniform
-                const f32x4e m = masses_of(v[u], vocab, b, lane, mq, inv_t);
-                sq += ((m[0] + m[1]) + m[2]) + m[3];
-            }
-        }
-        float zq = block_sum(sq, L.red);
+        const float *Q = draft.mass + (size_t)e * ld;
+        float zq = draft.z[e];
         bool have_resid = false;
         int next = -1, last_tok = -1;
         for (int i = 0; i < k; ++i) {
             const int c = td.pool_token[cbase + i];
-            const float pc = (have_resid ? resid[c] : expf((prow[c] - mp) * inv_t)) / zp;
-            const float ec = expf((qrow[c] - mq) * inv_t), qc = ec / zq;
+            const float pc = (have_resid ? resid[c] : P[c]) / zp;
+            const float ec = Q[c], qc = ec / zq;
             const float a = fminf(1.f, pc / qc);
             if (ua[d * (k + 1) + i] < a) {                // accepted (every thread takes the same decision)
                 const int node = td.pool_node[cbase + i];
@@ -605,34 +677,29 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
             }
             // rejected: P <- max(P / zp - Q / zq, 0) with its block sums, zp <- their total; the candidate leaves q
             __syncthreads();                              // resid[c] has been read by every thread
+            const float *from = have_resid ? resid : P;
+            const float yp = 1.0f / zp, yq = 1.0f / zq;
             for (int b0 = wave; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
                 f32x4e pv[DRAW_UNROLL], qv[DRAW_UNROLL];
 #pragma unroll
-                for (int u = 0; u < DRAW_UNROLL; ++u) {
-                    const int b = min(b0 + u * DRAW_WAVES, nblk - 1);
-                    pv[u] = load_ids(have_resid ? resid : prow, ld, b, lane);
-                    qv[u] = load_ids(qrow, ld, b, lane);
+                for (int x = 0; x < DRAW_UNROLL; ++x) {
+                    const int b = min(b0 + x * DRAW_WAVES, nblk - 1);
+                    pv[x] = load_masses(from, ld, b, lane);
+                    qv[x] = load_masses(Q, ld, b, lane);
                 }
 #pragma unroll
-                for (int u = 0; u < DRAW_UNROLL; ++u) {
-                    const int b = b0 + u * DRAW_WAVES;
+                for (int x = 0; x < DRAW_UNROLL; ++x) {
+                    const int b = b0 + x * DRAW_WAVES;
                     if (b >= nblk) break;                 // wave-uniform
                     const int id0 = b * DRAW_BLOCK + lane * 4;
-                    f32x4e pm = pv[u];
-                    if (have_resid) {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) if (id0 + j >= vocab) pm[j] = 0.f;
-                    } else {
-                        pm = masses_of(pm, vocab, b, lane, mp, inv_t);
-                    }
-                    f32x4e qm = masses_of(qv[u], vocab, b, lane, mq, inv_t);
+                    f32x4e qm = qv[x];
                     for (int j = 0; j < i; ++j) {
                         const int r = L.removed[j] - id0;
                         if (r >= 0 && r < 4) qm[r] = 0.f;
                     }
                     f32x4e r4;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) r4[j] = fmaxf(pm[j] / zp - qm[j] / zq, 0.f);
+                    for (int j = 0; j < 4; ++j) r4[j] = fmaxf(quotient(pv[x][j], zp, yp) - quotient(qm[j], zq, yq), 0.f);
                     if (id0 + 3 < ld) *reinterpret_cast<f32x4e *>(resid + id0) = r4;
                     const float s = wave_sum(((r4[0] + r4[1]) + r4[2]) + r4[3]);
                     if (lane == 0) L.bsum[b] = s;
@@ -646,21 +713,17 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
         }
         if (next >= 0) { cur = next; continue; }
         if (last_tok < 0) {                               // every candidate rejected: draw from the last residual
-            float before, total;
-            const float un = ua[d * (k + 1) + k];
-            const int b = find_block(L, nblk, un, &before, &total);
-            pick_in_block(L, b, un * total - before, before == -INFINITY, resid_masses);
-            __syncthreads();
-            if (tid == 0) g[cur] = L.i[2];
+            const int c = draw_token(ua[d * (k + 1) + k], resid);
+            if (tid == 0) g[cur] = c;
         }
         return;
     }
 }
 
-void launch_rejection_walk(const TreeDev &td, int k, int L, int vocab, const float *target_logits, const float *draft_logits,
-                           int ld, float temperature, const float *ua, float *resid, int32_t *g, hipStream_t st) {
-    hipLaunchKernelGGL(rejection_walk_kernel, dim3(1), dim3(DRAW_THREADS), 0, st, td, k, L, vocab, target_logits, draft_logits, ld,
-                       1.0f / temperature, ua, resid, g);
+void launch_rejection_walk(const TreeDev &td, int k, int L, int vocab, const DrawMasses &target, const DrawMasses &draft, int ld,
+                           const float *ua, float *resid, int32_t *g, hipStream_t st) {
+    hipLaunchKernelGGL(rejection_walk_kernel, dim3(1), dim3(DRAW_THREADS), 0, st, td, k, L, vocab, draw_blocks(vocab), target, draft, ld, ua,
+                       resid, g);
 }
 
 __global__ void copy_rows_f32_kernel(const float *__restrict__ src, int ld_src, float *__restrict__ dst, int ld_dst,
