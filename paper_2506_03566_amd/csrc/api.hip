@@ -50,6 +50,8 @@ struct Seq {
     int32_t *tree_slot, *tokens_dev, *walk_dev;
     void *feat_stash, *xin_tmp;
     int32_t *result_pinned, *result_dev;   // the commit kernel's result: host memory and its device address
+    TreeHost *tree_host, *tree_host_dev;   // the drafted tree as tree_finalize_kernel leaves it there, likewise
+    int tree_on_host;                      // ... and it is the present one
     int t, tree_ready, tree_n, tree_row0, prefilled;   // tree_row0: first row of its tree in the batch-wide arrays
     int active;                        // takes part in the rounds (poss_set_active)
     std::vector<int32_t> tokens;
@@ -91,6 +93,9 @@ struct poss_ctx {
     int state;
     poss_stats stats;
     void *pinned; size_t pinned_bytes;
+    int32_t *pinned_dev;               // its device address
+    TreeHost *tree_host_all;
+    int32_t *argmax_host, *argmax_host_dev;   // the chosen tokens of the first rows, written by the kernel that chooses them
     int32_t *result_pinned_all;
     hipEvent_t ev[6];                  // begin/end of the draft, verify and commit phases
     bool ev_pending[3];                // phase recorded, elapsed time not yet added to the statistics
@@ -594,19 +599,6 @@ void spec_catchup(poss_ctx *c, int b, int s, int upto) {
     }
 }
 
-int copy_tree_out(poss_ctx *c, Seq &sq, poss_tree *out) {
-    const int n = sq.tree_n;
-    out->n_nodes = n;
-    struct { void *dst; const void *src; size_t b; } cp[] = {
-        {out->token, sq.td.token, n * sizeof(int32_t)}, {out->parent, sq.td.parent, n * sizeof(int32_t)},
-        {out->depth, sq.td.depth, n * sizeof(int32_t)}, {out->pos, sq.td.pos, n * sizeof(int32_t)},
-        {out->mask, sq.td.mask, (size_t)n * MASK_WORDS * sizeof(uint64_t)}, {out->score, sq.td.score, n * sizeof(float)}};
-    for (auto &x : cp)
-        if (x.dst) HIP_TRY(c, hipMemcpyAsync(x.dst, x.src, x.b, hipMemcpyDeviceToHost, c->st));
-    HIP_TRY(c, hipStreamSynchronize(c->st));
-    return POSS_OK;
-}
-
 void pack_layer(poss_ctx *c, const void *const *src, const std::vector<void *> &dst, size_t base) {
     const poss_config &cf = c->cfg;
     const int dt = cf.dtype, d = cf.d_model, qd = cf.n_q_heads * cf.head_dim, kd = cf.n_kv_heads * cf.head_dim, F = cf.d_ffn;
@@ -631,6 +623,7 @@ void point_tree(poss_ctx *c, Seq &sq, int row0) {
     sq.td.depth = c->tree_depth_all + row0; sq.td.pos = c->tree_pos_all + row0;
     sq.td.mask = c->tree_mask_all + (size_t)row0 * MASK_WORDS; sq.td.score = c->tree_score_all + row0;
     sq.tree_slot = c->tree_slot_all + row0;
+    sq.tree_on_host = 0;
 }
 
 void reset_sequence(poss_ctx *c) {
@@ -672,6 +665,8 @@ void release_host(poss_ctx *c) {
     if (c->ud_pinned) (void)hipHostFree(c->ud_pinned);
     if (c->ua_pinned) (void)hipHostFree(c->ua_pinned);
     if (c->result_pinned_all) (void)hipHostFree(c->result_pinned_all);
+    if (c->tree_host_all) (void)hipHostFree(c->tree_host_all);
+    if (c->argmax_host) (void)hipHostFree(c->argmax_host);
 }
 
 }  // namespace
@@ -757,6 +752,13 @@ int poss_load(const poss_config *cfg, const poss_weights *w, void *workspace, si
         int32_t *dev = nullptr;
         LOAD_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&dev), c->result_pinned_all, 0));
         for (int b = 0; b < c->B; ++b) { c->seq[b].result_pinned = c->result_pinned_all + b * 64; c->seq[b].result_dev = dev + b * 64; }
+        LOAD_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->pinned_dev), c->pinned, 0));
+        LOAD_TRY(hipHostMalloc(reinterpret_cast<void **>(&c->tree_host_all), (size_t)c->B * sizeof(TreeHost), hipHostMallocDefault));
+        TreeHost *td = nullptr;
+        LOAD_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&td), c->tree_host_all, 0));
+        for (int b = 0; b < c->B; ++b) { c->seq[b].tree_host = c->tree_host_all + b; c->seq[b].tree_host_dev = td + b; c->seq[b].tree_on_host = 0; }
+        LOAD_TRY(hipHostMalloc(reinterpret_cast<void **>(&c->argmax_host), LAUNCH_ROWS * sizeof(int32_t), hipHostMallocDefault));
+        LOAD_TRY(hipHostGetDevicePointer(reinterpret_cast<void **>(&c->argmax_host_dev), c->argmax_host, 0));
     }
     c->temperature = 0.f; c->draft_m_temperature = 0.f;
     {
@@ -882,8 +884,8 @@ int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_
         }
         HIP_TRY(c, hipStreamSynchronize(c->st));          // the staging buffer is reused by the next chunk
     }
-    int32_t first = 0;
-    HIP_TRY(c, hipMemcpy(&first, c->argmax_dev, sizeof(int32_t), hipMemcpyDeviceToHost));
+    int32_t first = c->argmax_host[0];                    // (the stream has been waited for)
+    if (c->temperature > 0.f) HIP_TRY(c, hipMemcpy(&first, c->argmax_dev, sizeof(int32_t), hipMemcpyDeviceToHost));
     sq.tokens.assign(prompt, prompt + n_prompt);
     sq.tokens.push_back(first);
     sq.t = n_prompt;
@@ -939,11 +941,12 @@ static int head_and_choose(poss_ctx *c, const void *x, int rows, bool want_logit
     int n_seg = 0;
     const GemmShape g = run_head(c, rows, HEAD_ARGMAX, want_logits, &n_seg, x);
     if (ld_out) *ld_out = g.Npad;
+    int32_t *host = base == 0 ? c->argmax_host_dev : nullptr;     // (at most LAUNCH_ROWS rows)
     if (n_seg)
         launch_argmax_merge(c->topk_scratch, reinterpret_cast<const int *>(c->topk_scratch + (size_t)rows * n_seg), n_seg, rows,
-                            c->argmax_dev + base, c->st);
+                            c->argmax_dev + base, host, c->st);
     else
-        launch_argmax(c->logits, g.Npad, rows, c->cfg.vocab, c->topk_scratch, c->argmax_dev + base, c->st);
+        launch_argmax(c->logits, g.Npad, rows, c->cfg.vocab, c->topk_scratch, c->argmax_dev + base, host, c->st);
     return POSS_OK;
 }
 
@@ -960,6 +963,25 @@ static int sync_and_harvest(poss_ctx *c) {
         if (hipEventElapsedTime(&ms, c->ev[2 * i], c->ev[2 * i + 1]) == hipSuccess) *acc[i] += ms;
         c->ev_pending[i] = false;
     }
+    return POSS_OK;
+}
+
+// The tree of a sequence for the caller; waits for the stream.
+static int copy_tree_out(poss_ctx *c, Seq &sq, poss_tree *out) {
+    const int n = sq.tree_n;
+    out->n_nodes = n;
+    const TreeHost *h = sq.tree_host;
+    struct { void *dst; const void *src, *host; size_t b; } cp[] = {
+        {out->token, sq.td.token, h->token, n * sizeof(int32_t)}, {out->parent, sq.td.parent, h->parent, n * sizeof(int32_t)},
+        {out->depth, sq.td.depth, h->depth, n * sizeof(int32_t)}, {out->pos, sq.td.pos, h->pos, n * sizeof(int32_t)},
+        {out->mask, sq.td.mask, h->mask, (size_t)n * MASK_WORDS * sizeof(uint64_t)}, {out->score, sq.td.score, h->score, n * sizeof(float)}};
+    if (!sq.tree_on_host)
+        for (auto &x : cp)
+            if (x.dst) HIP_TRY(c, hipMemcpyAsync(x.dst, x.src, x.b, hipMemcpyDeviceToHost, c->st));
+    { int rc = sync_and_harvest(c); if (rc) return rc; }
+    if (sq.tree_on_host)                                   // a drafted tree: the kernel that finished it wrote it to host memory
+        for (auto &x : cp)
+            if (x.dst) memcpy(x.dst, x.host, x.b);
     return POSS_OK;
 }
 
@@ -1071,30 +1093,28 @@ int poss_draft_tree(poss_ctx *c, poss_tree *out) {
         int ts[8];
         const int32_t *toks[8];
         int32_t *slots[8];
+        TreeHost *hosts[8];
         for (int i = 0; i < B; ++i) {
             Seq &sq = c->seq[act[i]];
             tds[i] = sq.td; ts[i] = sq.t; toks[i] = sq.tokens_dev; slots[i] = sq.tree_slot;
+            hosts[i] = sq.tree_host_dev; sq.tree_on_host = 1;
             sq.tree_n = (cf.total_tokens < pool ? cf.total_tokens : pool) + 1;
             sq.tree_ready = 1;
         }
-        launch_tree_finalize(tds, B, k, L, cf.total_tokens, ts, toks, slots, c->st);
+        launch_tree_finalize(tds, B, k, L, cf.total_tokens, ts, toks, slots, hosts, c->st);
     }
     (void)hipEventRecord(c->ev[1], c->st);
     c->ev_pending[0] = true;
     HIP_TRY(c, hipGetLastError());
     if (!out) return POSS_OK;                    // nothing for the host: the work stays queued
-    int rc = copy_tree_out(c, c->seq[all[0]], out);             // the first active sequence's
-    if (rc) return rc;
-    return sync_and_harvest(c);
+    return copy_tree_out(c, c->seq[all[0]], out);               // the first active sequence's
 }
 
 int poss_get_tree_seq(poss_ctx *c, int32_t seq, poss_tree *out) {
     if (!c || !out) return POSS_E_INVALID_ARG;
     if (seq < 0 || seq >= c->B) return fail(c, POSS_E_INVALID_ARG, "poss_get_tree_seq: no sequence %d (batch %d)", seq, c->B);
     if (!c->seq[seq].tree_ready) return fail(c, POSS_E_BAD_STATE, "poss_get_tree_seq: no drafted tree");
-    int rc = copy_tree_out(c, c->seq[seq], out);
-    if (rc) return rc;
-    return sync_and_harvest(c);
+    return copy_tree_out(c, c->seq[seq], out);
 }
 
 int poss_debug_build_tree(poss_ctx *c, const int32_t *ids, const float *logp, poss_tree *out) {
@@ -1116,7 +1136,8 @@ int poss_debug_build_tree(poss_ctx *c, const int32_t *ids, const float *logp, po
     }
     {
         const int32_t *toks = sq.tokens_dev;
-        launch_tree_finalize(&sq.td, 1, k, L, cf.total_tokens, &sq.t, &toks, &sq.tree_slot, c->st);
+        launch_tree_finalize(&sq.td, 1, k, L, cf.total_tokens, &sq.t, &toks, &sq.tree_slot, &sq.tree_host_dev, c->st);
+        sq.tree_on_host = 1;
     }
     const int pool = k + (L - 1) * k * k;
     sq.tree_n = (cf.total_tokens < pool ? cf.total_tokens : pool) + 1;
@@ -1170,8 +1191,9 @@ int poss_verify_tree(poss_ctx *c, const poss_tree *tree, int32_t *argmax_out, vo
         return fail(c, POSS_E_BAD_STATE, "poss_verify_tree: with drawn children only the drafted tree can be verified (a caller's tree has no draft distributions)");
     (void)hipEventRecord(c->ev[2], c->st);
     if (tree) {
-        int32_t *stage = static_cast<int32_t *>(c->pinned);      // [tokens | parents | node counts]
+        int32_t *stage = static_cast<int32_t *>(c->pinned);      // [tokens | parents], read by the kernel where they are
         const int RA = c->rows_all;
+        TreeUpload ups[8];
         for (int i = 0; i < B; ++i) {
             const int b = act[i];
             Seq &sq = c->seq[b];
@@ -1180,13 +1202,11 @@ int poss_verify_tree(poss_ctx *c, const poss_tree *tree, int32_t *argmax_out, vo
             memcpy(stage + row0[i], tree[b].token, n * sizeof(int32_t));
             stage[row0[i]] = sq.tokens[t];                        // the root is always x_t
             memcpy(stage + RA + row0[i], tree[b].parent, n * sizeof(int32_t));
-            stage[2 * RA + i] = n;
-            HIP_TRY(c, hipMemcpyAsync(sq.td.token, stage + row0[i], n * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
-            HIP_TRY(c, hipMemcpyAsync(sq.td.parent, stage + RA + row0[i], n * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
-            HIP_TRY(c, hipMemcpyAsync(sq.td.n_nodes, stage + 2 * RA + i, sizeof(int32_t), hipMemcpyHostToDevice, c->st));
-            launch_tree_upload_finish(n, t, sq.td.token, sq.td.parent, sq.td.depth, sq.td.pos, sq.tree_slot, sq.td.mask, c->st);
+            ups[i] = TreeUpload{c->pinned_dev + row0[i], c->pinned_dev + RA + row0[i], n, t, sq.td.token, sq.td.parent, sq.td.depth,
+                                sq.td.pos, sq.tree_slot, sq.td.n_nodes, sq.td.mask};
             sq.tree_n = n; sq.tree_ready = 1;
         }
+        launch_tree_upload(ups, B, c->st);
     }                                     // (a drafted tree's slots were written when it was finalized)
     // The trees' rows are adjacent slices of the batch-wide arrays: one pass over all of them, or, when they
     // are more than a launch carries, one pass per group of sequences (the rows of a group are adjacent too;
@@ -1206,20 +1226,26 @@ int poss_verify_tree(poss_ctx *c, const poss_tree *tree, int32_t *argmax_out, vo
         target_forward(c, grows, c->tree_token_all + base, rm, segs, c->feats + (size_t)base * cf.d_model);
         int ld = 0;
         { int rc = head_and_choose(c, nullptr, grows, i0 == 0 && logits_out, c->tree_depth_all, act.data() + i0, i1 - i0, rel0, n_rows + i0, base, &ld, tree == nullptr); if (rc) return rc; }
-        if (i0 == 0 && logits_out)                         // before the next group overwrites the logits
+        if (i0 == 0 && logits_out && feat_out)             // before the next group overwrites the logits
+            launch_copy_rows2_f32(c->logits, ld, static_cast<float *>(logits_out), cf.vocab, cf.vocab, c->feats, cf.d_model,
+                                  static_cast<float *>(feat_out), cf.d_model, cf.d_model, n, c->st);
+        else if (i0 == 0 && logits_out)
             launch_copy_rows_f32(c->logits, ld, static_cast<float *>(logits_out), cf.vocab, n, cf.vocab, c->st);
         i0 = i1;
     }
     (void)hipEventRecord(c->ev[3], c->st);
     c->ev_pending[1] = true;
-    if (feat_out) launch_copy_rows_f32(c->feats, cf.d_model, static_cast<float *>(feat_out), cf.d_model, n, cf.d_model, c->st);
+    if (feat_out && !logits_out) launch_copy_rows_f32(c->feats, cf.d_model, static_cast<float *>(feat_out), cf.d_model, n, cf.d_model, c->st);
     HIP_TRY(c, hipGetLastError());
     c->state = ST_VERIFIED;
     // Nothing to hand over: stay queued.  (A caller's tree was staged in pinned memory; the only call
     // allowed next, poss_accept_and_commit, waits for the stream before that memory is touched again.)
     if (!argmax_out && !logits_out && !feat_out) return POSS_OK;
-    if (argmax_out) HIP_TRY(c, hipMemcpyAsync(argmax_out, c->argmax_dev, n * sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
-    return sync_and_harvest(c);
+    const bool on_host = !(c->temperature > 0.f);         // greedy choices are in host memory already
+    if (argmax_out && !on_host) HIP_TRY(c, hipMemcpyAsync(argmax_out, c->argmax_dev, n * sizeof(int32_t), hipMemcpyDeviceToHost, c->st));
+    { int rc = sync_and_harvest(c); if (rc) return rc; }
+    if (argmax_out && on_host) memcpy(argmax_out, c->argmax_host, n * sizeof(int32_t));
+    return POSS_OK;
 }
 
 int poss_accept_and_commit(poss_ctx *c, int32_t *path_idx_out, int32_t *n_accepted_out, int32_t *committed_out,
@@ -1230,12 +1256,14 @@ int poss_accept_and_commit(poss_ctx *c, int32_t *path_idx_out, int32_t *n_accept
     const int L = cf.depth;
     const std::vector<int> act = active_seqs(c);
     (void)hipEventRecord(c->ev[4], c->st);
-    for (int b : act) {
-        Seq &sq = c->seq[b];
+    CommitSeq cs[8];
+    for (size_t i = 0; i < act.size(); ++i) {
+        Seq &sq = c->seq[act[i]];
         const int row0 = sq.tree_row0;
-        launch_commit(c->md, cf.n_layers, sq.target_kv_dev, sq.td.token, sq.td.parent, c->argmax_dev + row0, sq.td.n_nodes, L, sq.t,
-                      c->feats + (size_t)row0 * cf.d_model, sq.feat_stash, sq.tokens_dev, sq.walk_dev, sq.result_dev, c->st);
+        cs[i] = CommitSeq{sq.target_kv_dev, sq.td.token, sq.td.parent, c->argmax_dev + row0, sq.td.n_nodes, sq.t,
+                          c->feats + (size_t)row0 * cf.d_model, sq.feat_stash, sq.tokens_dev, sq.walk_dev, sq.result_dev};
     }
+    launch_commit(c->md, cf.n_layers, cs, (int)act.size(), L, c->st);
     (void)hipEventRecord(c->ev[5], c->st);
     c->ev_pending[2] = true;
     { int rc = sync_and_harvest(c); if (rc) return rc; }

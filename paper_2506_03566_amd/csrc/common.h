@@ -145,9 +145,10 @@ void launch_embed_norm(const ModelDims &md, const void *embed, const int32_t *to
                        const void *gain, float *h, void *u, const int32_t *pos, const double *inv_freq,
                        float2 *cs, hipStream_t st);
 size_t argmax_scratch_floats(int rows, int vocab);
-void launch_argmax(const float *logits, int ld, int rows, int vocab, float *scratch, int32_t *out, hipStream_t st);
-// second stage alone: pv / pi hold n_seg partial winners per row
-void launch_argmax_merge(const float *pv, const int *pi, int n_seg, int rows, int32_t *out, hipStream_t st);
+void launch_argmax(const float *logits, int ld, int rows, int vocab, float *scratch, int32_t *out, int32_t *host_out, hipStream_t st);
+// second stage alone: pv / pi hold n_seg partial winners per row.  host_out, if given (host memory mapped into the device),
+// receives the same: no copy follows
+void launch_argmax_merge(const float *pv, const int *pi, int n_seg, int rows, int32_t *out, int32_t *host_out, hipStream_t st);
 // Temperature sampling: out[r] = first id whose cumulative probability under softmax(logits[r] / temperature)
 // exceeds u_by_depth[depth ? depth[r] : 0] (DEVICE arrays).  Returns false (nothing launched) for temperature <= 0
 // or a vocabulary beyond 4M entries.
@@ -156,6 +157,9 @@ bool launch_sample(const float *logits, int ld, int rows, int vocab, float tempe
                    const int32_t *depth, float *scratch, int32_t *out, hipStream_t st);
 void launch_copy_rows_f32(const float *src, int ld_src, float *dst, int ld_dst, int rows, int cols,
                           hipStream_t st);
+// two such copies of the same rows in one launch
+void launch_copy_rows2_f32(const float *src, int ld_src, float *dst, int ld_dst, int cols, const float *src2, int ld_src2, float *dst2,
+                           int ld_dst2, int cols2, int rows, hipStream_t st);
 
 // ---------------------------------------------------------------- attention
 struct AttnScratch { float *o; float *ml; };  // partial outputs [split][Hq][rows][dh], (m, l) pairs
@@ -220,9 +224,11 @@ void launch_topk_logsoftmax(const float *logits, int ld, int rows, int vocab, in
 // Both take the trees of n_seq <= TREE_BATCH_MAX sequences (arrays of n_seq entries): one workgroup each.
 constexpr int TREE_BATCH_MAX = 8;
 void launch_tree_expand(const TreeDev *tds, int n_seq, int d, int k, int L, int rows, int vocab, hipStream_t st);
-// also writes the KV slot of every node (slot_out[s][i] = t[s] + i), which the verification pass reads
+// also writes the KV slot of every node (slot_out[s][i] = t[s] + i), which the verification pass reads, and the tree into host
+// memory mapped into the device (host[s], laid out as TreeHost): the host reads it there, no copy follows
 void launch_tree_finalize(const TreeDev *tds, int n_seq, int k, int L, int n_keep, const int *t,
-                          const int32_t *const *tokens_dev, int32_t *const *slot_out, hipStream_t st);
+                          const int32_t *const *tokens_dev, int32_t *const *slot_out, struct TreeHost *const *host, hipStream_t st);
+struct TreeHost { int32_t token[MAX_ROWS], parent[MAX_ROWS], depth[MAX_ROWS], pos[MAX_ROWS]; float score[MAX_ROWS]; uint64_t mask[MAX_ROWS * MASK_WORDS]; };
 // rows of [embedding ; feature] pairs for one specialist pass
 struct DraftRowPlan {
     int n_rows;
@@ -244,15 +250,21 @@ void launch_assemble_pairs(const ModelDims &md, int i0, int n, const void *embed
                            void *x_out, int32_t *slot_out, const double *inv_freq, float2 *cs, hipStream_t st);
 
 // ---------------------------------------------------------------- accept + commit
-void launch_tree_upload_finish(int n, int t, const int32_t *token, const int32_t *parent, int32_t *depth,
-                               int32_t *pos, int32_t *slot, uint64_t *mask, hipStream_t st);
-// One launch: the greedy walk over the verified tree, then KV compaction, feature stash and token
+// Caller-supplied trees, one per sequence, in one launch: tokens and parents are read from host memory mapped into the device
+// and written, with depth, position, slot and mask, to the tree's arrays.
+struct TreeUpload {
+    const int32_t *token_src, *parent_src; int n, t;
+    int32_t *token, *parent, *depth, *pos, *slot, *n_nodes; uint64_t *mask;
+};
+void launch_tree_upload(const TreeUpload *ups, int n_seq, hipStream_t st);
+// One launch for all sequences: the greedy walk over the verified tree, then KV compaction, feature stash and token
 // stream.  walk_dev / result: [0] = m, [1] = bonus token, [2..2+m] = node indices of the accepted
 // path; result[32 + j] = committed token j.  result must be host memory mapped into the device.
-void launch_commit(const ModelDims &md, int n_layers, const KVCache *caches_dev, const int32_t *tree_token,
-                   const int32_t *tree_parent, const int32_t *g, const int32_t *n_nodes, int max_path, int t,
-                   const float *feats, void *feat_stash, int32_t *tokens_dev, int32_t *walk_dev, int32_t *result,
-                   hipStream_t st);
+struct CommitSeq {
+    const KVCache *caches; const int32_t *tree_token, *tree_parent, *g, *n_nodes; int t;
+    const float *feats; void *feat_stash; int32_t *tokens_dev, *walk_dev, *result;
+};
+void launch_commit(const ModelDims &md, int n_layers, const CommitSeq *seqs, int n_seq, int max_path, hipStream_t st);
 
 void launch_read_kv(const ModelDims &md, const KVCache &kv, int slot0, int n, float *k_out, float *v_out,
                     hipStream_t st);

@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void argmax_seg_kernel(const float *__restrict
 }
 
 __global__ __launch_bounds__(64) void argmax_merge_kernel(const float *__restrict__ pv, const int *__restrict__ pi, int n_seg,
-                                                          int32_t *__restrict__ out) {
+                                                          int32_t *__restrict__ out, int32_t *__restrict__ host_out) {
     const int rowi = blockIdx.x;
     float bv = -INFINITY; int bi = 0x7fffffff;
     for (int s = threadIdx.x; s < n_seg; s += 64) {
@@ -163,21 +163,24 @@ __global__ __launch_bounds__(64) void argmax_merge_kernel(const float *__restric
         if (better(v, i, bv, bi)) { bv = v; bi = i; }
     }
     wave_argmax(bv, bi);
-    if (threadIdx.x == 0) out[rowi] = bi == 0x7fffffff ? 0 : bi;        // no logit of the row compared (all NaN): token 0, not an id outside the vocabulary
+    if (threadIdx.x != 0) return;
+    if (bi == 0x7fffffff) bi = 0;                         // no logit of the row compared (all NaN): token 0, not an id outside the vocabulary
+    out[rowi] = bi;
+    if (host_out) host_out[rowi] = bi;
 }
 
 size_t argmax_scratch_floats(int rows, int vocab) { return (size_t)2 * rows * head_segments_max(vocab); }   // finest segmentation: the Head GEMM's tiles
 
-void launch_argmax_merge(const float *pv, const int *pi, int n_seg, int rows, int32_t *out, hipStream_t st) {
-    hipLaunchKernelGGL(argmax_merge_kernel, dim3(rows), dim3(64), 0, st, pv, pi, n_seg, out);
+void launch_argmax_merge(const float *pv, const int *pi, int n_seg, int rows, int32_t *out, int32_t *host_out, hipStream_t st) {
+    hipLaunchKernelGGL(argmax_merge_kernel, dim3(rows), dim3(64), 0, st, pv, pi, n_seg, out, host_out);
 }
 
-void launch_argmax(const float *logits, int ld, int rows, int vocab, float *scratch, int32_t *out, hipStream_t st) {
+void launch_argmax(const float *logits, int ld, int rows, int vocab, float *scratch, int32_t *out, int32_t *host_out, hipStream_t st) {
     const int n_seg = (vocab + ARGMAX_SEG - 1) / ARGMAX_SEG;
     float *pv = scratch;
     int *pi = reinterpret_cast<int *>(scratch + (size_t)rows * n_seg);
     hipLaunchKernelGGL(argmax_seg_kernel, dim3(n_seg, rows), dim3(256), 0, st, logits, ld, vocab, n_seg, pv, pi);
-    launch_argmax_merge(pv, pi, n_seg, rows, out, st);
+    launch_argmax_merge(pv, pi, n_seg, rows, out, host_out, st);
 }
 
 // ------------------------------------------------------------------ temperature sampling per row
@@ -736,6 +739,21 @@ void launch_copy_rows_f32(const float *src, int ld_src, float *dst, int ld_dst, 
                           hipStream_t st) {
     hipLaunchKernelGGL(copy_rows_f32_kernel, dim3((cols + 255) / 256, rows), dim3(256), 0, st, src, ld_src, dst,
                        ld_dst, cols);
+}
+
+__global__ void copy_rows2_f32_kernel(const float *__restrict__ src, int ld_src, float *__restrict__ dst, int ld_dst, int cols, int blocks,
+                                      const float *__restrict__ src2, int ld_src2, float *__restrict__ dst2, int ld_dst2, int cols2) {
+    const bool second = (int)blockIdx.x >= blocks;
+    const int c = ((int)blockIdx.x - (second ? blocks : 0)) * blockDim.x + threadIdx.x;
+    if (second) { if (c < cols2) dst2[(size_t)blockIdx.y * ld_dst2 + c] = src2[(size_t)blockIdx.y * ld_src2 + c]; }
+    else if (c < cols) dst[(size_t)blockIdx.y * ld_dst + c] = src[(size_t)blockIdx.y * ld_src + c];
+}
+
+void launch_copy_rows2_f32(const float *src, int ld_src, float *dst, int ld_dst, int cols, const float *src2, int ld_src2, float *dst2,
+                           int ld_dst2, int cols2, int rows, hipStream_t st) {
+    const int blocks = (cols + 255) / 256, blocks2 = (cols2 + 255) / 256;
+    hipLaunchKernelGGL(copy_rows2_f32_kernel, dim3(blocks + blocks2, rows), dim3(256), 0, st, src, ld_src, dst, ld_dst, cols, blocks, src2,
+                       ld_src2, dst2, ld_dst2, cols2);
 }
 
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {

@@ -310,6 +310,7 @@ struct TreeBatch {
     int t[TREE_BATCH_MAX];
     const int32_t *tokens_dev[TREE_BATCH_MAX];
     int32_t *slot_out[TREE_BATCH_MAX];
+    TreeHost *host[TREE_BATCH_MAX];
 };
 
 __global__ __launch_bounds__(256) void tree_expand_kernel(TreeBatch tb, int d, int k, int L, int rows, int vocab) {
@@ -372,6 +373,7 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int p
     const int t = tb.t[blockIdx.x];
     const int32_t *__restrict__ tokens_dev = tb.tokens_dev[blockIdx.x];
     int32_t *__restrict__ slot_out = tb.slot_out[blockIdx.x];
+    TreeHost *__restrict__ host = tb.host[blockIdx.x];
     __shared__ __attribute__((aligned(16))) float sc[POOL_MAX];
     __shared__ int16_t par[POOL_MAX];                 // candidate -> parent candidate (-1: the root)
     __shared__ int16_t new_idx[POOL_MAX];             // candidate -> node index in the tree, -1 if dropped
@@ -430,7 +432,10 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int p
     }
     if (tid == 0) {
         td.n_nodes[0] = total + 1;
-        td.token[0] = tokens_dev[t]; td.parent[0] = -1; td.depth[0] = 0; td.pos[0] = t; td.score[0] = 0.f;
+        const int root = tokens_dev[t];
+        host->token[0] = root; host->parent[0] = -1; host->depth[0] = 0; host->pos[0] = t; host->score[0] = 0.f;
+        host->mask[0] = 1ull; host->mask[1] = 0ull;
+        td.token[0] = root; td.parent[0] = -1; td.depth[0] = 0; td.pos[0] = t; td.score[0] = 0.f;
         td.mask[0] = 1ull; td.mask[1] = 0ull;
         td.node_pool[0] = -1;
         slot_out[0] = t;
@@ -456,15 +461,18 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int p
         }
         td.mask[ni * MASK_WORDS] = w0;
         td.mask[ni * MASK_WORDS + 1] = w1;
+        host->token[ni] = my_token[p]; host->parent[ni] = pp < 0 ? 0 : new_idx[pp]; host->depth[ni] = dep; host->pos[ni] = t + dep;
+        host->score[ni] = sc[i];
+        host->mask[ni * MASK_WORDS] = w0; host->mask[ni * MASK_WORDS + 1] = w1;
     }
 }
 
 void launch_tree_finalize(const TreeDev *tds, int n_seq, int k, int L, int n_keep, const int *t,
-                          const int32_t *const *tokens_dev, int32_t *const *slot_out, hipStream_t st) {
+                          const int32_t *const *tokens_dev, int32_t *const *slot_out, TreeHost *const *host, hipStream_t st) {
     if (n_seq < 1 || n_seq > TREE_BATCH_MAX) return;
     const int pool_n = k + (L - 1) * k * k;
     TreeBatch tb{};
-    for (int i = 0; i < n_seq; ++i) { tb.td[i] = tds[i]; tb.t[i] = t[i]; tb.tokens_dev[i] = tokens_dev[i]; tb.slot_out[i] = slot_out[i]; }
+    for (int i = 0; i < n_seq; ++i) { tb.td[i] = tds[i]; tb.t[i] = t[i]; tb.tokens_dev[i] = tokens_dev[i]; tb.slot_out[i] = slot_out[i]; tb.host[i] = host[i]; }
     hipLaunchKernelGGL(tree_finalize_kernel, dim3(n_seq), dim3(1024), 0, st, tb, pool_n, n_keep < pool_n ? n_keep : pool_n);
 }
 
@@ -580,25 +588,33 @@ void launch_assemble_pairs(const ModelDims &md, int i0, int n, const void *embed
 }
 
 // ------------------------------------------------------------------ caller-supplied tree -> depth/pos/slot/mask
-__global__ void tree_upload_finish_kernel(int n, int t, const int32_t *__restrict__ parent, int32_t *__restrict__ depth,
-                                          int32_t *__restrict__ pos, int32_t *__restrict__ slot,
-                                          uint64_t *__restrict__ mask) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+// One workgroup per sequence; the tree comes from host memory in one trip.
+struct UploadBatch { TreeUpload u[TREE_BATCH_MAX]; };
+__global__ __launch_bounds__(MAX_ROWS) void tree_upload_kernel(UploadBatch ub) {
+    __shared__ int32_t par[MAX_ROWS];
+    const TreeUpload &up = ub.u[blockIdx.x];
+    const int i = threadIdx.x, n = up.n, t = up.t;
+    const int tok = i < n ? up.token_src[i] : 0, p = i < n ? up.parent_src[i] : -1;
+    par[i] = p;
+    __syncthreads();
+    if (i == 0) up.n_nodes[0] = n;
     if (i >= n) return;
     uint64_t w0 = 0ull, w1 = 0ull;
     int dep = -1;
-    for (int u = i; u >= 0; u = parent[u]) {
+    for (int u = i; u >= 0; u = par[u]) {                 // (a parent precedes its node: checked on the host)
         if (u < 64) w0 |= 1ull << u; else w1 |= 1ull << (u - 64);
         ++dep;
     }
-    depth[i] = dep; pos[i] = t + dep; slot[i] = t + i;
-    mask[i * MASK_WORDS] = w0; mask[i * MASK_WORDS + 1] = w1;
+    up.token[i] = tok; up.parent[i] = p;
+    up.depth[i] = dep; up.pos[i] = t + dep; up.slot[i] = t + i;
+    up.mask[i * MASK_WORDS] = w0; up.mask[i * MASK_WORDS + 1] = w1;
 }
 
-void launch_tree_upload_finish(int n, int t, const int32_t *token, const int32_t *parent, int32_t *depth,
-                               int32_t *pos, int32_t *slot, uint64_t *mask, hipStream_t st) {
-    (void)token;
-    hipLaunchKernelGGL(tree_upload_finish_kernel, dim3(1), dim3(128), 0, st, n, t, parent, depth, pos, slot, mask);
+void launch_tree_upload(const TreeUpload *ups, int n_seq, hipStream_t st) {
+    if (n_seq < 1 || n_seq > TREE_BATCH_MAX) return;
+    UploadBatch ub{};
+    for (int i = 0; i < n_seq; ++i) ub.u[i] = ups[i];
+    hipLaunchKernelGGL(tree_upload_kernel, dim3(n_seq), dim3(MAX_ROWS), 0, st, ub);
 }
 
 // ------------------------------------------------------------------ greedy acceptance walk + commit
@@ -633,24 +649,23 @@ __device__ __forceinline__ void accept_walk_wave(const int32_t *__restrict__ tok
 // token (the bonus token for j = m) joins the stream; they also write the result the host reads:
 // result[0..2+m] = the walk, result[32 + j] = committed token j.  `result` is host memory the device
 // can write, so no copy follows the kernel.
+struct CommitBatch { CommitSeq s[TREE_BATCH_MAX]; };
 template <typename T>
-__global__ __launch_bounds__(256) void commit_kernel(const KVCache *__restrict__ caches, int n_kv_wgs, int hkv, int dh,
-                                                     const int32_t *__restrict__ tree_token,
-                                                     const int32_t *__restrict__ tree_parent,
-                                                     const int32_t *__restrict__ g, const int32_t *__restrict__ n_nodes,
-                                                     int max_path, int t, int d_model, const float *__restrict__ feats,
-                                                     T *__restrict__ feat_stash, int32_t *__restrict__ tokens_dev,
-                                                     int32_t *__restrict__ walk_dev, int32_t *__restrict__ result) {
+__global__ __launch_bounds__(256) void commit_kernel(CommitBatch cb, int n_kv_wgs, int hkv, int dh, int max_path, int d_model) {
+    const CommitSeq &cs = cb.s[blockIdx.y];
+    const int32_t *__restrict__ tree_token = cs.tree_token, *__restrict__ tree_parent = cs.tree_parent, *__restrict__ g = cs.g;
+    const int t = cs.t;
     extern __shared__ unsigned char smem[];
     __shared__ int32_t walk[32];                      // 3 + the longest path (depth <= 16)
-    if (threadIdx.x < 64) accept_walk_wave(tree_token, tree_parent, g, n_nodes[0], max_path, walk);
+    if (threadIdx.x < 64) accept_walk_wave(tree_token, tree_parent, g, cs.n_nodes[0], max_path, walk);
     __syncthreads();
     const int m = walk[0];
     if ((int)blockIdx.x < n_kv_wgs) {
+        if (m == 0) return;                               // the root's row is where it belongs (slot t)
         T *kbuf = reinterpret_cast<T *>(smem);
         const int n = (m + 1) * dh;
         T *vbuf = kbuf + n;
-        const KVCache kv = caches[blockIdx.x / hkv];
+        const KVCache kv = cs.caches[blockIdx.x / hkv];
         const int head = blockIdx.x % hkv;
         T *kc = static_cast<T *>(kv.k), *vc = static_cast<T *>(kv.vt);
         for (int e = threadIdx.x; e < n; e += blockDim.x) {
@@ -668,30 +683,28 @@ __global__ __launch_bounds__(256) void commit_kernel(const KVCache *__restrict__
     }
     const int j = blockIdx.x - n_kv_wgs;
     if (j > m) return;
-    const float *src = feats + (size_t)walk[2 + j] * d_model;
-    T *dst = feat_stash + (size_t)(t + j) * d_model;
+    const float *src = cs.feats + (size_t)walk[2 + j] * d_model;
+    T *dst = static_cast<T *>(cs.feat_stash) + (size_t)(t + j) * d_model;
     for (int i = threadIdx.x; i < d_model; i += blockDim.x) dst[i] = from_f<T>(src[i]);
     if (threadIdx.x == 0) {
         const int32_t tok = j < m ? tree_token[walk[2 + j + 1]] : walk[1];
-        tokens_dev[t + 1 + j] = tok;
-        result[32 + j] = tok;
+        cs.tokens_dev[t + 1 + j] = tok;
+        cs.result[32 + j] = tok;
     }
     if (j == 0 && (int)threadIdx.x < m + 3) {
-        walk_dev[threadIdx.x] = walk[threadIdx.x];
-        result[threadIdx.x] = walk[threadIdx.x];
+        cs.walk_dev[threadIdx.x] = walk[threadIdx.x];
+        cs.result[threadIdx.x] = walk[threadIdx.x];
     }
 }
 
-void launch_commit(const ModelDims &md, int n_layers, const KVCache *caches_dev, const int32_t *tree_token,
-                   const int32_t *tree_parent, const int32_t *g, const int32_t *n_nodes, int max_path, int t,
-                   const float *feats, void *feat_stash, int32_t *tokens_dev, int32_t *walk_dev, int32_t *result,
-                   hipStream_t st) {
+void launch_commit(const ModelDims &md, int n_layers, const CommitSeq *seqs, int n_seq, int max_path, hipStream_t st) {
+    if (n_seq < 1 || n_seq > TREE_BATCH_MAX) return;
     const size_t lds = (size_t)2 * (max_path + 1) * md.dh * dtype_size(md.dt);
     const int n_kv_wgs = n_layers * md.hkv;
+    CommitBatch cb{};
+    for (int i = 0; i < n_seq; ++i) cb.s[i] = seqs[i];
 #define POSS_COMMIT(T)                                                                                             \
-    hipLaunchKernelGGL((commit_kernel<T>), dim3(n_kv_wgs + max_path + 1), dim3(256), lds, st, caches_dev, n_kv_wgs,   \
-                       md.hkv, md.dh, tree_token, tree_parent, g, n_nodes, max_path, t, md.d, feats,               \
-                       static_cast<T *>(feat_stash), tokens_dev, walk_dev, result)
+    hipLaunchKernelGGL((commit_kernel<T>), dim3(n_kv_wgs + max_path + 1, n_seq), dim3(256), lds, st, cb, n_kv_wgs, md.hkv, md.dh, max_path, md.d)
     if (md.dt == DT_F32) { POSS_COMMIT(float); } else if (md.dt == DT_BF16) { POSS_COMMIT(bf16_t); } else { POSS_COMMIT(f16_t); }
 #undef POSS_COMMIT
 }
