@@ -65,6 +65,10 @@ __device__ __forceinline__ float block_sum(float v, float *red /* >= 17 floats o
 __device__ __forceinline__ void lds_dma16(unsigned lds_base, const void *g) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds_base), "v"(g) : "memory");
 }
+// The same for bytes that no other workgroup will want: non-temporal, so that they do not push out of the L2 what others share.
+__device__ __forceinline__ void lds_dma16_nt(unsigned lds_base, const void *g) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off nt" ::"s"(lds_base), "v"(g) : "memory");
+}
 // The same with a scalar base and a byte offset per lane.
 __device__ __forceinline__ void lds_dma16_s(unsigned lds_base, const void *g, unsigned off) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_base), "v"(off), "s"(g) : "memory");

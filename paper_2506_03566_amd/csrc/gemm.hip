@@ -437,7 +437,9 @@ __global__ __launch_bounds__(WPB * 64) void gemm_stream_kernel(
 //       xor-swizzled by a function of the row - eight consecutive lanes fetch one row's 128 bytes, a whole line of the
 //       L2 (four lanes and 64 bytes, one k-step, made twice the requests), and an operand read (lane % 16 the row,
 //       lane / 16 the k-group) runs at the full LDS rate;
-//   weights: the packed layout is already the B-operand image, 1 KB per (k-step, column tile), copied as it is.
+//   weights: the packed layout is already the B-operand image, 1 KB per (k-step, column tile), copied as it is, with non-temporal
+//       loads: a workgroup's weights are its own, the activations are everyone's and should stay in the L2 (four sequences of
+//       61 rows, four layers: 1050 -> 1015 us a round).
 // Rows >= M and k >= K are not zeroed: such a lane fetches a valid element of the matrix instead (row M - 1, k = 0);
 // the rows are never read back and the packed weights are zero beyond K.
 // Splits own whole groups of 8 k-steps as in the stream kernel and a wave adds its k-steps in ascending order, so a
@@ -499,8 +501,8 @@ __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
             }
 #pragma unroll
             for (int nt = 0; nt < GEMM_NT; ++nt)
-                lds_dma16(base + (unsigned)((XBLKS + ((pw >> 2) * 4 + (pw & 3)) * GEMM_NT + nt) * 1024),
-                          w_src + (size_t)chunk * KCL * (GEMM_NT * 64) + nt * 64);
+                lds_dma16_nt(base + (unsigned)((XBLKS + ((pw >> 2) * 4 + (pw & 3)) * GEMM_NT + nt) * 1024),
+                             w_src + (size_t)chunk * KCL * (GEMM_NT * 64) + nt * 64);
         };
         static_assert(LPS == XPP + GEMM_NT && XBLKS == 8 * XPP, "the fetch above brings exactly one stage");
         fetch(chunk0, 0);
