@@ -895,7 +895,7 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
                 *reinterpret_cast<f32x4 *>(h + n) = x[it];
                 if (h_copy) *reinterpret_cast<f32x4 *>(h_copy + n) = x[it];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) ss += x[it][j] * x[it][j];
+                for (int j = 0; j < 4; ++j) ss = fmaf(x[it][j], x[it][j], ss);   // (spelt out: which product is rounded on its own is not left to the compiler)
             } else {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
@@ -911,7 +911,7 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
                     v[j] += add[j];
                     h[n + j] = v[j];
                     if (h_copy) h_copy[n + j] = v[j];
-                    ss += v[j] * v[j];
+                    ss = fmaf(v[j], v[j], ss);
                 }
                 x[it] = v;
             }
