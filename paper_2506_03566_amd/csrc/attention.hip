@@ -540,101 +540,79 @@ __global__ __launch_bounds__(256 * KW) void attn_mfma_batch_kernel(AttnSeqs seqs
                                   static_cast<T *>(a.out_direct));
 }
 
-// out[m][qh][:] = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, splits in order.  The (max, sum) pairs of
-// all splits are fetched in one go and turned into weights once; the partial outputs are then read
-// four splits at a time so that their latencies overlap.
-constexpr int ATTN_MAX_SPLITS = 256;
-template <typename T>
-__device__ __forceinline__ void attn_merge_body(const int m, const float *__restrict__ o_part, const float *__restrict__ ml_part,
-                                                int n_splits, int hq, int hkv, int dh, int rho_pad, T *__restrict__ out) {
-    __shared__ float w_lds[ATTN_MAX_SPLITS];
-    __shared__ float den_lds;
-    const int qh = blockIdx.y, G = hq / hkv;
-    const int kvh = qh / G, rho = m * G + qh % G;
-    const size_t stride = (size_t)hkv * rho_pad;          // rows between consecutive splits
-    const size_t row0 = (size_t)kvh * rho_pad + rho;
-    // Up to 12 splits (the usual case): everything in registers and every load requested before the first use - one
-    // trip to memory, no barrier.  Each thread forms the weights itself (the (max, sum) pairs are the same addresses
-    // for the whole workgroup); sums run in split order, as in the general path.  Slots beyond n_splits re-read the
-    // last split and are not used.
-    auto in_registers = [&](auto nr_tag) {
-        constexpr int NR = decltype(nr_tag)::value;
-        const int i = (int)threadIdx.x < dh ? (int)threadIdx.x : dh - 1;
-        const float *src = o_part + row0 * dh + i;
-        float ms[NR], ls[NR], v[NR];
-#pragma unroll
-        for (int s0 = 0; s0 < NR; ++s0) {
-            const int sc = s0 < n_splits ? s0 : n_splits - 1;
-            const float2 ml = *reinterpret_cast<const float2 *>(ml_part + (row0 + sc * stride) * 2);
-            ms[s0] = ml.x; ls[s0] = ml.y;
-            v[s0] = src[(size_t)sc * stride * dh];
-        }
-        float M = -INFINITY;
-#pragma unroll
-        for (int s0 = 0; s0 < NR; ++s0) if (s0 < n_splits) M = fmaxf(M, ms[s0]);
-        float den = 0.f, num = 0.f;
-#pragma unroll
-        for (int s0 = 0; s0 < NR; ++s0)
-            if (s0 < n_splits) {
-                const float w = ms[s0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s0] - M);   // maxima are in the log2 domain
-                den += w * ls[s0];
-                num += w * v[s0];                         // a split without visible keys has weight 0 and O = 0
-            }
-        if ((int)threadIdx.x < dh) out[((size_t)m * hq + qh) * dh + i] = from_f<T>(num / den);
-    };
-    if (n_splits <= 4) { in_registers(std::integral_constant<int, 4>{}); return; }     // (workgroup-uniform)
-    if (n_splits <= 8) { in_registers(std::integral_constant<int, 8>{}); return; }
-    if (n_splits <= 12) { in_registers(std::integral_constant<int, 12>{}); return; }
-    for (int s0 = threadIdx.x; s0 < n_splits; s0 += blockDim.x) w_lds[s0] = ml_part[(row0 + s0 * stride) * 2];
-    __syncthreads();
-    float M = -INFINITY;
-    for (int s0 = 0; s0 < n_splits; ++s0) M = fmaxf(M, w_lds[s0]);
-    __syncthreads();
-    if (threadIdx.x == 0) {                               // one thread: the order of the sum is fixed
-        float den = 0.f;
-        for (int s0 = 0; s0 < n_splits; ++s0) {
-            const float ms = w_lds[s0];
-            const float w = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - M);   // maxima are in the log2 domain
-            w_lds[s0] = w;
-            den += w * ml_part[(row0 + s0 * stride) * 2 + 1];
-        }
-        den_lds = den;
-    }
-    __syncthreads();
-    const float den = den_lds;
-    for (int i = threadIdx.x; i < dh; i += blockDim.x) {
-        const float *src = o_part + row0 * dh + i;
-        float num = 0.f;
-        int s0 = 0;
-        for (; s0 + 4 <= n_splits; s0 += 4) {
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = src[(size_t)(s0 + j) * stride * dh];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) num += w_lds[s0 + j] * v[j];    // a split without visible keys has weight 0 and O = 0
-        }
-        for (; s0 < n_splits; ++s0) num += w_lds[s0] * src[(size_t)s0 * stride * dh];
-        out[((size_t)m * hq + qh) * dh + i] = from_f<T>(num / den);
-    }
-}
-
-template <typename T>
-__global__ void attn_merge_kernel(const float *__restrict__ o_part, const float *__restrict__ ml_part, int n_splits,
-                                  int hq, int hkv, int dh, int rho_pad, T *__restrict__ out) {
-    attn_merge_body<T>(blockIdx.x, o_part, ml_part, n_splits, hq, hkv, dh, rho_pad, out);
-}
-
-// The merge of several sequences' rows in one launch (blockIdx.x = row of the pass); sequences whose keys fit one
-// split wrote their rows directly and are skipped.
-template <typename T>
-__global__ void attn_merge_batch_kernel(AttnSeqs seqs, int hq, int hkv, int dh, T *__restrict__ out) {
-    int i = 0;
+// out[m][qh][:] = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, splits in order, for the rows of every sequence of a launch
+// (sequences whose keys fit one split wrote their rows directly and are skipped).  dh / 4 lanes per (row, query head), four
+// columns each.  Up to NR splits (the usual case, NR = 4, 8, 12): everything in registers and every load requested before the first
+// use - one trip to memory, no LDS, no barrier; each lane forms the weights itself (the (max, sum) pairs are the same addresses for
+// the group) and slots beyond n_splits re-read the last split and are not used.  NR = 0: any number of splits, two passes over
+// the (max, sum) pairs.  Four times 61 rows of the 8B shape, four
+// splits: 9.5 -> 5.9 us; 61 rows: 4.6 -> 4.5 (before: a workgroup per (row, head),
+// a column per lane).
+constexpr int ATTN_MAX_SPLITS = 256, MERGE_THREADS = 256;
+template <typename T, int NR>
+__global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(AttnSeqs seqs, int n_rows, int hq, int hkv, int dh, T *__restrict__ out) {
+    struct __attribute__((aligned(8))) Quad { T t[4]; };
+    const int lanes = dh >> 2, idx = blockIdx.x * (MERGE_THREADS / lanes) + (int)threadIdx.x / lanes, i = ((int)threadIdx.x % lanes) * 4;
+    const int row = idx / hq, qh = idx % hq;
+    if (row >= n_rows) return;
+    int si = 0;
     for (int j = 1; j < seqs.n; ++j)
-        if ((int)blockIdx.x >= seqs.s[j].row0) i = j;
-    const AttnSeq &a = seqs.s[i];
-    const int m = blockIdx.x - a.row0;
-    if (m >= a.rows || a.n_splits == 1) return;          // (workgroup-uniform)
-    attn_merge_body<T>(m, a.o_part, a.ml_part, a.n_splits, hq, hkv, dh, a.rho_pad, out + (size_t)a.row0 * hq * dh);
+        if (row >= seqs.s[j].row0) si = j;
+    const AttnSeq &a = seqs.s[si];
+    const int m = row - a.row0, n_splits = a.n_splits;
+    if (m >= a.rows || n_splits == 1) return;
+    const int G = hq / hkv, kvh = qh / G, rho = m * G + qh % G;
+    const size_t stride = (size_t)hkv * a.rho_pad;        // rows between consecutive splits
+    const size_t row0 = (size_t)kvh * a.rho_pad + rho;
+    const float *src = a.o_part + row0 * dh + i, *ml = a.ml_part + row0 * 2;
+    float M = -INFINITY, den = 0.f;
+    f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
+    // a split without visible keys has weight 0 and O = 0; maxima are in the log2 domain
+    if constexpr (NR > 0) {
+        float ms[NR], ls[NR];
+        f32x4 v[NR];
+#pragma unroll
+        for (int s = 0; s < NR; ++s) {
+            const int sc = s < n_splits ? s : n_splits - 1;
+            const float2 x = *reinterpret_cast<const float2 *>(ml + (size_t)sc * stride * 2);
+            ms[s] = x.x; ls[s] = x.y;
+            v[s] = *reinterpret_cast<const f32x4 *>(src + (size_t)sc * stride * dh);
+        }
+#pragma unroll
+        for (int s = 0; s < NR; ++s) if (s < n_splits) M = fmaxf(M, ms[s]);
+#pragma unroll
+        for (int s = 0; s < NR; ++s)
+            if (s < n_splits) {
+                const float w = ms[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s] - M);
+                den += w * ls[s];
+                num += w * v[s];
+            }
+    } else {
+        for (int s = 0; s < n_splits; ++s) M = fmaxf(M, ml[(size_t)s * stride * 2]);
+#pragma unroll 4
+        for (int s = 0; s < n_splits; ++s) {
+            const float2 x = *reinterpret_cast<const float2 *>(ml + (size_t)s * stride * 2);
+            const float w = x.x == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x.x - M);
+            den += w * x.y;
+            num += w * *reinterpret_cast<const f32x4 *>(src + (size_t)s * stride * dh);
+        }
+    }
+    Quad o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) o.t[j] = from_f<T>(num[j] / den);
+    *reinterpret_cast<Quad *>(out + ((size_t)row * hq + qh) * dh + i) = o;
+}
+
+// n_rows: rows that `out` holds for the sequences of the launch
+template <typename T>
+static void launch_merge_t(const ModelDims &md, const AttnSeqs &seqs, int n_rows, T *out, hipStream_t st) {
+    int most = 0;
+    for (int i = 0; i < seqs.n; ++i) if (seqs.s[i].n_splits > most) most = seqs.s[i].n_splits;
+    const int per = MERGE_THREADS / (md.dh >> 2);
+    dim3 grid((n_rows * md.hq + per - 1) / per), block(MERGE_THREADS);
+#define POSS_MERGE(NR) hipLaunchKernelGGL((attn_merge_kernel<T, NR>), grid, block, 0, st, seqs, n_rows, md.hq, md.hkv, md.dh, out)
+    if (most <= 4) POSS_MERGE(4); else if (most <= 8) POSS_MERGE(8); else if (most <= 12) POSS_MERGE(12); else POSS_MERGE(0);
+#undef POSS_MERGE
 }
 
 // float32 storage: one workgroup per (row, query head); exact two-pass softmax.  A thread takes whole keys for the scores
@@ -772,9 +750,12 @@ static void launch_attention_t(const ModelDims &md, const void *q, int rows, con
     if (md.dh == 128) POSS_ATTN_DH(128); else POSS_ATTN_DH(64);
 #undef POSS_ATTN_DH
 #undef POSS_ATTN
-    if (a.n_splits > 1)
-        hipLaunchKernelGGL((attn_merge_kernel<T>), dim3(rows, md.hq), dim3(md.dh < 64 ? 64 : md.dh), 0, st, sc.o, sc.ml,
-                           a.n_splits, md.hq, md.hkv, md.dh, a.rho_pad, static_cast<T *>(out));
+    if (a.n_splits > 1) {
+        AttnSeqs one;
+        one.n = 1;
+        one.s[0] = AttnSeq{q, rm.mask, direct, sc.o, sc.ml, kv, rows, n_prefix, region_len, a.bps, a.n_splits, a.n_row_groups, a.rho_pad, 0, 0};
+        launch_merge_t<T>(md, one, rows, static_cast<T *>(out), st);
+    }
 }
 
 template <typename T>
@@ -835,9 +816,7 @@ static void launch_attention_batch_t(const ModelDims &md, const void *q, const R
         AttnSeqs grp;
         grp.n = n;
         for (int i = 0; i < n; ++i) grp.s[i] = all[i];
-        const int rows_span = segs[n - 1].row0 + segs[n - 1].rows;       // sequences are in row order
-        hipLaunchKernelGGL((attn_merge_batch_kernel<T>), dim3(rows_span, md.hq), dim3(md.dh < 64 ? 64 : md.dh), 0, st, grp,
-                           md.hq, md.hkv, md.dh, static_cast<T *>(out));
+        launch_merge_t<T>(md, grp, segs[n - 1].row0 + segs[n - 1].rows, static_cast<T *>(out), st);      // (sequences are in row order)
     }
 }
 
