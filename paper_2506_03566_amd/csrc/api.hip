@@ -360,7 +360,7 @@ struct Seg { int b; const KVCache *kv; int q0, nq, x0, nx, n_prefix, region_len;
 // own cache.  On entry c->u holds T(rmsnorm(h) * attn_norm) and c->cs the rotary table of the rows;
 // on exit c->h is updated and c->u holds T(rmsnorm(h) * next_gain).
 void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int rows_all, int rows_q, const RowMeta &rm,
-               const void *next_gain, float *h_copy, bool drafter = false) {
+               const void *next_gain, float *h_copy, bool drafter = false, float *h_user = nullptr, int h_user_rows = 0) {
     const ModelDims &md = c->md;
     const int qd = md.hq * md.dh, kd = md.hkv * md.dh;
     EpiArgs e{};
@@ -394,13 +394,17 @@ void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int r
     es.mode = EPI_SILU; es.act = c->act; es.F = md.ffn;
     // K unsplit: the stream kernel then applies SiLU * up itself (one tile per workgroup already fills most CUs)
     run_gemm(c, w.wgu, gate_up_rows(md.ffn), md.d, c->u, md.d, rows_q, c->part, true, es);
-    run_gemm(c, w.wdown, md.d, md.ffn, c->act, md.ffn, rows_q, c->part, false, epi_residual(c, true, nullptr, h_copy, next_gain));
+    EpiArgs ed = epi_residual(c, true, nullptr, h_copy, next_gain);
+    ed.h_user = h_user; ed.h_user_rows = h_user_rows;
+    run_gemm(c, w.wdown, md.d, md.ffn, c->act, md.ffn, rows_q, c->part, false, ed);
 }
 
 // Target pass over `rows` rows (all of them full rows; segs says which belong to which sequence)
 // whose tokens / metadata are on the device.  Leaves features in c->feats and
 // T(rmsnorm_final(features)) in c->u.
-void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowMeta &rm, std::vector<Seg> segs, float *feats_out) {
+// feat_user (16-byte aligned): the features of the first feat_user_rows rows go there as well.
+void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowMeta &rm, std::vector<Seg> segs, float *feats_out,
+                    float *feat_user = nullptr, int feat_user_rows = 0) {
     const ModelDims &md = c->md;
     launch_embed_norm(md, c->embed, tokens_dev, rows, c->layers[0].attn_norm, c->h, c->u, rm.pos, c->inv_freq, c->cs, c->st);
     const int nl = c->cfg.n_layers;
@@ -409,7 +413,8 @@ void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowM
             launch_copy_rows_f32(c->h, md.d, c->taps_user + (size_t)l * rows * md.d, md.d, rows, md.d, c->st);
         const void *next_gain = l + 1 < nl ? c->layers[l + 1].attn_norm : c->final_norm;
         for (Seg &sg : segs) sg.kv = &c->seq[sg.b].target_kv[l];
-        run_layer(c, c->layers[l], segs, rows, rows, rm, next_gain, l + 1 == nl ? feats_out : nullptr);
+        run_layer(c, c->layers[l], segs, rows, rows, rm, next_gain, l + 1 == nl ? feats_out : nullptr, false, l + 1 == nl ? feat_user : nullptr,
+                  feat_user_rows);
     }
     if (c->taps_user)
         launch_copy_rows_f32(c->h, md.d, c->taps_user + (size_t)nl * rows * md.d, md.d, rows, md.d, c->st);
@@ -418,9 +423,9 @@ void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowM
 // Head(features) for the rows whose final-normed activations start at x (default: c->u).  head_mode 0: the logits,
 // c->logits[rows][Npad].  HEAD_ARGMAX / HEAD_TOPK (16-bit storage): the GEMM reduces its own column tiles into
 // c->topk_scratch - per row and tile the best (value, index), or the record of the k best with the tile's maximum and
-// sum of exponentials - and writes the logits only if asked; *n_seg_out receives the number of tiles.  Float32
-// storage has no such epilogue: it always writes logits and reports 0 tiles.
-GemmShape run_head(poss_ctx *c, int rows, int head_mode, bool write_logits, int *n_seg_out, const void *x = nullptr,
+// sum of exponentials - and writes logits only where asked, those of the first user_rows rows to user_logits[row][vocab];
+// *n_seg_out receives the number of tiles.  Float32 storage has no such epilogue: it always writes c->logits and reports 0 tiles.
+GemmShape run_head(poss_ctx *c, int rows, int head_mode, float *user_logits, int user_rows, int *n_seg_out, const void *x = nullptr,
                    float *logits_dst = nullptr) {
     EpiArgs e{};
     e.mode = EPI_PLAIN;
@@ -428,7 +433,7 @@ GemmShape run_head(poss_ctx *c, int rows, int head_mode, bool write_logits, int 
     if (head_mode && c->md.dt != DT_F32) {
         const GemmShape g0 = gemm_plan(c->md.dt, rows, c->md.vocab, c->md.d, 1);
         const int n_seg = gemm_head_segments(g0);
-        e.mode = EPI_HEAD; e.head_mode = head_mode; e.head_k = c->cfg.top_k; e.write_logits = write_logits ? 1 : 0;
+        e.mode = EPI_HEAD; e.head_mode = head_mode; e.head_k = c->cfg.top_k; e.logits = user_logits; e.logits_rows = user_rows;
         e.seg_out = c->topk_scratch;
         e.pv = c->topk_scratch; e.pi = reinterpret_cast<int *>(c->topk_scratch + (size_t)rows * n_seg);
         if (n_seg_out) *n_seg_out = n_seg;
@@ -445,7 +450,7 @@ void run_head_topk(poss_ctx *c, int rows, int depth) {
         const int V = c->cfg.vocab;
         const size_t row0 = depth == 1 ? 0 : 1 + (size_t)(depth - 2) * k;
         float *dst = c->dlogits + row0 * gemm_npad(V);
-        const GemmShape g = run_head(c, rows, 0, true, nullptr, nullptr, dst);
+        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, nullptr, dst);
         const DrawMasses m{c->draft_m.mass + row0 * gemm_npad(V), c->draft_m.bsum + row0 * draw_bsum_floats(1, V), c->draft_m.mx + row0,
                            c->draft_m.pm + row0 * draw_pm_floats(1, V), c->draft_m.z + row0};
         c->draft_m_temperature = c->temperature;
@@ -454,7 +459,7 @@ void run_head_topk(poss_ctx *c, int rows, int depth) {
         return;
     }
     int n_seg = 0;
-    const GemmShape g = run_head(c, rows, HEAD_TOPK, false, &n_seg);
+    const GemmShape g = run_head(c, rows, HEAD_TOPK, nullptr, 0, &n_seg);
     if (n_seg)
         launch_topk_merge(c->topk_scratch, n_seg, rows, c->cfg.top_k, c->topk_id_all, c->topk_logp_all, c->st);
     else
@@ -842,8 +847,8 @@ void poss_free(poss_ctx *c) {
 
 const char *poss_last_error(poss_ctx *c) { return c ? c->err : g_load_error; }
 
-static int head_and_choose(poss_ctx *c, const void *x, int rows, bool want_logits, const int32_t *depth, const int *seq_ids,
-                           int n_seq, const int *row0, const int *n_rows, int base, int *ld_out, bool drafted_tree = false);
+static int head_and_choose(poss_ctx *c, const void *x, int rows, float *user_logits, int user_rows, const int32_t *depth,
+                           const int *seq_ids, int n_seq, const int *row0, const int *n_rows, int base, int *ld_out, bool drafted_tree = false);
 
 int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_prompt, int32_t *first_token_out) {
     if (!c) return POSS_E_INVALID_ARG;
@@ -879,7 +884,7 @@ int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_
         if (c0 + rows == n_prompt) {
             // Head on the last row only: its normed activations sit at row rows-1 of c->u
             const char *last = static_cast<const char *>(c->u) + (size_t)(rows - 1) * md.d * dtype_size(md.dt);
-            { const int zero = 0, one = 1, id = seq; int rc = head_and_choose(c, last, 1, false, nullptr, &id, 1, &zero, &one, 0, nullptr); if (rc) return rc; }
+            { const int zero = 0, one = 1, id = seq; int rc = head_and_choose(c, last, 1, nullptr, 0, nullptr, &id, 1, &zero, &one, 0, nullptr); if (rc) return rc; }
             HIP_TRY(c, hipMemcpyAsync(sq.tokens_dev + n_prompt, c->argmax_dev, sizeof(int32_t), hipMemcpyDeviceToDevice, c->st));
         }
         HIP_TRY(c, hipStreamSynchronize(c->st));          // the staging buffer is reused by the next chunk
@@ -904,16 +909,18 @@ int poss_prefill(poss_ctx *c, const int32_t *prompt, int32_t n_prompt, int32_t *
 }
 
 // Head over `rows` rows of final-normed activations at x (nullptr: c->u), then the token the target chooses after
-// each: the argmax - reduced per column tile inside the Head GEMM, the logits written only if want_logits - or at
+// each: the argmax - reduced per column tile inside the Head GEMM, logits written only for the first user_rows rows, to
+// user_logits if that is given - or at
 // temperature > 0 a draw by inverse CDF with the uniform number of the row's depth (depth == nullptr: all rows use u[0]).
 // Sequence seq_ids[i] owns rows [row0[i], row0[i] + n_rows[i]) and has its own numbers; the rows' depths and results
-// sit `base` rows further on in the batch-wide arrays (the rows of earlier groups).  *ld_out: row stride of c->logits.
-static int head_and_choose(poss_ctx *c, const void *x, int rows, bool want_logits, const int32_t *depth, const int *seq_ids,
-                           int n_seq, const int *row0, const int *n_rows, int base, int *ld_out, bool drafted_tree) {
+// sit `base` rows further on in the batch-wide arrays (the rows of earlier groups).  *ld_out: row stride of c->logits, 0 where
+// the logits asked for are at user_logits already.
+static int head_and_choose(poss_ctx *c, const void *x, int rows, float *user_logits, int user_rows, const int32_t *depth,
+                           const int *seq_ids, int n_seq, const int *row0, const int *n_rows, int base, int *ld_out, bool drafted_tree) {
     if (c->temperature > 0.f && c->draft_sampling && drafted_tree) {
         // drawn children: the rejection walk over the target's and the drafter's logits writes the path as the g[] of a
         // greedy walk (g[node] = next token on the path), which is what the commit kernel follows
-        const GemmShape g = run_head(c, rows, 0, true, nullptr, x);
+        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, x);
         if (ld_out) *ld_out = g.Npad;
         const poss_config &cf = c->cfg;
         HIP_TRY(c, hipMemcpyAsync(c->ua_dev, c->ua_pinned, (size_t)(cf.depth + 1) * (cf.top_k + 1) * sizeof(float), hipMemcpyHostToDevice, c->st));
@@ -927,7 +934,7 @@ static int head_and_choose(poss_ctx *c, const void *x, int rows, bool want_logit
         return POSS_OK;
     }
     if (c->temperature > 0.f) {
-        const GemmShape g = run_head(c, rows, 0, true, nullptr, x);
+        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, x);
         if (ld_out) *ld_out = g.Npad;
         const int nu = POSS_MAX_DEPTH + 1, ld = g.Npad;
         HIP_TRY(c, hipMemcpyAsync(c->u_dev, c->u_pinned, (size_t)c->B * nu * sizeof(float), hipMemcpyHostToDevice, c->st));
@@ -939,8 +946,8 @@ static int head_and_choose(poss_ctx *c, const void *x, int rows, bool want_logit
         return POSS_OK;
     }
     int n_seg = 0;
-    const GemmShape g = run_head(c, rows, HEAD_ARGMAX, want_logits, &n_seg, x);
-    if (ld_out) *ld_out = g.Npad;
+    const GemmShape g = run_head(c, rows, HEAD_ARGMAX, user_logits, user_rows, &n_seg, x);
+    if (ld_out) *ld_out = n_seg ? 0 : g.Npad;
     int32_t *host = base == 0 ? c->argmax_host_dev : nullptr;     // (at most LAUNCH_ROWS rows)
     if (n_seg)
         launch_argmax_merge(c->topk_scratch, reinterpret_cast<const int *>(c->topk_scratch + (size_t)rows * n_seg), n_seg, rows,
@@ -1212,6 +1219,7 @@ int poss_verify_tree(poss_ctx *c, const poss_tree *tree, int32_t *argmax_out, vo
     // are more than a launch carries, one pass per group of sequences (the rows of a group are adjacent too;
     // as many sequences as fit: eight root-only trees, vanilla decoding of a batch, share one pass).
     const int n = n_rows[0];                               // host and device outputs: the first active sequence's rows
+    const bool feat_direct = feat_out && reinterpret_cast<uintptr_t>(feat_out) % 16 == 0;
     for (int i0 = 0; i0 < B;) {
         int i1 = i0, grows = 0;
         while (i1 < B && grows + n_rows[i1] <= c->launch_rows) grows += n_rows[i1++];
@@ -1223,19 +1231,17 @@ int poss_verify_tree(poss_ctx *c, const poss_tree *tree, int32_t *argmax_out, vo
             rel0[i - i0] = row0[i] - base;
             segs.push_back(Seg{act[i], nullptr, row0[i] - base, n_rows[i], grows, 0, c->seq[act[i]].t, n_rows[i]});
         }
-        target_forward(c, grows, c->tree_token_all + base, rm, segs, c->feats + (size_t)base * cf.d_model);
+        float *lg = i0 == 0 ? static_cast<float *>(logits_out) : nullptr;
+        target_forward(c, grows, c->tree_token_all + base, rm, segs, c->feats + (size_t)base * cf.d_model, i0 == 0 && feat_direct ? static_cast<float *>(feat_out) : nullptr, n);
         int ld = 0;
-        { int rc = head_and_choose(c, nullptr, grows, i0 == 0 && logits_out, c->tree_depth_all, act.data() + i0, i1 - i0, rel0, n_rows + i0, base, &ld, tree == nullptr); if (rc) return rc; }
-        if (i0 == 0 && logits_out && feat_out)             // before the next group overwrites the logits
-            launch_copy_rows2_f32(c->logits, ld, static_cast<float *>(logits_out), cf.vocab, cf.vocab, c->feats, cf.d_model,
-                                  static_cast<float *>(feat_out), cf.d_model, cf.d_model, n, c->st);
-        else if (i0 == 0 && logits_out)
-            launch_copy_rows_f32(c->logits, ld, static_cast<float *>(logits_out), cf.vocab, n, cf.vocab, c->st);
+        { int rc = head_and_choose(c, nullptr, grows, lg, n, c->tree_depth_all, act.data() + i0, i1 - i0, rel0, n_rows + i0, base, &ld, tree == nullptr); if (rc) return rc; }
+        if (lg && ld)                                      // before the next group overwrites the logits
+            launch_copy_rows_f32(c->logits, ld, lg, cf.vocab, n, cf.vocab, c->st);
         i0 = i1;
     }
     (void)hipEventRecord(c->ev[3], c->st);
     c->ev_pending[1] = true;
-    if (feat_out && !logits_out) launch_copy_rows_f32(c->feats, cf.d_model, static_cast<float *>(feat_out), cf.d_model, n, cf.d_model, c->st);
+    if (feat_out && !feat_direct) launch_copy_rows_f32(c->feats, cf.d_model, static_cast<float *>(feat_out), cf.d_model, n, cf.d_model, c->st);
     HIP_TRY(c, hipGetLastError());
     c->state = ST_VERIFIED;
     // Nothing to hand over: stay queued.  (A caller's tree was staged in pinned memory; the only call

@@ -98,14 +98,14 @@ struct EpiArgs {
     // every row its rotated key and its value written to cache slot slot[m]
     int rows_q; const float2 *cs; const int32_t *slot; void *q; KVCache kv; int hq, hkv, dh;
     int rope_packed;   // set by the launcher: the columns of a head are in the packed order of PackSrc::rope_dh
-    // EPI_RESIDUAL: h[m][n] = sum + bias[n] + (residual ? h[m][n] : 0); h_copy likewise; then, if
+    // EPI_RESIDUAL: h[m][n] = sum + bias[n] + (residual ? h[m][n] : 0); h_copy likewise, and rows below h_user_rows of h_user; then, if
     // gain != nullptr, u[m][n] = T(rmsnorm(h[m]) * gain[n]) - the operand of the next GEMM
-    float *h; const void *bias; int residual; float *h_copy; const void *gain; void *u;
+    float *h; const void *bias; int residual; float *h_copy, *h_user; int h_user_rows; const void *gain; void *u;
     // EPI_HEAD (N = vocabulary; the stream kernel's column tile is a "segment"; seg_out / pv, pi must hold
     // gemm_head_segments() entries per row): head_mode HEAD_ARGMAX: pv/pi[row * n_seg + seg] = best (value, index) of the
     // segment, ties to the lower index; HEAD_TOPK: seg_out[(row * n_seg + seg) * TOPK_REC ..] = the segment's record.
-    // write_logits != 0: the float32 logits are also written to the partial-plane buffer (row stride Npad).
-    int head_mode, head_k, write_logits; float *seg_out; float *pv; int *pi;
+    // logits != nullptr: the float32 logits of rows below logits_rows are also written there, row stride N (the caller's array).
+    int head_mode, head_k; float *logits; int logits_rows; float *seg_out; float *pv; int *pi;
     // EPI_SILU: columns [32j, 32j+16) hold gate[16j..16j+15], the next 16 up[16j..16j+15], so one MFMA lane
     // owns both factors of act[m][f] = T(silu(gate) * up); with S == 1 the stream kernel writes act itself
     void *act; int F;
@@ -157,9 +157,6 @@ bool launch_sample(const float *logits, int ld, int rows, int vocab, float tempe
                    const int32_t *depth, float *scratch, int32_t *out, hipStream_t st);
 void launch_copy_rows_f32(const float *src, int ld_src, float *dst, int ld_dst, int rows, int cols,
                           hipStream_t st);
-// two such copies of the same rows in one launch
-void launch_copy_rows2_f32(const float *src, int ld_src, float *dst, int ld_dst, int cols, const float *src2, int ld_src2, float *dst2,
-                           int ld_dst2, int cols2, int rows, hipStream_t st);
 
 // ---------------------------------------------------------------- attention
 struct AttnScratch { float *o; float *ml; };  // partial outputs [split][Hq][rows][dh], (m, l) pairs

@@ -741,21 +741,6 @@ void launch_copy_rows_f32(const float *src, int ld_src, float *dst, int ld_dst, 
                        ld_dst, cols);
 }
 
-__global__ void copy_rows2_f32_kernel(const float *__restrict__ src, int ld_src, float *__restrict__ dst, int ld_dst, int cols, int blocks,
-                                      const float *__restrict__ src2, int ld_src2, float *__restrict__ dst2, int ld_dst2, int cols2) {
-    const bool second = (int)blockIdx.x >= blocks;
-    const int c = ((int)blockIdx.x - (second ? blocks : 0)) * blockDim.x + threadIdx.x;
-    if (second) { if (c < cols2) dst2[(size_t)blockIdx.y * ld_dst2 + c] = src2[(size_t)blockIdx.y * ld_src2 + c]; }
-    else if (c < cols) dst[(size_t)blockIdx.y * ld_dst + c] = src[(size_t)blockIdx.y * ld_src + c];
-}
-
-void launch_copy_rows2_f32(const float *src, int ld_src, float *dst, int ld_dst, int cols, const float *src2, int ld_src2, float *dst2,
-                           int ld_dst2, int cols2, int rows, hipStream_t st) {
-    const int blocks = (cols + 255) / 256, blocks2 = (cols2 + 255) / 256;
-    hipLaunchKernelGGL(copy_rows2_f32_kernel, dim3(blocks + blocks2, rows), dim3(256), 0, st, src, ld_src, dst, ld_dst, cols, blocks, src2,
-                       ld_src2, dst2, ld_dst2, cols2);
-}
-
 __global__ void fill_u32_kernel(uint32_t *p, size_t n, uint32_t v) {
     size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     const size_t stride = (size_t)gridDim.x * blockDim.x;

@@ -131,7 +131,7 @@ __device__ __forceinline__ void tile_epilogue(const float *__restrict__ part, si
 // HEAD (K not split, columns = vocabulary): the workgroup reduces its column tile per row in its own epilogue - the
 // best (value, index) for greedy verification, or maximum, sum of exponentials and the k best for the drafter's
 // log-softmax + top-k - so that no kernel has to read the logits back; they are written only on request.
-struct HeadEpi { int mode, k, vocab, write_logits; float *seg_out; float *pv; int *pi; };
+struct HeadEpi { int mode, k, vocab; float *logits; int logits_rows; float *seg_out; float *pv; int *pi; };
 
 // (value, index) reductions over the 32 lanes of a half wave
 __device__ __forceinline__ void half_argmax(float &v, int &i) {
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(WPB * 64) void gemm_stream_kernel(
     if constexpr (HEAD) {
         constexpr int TW = WPB * GEMM_NT * 16;           // columns of the workgroup's tile = one segment
         static_assert((size_t)MT * 16 * TW * sizeof(float) <= sizeof(xs), "the tile fits the staging memory");
-        if (he.write_logits) {
+        if (he.logits) {                                 // straight to the caller's array
             const int nl = ngroup * (GEMM_NT * 16) + (lane & 15);
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
@@ -359,7 +359,10 @@ __global__ __launch_bounds__(WPB * 64) void gemm_stream_kernel(
                 for (int nt = 0; nt < GEMM_NT; ++nt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        part[(size_t)(mt * 16 + 4 * (lane >> 4) + r) * Npad + nl + nt * 16] = acc[mt][nt][r];
+                    {
+                        const int m = mt * 16 + 4 * (lane >> 4) + r, n = nl + nt * 16;
+                        if (m < he.logits_rows && n < he.vocab) he.logits[(size_t)m * he.vocab + n] = acc[mt][nt][r];
+                    }
         }
         float *tile = reinterpret_cast<float *>(&xs[0][0]);
         __syncthreads();                                 // every wave has read its last operand fragments
@@ -553,7 +556,7 @@ __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
     if constexpr (HEAD) {
         constexpr int TW = 4 * GEMM_NT * 16;
         static_assert((size_t)MT * 16 * TW * sizeof(float) <= sizeof(xs), "the tile fits the staging memory");
-        if (he.write_logits && !producer) {
+        if (he.logits && !producer) {
             const int nl = ngroup * (GEMM_NT * 16) + (lane & 15);
 #pragma unroll
             for (int mt = 0; mt < MTW; ++mt)
@@ -561,7 +564,10 @@ __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
                 for (int nt = 0; nt < GEMM_NT; ++nt)
 #pragma unroll
                     for (int r = 0; r < 4; ++r)
-                        part[(size_t)(row0 + mt * 16 + r) * Npad + nl + nt * 16] = acc[mt][nt][r];
+                    {
+                        const int m = row0 + mt * 16 + r, n = nl + nt * 16;
+                        if (m < he.logits_rows && n < he.vocab) he.logits[(size_t)m * he.vocab + n] = acc[mt][nt][r];
+                    }
         }
         float *tile = reinterpret_cast<float *>(&xs[0]);
         __syncthreads();
@@ -840,6 +846,7 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
     const T *bias = static_cast<const T *>(e.bias), *gain = static_cast<const T *>(e.gain);
     T *u = static_cast<T *>(e.u);
     float *h = e.h + (size_t)m * N, *h_copy = e.h_copy ? e.h_copy + (size_t)m * N : nullptr;
+    float *h_user = e.h_user && m < e.h_user_rows ? e.h_user + (size_t)m * N : nullptr;
     f32x4 x[MAXIT], gn[MAXIT];
     float ss = 0.f;
 #pragma unroll
@@ -863,6 +870,7 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
                 x[it] = v + add;
                 *reinterpret_cast<f32x4 *>(h + n) = x[it];
                 if (h_copy) *reinterpret_cast<f32x4 *>(h_copy + n) = x[it];
+                if (h_user) *reinterpret_cast<f32x4 *>(h_user + n) = x[it];
 #pragma unroll
                 for (int j = 0; j < 4; ++j) ss = fmaf(x[it][j], x[it][j], ss);   // (spelt out: which product is rounded on its own is not left to the compiler)
             } else {
@@ -880,6 +888,7 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
                     v[j] += add[j];
                     h[n + j] = v[j];
                     if (h_copy) h_copy[n + j] = v[j];
+                    if (h_user) h_user[n + j] = v[j];
                     ss = fmaf(v[j], v[j], ss);
                 }
                 x[it] = v;
@@ -1188,7 +1197,7 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
     const bool head = epi.mode == EPI_HEAD;
     if (g.Mpad > 128) {                                  // the tall kernel: one 128-column tile of 192 or 256 rows
         HeadEpi he{};
-        if (head) he = HeadEpi{epi.head_mode, epi.head_k, g.N, epi.write_logits, epi.seg_out, epi.pv, epi.pi};
+        if (head) he = HeadEpi{epi.head_mode, epi.head_k, g.N, epi.logits, epi.logits_rows, epi.seg_out, epi.pv, epi.pi};
         dim3 grid(g.Npad / GEMM_BLOCK_N, g.S), block(TALL_THREADS);
         const int ksteps = g.Kpad / GEMM_KSTEP;
         const u32x4 *w = static_cast<const u32x4 *>(Wp);
@@ -1226,7 +1235,7 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
     const bool wide = !fuse_silu && gemm_wide(g);
     const int wpb = wide ? 8 : 4;
     HeadEpi he{};
-    if (head) he = HeadEpi{epi.head_mode, epi.head_k, g.N, epi.write_logits, epi.seg_out, epi.pv, epi.pi};
+    if (head) he = HeadEpi{epi.head_mode, epi.head_k, g.N, epi.logits, epi.logits_rows, epi.seg_out, epi.pv, epi.pi};
     dim3 grid(g.Npad / (GEMM_NT * 16 * wpb), g.S), block(wpb * 64);
     const int ksteps = g.Kpad / GEMM_KSTEP;
     const u32x4 *w = static_cast<const u32x4 *>(Wp);
