@@ -77,6 +77,7 @@ struct poss_ctx {
     int rows_all;                      // rows of the batch-wide tree arrays
     std::vector<Seq> seq;
     // activations
+    size_t part_floats;                // what part holds
     float *h, *part, *logits, *feats, *fhat[2], *topk_scratch, *taps_user;
     float2 *cs;
     void *u, *xin, *q, *attn_out, *act;
@@ -314,6 +315,7 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
         ctx->cache_slots = slots; ctx->n_pages = pages; ctx->page_table = pt; ctx->cache_bytes_each = cache_each;
         ctx->seq = seqs;
         ctx->cs = cs;
+        ctx->part_floats = part_floats;
         ctx->h = h; ctx->part = part; ctx->logits = logits; ctx->feats = feats; ctx->fhat[0] = fhat0; ctx->fhat[1] = fhat1;
         ctx->topk_scratch = topk_scr; ctx->u = u; ctx->xin = xin; ctx->q = q; ctx->attn_out = ao; ctx->act = act;
         ctx->attn_sc = AttnScratch{ao_part, ml_part};
@@ -539,6 +541,23 @@ void run_block(poss_ctx *c, const void *Wp, int N, int K, int col0, const void *
     if (!launch_gemm_block(c->md.dt, M, N, K, col0, Wp, X, K, e, c->st)) c->launch_refused = true;
 }
 
+// h (+)= X W^T (+ bias), u = T(rmsnorm(h) * gain), stash = T(h)
+void run_block_residual(poss_ctx *c, const void *Wp, int N, int K, const void *X, int M, bool residual, const void *bias, const void *gain,
+                        void *stash) {
+    const int S = gemm_block_splits(M, N, K, c->part_floats);
+    EpiArgs e = epi_residual(c, residual, bias, nullptr, S > 1 ? gain : nullptr);
+    if (S > 1) {
+        EpiArgs p{};
+        p.mode = EPI_PLAIN;
+        if (!launch_gemm_block(c->md.dt, M, N, K, 0, Wp, X, K, p, c->st, S, c->part)) c->launch_refused = true;
+        e.h_stash = stash;
+        launch_residual_norm(c->md.dt, c->part, S, M, N, c->md.eps, e, c->st);
+        return;
+    }
+    run_block(c, Wp, N, K, 0, X, M, e);
+    launch_norm_rows(c->md, c->h, M, gain, c->u, stash, c->st);
+}
+
 EpiArgs epi_rope(poss_ctx *c, const KVCache &kv, int rows_q) {
     EpiArgs e{};
     e.mode = EPI_ROPE_KV; e.rows_q = rows_q; e.cs = c->cs; e.slot = c->row_slot; e.q = c->q; e.kv = kv;
@@ -558,15 +577,13 @@ void prefill_pass(poss_ctx *c, int b, int rows, int c0) {
         const LayerW &w = c->layers[l];
         run_block(c, w.wqkv, qd + 2 * kd, md.d, 0, c->u, rows, epi_rope(c, sq.target_kv[l], rows));
         launch_attention_prompt(md, c->q, rows, c->row_mask, c0, sq.target_kv[l], c->attn_out, c->st);
-        run_block(c, w.wo, md.d, qd, 0, c->attn_out, rows, epi_residual(c, true, nullptr, nullptr, nullptr));
-        launch_norm_rows(md, c->h, rows, w.mlp_norm, c->u, nullptr, c->st);
+        run_block_residual(c, w.wo, md.d, qd, c->attn_out, rows, true, nullptr, w.mlp_norm, nullptr);
         EpiArgs e{};
         e.mode = EPI_SILU; e.act = c->act; e.F = md.ffn;
         run_block(c, w.wgu, gate_up_rows(md.ffn), md.d, 0, c->u, rows, e);
-        run_block(c, w.wdown, md.d, md.ffn, 0, c->act, rows, epi_residual(c, true, nullptr, nullptr, nullptr));
         const bool last = l + 1 == nl;
-        launch_norm_rows(md, c->h, rows, last ? c->final_norm : c->layers[l + 1].attn_norm, c->u,
-                         last ? static_cast<char *>(sq.feat_stash) + (size_t)c0 * md.d * es : nullptr, c->st);
+        run_block_residual(c, w.wdown, md.d, md.ffn, c->act, rows, true, nullptr, last ? c->final_norm : c->layers[l + 1].attn_norm,
+                           last ? static_cast<char *>(sq.feat_stash) + (size_t)c0 * md.d * es : nullptr);
     }
 }
 
@@ -577,8 +594,7 @@ void catchup_pass(poss_ctx *c, int b, int s, int i0, int n) {
     Seq &sq = c->seq[b];
     const int qd = md.hq * md.dh, kd = md.hkv * md.dh;
     launch_assemble_pairs(md, i0, n, c->embed, sq.tokens_dev, sq.feat_stash, c->xin, c->row_slot, c->inv_freq, c->cs, c->st);
-    run_block(c, w.fc_w, md.d, 2 * md.d, 0, c->xin, n, epi_residual(c, false, c->cfg.fc_bias ? w.fc_b : nullptr, nullptr, nullptr));
-    launch_norm_rows(md, c->h, n, w.layer.attn_norm, c->u, nullptr, c->st);
+    run_block_residual(c, w.fc_w, md.d, 2 * md.d, c->xin, n, false, c->cfg.fc_bias ? w.fc_b : nullptr, w.layer.attn_norm, nullptr);
     run_block(c, w.layer.wqkv, qd + 2 * kd, md.d, qd, c->u, n, epi_rope(c, sq.spec_kv[s], 0));
 }
 

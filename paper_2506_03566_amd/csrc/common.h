@@ -98,9 +98,10 @@ struct EpiArgs {
     // every row its rotated key and its value written to cache slot slot[m]
     int rows_q; const float2 *cs; const int32_t *slot; void *q; KVCache kv; int hq, hkv, dh;
     int rope_packed;   // set by the launcher: the columns of a head are in the packed order of PackSrc::rope_dh
-    // EPI_RESIDUAL: h[m][n] = sum + bias[n] + (residual ? h[m][n] : 0); h_copy likewise, and rows below h_user_rows of h_user; then, if
+    // EPI_RESIDUAL: h[m][n] = sum + bias[n] + (residual ? h[m][n] : 0); h_copy likewise, and rows below h_user_rows of h_user;
+    // h_stash (16-bit types): the same in the storage type; then, if
     // gain != nullptr, u[m][n] = T(rmsnorm(h[m]) * gain[n]) - the operand of the next GEMM
-    float *h; const void *bias; int residual; float *h_copy, *h_user; int h_user_rows; const void *gain; void *u;
+    float *h; const void *bias; int residual; float *h_copy, *h_user; int h_user_rows; void *h_stash; const void *gain; void *u;
     // EPI_HEAD (N = vocabulary; the stream kernel's column tile is a "segment"; seg_out / pv, pi must hold
     // gemm_head_segments() entries per row): head_mode HEAD_ARGMAX: pv/pi[row * n_seg + seg] = best (value, index) of the
     // segment, ties to the lower index; HEAD_TOPK: seg_out[(row * n_seg + seg) * TOPK_REC ..] = the segment's record.
@@ -135,7 +136,12 @@ static inline int head_segments_max(int vocab) { return gemm_npad(vocab) / GEMM_
 // without its queries).  tile < 0: chosen by the shape.  Returns false, launching nothing, on arguments it does not take.
 constexpr int PREFILL_ROWS = 4096;             // rows of a prompt that one pass of such launches carries at most
 bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &epi,
-                       hipStream_t st, int tile = -1);
+                       hipStream_t st, int splits = 1, float *part = nullptr, int tile = -1);
+// EPI_PLAIN with splits > 1: plane s of part, [M][N], receives the sums over the s-th part of K.  The number of splits with which
+// this and launch_residual_norm are faster than EPI_RESIDUAL and launch_norm_rows (1: none), part holding part_floats.
+int gemm_block_splits(int M, int N, int K, size_t part_floats);
+// The epilogue EPI_RESIDUAL describes over S planes [rows][N] (16-bit types, N a multiple of 4).
+void launch_residual_norm(int dt, const float *part, int S, int rows, int N, float rms_eps, const EpiArgs &epi, hipStream_t st);
 
 // ---------------------------------------------------------------- launchers: elementwise
 // u[m] = T(rmsnorm(h[m]) * gain) and, if stash != nullptr, stash[m] = T(h[m]); d a multiple of 4, at most 16384

@@ -871,6 +871,12 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
                 *reinterpret_cast<f32x4 *>(h + n) = x[it];
                 if (h_copy) *reinterpret_cast<f32x4 *>(h_copy + n) = x[it];
                 if (h_user) *reinterpret_cast<f32x4 *>(h_user + n) = x[it];
+                if (e.h_stash) {
+                    Quad o;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) o.t[j] = from_f<T>(x[it][j]);
+                    *reinterpret_cast<Quad *>(static_cast<T *>(e.h_stash) + (size_t)m * N + n) = o;
+                }
 #pragma unroll
                 for (int j = 0; j < 4; ++j) ss = fmaf(x[it][j], x[it][j], ss);   // (spelt out: which product is rounded on its own is not left to the compiler)
             } else {
@@ -1079,6 +1085,15 @@ __global__ __launch_bounds__(ROPE_THREADS) void epilogue_rope_ranges_kernel(cons
                        : static_cast<T *>(kv.k) + k_offset(kv, sl, gh - e.hq, e.hkv, e.dh) + i;
     *reinterpret_cast<Quad *>(dst) = o1;
     *reinterpret_cast<Quad *>(dst + half) = o2;
+}
+
+void launch_residual_norm(int dt, const float *part, int S, int rows, int N, float eps, const EpiArgs &epi, hipStream_t st) {
+    int threads = round_up((N + 3) / 4, 64);
+    if (threads > 1024) threads = 1024;
+    if (dt == DT_BF16)
+        hipLaunchKernelGGL((epilogue_residual_norm_kernel<bf16_t, true>), dim3(rows), dim3(threads), 0, st, part, (size_t)rows * N, S, N, N, eps, epi);
+    else
+        hipLaunchKernelGGL((epilogue_residual_norm_kernel<f16_t, true>), dim3(rows), dim3(threads), 0, st, part, (size_t)rows * N, S, N, N, eps, epi);
 }
 
 // ------------------------------------------------------------------------------------------
