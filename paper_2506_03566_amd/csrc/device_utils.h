@@ -89,13 +89,42 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi) {
     return (v > bv) || (v == bv && i < bi);
 }
 
-__device__ __forceinline__ void wave_argmax(float &v, int &i) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(v, o, 64);
-        const int oi = __shfl_xor(i, o, 64);
-        if (better(ov, oi, v, i)) { v = ov; i = oi; }
+// One step of an argmax butterfly: the pair of lane l ^ OFF (OFF = 8, 4, 2, 1 by DPP; 16, 32 by the row swaps).
+__device__ __forceinline__ int as_int(float x) { return __builtin_bit_cast(int, x); }
+__device__ __forceinline__ float as_float(int x) { return __builtin_bit_cast(float, x); }
+template <int OFF>
+__device__ __forceinline__ void argmax_step(float &v, int &i) {
+    float ov; int oi;
+    if constexpr (OFF >= 16) {
+        float v2, i1, i2;
+        if constexpr (OFF == 32) { swap32(v, ov, v2); swap32(as_float(i), i1, i2); } else { swap16(v, ov, v2); swap16(as_float(i), i1, i2); }
+        oi = as_int(i1); v = v2; i = as_int(i2);          // the pair in the order (lower lane, upper lane)
+    } else {
+        const float fi = as_float(i);
+        ov = OFF == 8 ? xor8(v) : OFF == 4 ? xor4(v) : OFF == 2 ? xor2(v) : xor1(v);
+        oi = as_int(OFF == 8 ? xor8(fi) : OFF == 4 ? xor4(fi) : OFF == 2 ? xor2(fi) : xor1(fi));
     }
+    if (better(ov, oi, v, i)) { v = ov; i = oi; }
+}
+// over the 32 lanes of a half wave (all of them active; the other half need not be)
+__device__ __forceinline__ void half_argmax(float &v, int &i) {
+    argmax_step<16>(v, i); argmax_step<8>(v, i); argmax_step<4>(v, i); argmax_step<2>(v, i); argmax_step<1>(v, i);
+}
+__device__ __forceinline__ float half_max(float v) {
+    float a, b;
+    swap16(v, a, b); v = fmaxf(a, b);
+    v = fmaxf(v, xor8(v)); v = fmaxf(v, xor4(v)); v = fmaxf(v, xor2(v)); v = fmaxf(v, xor1(v));
+    return v;
+}
+__device__ __forceinline__ float half_sum(float v) {
+    float a, b;
+    swap16(v, a, b); v = a + b;
+    v += xor8(v); v += xor4(v); v += xor2(v); v += xor1(v);
+    return v;
+}
+__device__ __forceinline__ void wave_argmax(float &v, int &i) {
+    argmax_step<32>(v, i);
+    half_argmax(v, i);
 }
 
 // Workgroup-wide argmax; result valid in every thread.  red_v/red_i: >= 17 entries of LDS each.

@@ -133,17 +133,6 @@ __device__ __forceinline__ void tile_epilogue(const float *__restrict__ part, si
 // log-softmax + top-k - so that no kernel has to read the logits back; they are written only on request.
 struct HeadEpi { int mode, k, vocab; float *logits; int logits_rows; float *seg_out; float *pv; int *pi; };
 
-// (value, index) reductions over the 32 lanes of a half wave
-__device__ __forceinline__ void half_argmax(float &v, int &i) {
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) {
-        const float ov = __shfl_xor(v, o, 32);
-        const int oi = __shfl_xor(i, o, 32);
-        if (better(ov, oi, v, i)) { v = ov; i = oi; }
-    }
-}
-
-
 // ---- epilogues on a finished output tile, shared by the stream kernel and the tall kernel --------------------------
 // SiLU(gate) * up of a workgroup's rows x TW activation columns, collected in LDS (row stride TW + 8 elements: the four
 // row groups of a wave hit different banks) and written out so that a row leaves as one contiguous piece in 16-byte
@@ -159,7 +148,8 @@ __device__ __forceinline__ void silu_tile_store(const T *tile, T *__restrict__ a
 }
 
 // The Head's reduction of a tile of logits in LDS, tile[row][TW] = columns [col0, col0 + TW): one half wave per row (NHW
-// of them; shuffles stay inside a half).  HEAD_ARGMAX: the best (value, index) of the row's segment; HEAD_TOPK: maximum,
+// of them; the exchanges stay inside a half and in the vector ALU: by shuffles, about 100 cycles each, the ten rounds of a
+// drafted row cost 4 us of the Head's 167).  HEAD_ARGMAX: the best (value, index) of the row's segment; HEAD_TOPK: maximum,
 // sum of exp(l - max) in a fixed order, and the k best by k rounds of (argmax, remove).
 template <int TW, int NHW>
 __device__ __forceinline__ void head_tile_reduce(const float *tile, int M, const HeadEpi &he, int seg, int n_seg, int tid) {
@@ -181,14 +171,11 @@ __device__ __forceinline__ void head_tile_reduce(const float *tile, int M, const
             if (hl == 0) { he.pv[(size_t)row * n_seg + seg] = bv; he.pi[(size_t)row * n_seg + seg] = bi; }
             continue;
         }
-        float mx = bv;
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o, 32));
+        const float mx = half_max(bv);
         float se = 0.f;
 #pragma unroll
         for (int j = 0; j < NVH; ++j) se += v[j] > -INFINITY ? expf(v[j] - mx) : 0.f;
-#pragma unroll
-        for (int o = 16; o > 0; o >>= 1) se += __shfl_xor(se, o, 32);
+        se = half_sum(se);
         float *rec = he.seg_out + ((size_t)row * n_seg + seg) * TOPK_REC;
         if (hl == 0) { rec[0] = mx; rec[1] = se; }
         float my_v = -INFINITY; int my_i = 0x7fffffff;

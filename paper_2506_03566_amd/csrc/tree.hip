@@ -31,6 +31,22 @@ struct __attribute__((aligned(16))) TopkLds {
     float thr_w[4]; int cnt;
 };
 
+// How many of the cnt candidates are better than (cv, ci).  Sixteen bytes of values and of indices at a time, several in
+// flight; entries from cnt to the next multiple of 4 hold whatever they hold and are not counted.
+__device__ __forceinline__ int rank_among(const TopkLds &L, int cnt, float cv, int ci) {
+    int r = 0;
+#pragma unroll 4
+    for (int j = 0; j < cnt; j += 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(&L.cand_v[j]);
+        const int4 i = *reinterpret_cast<const int4 *>(&L.cand_i[j]);
+        r += better(v.x, i.x, cv, ci);
+        r += j + 1 < cnt && better(v.y, i.y, cv, ci);
+        r += j + 2 < cnt && better(v.z, i.z, cv, ci);
+        r += j + 3 < cnt && better(v.w, i.w, cv, ci);
+    }
+    return r;
+}
+
 template <int NV>
 __device__ __forceinline__ void block_topk_rounds(float (&v)[NV], int (&id)[NV], int k, float *s_val, int *s_id,
                                                   float &out_v, int &out_i) {
@@ -98,8 +114,7 @@ __device__ __forceinline__ void block_topk(float (&v)[NV], int (&id)[NV], int k,
     }
     if (tid < cnt) {
         const float cv = L.cand_v[tid]; const int ci = L.cand_i[tid];
-        int r = 0;
-        for (int j = 0; j < cnt; ++j) r += better(L.cand_v[j], L.cand_i[j], cv, ci);
+        const int r = rank_among(L, cnt, cv, ci);
         if (r < k) { L.out_v[r] = cv; L.out_i[r] = ci; }
     }
     __syncthreads();
@@ -211,8 +226,7 @@ __device__ __forceinline__ bool topk_merge_heads(const float *__restrict__ recs,
     if (cnt > TOPK_CAND) { __syncthreads(); return false; }   // (workgroup-uniform; L is reused by the full merge)
     if (tid < cnt) {
         const float cv = L.cand_v[tid]; const int ci = L.cand_i[tid];
-        int r = 0;
-        for (int j = 0; j < cnt; ++j) r += better(L.cand_v[j], L.cand_i[j], cv, ci);
+        const int r = rank_among(L, cnt, cv, ci);
         if (r < k) { L.out_v[r] = cv; L.out_i[r] = ci; }
     }
     __syncthreads();
@@ -314,11 +328,12 @@ struct TreeBatch {
 };
 
 __global__ __launch_bounds__(256) void tree_expand_kernel(TreeBatch tb, int d, int k, int L, int rows, int vocab) {
-    __shared__ float sc[256];
+    __shared__ __attribute__((aligned(16))) float sc[256];
     const TreeDev &td = tb.td[blockIdx.x];
     const int n_child = rows * k;
     const int base = d == 1 ? 0 : k + (d - 2) * k * k;
     const int tid = threadIdx.x;
+    sc[tid] = -INFINITY;                                  // (the ranking reads the scores four at a time)
     uint64_t pw0 = 0ull, pw1 = 0ull;                      // the parent's ancestor mask, asked for with the rest
     if (tid < n_child) {
         const int r = tid / k;
@@ -340,7 +355,14 @@ __global__ __launch_bounds__(256) void tree_expand_kernel(TreeBatch tb, int d, i
     if (d < L && tid < n_child) {
         const float s = sc[tid];
         int rank = 0;
-        for (int j = 0; j < n_child; ++j) rank += (sc[j] > s) || (sc[j] == s && j < tid);
+#pragma unroll 4
+        for (int j = 0; j < n_child; j += 4) {
+            const float4 o = *reinterpret_cast<const float4 *>(&sc[j]);
+            rank += (o.x > s) || (o.x == s && j < tid);
+            rank += (o.y > s) || (o.y == s && j + 1 < tid);
+            rank += (o.z > s) || (o.z == s && j + 2 < tid);
+            rank += (o.w > s) || (o.w == s && j + 3 < tid);
+        }
         if (rank < k) {
             const int r = tid / k, o = d * k + rank;
             td.fr_pool[o] = base + tid;
@@ -401,14 +423,28 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int p
         const int i = tid + p * 1024;
         keep[p] = false;
         if (i < pool_n) {
+            // candidates before this wave's 64 win ties (>=), those behind lose them (>): one comparison each; only among
+            // the 64 does the index decide
             const float s = sc[i];
+            const int d0 = __builtin_amdgcn_readfirstlane(i & ~63), d1 = min(d0 + 64, pool_n);
             int rank = 0;
-            for (int j = 0; j < pool_n; j += 4) {
+#pragma unroll 4
+            for (int j = 0; j < d0; j += 4) {
+                const float4 o = *reinterpret_cast<const float4 *>(&sc[j]);
+                rank += o.x >= s; rank += o.y >= s; rank += o.z >= s; rank += o.w >= s;
+            }
+#pragma unroll 4
+            for (int j = d0; j < d1; j += 4) {
                 const float4 o = *reinterpret_cast<const float4 *>(&sc[j]);
                 rank += (o.x > s) || (o.x == s && j < i);
                 rank += (o.y > s) || (o.y == s && j + 1 < i);
                 rank += (o.z > s) || (o.z == s && j + 2 < i);
                 rank += (o.w > s) || (o.w == s && j + 3 < i);
+            }
+#pragma unroll 4
+            for (int j = d1; j < pool_n; j += 4) {
+                const float4 o = *reinterpret_cast<const float4 *>(&sc[j]);
+                rank += o.x > s; rank += o.y > s; rank += o.z > s; rank += o.w > s;
             }
             keep[p] = rank < n_keep;
         }
