@@ -1,0 +1,99 @@
+"""Dispatch branches at the sizes where they can go wrong: draws from vocabularies around a block of 256 ids and beyond 1024 blocks,
+attention merged from 2 to 16 splits, and outputs that the kernels write straight into the caller's arrays."""
+import numpy as np
+import pytest
+
+from gpu_util import have_gpu, Pair, tol_for
+
+pytestmark = pytest.mark.gpu
+
+if have_gpu():
+    import torch
+    import paper_2506_03566_amd as P
+    from oracle.sampling import softmax_t
+    from oracle.tree import Tree
+    from synth import make_prompt
+
+
+# a block and one id less and more; segments of 4096; 1025 blocks: two blocks per share of the scan
+@pytest.mark.parametrize("vocab", [255, 256, 257, 4096, 4100, 262401])
+def test_drawn_children_lie_in_their_cdf_intervals(vocab):
+    """The children of the root and of one frontier node against the float64 inverse CDF of the library's own drafter logits
+    (float32 prefix sums of up to 262401 masses: within 3e-5 of the interval, the bound of the full-vocabulary test), and a whole
+    round of drafting, rejection walk and commit."""
+    print(f"draws from {vocab} ids", flush=True)
+    pair = Pair("c0_tiny_f32", vocab=vocab, d_model=64, n_q_heads=1, n_kv_heads=1, d_ffn=64, n_layers=1, n_specialists=1,
+                positions_per_specialist=6)
+    cfg, ctx, k = pair.cfg, pair.ctx, pair.cfg.top_k
+    ctx.prefill(make_prompt(cfg, n=12))
+    ctx.set_sampling(0.8, np.zeros(cfg.depth + 1, np.float32))
+    for seed in range(3):
+        rng = np.random.default_rng(seed)
+        UD = (rng.random((cfg.depth, k, k)) * 0.999).astype(np.float32)
+        UD[0, 0, 0], UD[0, 0, 1] = (0.0, 0.9999999) if seed == 0 else UD[0, 0, :2]       # the first and the last id with mass
+        ctx.set_draft_sampling(UD, (rng.random((cfg.depth + 1, k + 1)) * 0.999).astype(np.float32))
+        d = ctx.draft_tree().as_dict()
+        root = [i for i in range(1, d["n"]) if d["parent"][i] == 0]
+        q = softmax_t(ctx.debug_draft_logits(0, 1)[0].cpu().numpy().astype(np.float64), 0.8)
+        left = q.copy()
+        for j, node in enumerate(root):
+            c = d["token"][node]
+            cdf = np.cumsum(left) / left.sum()
+            lo, hi = (cdf[c - 1] if c else 0.0), cdf[c]
+            assert 0 <= c < vocab and lo - 3e-5 <= float(UD[0, 0, j]) < hi + 3e-5, (seed, j, c, lo, hi)
+            assert abs(d["score"][node] - np.log(q[c])) <= 1e-4
+            left[c] = 0.0
+        assert len({d["token"][i] for i in root}) == len(root) == k
+        ctx.verify_tree()
+        path, m, toks = ctx.accept_and_commit()
+        assert len(toks) == m + 1 and all(0 <= t < vocab for t in toks)
+    pair.close()
+
+
+# keys per split -> splits of the prefix and the tree's rows: 2, 4 (registers), 7, 12 (registers), 13 and 16 (the loop)
+@pytest.mark.parametrize("name", ["t_mid_bf16", "t_mid_f16"])
+@pytest.mark.parametrize("n_prompt,keys", [(60, 64), (240, 64), (430, 64), (750, 64), (800, 64), (1000, 64)])
+def test_attention_merged_from_any_number_of_splits(name, n_prompt, keys):
+    print(f"merge {name} prompt={n_prompt} keys per split={keys}", flush=True)
+    pair = Pair(name, n_layers=1, max_seq=1152, n_specialists=1)
+    cfg = pair.cfg
+    prompt = make_prompt(cfg, n=n_prompt)
+    o = pair.oracle()
+    o.prefill(prompt)
+    pair.ctx.prefill(prompt)
+    pair.ctx.set_tuning(0, keys)
+    tree = ([pair.ctx.tokens()[-1], 5, 6, 7, 8], [-1, 0, 0, 1, 3])
+    logits = torch.zeros(5, cfg.vocab, device="cuda")
+    pair.ctx.verify_tree(P.TreeArrays.from_lists(*tree), logits_out=logits)
+    o.tokens[-1] = tree[0][0]                              # (a near-tie may choose either first token)
+    _, want, _ = o.verify_tree(Tree(*tree))
+    assert np.abs(logits.cpu().numpy() - want).max() <= tol_for(cfg)
+    pair.close()
+
+
+@pytest.mark.parametrize("name,over", [("t_mid_f16", dict(vocab=5003)), ("t_mid_bf16", dict(vocab=4097)), ("c0_tiny_f32", dict(vocab=1001))])
+def test_outputs_end_where_the_callers_arrays_end(name, over):
+    """Logits and features written by the kernels themselves: an odd vocabulary, rows that are not whole tiles, a feature array
+    that is not aligned to 16 bytes; what lies around the arrays is untouched and both alignments give the same bits."""
+    print(f"outputs {name} {over}", flush=True)
+    pair = Pair(name, **over)
+    cfg, ctx = pair.cfg, pair.ctx
+    ctx.prefill(make_prompt(cfg, n=40))
+    tree = P.TreeArrays.from_lists([0, 5, 6, 7, 8], [-1, 0, 0, 1, 3])
+    got = []
+    for shift in (0, 1):
+        lo = torch.full((2 * cfg.vocab + 5 * cfg.vocab,), -7.0, device="cuda")
+        fe = torch.full((8 + 7 * cfg.d_model,), -7.0, device="cuda")
+        lv, fv = lo[cfg.vocab:6 * cfg.vocab], fe[4 + shift:4 + shift + 5 * cfg.d_model]
+        g = ctx.verify_tree(tree, logits_out=lv, feat_out=fv)[:5]
+        torch.cuda.synchronize()
+        assert (lo[:cfg.vocab] == -7).all() and (lo[6 * cfg.vocab:] == -7).all()
+        assert (fe[:4 + shift] == -7).all() and (fe[4 + shift + 5 * cfg.d_model:] == -7).all()
+        assert g.tolist() == lv.view(5, cfg.vocab).argmax(1).tolist()
+        got.append((lv.clone(), fv.clone()))
+        ctx.accept_and_commit()
+        if shift == 0:                                     # the same state again
+            ctx.reset()
+            ctx.prefill(make_prompt(cfg, n=40))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    pair.close()
