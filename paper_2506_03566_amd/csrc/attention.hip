@@ -542,7 +542,8 @@ __global__ __launch_bounds__(256 * KW) void attn_mfma_batch_kernel(AttnSeqs seqs
 
 // out[m][qh][:] = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, splits in order, for the rows of every sequence of a launch
 // (sequences whose keys fit one split wrote their rows directly and are skipped).  dh / 4 lanes per (row, query head), four
-// columns each.  Up to NR splits (the usual case, NR = 4, 8, 12): everything in registers and every load requested before the first
+// columns each; a workgroup stays within one row, so that which sequence it belongs to is scalar (looked up per lane, the
+// sequence's pointers cost a trip to memory of their own: 5.6 us in the round of the 8B shape).  Up to NR splits (the usual case, NR = 4, 8, 12): everything in registers and every load requested before the first
 // use - one trip to memory, no LDS, no barrier; each lane forms the weights itself (the (max, sum) pairs are the same addresses for
 // the group) and slots beyond n_splits re-read the last split and are not used.  NR = 0: any number of splits, two passes over
 // the (max, sum) pairs.  Four times 61 rows of the 8B shape, four
@@ -550,17 +551,16 @@ __global__ __launch_bounds__(256 * KW) void attn_mfma_batch_kernel(AttnSeqs seqs
 // a column per lane).
 constexpr int ATTN_MAX_SPLITS = 256, MERGE_THREADS = 256;
 template <typename T, int NR>
-__global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(AttnSeqs seqs, int n_rows, int hq, int hkv, int dh, T *__restrict__ out) {
+__global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(AttnSeqs seqs, int hq, int hkv, int dh, T *__restrict__ out) {
     struct __attribute__((aligned(8))) Quad { T t[4]; };
-    const int lanes = dh >> 2, idx = blockIdx.x * (MERGE_THREADS / lanes) + (int)threadIdx.x / lanes, i = ((int)threadIdx.x % lanes) * 4;
-    const int row = idx / hq, qh = idx % hq;
-    if (row >= n_rows) return;
+    const int lanes = dh >> 2, row = blockIdx.x, qh = blockIdx.y * (MERGE_THREADS / lanes) + (int)threadIdx.x / lanes;
+    const int i = ((int)threadIdx.x % lanes) * 4;
     int si = 0;
     for (int j = 1; j < seqs.n; ++j)
         if (row >= seqs.s[j].row0) si = j;
     const AttnSeq &a = seqs.s[si];
     const int m = row - a.row0, n_splits = a.n_splits;
-    if (m >= a.rows || n_splits == 1) return;
+    if (m >= a.rows || n_splits == 1 || qh >= hq) return;
     const int G = hq / hkv, kvh = qh / G, rho = m * G + qh % G;
     const size_t stride = (size_t)hkv * a.rho_pad;        // rows between consecutive splits
     const size_t row0 = (size_t)kvh * a.rho_pad + rho;
@@ -609,8 +609,8 @@ static void launch_merge_t(const ModelDims &md, const AttnSeqs &seqs, int n_rows
     int most = 0;
     for (int i = 0; i < seqs.n; ++i) if (seqs.s[i].n_splits > most) most = seqs.s[i].n_splits;
     const int per = MERGE_THREADS / (md.dh >> 2);
-    dim3 grid((n_rows * md.hq + per - 1) / per), block(MERGE_THREADS);
-#define POSS_MERGE(NR) hipLaunchKernelGGL((attn_merge_kernel<T, NR>), grid, block, 0, st, seqs, n_rows, md.hq, md.hkv, md.dh, out)
+    dim3 grid(n_rows, (md.hq + per - 1) / per), block(MERGE_THREADS);
+#define POSS_MERGE(NR) hipLaunchKernelGGL((attn_merge_kernel<T, NR>), grid, block, 0, st, seqs, md.hq, md.hkv, md.dh, out)
     if (most <= 4) POSS_MERGE(4); else if (most <= 8) POSS_MERGE(8); else if (most <= 12) POSS_MERGE(12); else POSS_MERGE(0);
 #undef POSS_MERGE
 }
