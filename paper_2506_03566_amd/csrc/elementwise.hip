@@ -1,6 +1,7 @@
 // Small kernels around the GEMMs: embedding gather + first RMSNorm, rotary table, argmax, row copies.  All arithmetic in
 // float32; values become the storage type only where they are the next GEMM's operand.
 #include "device_utils.h"
+#include "quotient.h"
 
 namespace poss {
 
@@ -611,15 +612,6 @@ void launch_draft_masses(const float *logits, int ld, int rows, int vocab, float
     launch_sample_children(logits, ld, rows, vocab, 0, temperature, m, nullptr, nullptr, nullptr, st);
 }
 
-// x / z with y = 1 / z (rounded to nearest), rounded to nearest as the division is: one correction makes the quotient faithful,
-// the second, its remainder exact, rounds it (Markstein).  Five operations where the compiler's division takes about ten; below
-// 2.4e-38, where the remainders underflow, the last bit may differ.
-__device__ __forceinline__ float quotient(float x, float z, float y) {
-    float q = x * y;
-    q = fmaf(fmaf(-q, z, x), y, q);
-    return fmaf(fmaf(-q, z, x), y, q);
-}
-
 // The walk, one workgroup.  The masses of the target's rows and the drafter's are there (draw_mass_kernel), so a rejection is one
 // pass that reads two rows, P and Q, and writes the residual with its block sums (before: two exponentials and two divisions per
 // id as well, and four passes per node for maxima and totals).  One round over 128256 ids: 401 -> 41 us, and 16 for the masses of
@@ -682,6 +674,7 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
             __syncthreads();                              // resid[c] has been read by every thread
             const float *from = have_resid ? resid : P;
             const float yp = 1.0f / zp, yq = 1.0f / zq;
+            const bool by_reciprocal = quotient_divisor(zp) && quotient_divisor(zq);      // (what is left of q can be nothing)
             for (int b0 = wave; b0 < nblk; b0 += DRAW_WAVES * DRAW_UNROLL) {
                 f32x4e pv[DRAW_UNROLL], qv[DRAW_UNROLL];
 #pragma unroll
@@ -701,8 +694,16 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
                         if (r >= 0 && r < 4) qm[r] = 0.f;
                     }
                     f32x4e r4;
+                    unsigned least = ~0u;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) r4[j] = fmaxf(quotient(pv[x][j], zp, yp) - quotient(qm[j], zq, yq), 0.f);
+                    for (int j = 0; j < 4; ++j) least = min(least, min(quotient_key(pv[x][j]), quotient_key(qm[j])));
+                    if (by_reciprocal && !__any(least < QUOTIENT_LEAST)) {
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) r4[j] = fmaxf(quotient(pv[x][j], zp, yp) - quotient(qm[j], zq, yq), 0.f);
+                    } else {                              // masses of 1e-30 and below (a low temperature), or no divisor for it
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) r4[j] = fmaxf(pv[x][j] / zp - qm[j] / zq, 0.f);
+                    }
                     if (id0 + 3 < ld) *reinterpret_cast<f32x4e *>(resid + id0) = r4;
                     const float s = wave_sum(((r4[0] + r4[1]) + r4[2]) + r4[3]);
                     if (lane == 0) L.bsum[b] = s;

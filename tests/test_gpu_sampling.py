@@ -214,6 +214,38 @@ def test_drawn_children_and_rejection_walk_equal_the_oracle(T):
     pair.close()
 
 
+def test_rejection_walk_with_masses_too_small_for_the_quotient():
+    """T = 0.02: masses down to 1e-33, which the walk divides by the long way.  Children, path and last token are the oracle's;
+    margins of 2e-3 (a logit's float32 error counts fifty-fold)."""
+    T = 0.02
+    pair = Pair("c0_tiny_f32", vocab=96)
+    cfg, ctx = pair.cfg, pair.ctx
+    o = pair.oracle()
+    prompt = make_prompt(cfg, n=24)
+    assert ctx.prefill(prompt) == o.prefill(prompt)
+    ctx.set_sampling(T, np.zeros(cfg.depth + 1, np.float32))
+    seed = rounds = small = 0
+    while rounds < 5 and seed < 200:
+        seed += 1
+        UD, UA = _numbers(cfg, seed)
+        otree = o.draft_tree(sampling=(T, UD))
+        opath, olast = o.verify_tree_sampled(otree, T, UA)
+        if min(o.draw_margins) < 2e-3 or (o.accept_margins and min(o.accept_margins) < 2e-3):
+            continue
+        _say(f"  numbers {seed} pass the screen, round {rounds} on the GPU")
+        small += sum(int(((q > 0) & (q / q.max() < 2.0 ** -100)).sum()) for q in o.last["draft_q"].values())
+        ctx.set_draft_sampling(UD, UA)
+        d = ctx.draft_tree().as_dict()
+        assert d["token"][1:] == otree.token[1:] and d["parent"] == otree.parent, f"seed {seed}"
+        ctx.verify_tree()
+        path, m, toks = ctx.accept_and_commit()
+        assert path == opath and toks[-1] == olast, f"seed {seed}"
+        o.accept_and_commit(path=opath, bonus=olast)
+        rounds += 1
+    assert rounds == 5 and small >= 5
+    pair.close()
+
+
 @pytest.mark.parametrize("name", ["t_mid_bf16", "t_mid_f16"])
 def test_drawn_children_at_16_bit_shapes_give_valid_rounds(name):
     """16-bit storage, vocabularies of thousands: draws fall too close to interval ends for a token-by-token comparison,
