@@ -46,6 +46,14 @@ __device__ __forceinline__ float lane_value(float v, int lane) {       // lane w
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), lane));
 }
 
+// What a lane of this wave wrote to LDS before it is what every lane reads behind it (LDS operations of a wave complete in
+// order: no instruction comes of this, it orders the compiler's accesses).
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum over a workgroup of up to 1024 threads, identical in every thread; fixed order.
 __device__ __forceinline__ float block_sum(float v, float *red /* >= 17 floats of LDS */) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = (blockDim.x + 63) >> 6;

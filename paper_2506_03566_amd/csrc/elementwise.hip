@@ -491,7 +491,7 @@ __global__ __launch_bounds__(DRAW_THREADS) void sample_children_kernel(const flo
     if (wave == 0) {
         const float uu = lane < k ? u[rowi * k + lane] : 0.f, mx = dm.mx[rowi];
         for (int b = lane; b < nblk; b += 64) bsum[b] = dm.bsum[(size_t)rowi * nblk + b];
-        __builtin_amdgcn_wave_barrier();
+        wave_lds_sync();
         // share t = blocks [t per, (t + 1) per); lane l of scan w has share 64 w + l: sh its sum, sc the inclusive scan over the 64
         auto share = [&](int t) {
             float s = 0.f;
@@ -561,7 +561,7 @@ __global__ __launch_bounds__(DRAW_THREADS) void sample_children_kernel(const flo
             for (int x = 0; x < 4; ++x) if (c - id0 == x) m[x] = 0.f;
             const float s = wave_sum(((m[0] + m[1]) + m[2]) + m[3]);      // the block's mass without the id just drawn, formed afresh
             if (lane == 0) bsum[b] = s;
-            __builtin_amdgcn_wave_barrier();
+            wave_lds_sync();
             const int t = b / per;
 #pragma unroll
             for (int w = 0; w < DRAW_WAVES; ++w)
