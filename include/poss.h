@@ -287,7 +287,8 @@ int poss_debug_gemm(int32_t dtype, const void *x, const void *w, void *y, int32_
  * splits x 128 x (N rounded up to 128) x 4 exceed the array are refused with POSS_E_CAPACITY and
  * nothing is launched.  Every call on a GPU uses that GPU's one array, on whatever stream: calls
  * that overlap on one GPU race, the caller serialises them.  Nothing in the array has to start at
- * zero; a call overwrites all of it that it reads. */
+ * zero; a call overwrites all of it that it reads.  Y may lie over X or W: every operand is then read before
+ * Y is written. */
 #define POSS_GEMM_STATIC_BYTES (32u << 20)
 int poss_gemm_static(int32_t dtype, const void *x, const void *w, void *y, int32_t M, int32_t N,
                      int32_t K, int32_t target_workgroups, void *hip_stream);

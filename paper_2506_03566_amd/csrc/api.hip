@@ -1573,9 +1573,9 @@ extern "C" int poss_gemm_static(int32_t dtype, const void *x, const void *w, voi
     EpiArgs epi{};
     epi.mode = EPI_PLAIN; epi.out = static_cast<float *>(y); epi.ld_out = N;
     // One launch on the row-major matrix where there is such a kernel: float32 (it is the packed layout) and 16-bit types up
-    // to 16 splits.  Otherwise (a caller's workgroup target, or few columns and K in the thousands) pack, stream, sum: every byte those
-    // kernels read is written first by this call, the packed matrix including its zero padding by the pack kernel, every row
-    // of every plane by the stream kernel.
+    // to 16 splits.  Otherwise (a caller's workgroup target, few columns and K in the thousands, or a result over an operand) pack,
+    // stream, sum: every byte those kernels read is written first by this call, the packed matrix including its zero padding by
+    // the pack kernel, every row of every plane by the stream kernel.
     float *part = reinterpret_cast<float *>(base + w_bytes);
     bool ok = true;
     if (dtype == DT_F32) {

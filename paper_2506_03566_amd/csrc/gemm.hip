@@ -792,9 +792,19 @@ __global__ __launch_bounds__(DIRECT_MAX_SPLITS * 64) void gemm_direct_kernel(con
     }
 }
 
+// Does [a, a + an) share a byte with [b, b + bn)?  A kernel that writes its result while other workgroups still read the operands
+// must not be given a result that lies over them; through partial planes (every operand is read before the result is written)
+// it may.
+static bool overlap(const void *a, size_t an, const void *b, size_t bn) {
+    const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+    return x < y + bn && y < x + an;
+}
+
 bool launch_gemm_direct(int dt, const GemmShape &g, const void *W, const void *X, float *y, hipStream_t st) {
     if (dt == DT_F32 || !W || !X || !y || g.M < 1 || g.M > MAX_ROWS || g.N < 1 || g.K < 8 || g.K % 8 || g.S < 1 || g.S > DIRECT_MAX_SPLITS) return false;
     if ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(X)) % 16) return false;      // 16-byte loads to LDS
+    const size_t y_bytes = (size_t)g.M * g.N * sizeof(float);
+    if (overlap(y, y_bytes, X, (size_t)g.M * g.K * 2) || overlap(y, y_bytes, W, (size_t)g.N * g.K * 2)) return false;
     // two row tiles per workgroup where there are two and the stages fit; the stages of S waves within 160 KB (64 KB asked for
     // with one or two splits leaves room for more than one workgroup per CU)
     const int row_tiles = (g.M + 15) / 16, mt = row_tiles == 1 || g.S > 13 ? 1 : 2, mparts = (row_tiles + mt - 1) / mt, ctiles = (g.N + 15) / 16;
@@ -1326,7 +1336,10 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
     }
     if (dt == DT_F32) {
         if (epi.mode == EPI_HEAD) return false;          // float32 storage reduces its logits with the two-stage kernels
-        const bool direct = epi.mode == EPI_PLAIN && epi.out;            // the sums are whole: straight to the caller
+        // the sums are whole: straight to the caller, unless that is over an operand
+        const size_t out_bytes = ((size_t)(g.M - 1) * epi.ld_out + g.N) * sizeof(float);
+        const bool direct = epi.mode == EPI_PLAIN && epi.out && !overlap(epi.out, out_bytes, X, ((size_t)(g.M - 1) * ldx + g.K) * sizeof(float)) &&
+                            !overlap(epi.out, out_bytes, Wp, (size_t)g.N * g.K * sizeof(float));
         launch_gemm_f32(static_cast<const float *>(Wp), static_cast<const float *>(X), ldx, direct ? epi.out : part,
                         direct ? epi.ld_out : g.Npad, g.M, g.N, g.K, st, ev_start, ev_stop);
         if (direct) return true;

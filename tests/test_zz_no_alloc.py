@@ -61,6 +61,21 @@ def test_static_gemm_is_the_packed_gemm_bit_for_bit(dtype, M, N, K, shift):
     assert torch.equal(y, want)
 
 
+@pytest.mark.parametrize("over", ["x", "w"])
+@pytest.mark.parametrize("dtype,M,N,K", [(0, 64, 1000, 1000), (0, 33, 70, 70), (1, 61, 704, 1408), (2, 16, 512, 1024)])
+def test_static_gemm_result_may_lie_over_an_operand(dtype, M, N, K, over):
+    """Y in the memory that held X or W: what one launch would read while it writes goes through the partial planes."""
+    print(f"gemm_static dtype={dtype} M={M} N={N} K={K} over {over}", flush=True)
+    x, w, _ = _case(dtype, M, N, K, M + N)
+    xd, wd = to_device(x, dtype), to_device(w, dtype)
+    want, _ = P.debug_gemm(dtype, xd, wd)
+    held = xd if over == "x" else wd
+    y = held.view(torch.float32).reshape(-1)[:M * N].view(M, N)
+    assert y.data_ptr() == held.data_ptr()
+    P.gemm_static(dtype, xd, wd, y)
+    assert torch.equal(y, want)
+
+
 def test_static_scratch_gemm_refuses_what_does_not_fit():
     lib = P.load_library()
     x = torch.zeros(8, 8192, dtype=torch.bfloat16, device="cuda")
