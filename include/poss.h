@@ -252,7 +252,9 @@ int poss_set_launch_rows(poss_ctx *ctx, int32_t rows);
 int poss_debug_build_tree(poss_ctx *ctx, const int32_t *ids, const float *logp, poss_tree *out);
 
 /* Copy target residual streams of the last target pass: DEVICE float32
- * [n_layers + 1][rows][d_model] (entry l = input of layer l; last = features). */
+ * [n_layers + 1][rows][d_model] (entry l = input of layer l; last = features).  Of a prompt: its last rows, those from the
+ * last multiple of POSS_LAUNCH_ROWS below its end on (rows = (n_prompt - 1) % POSS_LAUNCH_ROWS + 1).  The pass itself is the
+ * one that runs without taps. */
 int poss_debug_set_taps(poss_ctx *ctx, void *taps_dev_or_null);
 
 /* With drawn children (poss_set_draft_sampling), after poss_draft_tree: the drafter's logits of the expanded nodes

@@ -566,15 +566,21 @@ EpiArgs epi_rope(poss_ctx *c, const KVCache &kv, int rows_q) {
 }
 
 // More than LAUNCH_ROWS rows of a prompt, [c0, c0 + rows), through the target: the many-row kernels.  The rows' tokens are on
-// the device; their metadata is in c->row_*.  Features go to the sequence's stash, T(rmsnorm_final(features)) to c->u.
-void prefill_pass(poss_ctx *c, int b, int rows, int c0) {
+// the device; their metadata is in c->row_*.  Features go to the sequence's stash, T(rmsnorm_final(features)) to c->u; the last
+// n_taps rows' residual streams to the caller's taps.
+void prefill_pass(poss_ctx *c, int b, int rows, int c0, int n_taps) {
     const ModelDims &md = c->md;
     Seq &sq = c->seq[b];
     const int qd = md.hq * md.dh, kd = md.hkv * md.dh, nl = c->cfg.n_layers;
     const size_t es = dtype_size(md.dt);
     launch_embed_norm(md, c->embed, sq.tokens_dev + c0, rows, c->layers[0].attn_norm, c->h, c->u, c->row_pos, c->inv_freq, c->cs, c->st);
+    auto tap = [&](int entry) {
+        if (n_taps > 0)
+            launch_copy_rows_f32(c->h + (size_t)(rows - n_taps) * md.d, md.d, c->taps_user + (size_t)entry * n_taps * md.d, md.d, n_taps, md.d, c->st);
+    };
     for (int l = 0; l < nl; ++l) {
         const LayerW &w = c->layers[l];
+        tap(l);
         run_block(c, w.wqkv, qd + 2 * kd, md.d, 0, c->u, rows, epi_rope(c, sq.target_kv[l], rows));
         launch_attention_prompt(md, c->q, rows, c->row_mask, c0, sq.target_kv[l], c->attn_out, c->st);
         run_block_residual(c, w.wo, md.d, qd, c->attn_out, rows, true, nullptr, w.mlp_norm, nullptr);
@@ -585,6 +591,7 @@ void prefill_pass(poss_ctx *c, int b, int rows, int c0) {
         run_block_residual(c, w.wdown, md.d, md.ffn, c->act, rows, true, nullptr, last ? c->final_norm : c->layers[l + 1].attn_norm,
                            last ? static_cast<char *>(sq.feat_stash) + (size_t)c0 * md.d * es : nullptr);
     }
+    tap(nl);
 }
 
 // The same for the keys and values (alone: no queries are formed) of the pairs [i0, i0 + n) in specialist s.
@@ -877,17 +884,18 @@ int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_
         if (prompt[i] < 0 || prompt[i] >= c->cfg.vocab) return fail(c, POSS_E_INVALID_ARG, "poss_prefill: token id %d out of range at %d", prompt[i], i);
     const ModelDims &md = c->md;
     int32_t *stage = static_cast<int32_t *>(c->pinned);
-    // A long prompt goes through the many-row kernels, up to prefill_rows tokens a pass.  Up to STREAMED_PROMPT tokens (and with
-    // taps on) it is the weight-streaming kernels, LAUNCH_ROWS a pass, on two row ranges of at most MAX_ROWS (the width of a
+    // A long prompt goes through the many-row kernels, up to prefill_rows tokens a pass.  Up to STREAMED_PROMPT tokens
+    // it is the weight-streaming kernels, LAUNCH_ROWS a pass, on two row ranges of at most MAX_ROWS (the width of a
     // row's mask): the second range finds the keys of the first, written by the same layer's QKV epilogue, in its prefix.
-    const int most = c->taps_user || n_prompt <= STREAMED_PROMPT ? LAUNCH_ROWS : prefill_rows(c->cfg);
+    const int most = n_prompt <= STREAMED_PROMPT ? LAUNCH_ROWS : prefill_rows(c->cfg);
     for (int c0 = 0, rows; c0 < n_prompt; c0 += rows) {
         rows = prompt_chunk(n_prompt - c0, most);
         memcpy(stage, prompt + c0, rows * sizeof(int32_t));
         HIP_TRY(c, hipMemcpyAsync(sq.tokens_dev + c0, stage, rows * sizeof(int32_t), hipMemcpyHostToDevice, c->st));
         hipLaunchKernelGGL(causal_meta_kernel, dim3((rows + 255) / 256), dim3(256), 0, c->st, rows, c0, c->row_pos, c->row_slot, c->row_mask);
         if (rows > LAUNCH_ROWS) {
-            prefill_pass(c, seq, rows, c0);
+            // taps: the prompt's last LAUNCH_ROWS-row chunk, whatever a pass carries (chunks begin at multiples of LAUNCH_ROWS)
+            prefill_pass(c, seq, rows, c0, c->taps_user && c0 + rows == n_prompt ? (n_prompt - 1) % LAUNCH_ROWS + 1 : 0);
         } else {
             RowMeta rm{c->row_pos, c->row_slot, c->row_mask};
             std::vector<Seg> segs;

@@ -10,6 +10,7 @@ from gpu_util import have_gpu, Pair, tol_for
 pytestmark = pytest.mark.gpu
 
 if have_gpu():
+    import torch
     from oracle.model import specialist_kv
     from synth import make_prompt
 
@@ -51,4 +52,39 @@ def test_long_prompt_leaves_the_oracles_caches(name, n_prompt, over):
     assert pair.ctx.draft_tree().n == cfg.total_tokens + 1
     pair.ctx.verify_tree()
     assert len(pair.ctx.accept_and_commit()[2]) >= 1
+    pair.close()
+
+
+def caches(pair, n):
+    cfg, ctx = pair.cfg, pair.ctx
+    return ([ctx.debug_read_kv(-1, layer, 0, n) for layer in range(cfg.n_layers)] +
+            [ctx.debug_read_kv(s, 0, 0, n - 1) for s in range(cfg.n_specialists)])
+
+
+@pytest.mark.parametrize("name,n_prompt", [("t_mid_bf16", 600), ("t_mid_f16", 768), ("t_mid_f16", 1025)])
+def test_taps_show_the_pass_that_runs_without_them(name, n_prompt):
+    """The caches are bit for bit those of the same prompt without taps; the taps hold the rows of the prompt's last 256-row
+    chunk (88, 256 and 1 of them): the embeddings first, the oracle's features last, nothing behind them."""
+    print(f"taps {name} prompt={n_prompt}", flush=True)
+    pair = Pair(name, n_layers=2, max_seq=1280, n_specialists=2, positions_per_specialist=3)
+    cfg, ctx = pair.cfg, pair.ctx
+    prompt = make_prompt(cfg, n=n_prompt)
+    ctx.prefill(prompt)
+    want = caches(pair, n_prompt)
+    rows = (n_prompt - 1) % 256 + 1
+    buf = torch.full(((cfg.n_layers + 1) * rows * cfg.d_model + 64,), -7.0, device="cuda")
+    ctx.reset()
+    ctx.debug_set_taps(buf)
+    ctx.prefill(prompt)
+    ctx.debug_set_taps(None)
+    for (k, v), (wk, wv) in zip(caches(pair, n_prompt), want):
+        assert np.array_equal(k, wk) and np.array_equal(v, wv)
+    assert (buf[-64:] == -7).all()
+    taps = buf[:-64].view(cfg.n_layers + 1, rows, cfg.d_model)
+    ids = torch.as_tensor(np.asarray(prompt[-rows:]), device="cuda").long()
+    assert torch.equal(taps[0], pair.dev_weights["embed"][ids].float())
+    o = pair.oracle()
+    o.prefill(prompt)
+    feats = np.stack(o.feats[n_prompt - rows:n_prompt])
+    assert np.abs(taps[-1].cpu().numpy() - feats).max() <= tol_for(cfg) * max(1.0, np.abs(feats).max())
     pair.close()
