@@ -226,7 +226,8 @@ void poss_free(poss_ctx *ctx);
 
 /* ---- instrumentation -------------------------------------------------------------------- */
 
-/* Per-kernel timing of the weight-streaming GEMM (the kernel that carries the round's bytes).
+/* Per-kernel timing of the weight-streaming GEMM (the kernel that carries the round's bytes) and of the products that take
+ * its place in a long prompt.
  * enable != 0: every launch carries a pair of HIP events that take the kernel's begin and end
  * timestamps (slows the round slightly: use a pass of its own).  poss_gemm_profile sums the launches since the last call:
  * count, milliseconds, and algorithmic bytes (each launch's weight matrix once, in storage

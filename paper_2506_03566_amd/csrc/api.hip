@@ -331,17 +331,21 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
 }
 
 // ------------------------------------------------------------------------------------------ GEMM wrapper
+// The events of the next product's launch (none unless the caller asked for times): columns x K of a weight matrix.
+struct ProfileSlot { hipEvent_t start, stop; };
+ProfileSlot profile_slot(poss_ctx *c, int cols, int K) {
+    if (!c->prof_on || c->prof_n >= PROFILE_EVENTS) return ProfileSlot{nullptr, nullptr};
+    const int i = c->prof_n++;
+    c->prof_bytes += (double)cols * K * dtype_size(c->md.dt);
+    return ProfileSlot{c->prof_ev[2 * i], c->prof_ev[2 * i + 1]};
+}
+
 GemmShape run_gemm(poss_ctx *c, const void *Wp, int N, int K, const void *X, int ldx, int M, float *part,
                    bool single_split, EpiArgs epi, const RopeRanges *ranges = nullptr) {
     GemmShape g = gemm_plan(c->md.dt, M, N, K, single_split ? 1 : c->gemm_target_wgs);
-    const bool prof = c->prof_on && c->prof_n < PROFILE_EVENTS;
-    if (!launch_gemm(c->md.dt, g, Wp, X, ldx, part, epi, c->md.eps, c->st, prof ? c->prof_ev[2 * c->prof_n] : nullptr,
-                     prof ? c->prof_ev[2 * c->prof_n + 1] : nullptr, ranges))
+    const ProfileSlot p = profile_slot(c, N, K);
+    if (!launch_gemm(c->md.dt, g, Wp, X, ldx, part, epi, c->md.eps, c->st, p.start, p.stop, ranges))
         c->launch_refused = true;                   // reported by the next call that waits for the stream
-    if (prof) {
-        ++c->prof_n;
-        c->prof_bytes += (double)N * K * dtype_size(c->md.dt);
-    }
     return g;
 }
 
@@ -538,7 +542,8 @@ void spec_pass(poss_ctx *c, int s, std::vector<SeqPlan> &plans, int depth_index,
 }
 
 void run_block(poss_ctx *c, const void *Wp, int N, int K, int col0, const void *X, int M, const EpiArgs &e) {
-    if (!launch_gemm_block(c->md.dt, M, N, K, col0, Wp, X, K, e, c->st)) c->launch_refused = true;
+    const ProfileSlot p = profile_slot(c, N - col0, K);
+    if (!launch_gemm_block(c->md.dt, M, N, K, col0, Wp, X, K, e, c->st, p.start, p.stop)) c->launch_refused = true;
 }
 
 // h (+)= X W^T (+ bias), u = T(rmsnorm(h) * gain), stash = T(h)
@@ -547,9 +552,10 @@ void run_block_residual(poss_ctx *c, const void *Wp, int N, int K, const void *X
     const int S = gemm_block_splits(M, N, K, c->part_floats);
     EpiArgs e = epi_residual(c, residual, bias, nullptr, S > 1 ? gain : nullptr);
     if (S > 1) {
-        EpiArgs p{};
-        p.mode = EPI_PLAIN;
-        if (!launch_gemm_block(c->md.dt, M, N, K, 0, Wp, X, K, p, c->st, S, c->part)) c->launch_refused = true;
+        EpiArgs planes{};
+        planes.mode = EPI_PLAIN;
+        const ProfileSlot p = profile_slot(c, N, K);
+        if (!launch_gemm_block(c->md.dt, M, N, K, 0, Wp, X, K, planes, c->st, p.start, p.stop, S, c->part)) c->launch_refused = true;
         e.h_stash = stash;
         launch_residual_norm(c->md.dt, c->part, S, M, N, c->md.eps, e, c->st);
         return;

@@ -136,7 +136,8 @@ static inline int head_segments_max(int vocab) { return gemm_npad(vocab) / GEMM_
 // without its queries).  tile < 0: chosen by the shape.  Returns false, launching nothing, on arguments it does not take.
 constexpr int PREFILL_ROWS = 4096;             // rows of a prompt that one pass of such launches carries at most
 bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &epi,
-                       hipStream_t st, int splits = 1, float *part = nullptr, int tile = -1);
+                       hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, int splits = 1, float *part = nullptr,
+                       int tile = -1);
 // EPI_PLAIN with splits > 1: plane s of part, [M][N], receives the sums over the s-th part of K.  The number of splits with which
 // this and launch_residual_norm are faster than EPI_RESIDUAL and launch_norm_rows (1: none), part holding part_floats.
 int gemm_block_splits(int M, int N, int K, size_t part_floats);

@@ -12,6 +12,7 @@
 // formed transposed (weights as MFMA rows): a lane then holds four consecutive columns of one activation row, so the
 // epilogues read and write 8 and 16 bytes at a time.
 #include "device_utils.h"
+#include <hip/hip_ext.h>
 
 namespace poss {
 
@@ -246,14 +247,19 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
 // one round of 256 x 256 (109 us at K = 4096): 256 x 128: 56 / 109 with the chip not full, 65 / 109 with it; 128 x 128: 40 / 109
 // for up to one tile per CU, 68 / 109 for two.
 template <typename T, int EPI>
-static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, const EpiArgs &e, int tile, hipStream_t st) {
+static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, const EpiArgs &e, int tile, hipStream_t st,
+                           hipEvent_t ev_start, hipEvent_t ev_stop) {
     const u32x4 *w = static_cast<const u32x4 *>(Wp);
     const T *x = static_cast<const T *>(X);
     const int cols = g.N - g.col0;
 #define POSS_BLOCK(TM, TN, WM, WN, NST)                                                                                     \
     do {                                                                                                                    \
         g.tiles_m = (g.M + TM - 1) / TM; g.tiles_n = (cols + TN - 1) / TN;                                                   \
-        hipLaunchKernelGGL((gemm_block_kernel<T, TM, TN, WM, WN, NST, EPI>), dim3(g.tiles_m * g.tiles_n, g.splits), dim3(WM * WN * 64), 0, st, w, x, ldx, g, e); \
+        dim3 grid(g.tiles_m * g.tiles_n, g.splits), block(WM * WN * 64);                                                    \
+        if (ev_start && ev_stop)                                                                                            \
+            hipExtLaunchKernelGGL((gemm_block_kernel<T, TM, TN, WM, WN, NST, EPI>), grid, block, 0, st, ev_start, ev_stop, 0, w, x, ldx, g, e); \
+        else                                                                                                                \
+            hipLaunchKernelGGL((gemm_block_kernel<T, TM, TN, WM, WN, NST, EPI>), grid, block, 0, st, w, x, ldx, g, e);      \
     } while (0)
     if (tile == 0) POSS_BLOCK(256, 256, 2, 4, 5);
     else if (tile == 1) POSS_BLOCK(256, 128, 4, 2, 6);
@@ -292,16 +298,18 @@ int gemm_block_splits(int M, int N, int K, size_t part_floats) {
 }
 
 template <typename T>
-static void launch_block_t(const BlockGeom &g, const void *Wp, const void *X, int ldx, const EpiArgs &e, int tile, hipStream_t st) {
+static void launch_block_t(const BlockGeom &g, const void *Wp, const void *X, int ldx, const EpiArgs &e, int tile, hipStream_t st,
+                           hipEvent_t ev_start, hipEvent_t ev_stop) {
     switch (e.mode) {
-        case EPI_ROPE_KV: launch_block_e<T, EPI_ROPE_KV>(g, Wp, X, ldx, e, tile, st); break;
-        case EPI_RESIDUAL: launch_block_e<T, EPI_RESIDUAL>(g, Wp, X, ldx, e, tile, st); break;
-        case EPI_PLAIN: launch_block_e<T, EPI_PLAIN>(g, Wp, X, ldx, e, tile, st); break;
-        default: launch_block_e<T, EPI_SILU>(g, Wp, X, ldx, e, tile, st); break;
+        case EPI_ROPE_KV: launch_block_e<T, EPI_ROPE_KV>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
+        case EPI_RESIDUAL: launch_block_e<T, EPI_RESIDUAL>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
+        case EPI_PLAIN: launch_block_e<T, EPI_PLAIN>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
+        default: launch_block_e<T, EPI_SILU>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
     }
 }
 
-bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &e, hipStream_t st, int splits, float *part, int tile) {
+bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &e, hipStream_t st,
+                       hipEvent_t ev_start, hipEvent_t ev_stop, int splits, float *part, int tile) {
     if (!Wp || !X || M < 1 || N < 1 || K < 8 || K % 8 || col0 < 0 || col0 % 32 || col0 >= N || ldx < K || dt == DT_F32) return false;
     switch (e.mode) {
         case EPI_ROPE_KV:
@@ -317,7 +325,7 @@ bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, co
     if ((size_t)M * ldx * 2 > 0xffffffffull) return false;                // 32-bit lane offsets
     const BlockGeom g{M, N, K, Kpad / GEMM_KSTEP, col0, gemm_npad(N) / 16, 0, 0, e.mode == EPI_PLAIN ? splits : 1, part};
     if (tile < 0) tile = e.mode == EPI_PLAIN ? 0 : block_tile(M, N - col0);
-    if (dt == DT_BF16) launch_block_t<bf16_t>(g, Wp, X, ldx, e, tile, st); else launch_block_t<f16_t>(g, Wp, X, ldx, e, tile, st);
+    if (dt == DT_BF16) launch_block_t<bf16_t>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); else launch_block_t<f16_t>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop);
     return true;
 }
 

@@ -88,3 +88,19 @@ def test_taps_show_the_pass_that_runs_without_them(name, n_prompt):
     feats = np.stack(o.feats[n_prompt - rows:n_prompt])
     assert np.abs(taps[-1].cpu().numpy() - feats).max() <= tol_for(cfg) * max(1.0, np.abs(feats).max())
     pair.close()
+
+
+def test_profile_counts_the_products_of_a_long_prompt():
+    """Every product of the prompt's pass and of the specialists' catch-up, its weights once."""
+    pair = Pair("t_mid_bf16", n_layers=2, max_seq=1280, n_specialists=2, positions_per_specialist=3)
+    cfg, ctx = pair.cfg, pair.ctx
+    ctx.profile_gemm(True)
+    ctx.gemm_profile()
+    ctx.prefill(make_prompt(cfg, n=600))
+    launches, ms, nbytes = ctx.gemm_profile()
+    ctx.profile_gemm(False)
+    d, qd, kd, ffn = cfg.d_model, cfg.n_q_heads * cfg.head_dim, cfg.n_kv_heads * cfg.head_dim, cfg.d_ffn
+    assert launches == 4 * cfg.n_layers + 1 + 2 * cfg.n_specialists
+    assert nbytes == 2 * (cfg.n_layers * d * (2 * qd + 2 * kd + 3 * ffn) + cfg.vocab * d + cfg.n_specialists * d * (2 * d + 2 * kd))
+    assert 0 < ms < 100
+    pair.close()
