@@ -396,13 +396,16 @@ __global__ __launch_bounds__(WPB * 64) void gemm_stream_kernel(
 //       xor-swizzled by a function of the row - eight consecutive lanes fetch one row's 128 bytes, a whole line of the
 //       L2 (four lanes and 64 bytes, one k-step, made twice the requests), and an operand read (lane % 16 the row,
 //       lane / 16 the k-group) runs at the full LDS rate;
-//   weights: the packed layout is already the B-operand image, 1 KB per (k-step, column tile), copied as it is, with non-temporal
-//       loads: a workgroup's weights are its own, the activations are everyone's and should stay in the L2 (four sequences of
-//       61 rows, four layers: 1050 -> 1015 us a round).
+//   weights: the packed layout is already the B-operand image, 1 KB per (k-step, column tile), copied as it is.  Matrices of
+//       TALL_ONCE_BYTES and more with non-temporal loads: a workgroup's weights are its own, the activations are everyone's and
+//       should stay in the L2.  Smaller ones fit the eight L2s (32 MB) beside the activations and are still in the caches when
+//       the next pass comes.  Four sequences of 61 rows, four layers, us a pass, ordinary loads / non-temporal / by this rule:
+//       8B shape (33 MB and more) 899 / 880 / 866, 2048 wide 536 / 532 / 525, 640 wide (5 MB and less, Head 41) 403 / 425 / 399.
 // Rows >= M and k >= K are not zeroed: such a lane fetches a valid element of the matrix instead (row M - 1, k = 0);
 // the rows are never read back and the packed weights are zero beyond K.
 // Splits own whole groups of 8 k-steps as in the stream kernel and a wave adds its k-steps in ascending order, so a
 // row's sums are bit for bit those of the stream kernel.
+constexpr size_t TALL_ONCE_BYTES = (size_t)24 << 20;
 constexpr int TALL_KCL = 2, TALL_NST = 3, TALL_THREADS = 1024;   // (row tiles per workgroup, MT: 16, or 12 for up to 192 rows)
 
 // position of 16-byte unit u of row r (of a 16-row tile) inside the row's 128 bytes: u ^ tall_x_swizzle(r)
@@ -411,7 +414,7 @@ __device__ __forceinline__ int tall_x_swizzle(int r) { return (((r >> 1) & 1) <<
 template <typename T, int MT, bool FUSE_SILU, bool HEAD>
 __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
     const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx, float *__restrict__ part,
-    int M, int K, int Npad, int ksteps_total, T *__restrict__ act, int F, HeadEpi he) {
+    int M, int K, int Npad, int ksteps_total, int w_once, T *__restrict__ act, int F, HeadEpi he) {
     typedef __attribute__((address_space(3))) void *LdsPtr;
     constexpr int KCL = TALL_KCL, NST = TALL_NST, MTW = MT / 2;
     static_assert(KCS % KCL == 0, "a split's k-steps are whole stages");
@@ -459,9 +462,11 @@ __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
                 lds_dma16(base + (unsigned)((pw + 8 * j) * 1024), x_row[j] + (k < K ? k : 0));
             }
 #pragma unroll
-            for (int nt = 0; nt < GEMM_NT; ++nt)
-                lds_dma16_nt(base + (unsigned)((XBLKS + ((pw >> 2) * 4 + (pw & 3)) * GEMM_NT + nt) * 1024),
-                             w_src + (size_t)chunk * KCL * (GEMM_NT * 64) + nt * 64);
+            for (int nt = 0; nt < GEMM_NT; ++nt) {
+                const unsigned dst = base + (unsigned)((XBLKS + ((pw >> 2) * 4 + (pw & 3)) * GEMM_NT + nt) * 1024);
+                const u32x4 *src = w_src + (size_t)chunk * KCL * (GEMM_NT * 64) + nt * 64;
+                if (w_once) lds_dma16_nt(dst, src); else lds_dma16(dst, src);      // (wave-uniform)
+            }
         };
         static_assert(LPS == XPP + GEMM_NT && XBLKS == 8 * XPP, "the fetch above brings exactly one stage");
         fetch(chunk0, 0);
@@ -1211,6 +1216,7 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
         HeadEpi he{};
         if (head) he = HeadEpi{epi.head_mode, epi.head_k, g.N, epi.logits, epi.logits_rows, epi.seg_out, epi.pv, epi.pi};
         dim3 grid(g.Npad / GEMM_BLOCK_N, g.S), block(TALL_THREADS);
+        const int w_once = (size_t)g.Npad * g.Kpad * sizeof(T) >= TALL_ONCE_BYTES;
         const int ksteps = g.Kpad / GEMM_KSTEP;
         const u32x4 *w = static_cast<const u32x4 *>(Wp);
         const T *x = static_cast<const T *>(X);
@@ -1219,10 +1225,10 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
     do {                                                                                                      \
         if (ev_start && ev_stop)                                                                              \
             hipExtLaunchKernelGGL((gemm_tall_kernel<T, MT, FUSE, HD>), grid, block, 0, st, ev_start, ev_stop, 0, w, x, ldx, part, \
-                                  g.M, g.K, g.Npad, ksteps, act, FARG, he);                                   \
+                                  g.M, g.K, g.Npad, ksteps, w_once, act, FARG, he);                           \
         else                                                                                                  \
             hipLaunchKernelGGL((gemm_tall_kernel<T, MT, FUSE, HD>), grid, block, 0, st, w, x, ldx, part, g.M, g.K, g.Npad, \
-                               ksteps, act, FARG, he);                                                        \
+                               ksteps, w_once, act, FARG, he);                                                \
     } while (0)
 #define POSS_TALL_LAUNCH(FUSE, HD, FARG)                                                                      \
     do { if (g.Mpad <= 192) POSS_TALL_LAUNCH_MT(12, FUSE, HD, FARG); else POSS_TALL_LAUNCH_MT(16, FUSE, HD, FARG); } while (0)

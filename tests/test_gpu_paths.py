@@ -97,3 +97,21 @@ def test_outputs_end_where_the_callers_arrays_end(name, over):
             ctx.prefill(make_prompt(cfg, n=40))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
     pair.close()
+
+
+@pytest.mark.parametrize("dtype", [1, 2])
+@pytest.mark.parametrize("N,K", [(2944, 4096), (3072, 4096), (130, 24584)])
+def test_many_rows_are_the_streaming_kernels_whatever_the_matrix_size(dtype, N, K):
+    """More than 128 rows in a launch, matrices just below and at 24 MiB (how their weights are fetched changes there) and a thin
+    one: a row's sums are those of a launch with fewer rows, bit for bit, and the float64 product's (float32 sums)."""
+    print(f"many rows dtype={dtype} N={N} K={K}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    dt = torch.bfloat16 if dtype == 1 else torch.float16
+    x = torch.empty(200, K, device="cuda").normal_(generator=g).to(dt)
+    w = torch.empty(N, K, device="cuda").normal_(0.0, 0.02, generator=g).to(dt)
+    y, _ = P.debug_gemm(dtype, x, w)
+    for r0 in (0, 100):
+        few, _ = P.debug_gemm(dtype, x[r0:r0 + 100].contiguous(), w)
+        assert torch.equal(y[r0:r0 + 100], few)
+    err = float((y.double() - x.double() @ w.double().T).abs().max())
+    assert err < 2e-5 * np.sqrt(max(K, 256) / 256.0), err
