@@ -55,6 +55,28 @@ def test_long_prompt_leaves_the_oracles_caches(name, n_prompt, over):
     pair.close()
 
 
+# down projections of few columns and a long K: their planes are summed by the residual + norm epilogue.  Three splits of 64 pairs of
+# k-steps, four of 79 with an odd last k-step, five of 86; both types; the last layer's features go to the stash through it
+@pytest.mark.parametrize("name,n_prompt,ffn", [("t_mid_f16", 513, 4088), ("t_mid_f16", 600, 5000), ("t_mid_bf16", 700, 5480)])
+def test_split_products_leave_the_oracles_caches(name, n_prompt, ffn):
+    test_long_prompt_leaves_the_oracles_caches(name, n_prompt, dict(d_ffn=ffn))
+
+
+@pytest.mark.parametrize("name", ["t_mid_bf16", "t_mid_f16"])
+def test_unsplit_products_are_the_streaming_kernels_bit_for_bit(name):
+    """d_model of 512 and 640: the streaming kernels do not split the K of the QKV projection either, so the first layer's keys
+    and values of a long prompt are those of its first 500 tokens alone."""
+    pair = Pair(name, n_layers=1, max_seq=1280, n_specialists=1, positions_per_specialist=6)
+    prompt = make_prompt(pair.cfg, n=700)
+    pair.ctx.prefill(prompt[:500])
+    want = pair.ctx.debug_read_kv(-1, 0, 0, 500)
+    pair.ctx.reset()
+    pair.ctx.prefill(prompt)
+    got = pair.ctx.debug_read_kv(-1, 0, 0, 500)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
+    pair.close()
+
+
 def caches(pair, n):
     cfg, ctx = pair.cfg, pair.ctx
     return ([ctx.debug_read_kv(-1, layer, 0, n) for layer in range(cfg.n_layers)] +

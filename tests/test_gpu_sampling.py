@@ -246,6 +246,44 @@ def test_rejection_walk_with_masses_too_small_for_the_quotient():
     pair.close()
 
 
+@pytest.mark.parametrize("T1,T2", [(1.0, 0.7), (0.6, 1.1)])
+def test_temperature_changed_between_drafting_and_the_walk(T1, T2):
+    """Children drawn at T1, the walk at T2: target and drafter both at T2 (q of the drafter's logits at T2 is q at T1 to the
+    power T1 / T2, normalised), against the oracle as above, the same screen of margins."""
+    pair = Pair("c0_tiny_f32", vocab=96)
+    cfg, ctx = pair.cfg, pair.ctx
+    o = pair.oracle()
+    prompt = make_prompt(cfg, n=24)
+    assert ctx.prefill(prompt) == o.prefill(prompt)
+    seed, rounds, differs = 0, 0, 0
+    while rounds < 6 and seed < 400:
+        seed += 1
+        UD, UA = _numbers(cfg, 1000 + seed)
+        otree = o.draft_tree(sampling=(T1, UD))
+        at_t1 = o.verify_tree_sampled(otree, T1, UA)
+        q = {v: p ** (T1 / T2) for v, p in o.last["draft_q"].items()}
+        o.last["draft_q"] = {v: p / p.sum() for v, p in q.items()}
+        opath, olast = o.verify_tree_sampled(otree, T2, UA)
+        if min(o.draw_margins) < 2e-4 or (o.accept_margins and min(o.accept_margins) < 2e-4):
+            continue                                          # too close to call in float32: other numbers
+        _say(f"  T={T1} then {T2}: numbers {1000 + seed} pass the screen, round {rounds} on the GPU")
+        ctx.set_sampling(T1, np.zeros(cfg.depth + 1, np.float32))
+        ctx.set_draft_sampling(UD, UA)
+        d = ctx.draft_tree().as_dict()
+        assert d["token"][1:] == otree.token[1:] and d["parent"] == otree.parent, f"seed {seed}"
+        ctx.set_sampling(T2, np.zeros(cfg.depth + 1, np.float32))
+        ctx.verify_tree()
+        path, m, toks = ctx.accept_and_commit()
+        assert path == opath and toks[-1] == olast, f"seed {seed}"
+        o.accept_and_commit(path=opath, bonus=olast)
+        assert ctx.tokens() == o.tokens
+        rounds += 1
+        differs += (opath, olast) != at_t1
+    _say(f"  T={T1} then {T2}: {rounds} rounds, {differs} of them other than a walk at {T1}")
+    assert rounds == 6 and differs >= 1
+    pair.close()
+
+
 @pytest.mark.parametrize("name", ["t_mid_bf16", "t_mid_f16"])
 def test_drawn_children_at_16_bit_shapes_give_valid_rounds(name):
     """16-bit storage, vocabularies of thousands: draws fall too close to interval ends for a token-by-token comparison,
