@@ -132,12 +132,11 @@ int gemm_head_segments(const GemmShape &g);
 static inline int head_segments_max(int vocab) { return gemm_npad(vocab) / GEMM_BLOCK_N; }
 
 // The same product for many rows (gemm_block.hip): 16-bit types, one range of rows and one cache, the epilogues EPI_ROPE_KV,
-// EPI_RESIDUAL (h alone: the norm is launch_norm_rows) and EPI_SILU; columns [col0, N) are formed (col0 > 0: EPI_ROPE_KV
-// without its queries).  tile < 0: chosen by the shape.  Returns false, launching nothing, on arguments it does not take.
+// EPI_RESIDUAL (h alone: the norm is launch_norm_rows), EPI_SILU and, with splits, EPI_PLAIN; columns [col0, N) are formed (col0 > 0:
+// EPI_ROPE_KV without its queries).  Returns false, launching nothing, on arguments it does not take.
 constexpr int PREFILL_ROWS = 4096;             // rows of a prompt that one pass of such launches carries at most
 bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &epi,
-                       hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, int splits = 1, float *part = nullptr,
-                       int tile = -1);
+                       hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr, int splits = 1, float *part = nullptr);
 // EPI_PLAIN with splits > 1: plane s of part, [M][N], receives the sums over the s-th part of K.  The number of splits with which
 // this and launch_residual_norm are faster than EPI_RESIDUAL and launch_norm_rows (1: none), part holding part_floats.
 int gemm_block_splits(int M, int N, int K, size_t part_floats);

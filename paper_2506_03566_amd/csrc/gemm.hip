@@ -1158,7 +1158,6 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
                                    g.N, eps, epi);
             break;
         }
-        case EPI_ROPE_KV:               // per row range: epilogue_rope_ranges_kernel
         case EPI_HEAD: break;           // reduced inside the stream kernel
         case EPI_SILU:
             if (silu_done) break;       // applied inside the stream kernel

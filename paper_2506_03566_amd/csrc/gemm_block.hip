@@ -2,15 +2,14 @@
 // the operation that follows it in a Llama decoder layer in its epilogue.  The weights are the ones the streaming kernels use
 // (packed in operand order of v_mfma_f32_16x16x32); here each is used for hundreds of rows and the matrix pipe is the bound.
 //
-// A workgroup owns a TM x TN tile and the whole K (no partial planes).  Both operands go from memory straight into LDS, one
-// k-step of 32 per stage, NST stages in a ring: at k-step j a wave multiplies the fragments it read from LDS during j - 1,
-// reads those of j + 1 and asks for a share of stage j + NST - 1, all three interleaved (a run of LDS-direct loads would
-// stall the wave at issue while its SIMD has nothing to multiply), and there is one barrier per k-step.  Against 256 rows per
-// launch of gemm_tall_kernel (gate/up of the 8B shape: 16 x 69 us for 4096 rows, 870 TFLOP/s) 745 us (1291 TFLOP/s), and the
-// partial planes and their epilogue kernels are gone: a prompt of 8192 tokens through four layers and three specialists took
-// 45.5 ms, now 24.0.  The product is
-// formed transposed (weights as MFMA rows): a lane then holds four consecutive columns of one activation row, so the
-// epilogues read and write 8 and 16 bytes at a time.
+// A workgroup owns a TM x TN tile and the whole K, or (EPI_PLAIN) a part of it whose sums go to a plane.  Both operands go from
+// memory straight into LDS, one k-step of 32 per stage, NST stages in a ring: at k-step j a wave multiplies the fragments it
+// read from LDS during j - 1, reads those of j + 1 and asks for a share of stage j + NST - 1, all three interleaved (a run of
+// LDS-direct loads would stall the wave at issue while its SIMD has nothing to multiply), and there is one barrier per k-step.
+// Against 256 rows per launch of gemm_tall_kernel (gate/up of the 8B shape: 16 x 69 us for 4096 rows, 870 TFLOP/s) 745 us (1291
+// TFLOP/s), and the partial planes and their epilogue kernels are gone: a prompt of 8192 tokens through four layers and three
+// specialists took 45.5 ms, now 24.0.  The product is formed transposed (weights as MFMA rows): a lane then holds four
+// consecutive columns of one activation row, so the epilogues read and write 8 and 16 bytes at a time.
 #include "device_utils.h"
 #include <hip/hip_ext.h>
 
@@ -246,8 +245,18 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
 // sixteen MFMAs, 128 B/clk with two waves per SIMD.  The cost below is the measured time of a round of each shape, relative to
 // one round of 256 x 256 (109 us at K = 4096): 256 x 128: 56 / 109 with the chip not full, 65 / 109 with it; 128 x 128: 40 / 109
 // for up to one tile per CU, 68 / 109 for two.
+static int block_tiles(int M, int cols, int tm, int tn) { return ((M + tm - 1) / tm) * ((cols + tn - 1) / tn); }
+static int block_tile(int M, int cols, int *cost = nullptr) {
+    const int t0 = block_tiles(M, cols, 256, 256), t1 = block_tiles(M, cols, 256, 128), t2 = block_tiles(M, cols, 128, 128), rest = t2 % 512;
+    const int c0 = (t0 + 255) / 256 * 100, c1 = t1 <= 256 ? 58 : (t1 + 255) / 256 * 65;
+    const int c2 = t2 / 512 * 68 + (rest == 0 ? 0 : rest <= 256 ? 40 : 68);
+    const int tile = c0 <= c1 && c0 <= c2 ? 0 : c1 <= c2 ? 1 : 2;
+    if (cost) *cost = tile == 0 ? c0 : tile == 1 ? c1 : c2;
+    return tile;
+}
+
 template <typename T, int EPI>
-static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, const EpiArgs &e, int tile, hipStream_t st,
+static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, const EpiArgs &e, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
     const u32x4 *w = static_cast<const u32x4 *>(Wp);
     const T *x = static_cast<const T *>(X);
@@ -261,20 +270,15 @@ static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, 
         else                                                                                                                \
             hipLaunchKernelGGL((gemm_block_kernel<T, TM, TN, WM, WN, NST, EPI>), grid, block, 0, st, w, x, ldx, g, e);      \
     } while (0)
-    if (tile == 0) POSS_BLOCK(256, 256, 2, 4, 5);
-    else if (tile == 1) POSS_BLOCK(256, 128, 4, 2, 6);
-    else POSS_BLOCK(128, 128, 2, 2, 5);
+    if constexpr (EPI == EPI_PLAIN) {
+        POSS_BLOCK(256, 256, 2, 4, 5);                    // gemm_block_splits() counts on it
+    } else {
+        const int tile = block_tile(g.M, cols);
+        if (tile == 0) POSS_BLOCK(256, 256, 2, 4, 5);
+        else if (tile == 1) POSS_BLOCK(256, 128, 4, 2, 6);
+        else POSS_BLOCK(128, 128, 2, 2, 5);
+    }
 #undef POSS_BLOCK
-}
-
-static int block_tiles(int M, int cols, int tm, int tn) { return ((M + tm - 1) / tm) * ((cols + tn - 1) / tn); }
-static int block_tile(int M, int cols, int *cost = nullptr) {
-    const int t0 = block_tiles(M, cols, 256, 256), t1 = block_tiles(M, cols, 256, 128), t2 = block_tiles(M, cols, 128, 128), rest = t2 % 512;
-    const int c0 = (t0 + 255) / 256 * 100, c1 = t1 <= 256 ? 58 : (t1 + 255) / 256 * 65;
-    const int c2 = t2 / 512 * 68 + (rest == 0 ? 0 : rest <= 256 ? 40 : 68);
-    const int tile = c0 <= c1 && c0 <= c2 ? 0 : c1 <= c2 ? 1 : 2;
-    if (cost) *cost = tile == 0 ? c0 : tile == 1 ? c1 : c2;
-    return tile;
 }
 
 // K splits of a product whose sums a kernel of its own adds up (the residual + norm epilogue): with few tiles for the chip
@@ -298,18 +302,18 @@ int gemm_block_splits(int M, int N, int K, size_t part_floats) {
 }
 
 template <typename T>
-static void launch_block_t(const BlockGeom &g, const void *Wp, const void *X, int ldx, const EpiArgs &e, int tile, hipStream_t st,
+static void launch_block_t(const BlockGeom &g, const void *Wp, const void *X, int ldx, const EpiArgs &e, hipStream_t st,
                            hipEvent_t ev_start, hipEvent_t ev_stop) {
     switch (e.mode) {
-        case EPI_ROPE_KV: launch_block_e<T, EPI_ROPE_KV>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
-        case EPI_RESIDUAL: launch_block_e<T, EPI_RESIDUAL>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
-        case EPI_PLAIN: launch_block_e<T, EPI_PLAIN>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
-        default: launch_block_e<T, EPI_SILU>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); break;
+        case EPI_ROPE_KV: launch_block_e<T, EPI_ROPE_KV>(g, Wp, X, ldx, e, st, ev_start, ev_stop); break;
+        case EPI_RESIDUAL: launch_block_e<T, EPI_RESIDUAL>(g, Wp, X, ldx, e, st, ev_start, ev_stop); break;
+        case EPI_PLAIN: launch_block_e<T, EPI_PLAIN>(g, Wp, X, ldx, e, st, ev_start, ev_stop); break;
+        default: launch_block_e<T, EPI_SILU>(g, Wp, X, ldx, e, st, ev_start, ev_stop); break;
     }
 }
 
 bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, const void *X, int ldx, const EpiArgs &e, hipStream_t st,
-                       hipEvent_t ev_start, hipEvent_t ev_stop, int splits, float *part, int tile) {
+                       hipEvent_t ev_start, hipEvent_t ev_stop, int splits, float *part) {
     if (!Wp || !X || M < 1 || N < 1 || K < 8 || K % 8 || col0 < 0 || col0 % 32 || col0 >= N || ldx < K || dt == DT_F32) return false;
     switch (e.mode) {
         case EPI_ROPE_KV:
@@ -324,8 +328,7 @@ bool launch_gemm_block(int dt, int M, int N, int K, int col0, const void *Wp, co
     const int Kpad = gemm_kpad(dt, K);
     if ((size_t)M * ldx * 2 > 0xffffffffull) return false;                // 32-bit lane offsets
     const BlockGeom g{M, N, K, Kpad / GEMM_KSTEP, col0, gemm_npad(N) / 16, 0, 0, e.mode == EPI_PLAIN ? splits : 1, part};
-    if (tile < 0) tile = e.mode == EPI_PLAIN ? 0 : block_tile(M, N - col0);
-    if (dt == DT_BF16) launch_block_t<bf16_t>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop); else launch_block_t<f16_t>(g, Wp, X, ldx, e, tile, st, ev_start, ev_stop);
+    if (dt == DT_BF16) launch_block_t<bf16_t>(g, Wp, X, ldx, e, st, ev_start, ev_stop); else launch_block_t<f16_t>(g, Wp, X, ldx, e, st, ev_start, ev_stop);
     return true;
 }
 
