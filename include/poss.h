@@ -143,7 +143,9 @@ int poss_set_active(poss_ctx *ctx, int32_t seq, int32_t active);
 /* Causal target pass over the prompt (HOST int32 ids, 1 <= n_prompt, n_prompt + 1 <= max_seq),
  * then every specialist's keys/values for the pairs [x_j ; f_{j-1}], j = 1..n_prompt-1
  * (section 3.3: specialists do not share a cache).  *first_token_out = x_P, the target's greedy
- * token after the prompt; it becomes the root of the first tree. */
+ * token after the prompt; it becomes the root of the first tree.  A prompt of more than 512 tokens (16-bit types) runs kernels
+ * whose float32 sums are in another order than those of all other passes, the same for every batch and max_seq but not for every
+ * prompt length: its keys and values can differ in the last bits from those the same tokens get in a shorter prompt or a round. */
 int poss_prefill(poss_ctx *ctx, const int32_t *prompt, int32_t n_prompt, int32_t *first_token_out);
 /* The same for sequence seq (0 <= seq < batch).  Rounds can start once every sequence has its prompt. */
 int poss_prefill_seq(poss_ctx *ctx, int32_t seq, const int32_t *prompt, int32_t n_prompt, int32_t *first_token_out);

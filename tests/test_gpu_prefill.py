@@ -77,6 +77,19 @@ def test_unsplit_products_are_the_streaming_kernels_bit_for_bit(name):
     pair.close()
 
 
+@pytest.mark.parametrize("name,over", [("t_mid_bf16", dict(d_ffn=5480)), ("t_mid_f16", {})])
+def test_a_long_prompts_sums_do_not_hang_on_batch_or_capacity(name, over):
+    got = []
+    for max_seq, batch in ((768, 1), (8192, 1), (1280, 3)):
+        pair = Pair(name, lib_over=dict(batch=batch), n_layers=2, n_specialists=1, positions_per_specialist=6, max_seq=max_seq, **over)
+        pair.ctx.prefill(make_prompt(pair.cfg, n=700))
+        got.append(caches(pair, 700))
+        pair.close()
+    for other in got[1:]:
+        for (k, v), (wk, wv) in zip(other, got[0]):
+            assert np.array_equal(k, wk) and np.array_equal(v, wv)
+
+
 def caches(pair, n):
     cfg, ctx = pair.cfg, pair.ctx
     return ([ctx.debug_read_kv(-1, layer, 0, n) for layer in range(cfg.n_layers)] +
