@@ -117,7 +117,9 @@ typedef struct poss_stats {
     double  ms_draft, ms_verify, ms_commit;
 } poss_stats;
 
-/* Bytes of DEVICE workspace poss_load needs for this configuration (0 if it is invalid). */
+/* Bytes of DEVICE workspace poss_load needs for this configuration (0 if it is invalid).  Besides weights and caches: with 16-bit
+ * types and max_seq above 512 the activations of a prompt's pass, up to 4096 rows of them; with one sequence the probability
+ * masses of every drafted and verified row, whether or not children are drawn.  The figure belongs to this version of the library. */
 size_t poss_workspace_bytes(const poss_config *cfg);
 
 /* Create a context.  cfg, w: HOST structs (w's tensors DEVICE).  workspace: DEVICE memory of
@@ -281,12 +283,14 @@ int poss_debug_gemm(int32_t dtype, const void *x, const void *w, void *y, int32_
 /* ---- for callers that cannot allocate ------------------------------------------------------ */
 
 /* poss_debug_gemm for callers that may not allocate device memory or hand over a scratch buffer:
- * code under HIP graph capture, serving loops and harnesses that forbid hipMalloc.  Same kernels,
- * same result (Y[M, N] DEVICE float32 = X[M, K] . W[N, K]^T, X and W DEVICE row-major of `dtype`,
- * M <= POSS_MAX_ROWS), but the repacked weights and the split-K partial planes live in a
+ * code under HIP graph capture, serving loops and harnesses that forbid hipMalloc.  The same result
+ * bit for bit (Y[M, N] DEVICE float32 = X[M, K] . W[N, K]^T, X and W DEVICE row-major of `dtype`,
+ * M <= POSS_MAX_ROWS), in one launch on the matrix as it is, or, for more than 16 K splits, 16-bit operands
+ * that are not aligned to 16 bytes and a Y that lies over an operand, in three, with the repacked weights and the
+ * split-K partial planes in a
  * POSS_GEMM_STATIC_BYTES array inside the library's device image (each GPU the library runs on holds
  * its own copy until the process ends).  The call allocates nothing, creates no events and does
- * not wait: it enqueues three kernels on hip_stream (NULL = default stream) and returns; Y is valid
+ * not wait: it enqueues on hip_stream (NULL = default stream) and returns; Y is valid
  * once the stream has been waited for.  Shapes whose packed matrix
  * (N rounded up to 128) x (K rounded up to 256) x sizeof(dtype) plus planes
  * splits x 128 x (N rounded up to 128) x 4 exceed the array are refused with POSS_E_CAPACITY and

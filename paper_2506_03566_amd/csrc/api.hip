@@ -170,10 +170,13 @@ const char *check_config(const poss_config &c) {
 
 size_t esize(const poss_config &c) { return dtype_size(c.dtype); }
 
-// Prompts up to this many tokens stay with the weight-streaming kernels, two launches of 256 rows: their sums are those of every
-// other pass bit for bit, on which the children that a short request draws at a temperature hang, and the gain would be small
-// (prompt and catch-up of one specialist, four layers of the 8B shape: 260 tokens 1.50 ms streamed, 1.57 ms by the many-row
-// kernels; 384: 1.72, 1.78; 512: 2.02, 1.80).
+// Prompts up to this many tokens stay with the weight-streaming kernels: two launches of 256 rows.  Their sums are those of every
+// other pass bit for bit; the many-row kernels' are not (other splits of K and of the keys), and the children that a request
+// draws at a temperature hang on those bits.  The line is where results were held to what they had been, not where the time
+// would put it: the many-row kernels are ahead from 257 tokens on (prompt and catch-up of three specialists, four layers, ms,
+// streamed / many-row; 8B shape: 260 tokens 1.63 / 1.45, 384 1.88 / 1.56, 512 2.20 / 1.63, 513 2.61 / 1.93, 1024 4.46 / 2.52; 13B
+// shape: 260 2.31 / 1.86, 512 3.12 / 2.26; 512 wide: 260 0.73 / 0.41, 512 0.94 / 0.44).  With the streaming kernels' splits in the
+// many-row kernels it could move down to 256.
 constexpr int STREAMED_PROMPT = 2 * LAUNCH_ROWS;
 
 // Rows that one pass over a prompt carries: LAUNCH_ROWS of the weight-streaming kernels, or, 16-bit types, up to PREFILL_ROWS

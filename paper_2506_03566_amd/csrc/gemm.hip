@@ -720,8 +720,9 @@ __global__ __launch_bounds__(256) void gemm_qkv_rope_kernel(const u32x4 *__restr
 // whole 128-byte lines at a time, in the swizzled order of gemm_tall_kernel: fetched as operands, 64 bytes of 16 rows per
 // instruction, the same bytes took the CU's memory pipe twice as long.  NST stages in a ring: four where LDS holds them (few
 // splits: few waves to hide the latency), otherwise two.
-// 61 x 1720 x 5000: pack 9.6 + stream 6.1 + sum 3.6 us -> 8.9 us (14.5 fetched as operands into registers); 1 x 512 x 512:
-// three launches of 8.0 us -> 2.9 us.
+// With operands just touched, 61 x 1720 x 5000: pack 9.6 + stream 6.1 + sum 3.6 us -> 8.9 us (14.5 fetched as operands into
+// registers); 1 x 512 x 512: three launches of 8.0 us -> 2.9 us.  With operands that no cache holds the call gains less: 61 x 1700 x
+// 5000 23.7 -> 16.4 us from event to event, 1 x 512 x 512 11.1 -> 6.3.
 constexpr int DIRECT_MAX_SPLITS = 16;
 __device__ const u32x4 direct_zero = {0u, 0u, 0u, 0u};    // what a lane fetches where its k lies beyond K
 
