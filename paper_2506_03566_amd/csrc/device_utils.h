@@ -6,6 +6,21 @@ namespace poss {
 
 template <typename T> __device__ __forceinline__ float to_f(T v) { return (float)v; }
 template <typename T> __device__ __forceinline__ T from_f(float v) { return (T)v; }   // round to nearest even
+// Where several kernels form the same value they must round alike, and in fp16 the plain conversion does not: the compiler folds a
+// float32 product or multiply-add into it (v_fma_mixlo_f16: rounded once, from the exact result) in one kernel and converts the
+// float32 result (rounded twice) in the next, as its vectoriser decides.  The two differ in one value of ten thousand.
+// round_f: the float32 value, rounded.  mul_round: the product, rounded once (bf16 and float32: as float32 arithmetic gives it).
+template <typename T> __device__ __forceinline__ T round_f(float v) { return (T)v; }
+template <> __device__ __forceinline__ f16_t round_f<f16_t>(float v) {
+    asm("" : "+v"(v));                                    // the value itself, not what it was computed from
+    return (f16_t)v;
+}
+template <typename T> __device__ __forceinline__ T mul_round(float a, float b) { return (T)(a * b); }
+template <> __device__ __forceinline__ f16_t mul_round<f16_t>(float a, float b) {
+    f16_t r = (f16_t)(a * b);                             // v_fma_mixlo_f16, unless several conversions are made one
+    asm("" : "+v"(r));
+    return r;
+}
 
 // x of lane l ^ OFF as a second operand: bits 5 and 4 by the row-swap instructions of gfx950 (see rows_max below), the
 // others by DPP.  Nothing goes through the LDS crossbar, as a shuffle would (about 100 cycles a step).  Every lane of the wave

@@ -108,7 +108,8 @@ __global__ __launch_bounds__(1024) void norm_rows_kernel(const float *__restrict
         const int p = threadIdx.x + j * blockDim.x;
         v[j] = make_float4(0.f, 0.f, 0.f, 0.f);
         if (p < nv) { v[j] = src[p]; gv[j] = reinterpret_cast<const Quad *>(gain)[p]; }
-        ss += v[j].x * v[j].x; ss += v[j].y * v[j].y; ss += v[j].z * v[j].z; ss += v[j].w * v[j].w;
+        ss = fmaf(v[j].x, v[j].x, ss); ss = fmaf(v[j].y, v[j].y, ss);      // as the residual + norm epilogue does
+        ss = fmaf(v[j].z, v[j].z, ss); ss = fmaf(v[j].w, v[j].w, ss);
     }
     ss = block_sum(ss, red);
     const float rs = 1.0f / sqrtf(ss / (float)d + eps);
@@ -119,7 +120,7 @@ __global__ __launch_bounds__(1024) void norm_rows_kernel(const float *__restrict
         const float x[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
         Quad o;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) o.t[i] = from_f<T>(x[i] * rs * to_f(gv[j].t[i]));
+        for (int i = 0; i < 4; ++i) o.t[i] = mul_round<T>(x[i] * rs, to_f(gv[j].t[i]));
         reinterpret_cast<Quad *>(u + row * d)[p] = o;
         if (stash) {
 #pragma unroll

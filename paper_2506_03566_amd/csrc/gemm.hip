@@ -107,7 +107,7 @@ __device__ __forceinline__ void tile_epilogue(const float *__restrict__ part, si
         for (int r = r_begin + (t >> 6); r < r_end; r += 4) {
             const float g = sum_planes(part, plane, S, (size_t)r * Npad + cg);
             const float up = sum_planes(part, plane, S, (size_t)r * Npad + cg + 16);
-            act[(size_t)r * e.F + f] = from_f<T>(g / (1.0f + expf(-g)) * up);
+            act[(size_t)r * e.F + f] = mul_round<T>(g / (1.0f + expf(-g)), up);
         }
     } else {    // EPI_PLAIN: 32 threads x 4 columns per row, 8 rows per sweep
         const int c4 = (t & 31) * 4, n = n0 + c4;
@@ -329,7 +329,7 @@ __global__ __launch_bounds__(WPB * 64) void gemm_stream_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const float g = acc[mt][0][r], up = acc[mt][1][r];
-                tile[(mt * 16 + 4 * (lane >> 4) + r) * TWP + wave * 16 + (lane & 15)] = from_f<T>(g / (1.0f + expf(-g)) * up);
+                tile[(mt * 16 + 4 * (lane >> 4) + r) * TWP + wave * 16 + (lane & 15)] = mul_round<T>(g / (1.0f + expf(-g)), up);
             }
         __syncthreads();
         silu_tile_store<T, MT * 16, TW, WPB * 64>(tile, act, M, F, blockIdx.x * TW, tid);
@@ -538,7 +538,7 @@ __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float g = acc[mt][0][r], up = acc[mt][1][r];
-                    tile[(row0 + mt * 16 + r) * TWP + wn * 16 + (lane & 15)] = from_f<T>(g / (1.0f + expf(-g)) * up);
+                    tile[(row0 + mt * 16 + r) * TWP + wn * 16 + (lane & 15)] = mul_round<T>(g / (1.0f + expf(-g)), up);
                 }
         }
         __syncthreads();
@@ -914,12 +914,12 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
             if (n >= N) continue;
             Quad o;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o.t[j] = from_f<T>(x[it][j] * rs * gn[it][j]);
+            for (int j = 0; j < 4; ++j) o.t[j] = mul_round<T>(x[it][j] * rs, gn[it][j]);
             *reinterpret_cast<Quad *>(u + (size_t)m * N + n) = o;
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                if (n + j < N) u[(size_t)m * N + n + j] = from_f<T>(x[it][j] * rs * gn[it][j]);
+                if (n + j < N) u[(size_t)m * N + n + j] = mul_round<T>(x[it][j] * rs, gn[it][j]);
         }
     }
 }
@@ -1081,8 +1081,8 @@ __global__ __launch_bounds__(ROPE_THREADS) void epilogue_rope_ranges_kernel(cons
     for (int j = 0; j < 4; ++j) {
         float a, b;
         rope_pair(x1[j], x2[j], cs[j], a, b);
-        o1.t[j] = from_f<T>(a);
-        o2.t[j] = from_f<T>(b);
+        o1.t[j] = round_f<T>(a);
+        o2.t[j] = round_f<T>(b);
     }
     T *dst = gh < e.hq ? static_cast<T *>(e.q) + ((size_t)r * e.hq + gh) * e.dh + i
                        : static_cast<T *>(kv.k) + k_offset(kv, sl, gh - e.hq, e.hkv, e.dh) + i;

@@ -190,7 +190,7 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
                     const float gt = acc[nt][mt][r], up = acc[nt + 1][mt][r];
-                    o.v[r] = from_f<T>(gt / (1.0f + expf(-gt)) * up);
+                    o.v[r] = mul_round<T>(gt / (1.0f + expf(-gt)), up);
                 }
                 *reinterpret_cast<Quad<T> *>(act + (size_t)m * e.F + f) = o;
             }
@@ -218,8 +218,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
                 for (int r = 0; r < 4; ++r) {
                     float a, b;
                     rope_pair(x1[r], x2[r], cs[r], a, b);
-                    o1.v[r] = from_f<T>(a);
-                    o2.v[r] = from_f<T>(b);
+                    o1.v[r] = round_f<T>(a);
+                    o2.v[r] = round_f<T>(b);
                 }
                 T *dst = gh < e.hq ? static_cast<T *>(e.q) + ((size_t)m * e.hq + gh) * e.dh + i
                                    : static_cast<T *>(e.kv.k) + ((size_t)(pg * e.hkv + gh - e.hq) * P + in_pg) * e.dh + i;

@@ -77,6 +77,24 @@ def test_unsplit_products_are_the_streaming_kernels_bit_for_bit(name):
     pair.close()
 
 
+@pytest.mark.parametrize("name", ["t_mid_bf16", "t_mid_f16"])
+def test_first_rows_of_a_long_prompt_round_as_the_streaming_kernels_do(name):
+    """Products that neither path splits (K of at most 704) and rows that see at most 120 keys: every layer's keys and values of a
+    long prompt's first 120 tokens are those of these tokens alone, through norms, rotary embedding, SiLU and residual - in fp16
+    too, where a conversion can round a product once or twice."""
+    pair = Pair(name, n_layers=3, d_ffn=704, max_seq=1280, n_specialists=1, positions_per_specialist=6)
+    for seed in range(3):
+        prompt = np.random.default_rng(seed).integers(0, pair.cfg.vocab, 700).astype(np.int32)
+        got = []
+        for n in (120, 700):
+            pair.ctx.reset()
+            pair.ctx.prefill(prompt[:n])
+            got.append([pair.ctx.debug_read_kv(-1, layer, 0, 120) for layer in range(3)])
+        for layer in range(3):
+            assert all(np.array_equal(a, b) for a, b in zip(got[0][layer], got[1][layer])), (seed, layer)
+    pair.close()
+
+
 @pytest.mark.parametrize("name,over", [("t_mid_bf16", dict(d_ffn=5480)), ("t_mid_f16", {})])
 def test_a_long_prompts_sums_do_not_hang_on_batch_or_capacity(name, over):
     got = []
