@@ -694,14 +694,14 @@ __global__ __launch_bounds__(256) void gemm_qkv_rope_kernel(const u32x4 *__restr
                     float o1, o2;
                     rope_pair(a, b, e.cs[m * half + i], o1, o2);
                     T *dst = q + ((size_t)m * e.hq + gh) * e.dh;
-                    dst[i] = from_f<T>(o1);
-                    dst[i + half] = from_f<T>(o2);
+                    dst[i] = round_f<T>(o1);
+                    dst[i + half] = round_f<T>(o2);
                 } else if (gh < e.hq + e.hkv) {
                     float o1, o2;
                     rope_pair(a, b, e.cs[m * half + i], o1, o2);
                     T *dst = kc + k_offset(kv, e.slot[m], gh - e.hq, e.hkv, e.dh);
-                    dst[i] = from_f<T>(o1);
-                    dst[i + half] = from_f<T>(o2);
+                    dst[i] = round_f<T>(o1);
+                    dst[i + half] = round_f<T>(o2);
                 } else {
                     const int vh = gh - e.hq - e.hkv, sl = e.slot[m];
                     vc[vt_offset(kv, sl, vh, e.hkv, e.dh, i)] = from_f<T>(a);
