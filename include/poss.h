@@ -210,7 +210,8 @@ int poss_set_sampling(poss_ctx *ctx, float temperature, const float *u, int32_t 
  * walk with a token drawn from the last residual (u_accept[d * (top_k + 1) + top_k]), with an accepted child that
  * the tree had dropped, or at a node without drawn children with a token drawn from the target's distribution.
  * That last token takes the bonus token's place in poss_accept_and_commit; every committed token is
- * distributed as the target's softmax(logits / temperature) given its prefix.  argmax_out of poss_verify_tree
+ * distributed as the target's softmax(logits / temperature) given its prefix.  Where fewer than top_k ids have any mass
+ * left in float32 (a low temperature) the other slots carry token 0 and count as no child.  argmax_out of poss_verify_tree
  * then holds, for the nodes of the accepted path, the token that follows them, and -1 elsewhere.
  * u_draft: HOST float32 [depth][top_k][top_k]; u_accept: HOST float32 [depth + 1][top_k + 1]; all in [0, 1);
  * copied before the call returns, in force until the next call.  One sequence per context.  enable == 0:

@@ -633,6 +633,20 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
         __syncthreads();
         return L.i[2];
     };
+    // what a row of the drafter's holds without the first n removed ids
+    auto mass_left = [&](const float *Q, int n) {
+        float s = 0.f;
+        for (int b = wave; b < nblk; b += DRAW_WAVES) {
+            f32x4e m = load_masses(Q, ld, b, lane);
+            const int id0 = b * DRAW_BLOCK + lane * 4;
+            for (int j = 0; j < n; ++j) {
+                const int r = L.removed[j] - id0;
+                if (r >= 0 && r < 4) m[r] = 0.f;
+            }
+            s += ((m[0] + m[1]) + m[2]) + m[3];
+        }
+        return block_sum(s, L.red);
+    };
     const int n_nodes = td.n_nodes[0];
     for (int i = tid; i < n_nodes; i += DRAW_THREADS) g[i] = -1;
     int cur = 0;
@@ -662,8 +676,13 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
         int next = -1, last_tok = -1;
         for (int i = 0; i < k; ++i) {
             const int c = td.pool_token[cbase + i];
-            const float pc = (have_resid ? resid[c] : P[c]) / zp;
-            const float ec = Q[c], qc = ec / zq;
+            const float ec = Q[c];
+            // At a low temperature fewer than k ids may have any mass in float32: the slots behind them hold an id without mass, or one
+            // drawn before, and no child.
+            bool drawn = ec > 0.f;
+            for (int j = 0; j < i; ++j) drawn = drawn && L.removed[j] != c;
+            if (!drawn) break;
+            const float pc = (have_resid ? resid[c] : P[c]) / zp, qc = ec / zq;
             const float a = fminf(1.f, pc / qc);
             if (ua[d * (k + 1) + i] < a) {                // accepted (every thread takes the same decision)
                 const int node = td.pool_node[cbase + i];
@@ -714,14 +733,25 @@ __global__ __launch_bounds__(DRAW_THREADS) void rejection_walk_kernel(TreeDev td
             __syncthreads();
             (void)find_block(L, nblk, 0.f, &before_unused, &zp);   // (its barriers also publish resid[])
             zq -= ec;
+            if (!(zq > 0.f)) zq = mass_left(Q, i + 1);    // (the candidate had all the mass that float32 sees beside it)
             have_resid = true;
+            if (!(zp > 0.f)) break;                       // p and q alike to the last bit: nothing to draw from but p
         }
-        if (next >= 0) { cur = next; continue; }
-        if (last_tok < 0) {                               // every candidate rejected: draw from the last residual
-            const int c = draw_token(ua[d * (k + 1) + k], resid);
+        if (next < 0 && last_tok < 0) {                   // every candidate rejected: draw from the last residual
+            const bool from_resid = have_resid && zp > 0.f;
+            if (have_resid && !from_resid) {
+                __syncthreads();
+                for (int b = tid; b < nblk; b += DRAW_THREADS) L.bsum[b] = target.bsum[(size_t)cur * nblk + b];
+                __syncthreads();
+            }
+            const int c = draw_token(ua[d * (k + 1) + k], from_resid ? resid : P);
             if (tid == 0) g[cur] = c;
+            // a child that carries the token all the same (the id of an empty slot) is where the commit goes on
+            for (int i = 0; i < k && next < 0; ++i)
+                if (td.pool_token[cbase + i] == c && td.pool_node[cbase + i] >= 0) next = td.pool_node[cbase + i];
         }
-        return;
+        if (next < 0) return;
+        cur = next;
     }
 }
 

@@ -246,6 +246,37 @@ def test_rejection_walk_with_masses_too_small_for_the_quotient():
     pair.close()
 
 
+@pytest.mark.parametrize("vocab", [12, 96])
+def test_walk_where_fewer_than_k_children_have_mass(vocab):
+    """T = 0.002: in float32 most nodes have one or two ids with any mass left, so there are fewer than k children to draw.  What
+    the walk commits must still have mass in the target's distribution at its node (its logit within 87 T of the largest:
+    exp(-87) is the smallest normal float32), a path must be a root path and its tokens the tree's, whichever id the empty slots carry
+    (a vocabulary of 12: often the very id that the target chooses)."""
+    T = 0.002
+    pair = Pair("c0_tiny_f32", vocab=vocab)
+    cfg, ctx = pair.cfg, pair.ctx
+    ctx.prefill(make_prompt(cfg, n=24))
+    ctx.set_sampling(T, np.zeros(cfg.depth + 1, np.float32))
+    few = 0
+    for rnd in range(40):
+        UD, UA = _numbers(cfg, 500 + rnd)
+        ctx.set_draft_sampling(UD, UA)
+        d = ctx.draft_tree().as_dict()
+        q = ctx.debug_draft_logits(0, 1 + (cfg.depth - 1) * cfg.top_k).cpu().numpy()
+        few += int(((np.exp((q - q.max(1, keepdims=True)) / np.float32(T)) > 0).sum(1) < cfg.top_k).sum())
+        logits = torch.zeros(d["n"], vocab, device="cuda")
+        ctx.verify_tree(None, logits_out=logits)
+        path, m, toks = ctx.accept_and_commit()
+        lg = logits.cpu().numpy().astype(np.float64)
+        assert path[0] == 0 and all(d["parent"][b] == a for a, b in zip(path, path[1:]))
+        assert toks[:-1] == [d["token"][n] for n in path[1:]]
+        for node, tok in zip(path, toks):
+            assert 0 <= tok < vocab and lg[node].max() - lg[node][tok] <= 87 * T, (rnd, node, tok, int(lg[node].argmax()))
+    _say(f"  vocabulary {vocab}: {few} expanded nodes with empty slots in 40 rounds")
+    assert few >= 100
+    pair.close()
+
+
 @pytest.mark.parametrize("T1,T2", [(1.0, 0.7), (0.6, 1.1)])
 def test_temperature_changed_between_drafting_and_the_walk(T1, T2):
     """Children drawn at T1, the walk at T2: target and drafter both at T2 (q of the drafter's logits at T2 is q at T1 to the
