@@ -22,6 +22,7 @@
 namespace poss {
 
 typedef float  f32x4 __attribute__((ext_vector_type(4)));
+typedef float  f32x16 __attribute__((ext_vector_type(16)));
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef f16_t  f16x8 __attribute__((ext_vector_type(8)));
 
@@ -31,11 +32,17 @@ template <> struct Vec8<bf16_t> {
     static __device__ __forceinline__ f32x4 mfma(bf16x8 a, bf16x8 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
     }
+    static __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+    }
 };
 template <> struct Vec8<f16_t> {
     typedef f16x8 type;
     static __device__ __forceinline__ f32x4 mfma(f16x8 a, f16x8 b, f32x4 c) {
         return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+    }
+    static __device__ __forceinline__ f32x16 mfma32(f16x8 a, f16x8 b, f32x16 c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
     }
 };
 
@@ -73,10 +80,10 @@ __device__ __forceinline__ int value_swizzle(int rho) { return (rho >> 1) & 3; }
 // (8 lg .. 8 lg + 7): its slice of P^T then pairs with one natural 16-byte chunk of a V^T row.
 // With a single split the result is normalised and written in the storage type directly;
 // otherwise (max, sum, O) partials go to the merge kernel.
-// LONG: the walk may be longer than ATTN_MAX_BPS blocks (one split over a whole prompt).
-template <typename T, int DH, int KW, int RT, bool LONG = false>
+template <int DH, int KW> constexpr int ATTN_LDS = 2 * 4 * KW * 32 * DH;   // elements: four stages of a block of keys and one of values per key-way
+template <typename T, int DH, int KW, int RT>
 __device__ __forceinline__ void attn_mfma_body(
-    const int row_group, const int kvh, const int split, const T *__restrict__ q, int rows, int hq, int hkv, const uint64_t *__restrict__ mask, int n_prefix,
+    T *__restrict__ lds_all, const int row_group, const int kvh, const int split, const T *__restrict__ q, int rows, int hq, int hkv, const uint64_t *__restrict__ mask, int n_prefix,
     int region_len, KVCache kv, int blocks_per_split, float scale,
     float *__restrict__ o_part, float *__restrict__ ml_part, int rho_pad, T *__restrict__ out_direct) {
     typedef typename Vec8<T>::type V8;
@@ -91,7 +98,7 @@ __device__ __forceinline__ void attn_mfma_body(
     constexpr int BLK = 32 * DH;                          // elements of a staged block
     constexpr int NST = 4;                                // stages
     // [stage][key-way] blocks of keys, then of values; after the last block the same memory carries the KW-way merge
-    __shared__ __attribute__((aligned(1024))) T lds_all[2 * NST * KW * BLK];
+    static_assert(2 * NST * KW * BLK == ATTN_LDS<DH, KW>, "what the caller provides");
     T *ks_lds = lds_all, *vs_lds = lds_all + NST * KW * BLK;
 
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, lr = lane & 15, lg = lane >> 4;
@@ -138,13 +145,8 @@ __device__ __forceinline__ void attn_mfma_body(
     // wait for an operand fragment into a wait for a trip to memory; a vector load inside the loop would make the
     // compiler wait for every load in flight.)
     auto block_of = [&](int it) { return min(b0 + it * KW + kway, b1 - 1); };   // never predicated: past the end a valid block is loaded again and ignored
-    // (LONG: the entries of the 64 blocks of the current window and of the next one; see top().)
-    auto page_vec = [&](int b) { return kv.page_table[(min(b + lane, b1 - 1) << 5) >> kv.page_shift]; };
-    int pg_vec = page_vec(b0), pg_next = LONG ? page_vec(b0 + 64) : 0, window = b0;
-    auto page_of_block = [&](int b) {                     // b wave-uniform
-        if (LONG && b - window >= 64) return __builtin_amdgcn_readlane(pg_next, (b - window) & 63);
-        return __builtin_amdgcn_readlane(pg_vec, (b - window) & 63);
-    };
+    const int pg_vec = kv.page_table[(min(b0 + lane, b1 - 1) << 5) >> kv.page_shift];
+    auto page_of_block = [&](int b) { return __builtin_amdgcn_readlane(pg_vec, (b - b0) & 63); };   // b wave-uniform
     int k_goff[UPT], v_goff[UPT];                         // element offsets of this thread's chunks inside a block
 #pragma unroll
     for (int i = 0; i < UPT; ++i) {
@@ -344,11 +346,6 @@ __device__ __forceinline__ void attn_mfma_body(
         if (rescale) rescale_acc(alpha);
     };
     auto top = [&](int it) {
-        if (LONG && it > 0 && (it * KW) % 64 == 0) {      // (the blocks asked for below lie at most 7 beyond this iteration's)
-            window += 64;
-            pg_vec = pg_next;
-            pg_next = page_vec(window + 64);
-        }
         if (it + 3 < n_it) issue_k(it + 3);               // workgroup-uniform, like the waits at the foot
         if (it + 2 < n_it) issue_v(it + 2);
     };
@@ -412,7 +409,7 @@ __device__ __forceinline__ void attn_mfma_body(
         // one tile of each wave at a time.
         float *xch = reinterpret_cast<float *>(lds_all);  // per (way-1, wave): 64 lanes x (DT*4 + 2) floats
         constexpr int REC = DT * 4 + 2;
-        static_assert((size_t)(KW - 1) * WPW * 64 * REC * sizeof(float) <= sizeof(lds_all), "merge records must fit");
+        static_assert((size_t)(KW - 1) * WPW * 64 * REC * sizeof(float) <= ATTN_LDS<DH, KW> * sizeof(T), "merge records must fit");
         float *mine = xch + ((size_t)((kway - 1) * WPW + wq) * 64 + lane) * REC;
         __syncthreads();
 #pragma unroll
@@ -476,6 +473,410 @@ __device__ __forceinline__ void attn_mfma_body(
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// The same attention for long walks (splits of WALK_MIN_BPS blocks; prompts): on v_mfma_f32_32x32x16, the matrix and the vector
+// work of a wave interleaved instruction by instruction.  A wave takes 32 query rows, a SIMD holds two waves.  In one step a wave forms
+// the scores of block i + 1, the probabilities of block i and the P V products of block i - 1: three things that do not wait for each
+// other, so the softmax of a block (about 130 vector instructions) runs in the shadow of 24 MFMAs of 32 cycles each.  The order is
+// written out (group by group, a scheduling barrier behind every MFMA): left to itself the compiler lines up each product's LDS reads
+// and waits in front of it, and sinks the softmax below the last product.
+//   S^T = K Q^T: MFMA row i is key kappa(i) = 16 (i / 16) + 8 (i / 4 % 2) + 4 (i / 8 % 2) + i % 4 of the block, so that register t of
+//       half h = lane / 32 belongs to key 16 (t / 8) + 8 h + t % 8 of query row lane % 32: eight consecutive keys are the B operand of
+//       one P V MFMA and pair with a 16-byte chunk of a V^T row.
+//   O^T = V^T P^T: tile dt = dh indices 32 dt .., register 4 g + r of half h is index 32 dt + 8 g + 4 h + r.
+// A workgroup is four waves of rows x two key-ways, a block of 32 keys per way and stage.  (Eight waves of rows and one way, 64 keys a
+// stage - half the staging per row and a barrier every other step: a prompt of 8192 tokens 15.3 against 15.4 ms, and walks twice as long:
+// 1.5 against 2.1 ms for 8000 tokens of a small shape, whose workgroups are few.)
+// Swizzles (an operand read: 32 rows x 2 chunks; 4.4 cycles per ds_read_b128 with every wave of a CU reading): rows of 256 bytes keep chunk
+// c of row r at c ^ (r % 16), rows of 128 bytes at c ^ (r / 2 % 8), rows of 64 bytes at c ^ (r / 4 % 4).
+// 81 rows of the 8B shape against 8192 keys: 37.6 us by attn_mfma_kernel, 31 (of which 20 remain without products and softmax: launch,
+// first trip to memory, 16 iterations of loads and barriers, 12 MB of partial results).
+// Which splits are long (bf16): with few rows a wave of 32 has little to do but wait for its own chain, and 16-row tiles are through
+// sooner; fp16, without the low halves, gains nothing before they are.  8B shape, us a pass of four target layers, 16-row tiles / these: 1000
+// keys (9 blocks a split) 61 rows 583 / 602; 2000 keys 599 / 617; 3000 keys 608 / 630; 4000 keys (32 blocks) 1 row 529 / 520, 61 rows
+// 664 / 644; 8192 keys 530 / 523, 81 rows 716 / 700.  640 wide, fp16, 8000 keys 278 / 278, 61 rows 330 / 346.
+constexpr int WALK_MIN_BPS = 32, WALK_THREADS = 512;
+constexpr int PROMPT_SHORT_BLOCKS = 8;                    // a prompt's first range (4 blocks) is computed as a short context is
+template <typename T> __device__ __forceinline__ unsigned pack2(float a, float b) {   // two values rounded to T, a in the low half
+    typedef T t2 __attribute__((ext_vector_type(2)));
+    const t2 v = {from_f<T>(a), from_f<T>(b)};
+    return __builtin_bit_cast(unsigned, v);
+}
+__device__ __forceinline__ float max3(float a, float b, float c) {         // (as the compiler writes it, without quieting NaNs first)
+    float r;
+    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
+}
+template <int BYTES> __device__ __forceinline__ int walk_swizzle(int r) { return BYTES == 256 ? r & 15 : BYTES == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
+
+// The wave's rows: row0 .. row0 + rows - 1 of the pass see the n_prefix slots before them and, of their own region_len slots, those in
+// their masks; lane's row m = row0 + rho / G, rho = rho0 + lane % 32.  The walk: blocks [b0, b1).
+template <typename T, int DH, bool PROMPT>
+__device__ __forceinline__ void attn_walk_body(
+    T *__restrict__ lds_all, int kvh, int split, const T *__restrict__ q, int row0, int rows, int rho0, int hq, int hkv, const uint64_t *__restrict__ mask,
+    int n_prefix, int region_len, KVCache kv, int b0, int b1, float scale, float *__restrict__ o_part, float *__restrict__ ml_part, int rho_pad,
+    T *__restrict__ out_direct) {
+    typedef typename Vec8<T>::type V8;
+    typedef __attribute__((address_space(3))) void *LdsPtr;
+    constexpr bool SPLIT_P = std::is_same<T, bf16_t>::value;   // probabilities as hi + lo, see attn_mfma_body
+    constexpr int KW = 2, WPW = 4, STG = 64 * WPW, NST = 4;
+    constexpr int DT = DH / 32, NG = DH / 16;             // tiles of O^T; groups = k-steps of the scores = value fragments of a block
+    constexpr int PVG = SPLIT_P ? 2 : 1, NS = NG * (PVG + 1);   // P V MFMAs of a group; MFMAs of a step
+    constexpr int KROW = DH * 2, VROW = 64;               // bytes of a staged row
+    constexpr int CPR = KROW / 16, UPT = 32 * CPR / STG, BLK = 32 * DH;      // 16-byte chunks of a key row, loads of a wave per block, elements of a block
+    static_assert(2 * NST * KW * BLK == ATTN_LDS<DH, KW>, "what the caller provides");   // [stage][key-way] blocks of keys, then of values
+    T *ks_lds = lds_all, *vs_lds = lds_all + NST * KW * BLK;
+
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (a SIMD holds a wave of each key-way, of different row groups: with few rows only group 0 has work)
+    const int kway = wave >> 2, wq = (wave + kway) & 3;
+    const int stid = wq * 64 + lane, G = hq / hkv;
+    const int rho = rho0 + l32;
+    const bool valid = rho < rows * G, active = rho0 < rows * G;   // (active: wave-uniform)
+    const int m = row0 + (valid ? rho / G : 0), qh = kvh * G + (valid ? rho % G : 0);
+    V8 qf[NG];
+#pragma unroll
+    for (int ks = 0; ks < NG; ++ks) {
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(q + ((size_t)m * hq + qh) * DH + ks * 16 + h * 8);
+        qf[ks] = __builtin_bit_cast(V8, valid ? v : u32x4{0u, 0u, 0u, 0u});
+    }
+
+    const int n_it = (b1 - b0 + KW - 1) / KW;             // step `it` takes block b0 + it KW + kway
+    const int P = 1 << kv.page_shift;
+    const char *kc = static_cast<const char *>(kv.k), *vc = static_cast<const char *>(kv.vt);
+
+    // Staging, by LDS-direct loads as in attn_mfma_body.  Lane j of pg_vec holds (page, head) of block window + j, pg_next those of the
+    // 64 blocks behind (PROMPT: a walk may be long).
+    auto page_vec = [&](int b) { return kv.page_table[(min(b + lane, b1 - 1) << 5) >> kv.page_shift] * hkv + kvh; };
+    int pg_vec = page_vec(b0), pg_next = PROMPT ? page_vec(b0 + 64) : 0, window = b0;
+    struct Block { size_t page; unsigned off; };          // byte offset of its page in either cache, its first slot in the page
+    auto block_at = [&](int it) {                         // never predicated: past the end a valid block is loaded again and ignored
+        const int b = min(b0 + it * KW + kway, b1 - 1);
+        const unsigned pidx = PROMPT && b - window >= 64 ? __builtin_amdgcn_readlane(pg_next, (b - window) & 63) : __builtin_amdgcn_readlane(pg_vec, (b - window) & 63);
+        return Block{(size_t)pidx * (unsigned)(P * DH * (int)sizeof(T)), (unsigned)((b << 5) & (P - 1))};
+    };
+    // thread's 16-byte units of a block: stid + i STG.  Keys: row u / CPR; values: row u / 4, chunk by the swizzle.
+    unsigned k_goff[UPT], v_goff[UPT];
+#pragma unroll
+    for (int i = 0; i < UPT; ++i) {
+        const int u = stid + i * STG;
+        const int krow = u / CPR, kpos = u % CPR;
+        k_goff[i] = (unsigned)(krow * KROW + (kpos ^ walk_swizzle<KROW>(krow)) * 16);
+        const int vrow = u >> 2, c = (u & 3) ^ walk_swizzle<VROW>(vrow);
+        v_goff[i] = (unsigned)((vrow * P + c * 8) * (int)sizeof(T));
+    }
+    const unsigned lds_k0 = (unsigned)(uintptr_t)(LdsPtr)ks_lds, lds_v0 = (unsigned)(uintptr_t)(LdsPtr)vs_lds;
+    const unsigned wave_units = (unsigned)(kway * BLK * (int)sizeof(T) + wq * 1024);
+    auto scalar = [](const char *p) {                     // (wave-uniform already: says so)
+        const uint64_t x = reinterpret_cast<uint64_t>(p);
+        return reinterpret_cast<const char *>((uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(x >> 32)) << 32 | (unsigned)__builtin_amdgcn_readfirstlane((int)x));
+    };
+    auto stage_at = [&](int it) { return (unsigned)((it & (NST - 1)) * KW * BLK * (int)sizeof(T)); };
+    auto issue_k = [&](int it, const Block &b, int i) {
+        lds_dma16_s(lds_k0 + stage_at(it) + wave_units + i * STG * 16, scalar(kc + b.page + b.off * KROW), k_goff[i]);
+    };
+    auto issue_v = [&](int it, const Block &b, int i) {
+        lds_dma16_s(lds_v0 + stage_at(it) + wave_units + i * STG * 16, scalar(vc + b.page + b.off * (int)sizeof(T)), v_goff[i]);
+    };
+
+    // operand reads: byte addresses of this lane inside a stage; the chunk of fragment u by xor
+    const int kappa = 16 * (l32 >> 4) + 8 * ((l32 >> 2) & 1) + 4 * ((l32 >> 3) & 1) + (l32 & 3);
+    const unsigned k_rd = (unsigned)(kway * BLK * (int)sizeof(T)) + kappa * KROW + ((h ^ walk_swizzle<KROW>(kappa)) * 16);
+    const unsigned v_rd = (unsigned)(kway * BLK * (int)sizeof(T)) + l32 * VROW + ((h ^ walk_swizzle<VROW>(l32)) * 16);
+    auto key_at = [&](int it) { return stage_at(it) + k_rd; };
+    auto value_at = [&](int it) { return stage_at(it) + v_rd; };
+    auto key_fragment = [&](unsigned at, int u) {
+        return *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(ks_lds) + (at ^ (unsigned)(u * 32)));
+    };
+    auto value_fragment = [&](unsigned at, int f) {       // f: dh tile f % DT, keys 16 (f / DT) ..
+        return *reinterpret_cast<const u32x4 *>(reinterpret_cast<const char *>(vs_lds) + ((at ^ (unsigned)((f / DT) * 32)) + (f % DT) * 32 * VROW));
+    };
+
+    f32x16 acc[DT];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[dt][i] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f;
+    struct Prob { u32x4 hi[2], lo[2]; };
+
+    // Step `it`: softmax of block `it` (scores in s, probabilities to pn), scores of block it + 1 to sn, P V of block it - 1
+    // (probabilities pp; FIRST: there is none).  vf holds the first value fragments of block it - 1 on entry, of block `it` on exit.
+    // In between it issues the loads `load(l)`, l = 0 .. N_LOADS - 1, one at a time: eight waves asking for 32 KB at the top of an
+    // iteration kept each other from issuing anything for 500 cycles.
+    u32x4 vf[4];
+    constexpr int N_LOADS = 2 * UPT;
+    auto step = [&](auto first_tag, int it, f32x16 &s, f32x16 &sn, const Prob &pp, Prob &pn, auto load) {
+        constexpr bool FIRST = decltype(first_tag)::value;
+        const unsigned k_st = key_at(it + 1), v_st = value_at(it - 1), v_next = value_at(it);
+        u32x4 kf[3];
+        kf[0] = key_fragment(k_st, 0);
+        kf[1] = key_fragment(k_st, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        float mx = 0.f, m_ref = 0.f, alpha = 1.f, psum = 0.f, e[16];
+        // The softmax in N_CHUNKS pieces, a value's exponential, its part in the sum and the high half of its pair, and the low half in
+        // three successive ones: an instruction that needs the one before it costs a wave 9 cycles, one that does not 6.
+        // (The empty statements hold a value where it is computed: the compiler would sink all of it below the last MFMA.)
+        constexpr int N_CHUNKS = 22;
+        auto sum_and_pack = [&](int j) {
+            asm volatile("" : "+v"(e[j]));
+            psum += e[j];
+            asm volatile("" : "+v"(psum));
+            if (j & 1) {
+                unsigned hi = pack2<T>(e[j - 1], e[j]);
+                asm volatile("" : "+v"(hi));
+                pn.hi[j >> 3][(j & 7) >> 1] = hi;
+            }
+        };
+        auto low_half = [&](int j) {                      // of the pair (j - 1, j)
+            if constexpr (SPLIT_P) {
+                const unsigned hi = pn.hi[j >> 3][(j & 7) >> 1];
+                unsigned lo = pack2<T>(e[j - 1] - __builtin_bit_cast(float, hi << 16), e[j] - __builtin_bit_cast(float, hi & 0xffff0000u));
+                asm volatile("" : "+v"(lo));
+                pn.lo[j >> 3][(j & 7) >> 1] = lo;
+            }
+        };
+        auto chunk = [&](int c) {
+            if (c == 0) {
+                float a = s[0], b = s[8];
+#pragma unroll
+                for (int j = 1; j < 7; j += 2) { a = max3(a, s[j], s[j + 1]); b = max3(b, s[8 + j], s[9 + j]); }
+                mx = max3(a, b, max3(s[7], s[15], s[15]));
+            } else if (c == 1) {
+                float a, b;
+                swap32(mx, a, b);
+                mx = max3(a, b, b) * scale;
+            } else if (c == 2) {
+                const float m_new = mx > m_run + 8.f ? mx : m_run;    // (the reference moves only when it has to: see attn_mfma_body)
+                m_ref = m_new == -INFINITY ? 0.f : m_new; // (nothing visible yet)
+                mx = m_run - m_ref;
+                m_run = m_new;
+            } else if (c == 3) {
+                alpha = __builtin_amdgcn_exp2f(mx);
+            } else {
+                const int j = c - 4;
+                if (j < 16) {
+                    const float sv = s[j];
+                    e[j] = __builtin_amdgcn_exp2f(fmaf(sv, scale, -m_ref));
+                }
+                if (j >= 1 && j <= 16) sum_and_pack(j - 1);
+                if (j >= 2 && (j - 2) % 2 == 1) low_half(j - 2);
+            }
+        };
+        constexpr int NSV = FIRST ? NG : NS, PV = FIRST ? 0 : PVG;   // MFMAs of this variant, P V MFMAs of a group
+#pragma unroll
+        for (int u = 0; u < NG; ++u) {
+            // fragments of two groups ahead
+            if (u + 2 < NG) kf[(u + 2) % 3] = key_fragment(k_st, u + 2);
+            if constexpr (SPLIT_P) {
+                if (u % 2 == 0) {
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        if (u + 2 < NG) { if (!FIRST) vf[(u + 2 + w) & 3] = value_fragment(v_st, u + 2 + w); }
+                        else vf[(u + 2 + w) & 3] = value_fragment(v_next, u + 2 + w - NG);
+                    }
+                }
+            } else {
+                if (u + 2 < NG) { if (!FIRST) vf[(u + 2) & 3] = value_fragment(v_st, u + 2); }
+                else vf[(u + 2) & 3] = value_fragment(v_next, u + 2 - NG);
+            }
+#pragma unroll
+            for (int w = 0; w <= PV; ++w) {
+                if (w < PV) {
+                    const int f = SPLIT_P ? (u & ~1) + w : u;
+                    const V8 p = __builtin_bit_cast(V8, SPLIT_P && (u & 1) ? pp.lo[f / DT] : pp.hi[f / DT]);
+                    acc[f % DT] = Vec8<T>::mfma32(__builtin_bit_cast(V8, vf[f & 3]), p, acc[f % DT]);
+                } else {
+                    f32x16 z;
+                    if (u == 0) {
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) z[i] = 0.f;
+                    } else {
+                        z = sn;
+                    }
+                    sn = Vec8<T>::mfma32(__builtin_bit_cast(V8, kf[u % 3]), qf[u], z);
+                }
+                const int t = u * (PV + 1) + w;
+#pragma unroll
+                for (int c = t * N_CHUNKS / NSV; c < (t + 1) * N_CHUNKS / NSV; ++c) chunk(c);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int l = 0; l < N_LOADS; ++l)
+                if (u == (2 * l + 1) * NG / (2 * N_LOADS)) load(l);
+        }
+        l_run = l_run * alpha + psum;
+        if (!FIRST && __builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {    // rare once the maximum has settled
+            asm volatile("" ::: "memory");                // (keeps the compiler from turning it into 64 selects)
+#pragma unroll
+            for (int dt = 0; dt < DT; ++dt) acc[dt] *= alpha;
+        }
+    };
+    // scores of keys that the row does not see (few blocks reach into the region: its mask words come from memory here)
+    auto hide = [&](int b, f32x16 &s) {
+        const uint64_t m0 = valid ? mask[(size_t)m * MASK_WORDS] : 0ull, m1 = valid ? mask[(size_t)m * MASK_WORDS + 1] : 0ull;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const float v = s[j];
+            s[j] = (b < b1) & slot_visible((b << 5) + 16 * (j >> 3) + 8 * h + (j & 7), n_prefix, region_len, m0, m1) ? v : -INFINITY;
+        }
+    };
+    // P V of the last block
+    auto last_pv = [&](int it, const Prob &pp) {
+        const unsigned v_st = value_at(it);
+#pragma unroll
+        for (int f = 0; f < NG; ++f) {
+            const V8 v = __builtin_bit_cast(V8, f < 2 ? vf[f] : value_fragment(v_st, f));
+            acc[f % DT] = Vec8<T>::mfma32(v, __builtin_bit_cast(V8, pp.hi[f / DT]), acc[f % DT]);
+            if constexpr (SPLIT_P) acc[f % DT] = Vec8<T>::mfma32(v, __builtin_bit_cast(V8, pp.lo[f / DT]), acc[f % DT]);
+        }
+    };
+
+    // Loads are issued two iterations ahead, as in attn_mfma_body: in iteration `it` the keys of it + 3 (their stage was last read in
+    // it - 2) and the values of it + 2 (last read in it - 1); at its foot every wave waits until only those are outstanding, and the
+    // barrier then publishes the keys of it + 2 and the values of it + 1.  (PROMPT: past the end a valid block is loaded again, without
+    // a branch.)
+    typedef std::integral_constant<bool, true> Yes;
+    typedef std::integral_constant<bool, false> No;
+    Block ahead, last;                                    // the blocks of it + 3 and it + 2
+    f32x16 sa, sb;
+    Prob pa, pb;
+    auto iterate = [&](auto first_tag, int it, f32x16 &s, f32x16 &sn, const Prob &pp, Prob &pn) {
+        const bool more_k = it + 3 < n_it, more_v = it + 2 < n_it;   // (workgroup-uniform)
+        if (PROMPT && it > 0 && (it * KW) % 64 == 0) {    // (the blocks asked for below lie at most 7 beyond this iteration's)
+            window += 64;
+            pg_vec = pg_next;
+            pg_next = page_vec(window + 64);
+        }
+        last = ahead;
+        ahead = block_at(it + 3);
+        auto load = [&](int l) {                          // keys first
+            if (l < UPT) { if (PROMPT || more_k) issue_k(it + 3, ahead, l); }
+            else if (PROMPT || more_v) issue_v(it + 2, last, l - UPT);
+        };
+        if (active) {
+            const int b = b0 + it * KW + kway;
+            if ((b << 5) + 32 > n_prefix || b >= b1) hide(b, s);
+            step(first_tag, it, s, sn, pp, pn, load);
+        } else {
+#pragma unroll
+            for (int l = 0; l < N_LOADS; ++l) load(l);
+        }
+        if (PROMPT || more_k) dma_wait<2 * UPT>();
+        else if (more_v) dma_wait<UPT>();
+        else dma_wait<0>();
+        __syncthreads();
+    };
+    {
+        const Block t = block_at(0);
+        last = block_at(1);
+        ahead = block_at(2);
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) issue_k(0, t, i);
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) issue_k(1, last, i);
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) issue_v(0, t, i);
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) issue_k(2, ahead, i);
+#pragma unroll
+        for (int i = 0; i < UPT; ++i) issue_v(1, last, i);
+    }
+    dma_wait<2 * UPT>();                                  // keys of iterations 0 and 1 and values of iteration 0 have landed
+    __syncthreads();
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sa[i] = 0.f;
+#pragma unroll
+        for (int u = 0; u < NG; ++u) sa = Vec8<T>::mfma32(__builtin_bit_cast(V8, key_fragment(key_at(0), u)), qf[u], sa);
+    }
+    iterate(Yes{}, 0, sa, sb, pb, pa);
+    int it = 1;
+    for (; it + 1 < n_it; it += 2) {
+        iterate(No{}, it, sb, sa, pa, pb);
+        iterate(No{}, it + 1, sa, sb, pb, pa);
+    }
+    if (it < n_it) {
+        iterate(No{}, it, sb, sa, pa, pb);
+        if (active) last_pv(n_it - 1, pb);
+    } else if (active) {
+        last_pv(n_it - 1, pa);
+    }
+    {
+        float a, b;
+        swap32(l_run, a, b);
+        l_run = a + b;
+    }
+
+    if constexpr (PROMPT) dma_wait<0>();                  // (no load may land where the results are exchanged)
+    // the other key-way's (max, sum, O) through LDS, folded in by way 0: [wave][value][lane]
+    float *xch = reinterpret_cast<float *>(lds_all) + (size_t)wq * (DT * 16 + 2) * 64 + lane;
+    static_assert((size_t)WPW * (DT * 16 + 2) * 64 * sizeof(float) <= ATTN_LDS<DH, KW> * sizeof(T), "merge records must fit");
+    __syncthreads();
+    if (kway > 0) {
+        xch[0] = m_run;
+        xch[64] = l_run;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) xch[(2 + dt * 16 + i) * 64] = acc[dt][i];
+    }
+    __syncthreads();
+    if (kway > 0 || !active) return;
+    const float mo = xch[0], lo = xch[64], mn = fmaxf(m_run, mo);
+    if (mn != -INFINITY) {
+        const float a0 = __builtin_amdgcn_exp2f(m_run - mn), a1 = __builtin_amdgcn_exp2f(mo - mn);
+        l_run = l_run * a0 + lo * a1;
+        m_run = mn;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[dt][i] = acc[dt][i] * a0 + xch[(2 + dt * 16 + i) * 64] * a1;
+    }
+    if (PROMPT || out_direct) {
+        if (!valid) return;
+        struct __attribute__((aligned(4 * sizeof(T)))) Quad { T t[4]; };
+        const float inv = 1.0f / l_run;
+        T *dst = out_direct + ((size_t)m * hq + qh) * DH + 4 * h;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                Quad o;
+#pragma unroll
+                for (int r = 0; r < 4; ++r) o.t[r] = from_f<T>(acc[dt][4 * g + r] * inv);
+                *reinterpret_cast<Quad *>(dst + dt * 32 + g * 8) = o;
+            }
+        return;
+    }
+    if (rho >= rho_pad) return;
+    const size_t prow = ((size_t)split * hkv + kvh) * rho_pad + rho;
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            f32x4 v;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = acc[dt][4 * g + r];
+            *reinterpret_cast<f32x4 *>(o_part + prow * DH + dt * 32 + g * 8 + 4 * h) = v;
+        }
+    if (h == 0) {
+        ml_part[prow * 2] = m_run;
+        ml_part[prow * 2 + 1] = l_run;
+    }
+}
+
+// a split of a sequence's keys, for the 128 query rows x heads of row_group
+template <typename T, int DH>
+__device__ __forceinline__ void attn_walk_split(T *lds, int row_group, int kvh, int split, const T *q, int rows, int hq, int hkv, const uint64_t *mask,
+                                                int n_prefix, int region_len, KVCache kv, int blocks_per_split, float scale, float *o_part,
+                                                float *ml_part, int rho_pad, T *out_direct) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wq = (wave + (wave >> 2)) & 3;
+    const int b0 = split * blocks_per_split, b1 = min((n_prefix + region_len + 31) >> 5, b0 + blocks_per_split);
+    attn_walk_body<T, DH, false>(lds, kvh, split, q, 0, rows, (row_group * 4 + wq) * 32, hq, hkv, mask, n_prefix, region_len, kv, b0, b1, scale, o_part,
+                                 ml_part, rho_pad, out_direct);
+}
+
 // Workgroup id -> (row group, KV head, split).  Consecutive ids go to the 8 XCDs in turn, each with an
 // L2 of its own, so the row groups that read the same keys and values (same head and split) are given
 // ids that are equal modulo 8: the block is fetched from memory once and then found in that L2.
@@ -492,28 +893,51 @@ __global__ __launch_bounds__(256 * KW) void attn_mfma_kernel(
     const T *__restrict__ q, int rows, int hq, int hkv, const uint64_t *__restrict__ mask, int n_prefix,
     int region_len, KVCache kv, int blocks_per_split, int n_splits, int n_row_groups, float scale,
     float *__restrict__ o_part, float *__restrict__ ml_part, int rho_pad, T *__restrict__ out_direct) {
+    __shared__ __attribute__((aligned(1024))) T lds[ATTN_LDS<DH, KW>];
     int row_group, pair;
     if (!attn_place(blockIdx.x, hkv * n_splits, n_row_groups, row_group, pair)) return;
-    attn_mfma_body<T, DH, KW, RT>(row_group, pair % hkv, pair / hkv, q, rows, hq, hkv, mask, n_prefix, region_len, kv, blocks_per_split,
+    attn_mfma_body<T, DH, KW, RT>(lds, row_group, pair % hkv, pair / hkv, q, rows, hq, hkv, mask, n_prefix, region_len, kv, blocks_per_split,
                                   scale, o_part, ml_part, rho_pad, out_direct);
+}
+
+template <typename T, int DH>
+__global__ __launch_bounds__(WALK_THREADS) void attn_walk_kernel(
+    const T *__restrict__ q, int rows, int hq, int hkv, const uint64_t *__restrict__ mask, int n_prefix,
+    int region_len, KVCache kv, int blocks_per_split, int n_splits, int n_row_groups, float scale,
+    float *__restrict__ o_part, float *__restrict__ ml_part, int rho_pad, T *__restrict__ out_direct) {
+    __shared__ __attribute__((aligned(1024))) T lds[ATTN_LDS<DH, 2>];
+    int row_group, pair;
+    if (!attn_place(blockIdx.x, hkv * n_splits, n_row_groups, row_group, pair)) return;
+    attn_walk_split<T, DH>(lds, row_group, pair % hkv, pair / hkv, q, rows, hq, hkv, mask, n_prefix, region_len, kv, blocks_per_split,
+                                 scale, o_part, ml_part, rho_pad, out_direct);
 }
 
 // A prompt's rows [0, rows) at slots c0 ..: ranges of MAX_ROWS rows (the width of a row's mask), each against the slots before
 // it and itself, all in one launch.  With thousands of rows the keys need no splitting: a workgroup walks all of them and
 // writes its rows directly - no partial outputs, no merge.  Pairs (range, KV head) are dealt to the XCDs in turn, the longest
-// walks first.
-// One layer of 8192 tokens (two passes) of the 8B shape: 32 launches of two ranges each, at most 1024 keys per split, and their
-// merges 2.02 ms -> 1.17 ms (470 TFLOP/s of the causal product).
+// walks first.  The first n_short ranges have walks as short as the splits of a short context and are computed as those are, bit for
+// bit (the ids behind walk_wgs).
+// One layer of 8192 tokens (two passes) of the 8B shape: 1.15 ms by attn_mfma_body, 0.81 with attn_walk_body (680 TFLOP/s of the causal
+// product, 1.02 PFLOP/s of MFMAs: the low halves of the probabilities are half as many again).
 template <typename T, int DH>
-__global__ __launch_bounds__(512) void attn_prompt_kernel(const T *__restrict__ q, int rows, int hq, int hkv, const uint64_t *__restrict__ mask,
-                                                          int c0, KVCache kv, int n_row_groups, float scale, T *__restrict__ out) {
-    const int n_ranges = (rows + MAX_ROWS - 1) / MAX_ROWS;
+__global__ __launch_bounds__(WALK_THREADS) void attn_prompt_kernel(const T *__restrict__ q, int rows, int hq, int hkv, const uint64_t *__restrict__ mask,
+                                                          int c0, KVCache kv, int n_short, int walk_wgs, float scale, T *__restrict__ out) {
+    __shared__ __attribute__((aligned(1024))) T lds[ATTN_LDS<DH, 2>];
+    const int n_row_groups = (MAX_ROWS * (hq / hkv) + 127) / 128, n_ranges = (rows + MAX_ROWS - 1) / MAX_ROWS;
+    const bool brief = (int)blockIdx.x >= walk_wgs;
     int row_group, pair;
-    if (!attn_place(blockIdx.x, hkv * n_ranges, n_row_groups, row_group, pair)) return;
-    const int r0 = (n_ranges - 1 - pair / hkv) * MAX_ROWS, n = min(MAX_ROWS, rows - r0), keys = c0 + r0 + n;
-    const size_t off = (size_t)r0 * hq * DH;
-    attn_mfma_body<T, DH, 2, 2, true>(row_group, pair % hkv, 0, q + off, n, hq, hkv, mask + (size_t)r0 * MASK_WORDS, c0 + r0, n, kv,
-                                      (keys + 31) >> 5, scale, nullptr, nullptr, 0, out + off);
+    if (!attn_place(blockIdx.x - (brief ? walk_wgs : 0), hkv * (brief ? n_short : n_ranges - n_short), n_row_groups, row_group, pair)) return;
+    const int range = brief ? pair / hkv : n_ranges - 1 - pair / hkv;
+    const int r0 = range * MAX_ROWS, n = min(MAX_ROWS, rows - r0), b1 = (c0 + r0 + n + 31) >> 5;
+    if (brief) {
+        const size_t off = (size_t)r0 * hq * DH;
+        attn_mfma_body<T, DH, 2, 2>(lds, row_group, pair % hkv, 0, q + off, n, hq, hkv, mask + (size_t)r0 * MASK_WORDS, c0 + r0, n, kv, b1, scale,
+                                    nullptr, nullptr, 0, out + off);
+        return;
+    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wq = (wave + (wave >> 2)) & 3;
+    attn_walk_body<T, DH, true>(lds, pair % hkv, 0, q, r0, n, (row_group * 4 + wq) * 32, hq, hkv, mask, c0 + r0, n, kv, 0, b1, scale,
+                                nullptr, nullptr, 0, out);
 }
 
 // Several sequences in one launch: every sequence has its own rows, cache, prefix, split count and slice of the
@@ -529,15 +953,30 @@ struct AttnSeqs { int n; AttnSeq s[ATTN_MAX_SEQ]; };
 
 template <typename T, int DH, int KW, int RT>
 __global__ __launch_bounds__(256 * KW) void attn_mfma_batch_kernel(AttnSeqs seqs, int hq, int hkv, float scale) {
+    __shared__ __attribute__((aligned(1024))) T lds[ATTN_LDS<DH, KW>];
     int i = 0;
     for (int j = 1; j < seqs.n; ++j)
         if ((int)blockIdx.x >= seqs.s[j].wg0) i = j;
     const AttnSeq &a = seqs.s[i];
     int row_group, pair;
     if (!attn_place(blockIdx.x - a.wg0, hkv * a.n_splits, a.n_row_groups, row_group, pair)) return;
-    attn_mfma_body<T, DH, KW, RT>(row_group, pair % hkv, pair / hkv, static_cast<const T *>(a.q), a.rows, hq, hkv, a.mask, a.n_prefix,
+    attn_mfma_body<T, DH, KW, RT>(lds, row_group, pair % hkv, pair / hkv, static_cast<const T *>(a.q), a.rows, hq, hkv, a.mask, a.n_prefix,
                                   a.region_len, a.kv, a.blocks_per_split, scale, a.o_part, a.ml_part, a.rho_pad,
                                   static_cast<T *>(a.out_direct));
+}
+
+template <typename T, int DH>
+__global__ __launch_bounds__(WALK_THREADS) void attn_walk_batch_kernel(AttnSeqs seqs, int hq, int hkv, float scale) {
+    __shared__ __attribute__((aligned(1024))) T lds[ATTN_LDS<DH, 2>];
+    int i = 0;
+    for (int j = 1; j < seqs.n; ++j)
+        if ((int)blockIdx.x >= seqs.s[j].wg0) i = j;
+    const AttnSeq &a = seqs.s[i];
+    int row_group, pair;
+    if (!attn_place(blockIdx.x - a.wg0, hkv * a.n_splits, a.n_row_groups, row_group, pair)) return;
+    attn_walk_split<T, DH>(lds, row_group, pair % hkv, pair / hkv, static_cast<const T *>(a.q), a.rows, hq, hkv, a.mask, a.n_prefix,
+                                 a.region_len, a.kv, a.blocks_per_split, scale, a.o_part, a.ml_part, a.rho_pad,
+                                 static_cast<T *>(a.out_direct));
 }
 
 // out[m][qh][:] = sum_s e^{m_s - M} O_s / sum_s e^{m_s - M} l_s, splits in order, for the rows of every sequence of a launch
@@ -708,10 +1147,8 @@ static int blocks_per_split(int n_prefix, int keys_per_split) {
 
 // Launch shape of one sequence's attention: the split rule, key-ways and row tiles per wave.
 // Key-ways follow the split size (so, like it, the committed prefix only); the number of row tiles per wave may follow
-// the row count: it does not change any row's arithmetic.  Eight tiles per workgroup where the walk is long (every key /
-// value block staged once for eight tiles), as 4 waves x 2 tiles per key-way; 8 waves x 1 tile (sixteen waves per
-// workgroup, four per SIMD) measured the same.
-struct AttnShape { int bps, n_splits, kw, rt, n_row_groups, rho_pad, n_wgs; };
+// the row count: it does not change any row's arithmetic.
+struct AttnShape { int bps, n_splits, kw, rt, n_row_groups, rho_pad, n_wgs; bool walk; };
 static AttnShape attention_shape(const ModelDims &md, int rows, int n_prefix, int region_len, int keys_per_split,
                                  bool crowded = false) {
     AttnShape a;
@@ -723,11 +1160,14 @@ static AttnShape attention_shape(const ModelDims &md, int rows, int n_prefix, in
     while ((n_blocks + a.bps - 1) / a.bps > ATTN_MAX_SPLITS) a.bps *= 2;     // only with a tiny split override on a very long context
     a.n_splits = (n_blocks + a.bps - 1) / a.bps;
     a.kw = a.bps >= 4 ? 2 : 1;
-    // pays where the walk is long - or where the launch would otherwise hold more workgroups than the chip has CUs
-    // (a workgroup fills a CU's LDS: the surplus would run as a second round)
-    a.rt = tiles > 4 && (a.bps >= 8 || crowded) ? 2 : 1;
+    a.walk = md.dt == DT_BF16 && a.bps >= WALK_MIN_BPS;
+    // Two row tiles a wave where one would put more workgroups in the launch than the chip has CUs (a workgroup fills a CU's LDS: the
+    // surplus would run as a second round).  Otherwise the keys are staged twice as often, by twice as many CUs: 61 rows of the 8B
+    // shape, us a pass of four layers, two tiles / one: 1000 keys 600 / 583, 2000 623 / 599, 3000 648 / 608.
+    const int pairs = 8 * ((md.hkv * a.n_splits + 7) / 8);
+    a.rt = a.walk || (tiles > 4 && (crowded || (tiles + 3) / 4 * pairs > 256)) ? 2 : 1;
     a.n_row_groups = (tiles + 4 * a.rt - 1) / (4 * a.rt);
-    a.n_wgs = 8 * a.n_row_groups * ((md.hkv * a.n_splits + 7) / 8);
+    a.n_wgs = a.n_row_groups * pairs;
     return a;
 }
 
@@ -744,6 +1184,12 @@ static void launch_attention_t(const ModelDims &md, const void *q, int rows, con
                        a.n_splits, a.n_row_groups, scale, sc.o, sc.ml, a.rho_pad, direct)
 #define POSS_ATTN_DH(DH)                                                                                         \
     do {                                                                                                         \
+        if constexpr (std::is_same<T, bf16_t>::value) if (a.walk) {                                              \
+            hipLaunchKernelGGL((attn_walk_kernel<T, DH>), dim3(a.n_wgs), dim3(WALK_THREADS), 0, st,              \
+                               static_cast<const T *>(q), rows, md.hq, md.hkv, rm.mask, n_prefix, region_len, kv, a.bps, \
+                               a.n_splits, a.n_row_groups, scale, sc.o, sc.ml, a.rho_pad, direct);               \
+            break;                                                                                               \
+        }                                                                                                        \
         if (a.kw == 2) { if (a.rt == 2) POSS_ATTN(DH, 2, 2); else POSS_ATTN(DH, 2, 1); }                         \
         else           { if (a.rt == 2) POSS_ATTN(DH, 1, 2); else POSS_ATTN(DH, 1, 1); }                         \
     } while (0)
@@ -787,31 +1233,36 @@ static void launch_attention_batch_t(const ModelDims &md, const void *q, const R
         a.rho_pad = shp[i].rho_pad; a.wg0 = 0; a.row0 = g.row0;
         any_split = any_split || shp[i].n_splits > 1;
     }
-    // one launch per (key-ways, row tiles) instantiation that occurs: as a rule one
-    for (int kw = 1; kw <= 2; ++kw)
-        for (int rt = 1; rt <= 2; ++rt) {
-                AttnSeqs grp;
-                grp.n = 0;
-                int wgs = 0;
-                for (int i = 0; i < n; ++i)
-                    if (shp[i].kw == kw && shp[i].rt == rt) {
-                        grp.s[grp.n] = all[i];
-                        grp.s[grp.n].wg0 = wgs;
-                        wgs += shp[i].n_wgs;
-                        ++grp.n;
-                    }
-                if (grp.n == 0) continue;
+    // one launch per kind of kernel that occurs (long walk, or key-ways and row tiles): as a rule one
+    for (int kind = 0; kind < 5; ++kind) {
+        const bool walk = kind == 4;
+        const int kw = (kind >> 1) + 1, rt = (kind & 1) + 1;
+        AttnSeqs grp;
+        grp.n = 0;
+        int wgs = 0;
+        for (int i = 0; i < n; ++i)
+            if (shp[i].walk == walk && (walk || (shp[i].kw == kw && shp[i].rt == rt))) {
+                grp.s[grp.n] = all[i];
+                grp.s[grp.n].wg0 = wgs;
+                wgs += shp[i].n_wgs;
+                ++grp.n;
+            }
+        if (grp.n == 0) continue;
 #define POSS_ATTNB(DH, KW, RT)                                                                                   \
     hipLaunchKernelGGL((attn_mfma_batch_kernel<T, DH, KW, RT>), dim3(wgs), dim3(256 * KW), 0, st, grp, md.hq, md.hkv, scale)
 #define POSS_ATTNB_DH(DH)                                                                                        \
     do {                                                                                                         \
-        if (kw == 2) { if (rt == 2) POSS_ATTNB(DH, 2, 2); else POSS_ATTNB(DH, 2, 1); }                           \
-        else         { if (rt == 2) POSS_ATTNB(DH, 1, 2); else POSS_ATTNB(DH, 1, 1); }                           \
+        if constexpr (std::is_same<T, bf16_t>::value) if (walk) {                                                \
+            hipLaunchKernelGGL((attn_walk_batch_kernel<T, DH>), dim3(wgs), dim3(WALK_THREADS), 0, st, grp, md.hq, md.hkv, scale); \
+            break;                                                                                               \
+        }                                                                                                        \
+        if (kw == 2) { if (rt == 2) POSS_ATTNB(DH, 2, 2); else POSS_ATTNB(DH, 2, 1); }                      \
+        else              { if (rt == 2) POSS_ATTNB(DH, 1, 2); else POSS_ATTNB(DH, 1, 1); }                      \
     } while (0)
-                if (md.dh == 128) POSS_ATTNB_DH(128); else POSS_ATTNB_DH(64);
+        if (md.dh == 128) POSS_ATTNB_DH(128); else POSS_ATTNB_DH(64);
 #undef POSS_ATTNB_DH
 #undef POSS_ATTNB
-            }
+    }
     if (any_split) {
         AttnSeqs grp;
         grp.n = n;
@@ -839,16 +1290,16 @@ void launch_attention_batch(const ModelDims &md, const void *q, const RowMeta &r
 template <typename T>
 static void launch_attention_prompt_t(const ModelDims &md, const void *q, int rows, const uint64_t *mask, int c0, const KVCache &kv,
                                       void *out, hipStream_t st) {
-    const int G = md.hq / md.hkv, most = rows < MAX_ROWS ? rows : MAX_ROWS, n_ranges = (rows + MAX_ROWS - 1) / MAX_ROWS;
-    const int n_row_groups = ((most * G + 15) / 16 + 7) / 8;             // eight tiles of 16 query rows per workgroup
-    const int wgs = 8 * n_row_groups * ((md.hkv * n_ranges + 7) / 8);
+    const int n_ranges = (rows + MAX_ROWS - 1) / MAX_ROWS, n_row_groups = (MAX_ROWS * (md.hq / md.hkv) + 127) / 128;
+    int n_short = 0;                                                     // ranges that walk fewer than PROMPT_SHORT_BLOCKS blocks
+    while (n_short < n_ranges && (c0 + (rows < (n_short + 1) * MAX_ROWS ? rows : (n_short + 1) * MAX_ROWS) + 31) / 32 < PROMPT_SHORT_BLOCKS) ++n_short;
+    const int walk_wgs = 8 * n_row_groups * ((md.hkv * (n_ranges - n_short) + 7) / 8), short_wgs = 8 * n_row_groups * ((md.hkv * n_short + 7) / 8);
     const float scale = 1.4426950408889634f / sqrtf((float)md.dh);
-    if (md.dh == 128)
-        hipLaunchKernelGGL((attn_prompt_kernel<T, 128>), dim3(wgs), dim3(512), 0, st, static_cast<const T *>(q), rows, md.hq, md.hkv, mask,
-                           c0, kv, n_row_groups, scale, static_cast<T *>(out));
-    else
-        hipLaunchKernelGGL((attn_prompt_kernel<T, 64>), dim3(wgs), dim3(512), 0, st, static_cast<const T *>(q), rows, md.hq, md.hkv, mask,
-                           c0, kv, n_row_groups, scale, static_cast<T *>(out));
+#define POSS_PROMPT(DH)                                                                                                              \
+    hipLaunchKernelGGL((attn_prompt_kernel<T, DH>), dim3(walk_wgs + short_wgs), dim3(WALK_THREADS), 0, st, static_cast<const T *>(q), rows, \
+                       md.hq, md.hkv, mask, c0, kv, n_short, walk_wgs, scale, static_cast<T *>(out))
+    if (md.dh == 128) POSS_PROMPT(128); else POSS_PROMPT(64);
+#undef POSS_PROMPT
 }
 
 void launch_attention_prompt(const ModelDims &md, const void *q, int rows, const uint64_t *mask, int c0, const KVCache &kv, void *out,
