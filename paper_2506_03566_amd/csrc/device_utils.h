@@ -203,16 +203,20 @@ __device__ __forceinline__ void rope_pair(float x1, float x2, float2 cs, float &
     o2 = __builtin_fmaf(x2, cs.x, q);
 }
 
-// Element offsets into the paged caches.
-__device__ __forceinline__ size_t k_offset(const KVCache &kv, int slot, int head, int hkv, int dh) {
+// Element offsets into the paged caches; _in: with the slot's physical page already looked up.
+__device__ __forceinline__ size_t k_offset_in(const KVCache &kv, int pg, int slot, int head, int hkv, int dh) {
     const int P = 1 << kv.page_shift;
-    const int pg = kv.page_table[slot >> kv.page_shift];
     return ((size_t)(pg * hkv + head) * P + (slot & (P - 1))) * dh;
 }
-__device__ __forceinline__ size_t vt_offset(const KVCache &kv, int slot, int head, int hkv, int dh, int row) {
+__device__ __forceinline__ size_t vt_offset_in(const KVCache &kv, int pg, int slot, int head, int hkv, int dh, int row) {
     const int P = 1 << kv.page_shift;
-    const int pg = kv.page_table[slot >> kv.page_shift];
     return ((size_t)(pg * hkv + head) * dh + row) * P + (slot & (P - 1));
+}
+__device__ __forceinline__ size_t k_offset(const KVCache &kv, int slot, int head, int hkv, int dh) {
+    return k_offset_in(kv, kv.page_table[slot >> kv.page_shift], slot, head, hkv, dh);
+}
+__device__ __forceinline__ size_t vt_offset(const KVCache &kv, int slot, int head, int hkv, int dh, int row) {
+    return vt_offset_in(kv, kv.page_table[slot >> kv.page_shift], slot, head, hkv, dh, row);
 }
 
 }  // namespace poss

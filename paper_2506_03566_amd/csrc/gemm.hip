@@ -588,21 +588,182 @@ __global__ __launch_bounds__(TALL_THREADS) void gemm_tall_kernel(
 }
 
 // ------------------------------------------------------------------------------------------
-// The QKV projection with its epilogue inside: K split INSIDE the workgroup.  One 32-column tile per workgroup, the
-// k-steps dealt to its four waves in contiguous quarters; a wave loads its own operands straight into registers (an A
-// fragment of v_mfma 16x16x32 is 16 contiguous bytes of one activation row, and with K split among the waves no two of
-// them want the same fragment: no LDS hop, no barrier in the loop).  The four partial tiles meet in LDS and are added
-// in wave order, so the workgroup holds finished sums and applies the rotary embedding and writes queries, keys and
-// values itself: no partial planes, no epilogue kernel.  The weight rows are packed so that the two 16-column tiles
-// of a wave are dims [16j, 16j+16) and [16j + dh/2, ..) of one head: a lane owns both members of a rotary pair.
+// The QKV projection with its epilogue inside: K split INSIDE the workgroup.  One 32-column tile per workgroup; a pair of waves owns a
+// K split - the very splits, and inside them the very order, of the streaming kernel.  Each brings half of the pair's operands into LDS
+// by LDS-direct loads, two k-steps a stage, NST stages in a ring: activations in whole 128-byte lines under the swizzle of
+// gemm_tall_kernel, weights as they are packed.  A pair's waves take half of the row tiles each (one row tile: of the columns).  The
+// partial tiles meet in LDS and are added in split order, so the workgroup holds finished sums and applies the rotary embedding and
+// writes queries, keys and values itself: no partial planes, no epilogue kernel.  The weight rows are packed so that the two 16-column
+// tiles of a group are dims [16j, 16j+16) and [16j + dh/2, ..) of one head: a lane owns both members of a rotary pair.
 // Bitwise repeatable; a row's result does not depend on the rows around it.
+// Every workgroup reads every row over the whole K, so it is for few rows or small matrices (QKV_FUSED_BYTES below).
+constexpr int QKV_MAX_SPLITS = 4;
+constexpr int QKV_STAGE_BYTES(int mt) { return (2 * mt + 2 * GEMM_NT) * 1024; }   // of one wave
 struct QkvEpi { const float2 *cs; const int32_t *slot; void *q; int hq, hkv, dh; RopeRanges rr; };
 
-template <typename T, int MT, int PF>
-__global__ __launch_bounds__(256) void gemm_qkv_rope_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx,
-                                                           int M, int K, int ksteps_total, QkvEpi e) {
+// What the epilogue needs of a lane's four rows (4 * (lane / 16) .. of row tile mt) besides their sums, for head gh and rotary pair i:
+// asked for ahead of the partial tiles' exchange, whatever the rows turn out to be (row by row, behind the branches on what a row is,
+// the same loads were a dependent trip to memory each).
+struct QkvRows { float2 cs[4]; int slot[4], page[4]; };
+__device__ __forceinline__ void qkv_rows(const QkvEpi &e, int gh, int i, int mt, int M, int lane, QkvRows &rows) {
+    const int half = e.dh >> 1, m0 = mt * 16 + 4 * (lane >> 4);
+    if (gh >= e.hq) {                                     // (workgroup-uniform)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) rows.slot[r] = e.slot[min(m0 + r, M - 1)];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) rows.cs[r] = e.cs[min(m0 + r, M - 1) * half + i];
+}
+__device__ __forceinline__ void qkv_pages(const QkvEpi &e, int gh, QkvRows &rows) {   // of their slots; the slots have to be there
+    if (gh >= e.hq) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)                       // (all ranges have one page table: ranges_ok)
+            rows.page[r] = e.rr.kv[0].page_table[rows.slot[r] >> e.rr.kv[0].page_shift];
+    }
+}
+// The finished sums x1, x2 of pair (i, i + dh / 2) of head gh for a lane's four rows, rotated and written.
+template <typename T>
+__device__ __forceinline__ void qkv_store(const QkvEpi &e, int gh, int i, int mt, int M, int lane, f32x4 x1, f32x4 x2, const QkvRows &rows) {
+    const int half = e.dh >> 1;
+    if (gh >= e.hq + 2 * e.hkv) return;                   // padding columns
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int m = mt * 16 + 4 * (lane >> 4) + r;
+        float o1, o2;
+        rope_pair(x1[r], x2[r], rows.cs[r], o1, o2);
+        for (int qi = 0; qi < e.rr.n; ++qi) {             // (workgroup-uniform) the sequences that share this launch
+            if (m < e.rr.r0[qi] || m >= e.rr.r1[qi] || m >= M) continue;
+            const KVCache &kv = e.rr.kv[qi];
+            if (gh < e.hq) {
+                if (m >= e.rr.rows_q[qi]) continue;
+                T *dst = static_cast<T *>(e.q) + ((size_t)m * e.hq + gh) * e.dh;
+                dst[i] = round_f<T>(o1);
+                dst[i + half] = round_f<T>(o2);
+            } else if (gh < e.hq + e.hkv) {
+                T *dst = static_cast<T *>(kv.k) + k_offset_in(kv, rows.page[r], rows.slot[r], gh - e.hq, e.hkv, e.dh);
+                dst[i] = round_f<T>(o1);
+                dst[i + half] = round_f<T>(o2);
+            } else {
+                T *dst = static_cast<T *>(kv.vt) + vt_offset_in(kv, rows.page[r], rows.slot[r], gh - e.hq - e.hkv, e.hkv, e.dh, i);
+                dst[0] = from_f<T>(x1[r]);
+                dst[(size_t)half << kv.page_shift] = from_f<T>(x2[r]);
+            }
+        }
+    }
+}
+// The partial tiles of S splits, red[split][row tile, column tile][64], added in split order (as sum_planes4 adds planes), rotated and
+// written.  D tile: lane -> column lane % 16, register r -> row 4 * (lane / 16) + r.  Wave w of n_waves finishes row tiles w, w + n_waves, ..,
+// the first of them with the rows it has been given.
+template <typename T, int MT>
+__device__ __forceinline__ void qkv_epilogue(const f32x4 *red, int S, int gh, int i, int M, int wave, int n_waves, int lane, const QkvEpi &e, QkvRows &rows) {
+    for (int mt = wave; mt < MT; mt += n_waves) {
+        if (mt != wave) {
+            qkv_rows(e, gh, i, mt, M, lane, rows);
+            qkv_pages(e, gh, rows);
+        }
+        f32x4 x1 = f32x4{0.f, 0.f, 0.f, 0.f}, x2 = x1;
+        for (int sp = 0; sp < S; ++sp) {
+            x1 += red[(sp * (MT * GEMM_NT) + mt * GEMM_NT) * 64 + lane];
+            x2 += red[(sp * (MT * GEMM_NT) + mt * GEMM_NT + 1) * 64 + lane];
+        }
+        qkv_store<T>(e, gh, i, mt, M, lane, x1, x2, rows);
+    }
+}
+
+template <typename T, int MT, int NST>
+__global__ __launch_bounds__(QKV_MAX_SPLITS * 128) void gemm_qkv_rope_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx,
+                                                                             int M, int K, int ksteps_total, QkvEpi e) {
+    typedef __attribute__((address_space(3))) void *LdsPtr;
     constexpr int NTILE = MT * GEMM_NT;
-    __shared__ f32x4 red[4][NTILE][64];
+    constexpr int XBLKS = 2 * MT, BLKS = XBLKS + 2 * GEMM_NT;        // 1 KB blocks of a stage (two k-steps): activations, then weights
+    constexpr int XPW = XBLKS / 2, LPW = BLKS / 2;                   // of which a wave of the pair loads half
+    constexpr int MTW = MT > 1 ? MT / 2 : 1, NTW = MT > 1 ? GEMM_NT : 1;   // what it multiplies: half of the row tiles (one row tile: of the columns)
+    static_assert(BLKS * 1024 == QKV_STAGE_BYTES(MT) && GEMM_NT == 2 && (MT == 1 || MT % 2 == 0) && KCS % 2 == 0, "two equal halves, whole stages");
+    extern __shared__ __attribute__((aligned(1024))) u32x4 qlds[];   // [split][NST][BLKS * 64]; at the end [split][NTILE][64] partial tiles
+    const int S = blockDim.x >> 7, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, tile = blockIdx.x;
+    const int split = wave >> 1, p = wave & 1, lr = lane & 15, lg = lane >> 4;
+    const int n_chunks = ksteps_total / KCS, k0 = split * n_chunks / S * KCS, n_st = ((split + 1) * n_chunks / S * KCS - k0) / 2;
+    const int n_most = (n_chunks + S - 1) / S * (KCS / 2);           // stages of the longest split
+    const u32x4 *w_src = Wp + ((size_t)tile * ksteps_total + k0) * (GEMM_NT * 64) + p * 64 + lane;
+    const T *x_row[XPW];                                  // load j: rows 8 (2 j + p) + lane / 8, eight lanes per row
+    int f_k[XPW];
+#pragma unroll
+    for (int j = 0; j < XPW; ++j) {
+        const int m = (2 * j + p) * 8 + (lane >> 3);
+        x_row[j] = X + (size_t)(m < M ? m : M - 1) * ldx;             // rows beyond M repeat the last (never stored)
+        f_k[j] = k0 * GEMM_KSTEP + ((lane & 7) ^ tall_x_swizzle(m & 15)) * 8;
+    }
+    const unsigned lds0 = (unsigned)(uintptr_t)(LdsPtr)qlds + (unsigned)(split * NST * BLKS * 1024 + p * 1024);
+    auto fetch = [&](int st) {
+        const unsigned base = lds0 + (unsigned)((st % NST) * BLKS * 1024);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) lds_dma16_nt(base + (XBLKS + 2 * i) * 1024, w_src + (size_t)(st * 2 + i) * (GEMM_NT * 64));
+#pragma unroll
+        for (int j = 0; j < XPW; ++j) {
+            const int k = f_k[j] + st * (2 * GEMM_KSTEP);             // beyond K (the packed weights are zero there): the row's first elements
+            lds_dma16(base + 2 * j * 1024, x_row[j] + (k < K ? k : 0));
+        }
+    };
+    f32x4 acc[MTW][NTW];
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int mt0 = MT > 1 ? p * MTW : 0, nt0 = MT > 1 ? 0 : p;
+    const u32x4 *xb = qlds + split * NST * BLKS * 64 + mt0 * 128 + lr * 8, *wb = qlds + (split * NST * BLKS + XBLKS + nt0) * 64 + lane;
+    const int swz = tall_x_swizzle(lr);
+#pragma unroll
+    for (int st = 0; st < NST - 1; ++st) if (st < n_st) fetch(st);
+    for (int st = 0; st < n_most; ++st) {
+        // the stage has landed once only the loads of the NST - 2 behind it are outstanding; behind the barrier its other half has,
+        // too, and every wave has read the stage before it for the last time
+        if (st + NST - 1 <= n_st) dma_wait<(NST - 2) * LPW>(); else dma_wait<0>();
+        __syncthreads();
+        if (st + NST - 1 < n_st) fetch(st + NST - 1);
+        if (st < n_st) {                                  // (wave-uniform)
+            const int at = (st % NST) * BLKS * 64;
+            u32x4 a[2][MTW], w[2][NTW];
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) {
+#pragma unroll
+                for (int nt = 0; nt < NTW; ++nt) w[ks][nt] = wb[at + (ks * GEMM_NT + nt) * 64];
+#pragma unroll
+                for (int mt = 0; mt < MTW; ++mt) a[ks][mt] = xb[at + mt * 128 + ((ks * 4 + lg) ^ swz)];
+            }
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+                for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+                    for (int nt = 0; nt < NTW; ++nt) acc[mt][nt] = Mfma<T>::run(a[ks][mt], w[ks][nt], acc[mt][nt]);
+        }
+    }
+    const int tph = e.dh >> 5, gh = tile / tph, pi = (tile % tph) * 16 + (lane & 15);   // 32-column tiles per head; the lane's pair
+    QkvRows rows;
+    if (wave < MT) {
+        qkv_rows(e, gh, pi, wave, M, lane, rows);
+        qkv_pages(e, gh, rows);
+    }
+    __syncthreads();                                      // every wave is done with its stages
+    f32x4 *red = reinterpret_cast<f32x4 *>(qlds);
+#pragma unroll
+    for (int mt = 0; mt < MTW; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) red[(split * NTILE + (mt0 + mt) * GEMM_NT + nt0 + nt) * 64 + lane] = acc[mt][nt];
+    __syncthreads();
+    qkv_epilogue<T, MT>(red, S, gh, pi, M, wave, 2 * S, lane, e, rows);
+}
+
+// One row tile and four splits (plain decoding and the first drafting passes at the 8B shape): a wave's operands straight into
+// registers, PF k-steps in flight (an A fragment of v_mfma 16x16x32 is 16 contiguous bytes of one activation row, and with K split
+// among the waves no two of them want the same fragment): no LDS hop, no barrier in the loop.  4096 -> 6144, us with the boundary to
+// the next launch, this kernel / the one above: 1 row 10.1 / 11.2, 10 rows 11.7 / 12.2; two row tiles of it, 20 rows 13.8 / 13.1,
+// 31 rows 16.1 / 14.0 (64-byte pieces of the rows).
+template <typename T, int PF>
+__global__ __launch_bounds__(256) void gemm_qkv_row_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx,
+                                                           int M, int K, int ksteps_total, QkvEpi e) {
+    constexpr int MT = 1, NTILE = GEMM_NT;
+    __shared__ f32x4 red[4 * NTILE * 64];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, tile = blockIdx.x;
     const int w0 = wave * ksteps_total / 4, w1 = (wave + 1) * ksteps_total / 4, n_w = w1 - w0;
     const u32x4 *wp = Wp + ((size_t)tile * ksteps_total + w0) * (GEMM_NT * 64) + lane;      // this wave's first k-step
@@ -667,49 +828,18 @@ __global__ __launch_bounds__(256) void gemm_qkv_rope_kernel(const u32x4 *__restr
             for (int nt = 0; nt < GEMM_NT; ++nt) acc[mt][nt] = Mfma<T>::run(a[mt], w[nt], acc[mt][nt]);
     }
 
+    const int tph = e.dh >> 5, gh = tile / tph, pi = (tile % tph) * 16 + (lane & 15);   // 32-column tiles per head; the lane's pair
+    QkvRows rows;
+    if (wave < MT) {
+        qkv_rows(e, gh, pi, wave, M, lane, rows);
+        qkv_pages(e, gh, rows);
+    }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < GEMM_NT; ++nt) red[wave][mt * GEMM_NT + nt][lane] = acc[mt][nt];
+        for (int nt = 0; nt < GEMM_NT; ++nt) red[(wave * NTILE + mt * GEMM_NT + nt) * 64 + lane] = acc[mt][nt];
     __syncthreads();
-    // D tile: lane -> column c = lane % 16, register r -> row 4 * (lane / 16) + r.  Wave w finishes row tiles w, w + 4.
-    const int half = e.dh >> 1, tph = half >> 4;          // 32-column tiles per head
-    const int gh = tile / tph, i = (tile % tph) * 16 + (lane & 15);
-    if (gh >= e.hq + 2 * e.hkv) return;                   // padding columns
-    T *q = static_cast<T *>(e.q);
-    for (int mt = wave; mt < MT; mt += 4) {
-        const f32x4 x1 = ((red[0][mt * GEMM_NT][lane] + red[1][mt * GEMM_NT][lane]) + red[2][mt * GEMM_NT][lane]) + red[3][mt * GEMM_NT][lane];
-        const f32x4 x2 = ((red[0][mt * GEMM_NT + 1][lane] + red[1][mt * GEMM_NT + 1][lane]) + red[2][mt * GEMM_NT + 1][lane]) + red[3][mt * GEMM_NT + 1][lane];
-        for (int qi = 0; qi < e.rr.n; ++qi) {             // (workgroup-uniform) the sequences that share this launch
-            const int r0 = e.rr.r0[qi], r1 = e.rr.r1[qi], rows_q = e.rr.rows_q[qi];
-            const KVCache kv = e.rr.kv[qi];
-            T *kc = static_cast<T *>(kv.k), *vc = static_cast<T *>(kv.vt);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int m = mt * 16 + 4 * (lane >> 4) + r;
-                if (m < r0 || m >= r1 || m >= M) continue;
-                const float a = x1[r], b = x2[r];
-                if (gh < e.hq) {
-                    if (m >= rows_q) continue;
-                    float o1, o2;
-                    rope_pair(a, b, e.cs[m * half + i], o1, o2);
-                    T *dst = q + ((size_t)m * e.hq + gh) * e.dh;
-                    dst[i] = round_f<T>(o1);
-                    dst[i + half] = round_f<T>(o2);
-                } else if (gh < e.hq + e.hkv) {
-                    float o1, o2;
-                    rope_pair(a, b, e.cs[m * half + i], o1, o2);
-                    T *dst = kc + k_offset(kv, e.slot[m], gh - e.hq, e.hkv, e.dh);
-                    dst[i] = round_f<T>(o1);
-                    dst[i + half] = round_f<T>(o2);
-                } else {
-                    const int vh = gh - e.hq - e.hkv, sl = e.slot[m];
-                    vc[vt_offset(kv, sl, vh, e.hkv, e.dh, i)] = from_f<T>(a);
-                    vc[vt_offset(kv, sl, vh, e.hkv, e.dh, i + half)] = from_f<T>(b);
-                }
-            }
-        }
-    }
+    qkv_epilogue<T, MT>(red, 4, gh, pi, M, wave, 4, lane, e, rows);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1171,28 +1301,45 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
     }
 }
 
+// Is the QKV projection one kernel?  Its workgroups, one per 32 columns, each read all rows over the whole K: these bytes, together,
+// are what it pays for the partial planes and the epilogue kernel that it saves (both kernels give the same bits).  Stream and
+// epilogue / one kernel, us with the boundaries between launches:
+//   4096 -> 6144 (4 splits)   20 rows (50 MB) 13.9 / 13.3, 31 rows (50 MB) 16.2 / 14.0, 47 rows (101 MB) 15.6 / 15.9, 61 rows 15.7 / 17.1
+//   5120 -> 15360 (2 splits)  1 row (79 MB) 28.3 / 26.6, 10 rows 28.4 / 26.7, 31 rows (157 MB) 30.0 / 32.0, 61 rows (315 MB) 32.1 / 42.0
+//   640 -> 1920 (1 split)     1 row 8.3 / 5.8, 10 rows 8.9 / 6.2, 31 rows 9.3 / 7.4, 61 rows (5 MB) 10.4 / 9.3
+//   512 -> 768 (1 split)      1 row 7.0 / 5.0, 10 rows 7.4 / 5.4, 31 rows 7.7 / 6.0, 61 rows (2 MB) 8.6 / 8.1
+constexpr size_t QKV_FUSED_BYTES = (size_t)80 << 20;
+static bool qkv_fused(const GemmShape &g) {
+    return g.Mpad <= 64 && g.S <= QKV_MAX_SPLITS && (size_t)(g.Npad / (GEMM_NT * 16)) * g.Mpad * g.K * 2 <= QKV_FUSED_BYTES;
+}
+
 // The QKV projection of 16-bit types: one kernel, rotary embedding and cache writes included.
 template <typename T>
 static void launch_qkv_rope_t(const GemmShape &g, const void *Wp, const void *X, int ldx, const EpiArgs &epi, const RopeRanges &rr,
                               hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
     QkvEpi qe{epi.cs, epi.slot, epi.q, epi.hq, epi.hkv, epi.dh, rr};
-    dim3 grid(g.Npad / (GEMM_NT * 16)), block(256);
+    dim3 grid(g.Npad / (GEMM_NT * 16)), block(g.S * 128);
     const int ksteps = g.Kpad / GEMM_KSTEP;
     const u32x4 *w = static_cast<const u32x4 *>(Wp);
     const T *x = static_cast<const T *>(X);
-#define POSS_QKV_LAUNCH(MT, PFV)                                                                              \
+#define POSS_QKV_LAUNCH(MT, NST)                                                                              \
     do {                                                                                                      \
+        const size_t lds = (size_t)g.S * NST * QKV_STAGE_BYTES(MT);                                           \
         if (ev_start && ev_stop)                                                                              \
-            hipExtLaunchKernelGGL((gemm_qkv_rope_kernel<T, MT, PFV>), grid, block, 0, st, ev_start, ev_stop, 0, w, x, ldx, g.M, g.K, ksteps, qe); \
+            hipExtLaunchKernelGGL((gemm_qkv_rope_kernel<T, MT, NST>), grid, block, lds, st, ev_start, ev_stop, 0, w, x, ldx, g.M, g.K, ksteps, qe); \
         else                                                                                                  \
-            hipLaunchKernelGGL((gemm_qkv_rope_kernel<T, MT, PFV>), grid, block, 0, st, w, x, ldx, g.M, g.K, ksteps, qe); \
+            hipLaunchKernelGGL((gemm_qkv_rope_kernel<T, MT, NST>), grid, block, lds, st, w, x, ldx, g.M, g.K, ksteps, qe); \
     } while (0)
     switch (g.Mpad / 16) {
-        case 1: POSS_QKV_LAUNCH(1, 8); break;
-        case 2: POSS_QKV_LAUNCH(2, 8); break;
-        case 4: POSS_QKV_LAUNCH(4, 8); break;
-        case 6: POSS_QKV_LAUNCH(6, 4); break;
-        default: POSS_QKV_LAUNCH(8, 4); break;
+        case 1:
+            if (g.S != 4 || ksteps % 32) { POSS_QKV_LAUNCH(1, 6); break; }
+            if (ev_start && ev_stop)
+                hipExtLaunchKernelGGL((gemm_qkv_row_kernel<T, 8>), grid, dim3(256), 0, st, ev_start, ev_stop, 0, w, x, ldx, g.M, g.K, ksteps, qe);
+            else
+                hipLaunchKernelGGL((gemm_qkv_row_kernel<T, 8>), grid, dim3(256), 0, st, w, x, ldx, g.M, g.K, ksteps, qe);
+            break;
+        case 2: POSS_QKV_LAUNCH(2, 5); break;
+        default: POSS_QKV_LAUNCH(4, 3); break;
     }
 #undef POSS_QKV_LAUNCH
 }
@@ -1200,13 +1347,7 @@ static void launch_qkv_rope_t(const GemmShape &g, const void *Wp, const void *X,
 template <typename T>
 static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int ldx, float *part,
                           const EpiArgs &epi, float eps, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop, const RopeRanges *rr) {
-    // The QKV projection of at most 32 rows (draft passes, plain decoding) runs as one kernel with the K split inside the
-    // workgroup; with more rows that kernel's activation traffic (every workgroup reads every row over the whole K)
-    // outweighs the partial planes and the epilogue kernel it saves: 25 us against 13.6 + 4.9 us at 61 rows of the 8B shape.
-    // It is used only where its four waves own exactly the four splits the streaming kernel would take (four splits, chunk
-    // count a multiple of four) and adds them in the same order: a row then gets bit for bit the same sums from either
-    // kernel, whatever the number of rows that share its launch.
-    if (epi.mode == EPI_ROPE_KV && g.Mpad <= 32 && g.S == 4 && (g.Kpad / GEMM_KCHUNK) % 4 == 0) {
+    if (epi.mode == EPI_ROPE_KV && qkv_fused(g)) {
         launch_qkv_rope_t<T>(g, Wp, X, ldx, epi, *rr, st, ev_start, ev_stop);
         return;
     }
@@ -1306,7 +1447,7 @@ static bool gemm_args_ok(const GemmShape &g, const void *Wp, const void *X, cons
     if (!Wp || !X || !part || g.M < 1 || g.M > LAUNCH_ROWS || g.S < 1) return false;
     switch (e.mode) {
         case EPI_PLAIN: return e.out || g.S == 1;          // unsplit: plane 0 is the result
-        case EPI_ROPE_KV: return e.q && e.cs && e.slot && (e.dh == 64 || e.dh == 128 || !e.dh);   // caches: checked per range
+        case EPI_ROPE_KV: return e.q && e.cs && e.slot && (e.dh == 64 || e.dh == 128);   // caches: checked per range
         case EPI_RESIDUAL: return e.h && (!e.gain || e.u);
         case EPI_SILU: return e.act != nullptr;
         case EPI_HEAD:
@@ -1317,16 +1458,16 @@ static bool gemm_args_ok(const GemmShape &g, const void *Wp, const void *X, cons
     }
 }
 
-static bool ranges_ok(const GemmShape &g, const EpiArgs &epi, RopeRanges &rr) {
+static bool ranges_ok(const GemmShape &g, RopeRanges &rr) {
     if (rr.n < 1 || rr.n > ROPE_MAX_RANGES) return false;
     int blocks = 0;
     for (int i = 0; i < rr.n; ++i) {
         if (rr.r0[i] < 0 || rr.r1[i] > g.M || rr.r0[i] >= rr.r1[i]) return false;
         if (!rr.kv[i].k || !rr.kv[i].vt || !rr.kv[i].page_table) return false;
+        if (rr.kv[i].page_table != rr.kv[0].page_table || rr.kv[i].page_shift != rr.kv[0].page_shift) return false;   // a context has one
         rr.blk0[i] = blocks;
         blocks += (rr.r1[i] - rr.r0[i] + EPI_ROWS_PAIR - 1) / EPI_ROWS_PAIR;
     }
-    (void)epi;
     return true;
 }
 
@@ -1338,7 +1479,7 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
     if (epi.mode == EPI_ROPE_KV) {
         if (ranges) rr = *ranges;
         else { rr.n = 1; rr.r0[0] = 0; rr.r1[0] = g.M; rr.rows_q[0] = epi.rows_q; rr.kv[0] = epi.kv; }
-        if (!ranges_ok(g, epi, rr)) return false;
+        if (!ranges_ok(g, rr)) return false;
     }
     if (dt == DT_F32) {
         if (epi.mode == EPI_HEAD) return false;          // float32 storage reduces its logits with the two-stage kernels

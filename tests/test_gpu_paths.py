@@ -134,3 +134,26 @@ def test_keys_do_not_hang_on_how_many_rows_share_the_projection(name):
         for other in got[1:]:
             assert np.array_equal(got[0][0], other[0]) and np.array_equal(got[0][1], other[1]), seed
     pair.close()
+
+
+# K splits of the QKV projection: one (512, 640 - a last chunk that is half padding), two (1024; 1192 - uneven, K ends inside a k-step),
+# three (1536), four (2048; 1800); both head widths
+@pytest.mark.parametrize("name,d_model,head_dim", [("t_mid_bf16", 512, 64), ("t_mid_f16", 640, 128), ("t_mid_bf16", 1024, 128),
+                                                   ("t_mid_f16", 1192, 64), ("t_mid_bf16", 1536, 64), ("t_mid_f16", 2048, 64),
+                                                   ("t_mid_bf16", 1800, 128)])
+def test_projection_with_its_epilogue_inside_gives_the_streaming_kernels_bits(name, d_model, head_dim):
+    """Keys and values of a prompt's first rows: up to 64 rows in a launch by the one-kernel form (row tiles of 16, 32 and 64 rows),
+    120 rows by the streaming kernel and its epilogue; the same bits."""
+    print(f"qkv {name} d_model={d_model} head_dim={head_dim}", flush=True)
+    pair = Pair(name, n_layers=1, d_model=d_model, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ffn=256, vocab=300, n_specialists=1,
+                positions_per_specialist=6)
+    prompt = np.random.default_rng(d_model).integers(0, pair.cfg.vocab, 120).astype(np.int32)
+    pair.ctx.prefill(prompt)
+    want_k, want_v = pair.ctx.debug_read_kv(-1, 0, 0, 64)
+    assert np.abs(want_k).max() > 0 and np.abs(want_v).max() > 0
+    for n in (1, 15, 16, 17, 31, 32, 33, 47, 49, 63, 64):
+        pair.ctx.reset()
+        pair.ctx.prefill(prompt[:n])
+        k, v = pair.ctx.debug_read_kv(-1, 0, 0, n)
+        assert np.array_equal(k, want_k[:n]) and np.array_equal(v, want_v[:n]), n
+    pair.close()
