@@ -1061,21 +1061,34 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
 // one row, and the four MFMAs of a k-step take one of them each, the same permutation of k on both sides - and the four
 // partial tiles are added in wave order.  F32_PF k-steps are in flight.  A row's sums depend on K alone.
 // 64 x 768 x 256: 36.7 -> 3.7 us, 4 x 256 x 256: 46.7 -> 4.0 us (before: one thread per output, walking k and a row of W of
-// its own); 128 x 1700 x 2400 by 32 x 32 tiles: 26 us (40 TFLOP/s).
-constexpr int F32_PF = 4, F32_KSTEP = 16;
+// its own); 128 x 1700 x 2400 by 32 x 32 tiles: 26 us (40 TFLOP/s).  (8 and 16 waves, 2 to 8 k-steps in flight: within 0.3 us.)
+// EPI (NT = 2): the sums are whole, so the epilogue of gate and up (columns 32 b .. are the gates of 16 units, the next 16 their ups)
+// or of the QKV projection (columns of 16 rotary pairs of a head: dims 16 j .. and their partners, dh / 2 further) is applied to them
+// here, in the operations and the order of the kernels that do it to planes: one launch of 4.4 us instead of 3.8 + 2.9 for gate and up,
+// 5.8 instead of 4.0 + 4.4 for QKV (its slots and pages are a chain of three loads), and a boundary between launches less.  A request
+// of the 256 wide shape (prompt and first round, with topk_row_kernel): 773 -> 667 us, 163 -> 134 launches.
+constexpr int F32_WAVES = 4, F32_PF = 4, F32_KSTEP = 16;
+struct F32Epi { float *act; int F; QkvEpi qkv; };
 
-template <int MT, int NT, bool VEC>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__ W, const float *__restrict__ X, int ldx,
-                                                       float *__restrict__ out, int ld_out, int M, int N, int K) {
-    __shared__ f32x4 red[4][MT * NT][64];
+template <int MT, int NT, bool VEC, int EPI>
+__global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(const float *__restrict__ W, const float *__restrict__ X, int ldx,
+                                                                  float *__restrict__ out, int ld_out, int M, int N, int K, F32Epi epi) {
+    static_assert(EPI == EPI_PLAIN || NT == 2, "a lane holds both columns of a pair");
+    __shared__ f32x4 red[F32_WAVES][MT * NT][64];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
-    const int m0 = blockIdx.y * (16 * MT), n0 = blockIdx.x * (16 * NT);
+    const int m0 = blockIdx.y * (16 * MT), half = epi.qkv.dh >> 1;
+    const int n0 = EPI == EPI_ROPE_KV ? (int)blockIdx.x / (half >> 4) * epi.qkv.dh + (int)blockIdx.x % (half >> 4) * 16
+                                      : (int)blockIdx.x * (16 * NT);
+    const int n_step = EPI == EPI_ROPE_KV ? half : 16;    // from a column tile to the next
     const float *xp[MT], *wp[NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) xp[mt] = X + (size_t)min(m0 + mt * 16 + lr, M - 1) * ldx;    // rows and columns beyond the
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) wp[nt] = W + (size_t)min(n0 + nt * 16 + lr, N - 1) * K;      // matrix repeat the last (never stored)
-    const int n_ks = (K + F32_KSTEP - 1) / F32_KSTEP, k0 = wave * n_ks / 4, k1 = (wave + 1) * n_ks / 4;
+    for (int nt = 0; nt < NT; ++nt) wp[nt] = W + (size_t)min(n0 + nt * n_step + lr, N - 1) * K;   // matrix repeat the last (never stored)
+    QkvRows rows;
+    if constexpr (EPI == EPI_ROPE_KV)
+        if (wave < MT) qkv_rows(epi.qkv, n0 / epi.qkv.dh, n0 % epi.qkv.dh + lr, m0 / 16 + wave, M, lane, rows);
+    const int n_ks = (K + F32_KSTEP - 1) / F32_KSTEP, k0 = wave * n_ks / F32_WAVES, k1 = (wave + 1) * n_ks / F32_WAVES;
     auto load = [&](const float *row, int ks) {           // four k of this lane; zero beyond K, and from k1 on
         const int k = ks * F32_KSTEP + lg * 4;
         f32x4 v = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -1119,6 +1132,8 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
                     for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[p][mt][j], fb[p][nt][j], acc[mt][nt], 0, 0, 0);
     };
     fetch(k0, a[0], b[0]);
+    if constexpr (EPI == EPI_ROPE_KV)
+        if (wave < MT) qkv_pages(epi.qkv, n0 / epi.qkv.dh, rows);
     for (int ks = k0; ks < k1; ks += 2 * F32_PF) {        // (a k-step beyond k1 is all zeros: it changes no sum)
         fetch(ks + F32_PF, a[1], b[1]);
         multiply(a[0], b[0]);
@@ -1131,8 +1146,33 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) red[wave][mt * NT + nt][lane] = acc[mt][nt];
     __syncthreads();
-    for (int t = wave; t < MT * NT; t += 4) {             // D tile: lane -> column lane % 16, register r -> row 4 * (lane / 16) + r
-        const f32x4 v = ((red[0][t][lane] + red[1][t][lane]) + red[2][t][lane]) + red[3][t][lane];
+    auto sum_of = [&](int t) {
+        f32x4 v = red[0][t][lane];
+#pragma unroll
+        for (int w = 1; w < F32_WAVES; ++w) v += red[w][t][lane];
+        return v;
+    };
+    if constexpr (EPI == EPI_SILU) {
+        if (wave >= MT) return;
+        const f32x4 g = sum_of(wave * NT);
+        const f32x4 up = sum_of(wave * NT + 1);
+        const int f = blockIdx.x * 16 + lr;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = m0 + wave * 16 + lg * 4 + r;
+            if (m < M && f < epi.F) epi.act[(size_t)m * epi.F + f] = mul_round<float>(g[r] / (1.0f + expf(-g[r])), up[r]);
+        }
+        return;
+    }
+    if constexpr (EPI == EPI_ROPE_KV) {
+        if (wave >= MT) return;
+        const f32x4 a = sum_of(wave * NT);
+        const f32x4 b = sum_of(wave * NT + 1);
+        qkv_store<float>(epi.qkv, n0 / epi.qkv.dh, n0 % epi.qkv.dh + lr, m0 / 16 + wave, M, lane, a, b, rows);
+        return;
+    }
+    for (int t = wave; t < MT * NT; t += F32_WAVES) {     // D tile: lane -> column lane % 16, register r -> row 4 * (lane / 16) + r
+        const f32x4 v = sum_of(t);
         const int n = n0 + (t % NT) * 16 + lr;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
@@ -1143,18 +1183,20 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(const float *__restrict__
 }
 
 // Two row tiles and two column tiles per workgroup where there are rows for it (half the operand traffic of 16 x 16).
-static void launch_gemm_f32(const float *W, const float *X, int ldx, float *out, int ld_out, int M, int N, int K, hipStream_t st,
+template <int EPI>
+static void launch_gemm_f32(const float *W, const float *X, int ldx, float *out, int ld_out, int M, int N, int K, const F32Epi &epi, hipStream_t st,
                             hipEvent_t ev_start, hipEvent_t ev_stop) {
     const bool vec = K % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
+    constexpr int NT1 = EPI == EPI_PLAIN ? 1 : 2;
 #define POSS_F32(MT, NT, VEC)                                                                                              \
     do {                                                                                                                   \
-        dim3 grid((N + 16 * NT - 1) / (16 * NT), (M + 16 * MT - 1) / (16 * MT)), block(256);                               \
+        dim3 grid((N + 16 * NT - 1) / (16 * NT), (M + 16 * MT - 1) / (16 * MT)), block(F32_WAVES * 64);                    \
         if (ev_start && ev_stop)                                                                                           \
-            hipExtLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC>), grid, block, 0, st, ev_start, ev_stop, 0, W, X, ldx, out, ld_out, M, N, K); \
+            hipExtLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC, EPI>), grid, block, 0, st, ev_start, ev_stop, 0, W, X, ldx, out, ld_out, M, N, K, epi); \
         else                                                                                                               \
-            hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC>), grid, block, 0, st, W, X, ldx, out, ld_out, M, N, K);        \
+            hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC, EPI>), grid, block, 0, st, W, X, ldx, out, ld_out, M, N, K, epi); \
     } while (0)
-    if (M <= 16 || (size_t)M * N < 64 * 1024) { if (vec) POSS_F32(1, 1, true); else POSS_F32(1, 1, false); }
+    if (M <= 16 || (size_t)M * N < 64 * 1024) { if (vec) POSS_F32(1, NT1, true); else POSS_F32(1, NT1, false); }
     else { if (vec) POSS_F32(2, 2, true); else POSS_F32(2, 2, false); }
 #undef POSS_F32
 }
@@ -1487,17 +1529,20 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
         const size_t out_bytes = ((size_t)(g.M - 1) * epi.ld_out + g.N) * sizeof(float);
         const bool direct = epi.mode == EPI_PLAIN && epi.out && !overlap(epi.out, out_bytes, X, ((size_t)(g.M - 1) * ldx + g.K) * sizeof(float)) &&
                             !overlap(epi.out, out_bytes, Wp, (size_t)g.N * g.K * sizeof(float));
-        launch_gemm_f32(static_cast<const float *>(Wp), static_cast<const float *>(X), ldx, direct ? epi.out : part,
-                        direct ? epi.ld_out : g.Npad, g.M, g.N, g.K, st, ev_start, ev_stop);
-        if (direct) return true;
-        if (epi.mode == EPI_ROPE_KV) {                   // rotary + cache writes per row range, one launch
-            const size_t plane = (size_t)g.Mpad * g.Npad;
-            int blocks = rr.blk0[rr.n - 1] + (rr.r1[rr.n - 1] - rr.r0[rr.n - 1] + EPI_ROWS_PAIR - 1) / EPI_ROWS_PAIR;
-            dim3 egrid(g.Npad / GEMM_BLOCK_N, blocks), eb(ROPE_THREADS);
-            hipLaunchKernelGGL((epilogue_rope_ranges_kernel<float>), egrid, eb, 0, st, part, plane, g.S, g.Npad, rr, epi);
-        } else {
-            launch_epilogue_t<float>(g, part, epi, eps, false, st);
+        const float *w = static_cast<const float *>(Wp), *x = static_cast<const float *>(X);
+        F32Epi fe{};
+        if (epi.mode == EPI_SILU) {
+            fe.act = static_cast<float *>(epi.act); fe.F = epi.F;
+            launch_gemm_f32<EPI_SILU>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+            return true;
         }
+        if (epi.mode == EPI_ROPE_KV) {
+            fe.qkv = QkvEpi{epi.cs, epi.slot, epi.q, epi.hq, epi.hkv, epi.dh, rr};
+            launch_gemm_f32<EPI_ROPE_KV>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+            return true;
+        }
+        launch_gemm_f32<EPI_PLAIN>(w, x, ldx, direct ? epi.out : part, direct ? epi.ld_out : g.Npad, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+        if (!direct) launch_epilogue_t<float>(g, part, epi, eps, false, st);
     } else if (dt == DT_BF16) {
         launch_gemm_t<bf16_t>(g, Wp, X, ldx, part, epi, eps, st, ev_start, ev_stop, epi.mode == EPI_ROPE_KV ? &rr : nullptr);
     } else {

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 if have_gpu():
     import torch
     import paper_2506_03566_amd as P
-    from synth import make_prompt
+    from synth import get_config, make_prompt, make_weights
     from synth.gpu import to_device
 
 
@@ -42,4 +42,53 @@ def test_f32_attention_head_sizes_and_key_counts(head_dim, n_prompt):
     pair.ctx.verify_tree(P.TreeArrays.from_lists(*tree), logits_out=logits)
     _, want, _ = o.verify_tree(Tree(*tree))
     assert np.abs(logits.cpu().numpy() - want).max() <= tol_for(cfg)
+    pair.close()
+
+
+# rows around a row tile and the change to two tiles by two (64 K sums); d_ffn that ends inside a group of 16 units, odd (scalar loads
+# in the down projection); both head widths, K above and below what four waves keep in flight
+@pytest.mark.parametrize("over", [dict(d_model=256, n_kv_heads=2, d_ffn=333), dict(d_model=72, n_q_heads=3, n_kv_heads=1, head_dim=128, d_ffn=17),
+                                  dict(d_model=600, n_q_heads=6, n_kv_heads=3, d_ffn=1030)])
+def test_f32_rows_do_not_hang_on_the_rows_around_them(over):
+    """SiLU, rotary embedding and cache writes inside the products: the first layer's keys and values of a prompt's first rows are the
+    same bits for any number of rows in the launch (later layers follow the attention, whose threads share out all the keys of the
+    launch), the logits behind the last layer the oracle's."""
+    print(f"f32 layers {over}", flush=True)
+    pair = Pair("c0_tiny_f32", **over)
+    cfg, prompt = pair.cfg, make_prompt(pair.cfg, n=120)
+    pair.ctx.prefill(prompt)
+    want = pair.ctx.debug_read_kv(-1, 0, 0, 120)
+    from oracle.tree import Tree
+    for n in (1, 2, 15, 16, 17, 33, 64, 65, 100):
+        pair.ctx.reset()
+        o = pair.oracle()
+        o.prefill(prompt[:n])
+        assert pair.ctx.prefill(prompt[:n]) == o.tokens[-1]
+        for got, whole in zip(pair.ctx.debug_read_kv(-1, 0, 0, n), want):
+            assert np.array_equal(got, whole[:n]), n
+        tree = ([o.tokens[-1], 5, 6, 7], [-1, 0, 0, 1])
+        logits = torch.zeros(4, cfg.vocab, device="cuda")
+        pair.ctx.verify_tree(P.TreeArrays.from_lists(*tree), logits_out=logits)
+        assert np.abs(logits.cpu().numpy() - o.verify_tree(Tree(*tree))[1]).max() <= tol_for(cfg), n
+    pair.close()
+
+
+# fewer ids than threads, around them, the last count of one launch and the first of two; 5 children: the third pair of equals is cut
+@pytest.mark.parametrize("vocab,k", [(17, 16), (200, 5), (255, 5), (257, 16), (4095, 5), (4096, 16), (4097, 5)])
+def test_f32_children_with_equal_logits(vocab, k):
+    """Every even id's row of the head matrix is also the next odd id's: the k best of pairs of equal logits, lower ids first."""
+    print(f"f32 children vocab={vocab} k={k}", flush=True)
+    over = dict(vocab=vocab, top_k=k, depth=1, total_tokens=k, n_layers=1, n_specialists=1, positions_per_specialist=1, d_model=64,
+                n_q_heads=1, n_kv_heads=1, d_ffn=64)
+    st = make_weights(get_config("c0_tiny_f32", **over))
+    st["lm_head"][1::2] = st["lm_head"][:vocab - 1:2][:len(st["lm_head"][1::2])]
+    pair = Pair("c0_tiny_f32", storage=st, **over)
+    prompt = make_prompt(pair.cfg, n=20)
+    o = pair.oracle()
+    o.prefill(prompt)
+    pair.ctx.prefill(prompt)
+    o.tokens[-1] = int(pair.ctx.tokens()[-1])
+    got, want = pair.ctx.draft_tree().as_dict(), o.draft_tree()
+    assert got["token"] == want.token and got["parent"] == want.parent
+    assert np.abs(np.array(got["score"]) - np.array(want.score)).max() <= 1e-4
     pair.close()
