@@ -43,16 +43,19 @@ struct BlockGeom {
     float *part;
 };
 
+template <int TM, int TN, int NST> constexpr int BLOCK_LDS_UNITS = NST * (TM + TN) / 16 * 64;   // 16 bytes each
+
+// One workgroup's tile: number bid of the tiles of g.
 template <typename T, int TM, int TN, int WM, int WN, int NST, int EPI>
-__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx,
-                                                                    BlockGeom g, EpiArgs e) {
+__device__ __forceinline__ void gemm_block_body(u32x4 *__restrict__ xs, const int bid, const u32x4 *__restrict__ Wp, const T *__restrict__ X,
+                                                int ldx, const BlockGeom &g, const EpiArgs &e) {
     typedef __attribute__((address_space(3))) void *LdsPtr;
     constexpr int WAVES = WM * WN, MTW = TM / (16 * WM), NTW = TN / (16 * WN);
     constexpr int XB = TM / 16, WB = TN / 16;                             // 1 KB operand blocks of a stage
     constexpr int XPW = XB / WAVES, WPW = WB / WAVES, LPS = XPW + WPW;    // loads of a wave per stage
     constexpr int STAGE_UNITS = (XB + WB) * 64;
     static_assert(XPW * WAVES == XB && WPW * WAVES == WB && NTW % 2 == 0 && NTW <= MTW && LPS <= MTW && NST >= 3, "tile shape");
-    __shared__ __attribute__((aligned(1024))) u32x4 xs[NST * STAGE_UNITS];
+    static_assert(NST * STAGE_UNITS == BLOCK_LDS_UNITS<TM, TN, NST>, "what the caller provides");
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int wm = wave % WM, wn = wave / WM;
 
@@ -60,8 +63,8 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
     // the ~32 it works on at a time are about 8 row tiles x 4 column tiles and share their operands in its L2.
     int id;
     {
-        const int n = g.tiles_m * g.tiles_n, q = n >> 3, r = n & 7, x = (int)blockIdx.x & 7;
-        id = x * q + (x < r ? x : r) + ((int)blockIdx.x >> 3);
+        const int n = g.tiles_m * g.tiles_n, q = n >> 3, r = n & 7, x = bid & 7;
+        id = x * q + (x < r ? x : r) + (bid >> 3);
     }
     constexpr int GM = 2048 / TM;
     const int grp = id / (GM * g.tiles_n), in_grp = id - grp * (GM * g.tiles_n);
@@ -231,6 +234,25 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
     dma_wait<0>();                                        // the stages nobody reads: LDS must not be given back before they land
 }
 
+template <typename T, int TM, int TN, int WM, int WN, int NST, int EPI>
+__global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx,
+                                                                    BlockGeom g, EpiArgs e) {
+    __shared__ __attribute__((aligned(1024))) u32x4 xs[BLOCK_LDS_UNITS<TM, TN, NST>];
+    gemm_block_body<T, TM, TN, WM, WN, NST, EPI>(xs, blockIdx.x, Wp, X, ldx, g, e);
+}
+
+// Two tile shapes in one launch: whole rounds of 256 x 256 tiles (the columns of g), then 256 x 128 tiles for the columns that are
+// left (those of rest), which the CUs take up as they become free.  A row's sums are the same either way.
+template <typename T, int EPI>
+__global__ __launch_bounds__(512, 2) void gemm_block_mixed_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx, BlockGeom g,
+                                                                 BlockGeom rest, EpiArgs e) {
+    __shared__ __attribute__((aligned(1024))) u32x4 xs[BLOCK_LDS_UNITS<256, 256, 5>];
+    static_assert(BLOCK_LDS_UNITS<256, 256, 5> >= BLOCK_LDS_UNITS<256, 128, 6>, "both shapes fit");
+    const int first = g.tiles_m * g.tiles_n;
+    if ((int)blockIdx.x < first) gemm_block_body<T, 256, 256, 2, 4, 5, EPI>(xs, blockIdx.x, Wp, X, ldx, g, e);
+    else gemm_block_body<T, 256, 128, 4, 2, 6, EPI>(xs, (int)blockIdx.x - first, Wp, X, ldx, rest, e);
+}
+
 // ------------------------------------------------------------------------------------------
 // Tile shapes: 256 x 256 (eight waves of 128 x 64, five stages), 256 x 128 (eight of 64 x 64, six) and 128 x 128 (four waves, five
 // stages, two workgroups per CU).  Measured (bf16, us and TFLOP/s):
@@ -246,12 +268,27 @@ __global__ __launch_bounds__(WM * WN * 64, 2) void gemm_block_kernel(const u32x4
 // one round of 256 x 256 (109 us at K = 4096): 256 x 128: 56 / 109 with the chip not full, 65 / 109 with it; 128 x 128: 40 / 109
 // for up to one tile per CU, 68 / 109 for two.
 static int block_tiles(int M, int cols, int tm, int tn) { return ((M + tm - 1) / tm) * ((cols + tn - 1) / tn); }
+// Column tiles of 256 that fill whole rounds of the chip, with something left over: the fourth choice (gemm_block_mixed_kernel) is 256 x
+// 256 tiles for these columns and 256 x 128 for the rest, where the last round would be less than about half full.  4096 x 6144 (K =
+// 4096): 226 -> 195 us; a prompt through four layers, us, best single shape / so: 8B 1200 tokens 2757 / 2684, 3500 tokens 6607 / 6368,
+// 8192 tokens 15690 / 15455; 13B 600 tokens 2640 / 2480, 4096 tokens 11920 / 11240.  With a few tiles left over there is little to gain
+// (3000 tokens of 13B, 16 of 1296: 8030 / 8100), hence the 4 %: such a round has the chip's power to itself.
+static int block_whole_rounds(int M, int cols) {
+    const int rounds = block_tiles(M, cols, 256, 256) / 256, n = rounds * 256 / ((M + 255) / 256);
+    return rounds > 0 && n * 256 < cols ? n : 0;
+}
 static int block_tile(int M, int cols, int *cost = nullptr) {
     const int t0 = block_tiles(M, cols, 256, 256), t1 = block_tiles(M, cols, 256, 128), t2 = block_tiles(M, cols, 128, 128), rest = t2 % 512;
-    const int c0 = (t0 + 255) / 256 * 100, c1 = t1 <= 256 ? 58 : (t1 + 255) / 256 * 65;
+    const auto rounds_1 = [](int t) { return t <= 256 ? 58 : (t + 255) / 256 * 65; };
+    const int c0 = (t0 + 255) / 256 * 100, c1 = rounds_1(t1);
     const int c2 = t2 / 512 * 68 + (rest == 0 ? 0 : rest <= 256 ? 40 : 68);
-    const int tile = c0 <= c1 && c0 <= c2 ? 0 : c1 <= c2 ? 1 : 2;
-    if (cost) *cost = tile == 0 ? c0 : tile == 1 ? c1 : c2;
+    int tile = c0 <= c1 && c0 <= c2 ? 0 : c1 <= c2 ? 1 : 2, c = tile == 0 ? c0 : tile == 1 ? c1 : c2;
+    if (const int whole = block_whole_rounds(M, cols)) {
+        const int c3 = t0 / 256 * 100 + rounds_1(block_tiles(M, cols - whole * 256, 256, 128));
+        // (a round of 256 x 256 tiles that is nearly empty takes 79)
+        if (c3 * 1.04 < (tile == 0 ? c0 - 21 * (256 - t0 % 256) / 256 : c)) { tile = 3; c = c3; }
+    }
+    if (cost) *cost = c;
     return tile;
 }
 
@@ -274,7 +311,18 @@ static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, 
         POSS_BLOCK(256, 256, 2, 4, 5);                    // gemm_block_splits() counts on it
     } else {
         const int tile = block_tile(g.M, cols);
-        if (tile == 0) POSS_BLOCK(256, 256, 2, 4, 5);
+        if (tile == 3) {
+            BlockGeom rest = g;
+            g.tiles_m = rest.tiles_m = (g.M + 255) / 256;
+            g.tiles_n = block_whole_rounds(g.M, cols);
+            rest.col0 += g.tiles_n * 256;
+            rest.tiles_n = (g.N - rest.col0 + 127) / 128;
+            dim3 grid(g.tiles_m * (g.tiles_n + rest.tiles_n)), block(512);
+            if (ev_start && ev_stop)
+                hipExtLaunchKernelGGL((gemm_block_mixed_kernel<T, EPI>), grid, block, 0, st, ev_start, ev_stop, 0, w, x, ldx, g, rest, e);
+            else
+                hipLaunchKernelGGL((gemm_block_mixed_kernel<T, EPI>), grid, block, 0, st, w, x, ldx, g, rest, e);
+        } else if (tile == 0) POSS_BLOCK(256, 256, 2, 4, 5);
         else if (tile == 1) POSS_BLOCK(256, 128, 4, 2, 6);
         else POSS_BLOCK(128, 128, 2, 2, 5);
     }

@@ -157,3 +157,23 @@ def test_profile_counts_the_products_of_a_long_prompt():
     assert nbytes == 2 * (cfg.n_layers * d * (2 * qd + 2 * kd + 3 * ffn) + cfg.vocab * d + cfg.n_specialists * d * (2 * d + 2 * kd))
     assert 0 < ms < 100
     pair.close()
+
+
+# 4096 rows: 16 row tiles, 18 or 17 column tiles of 256 - one round of the larger tiles, then 64 or 32 of the smaller.  QKV (the rest: values), gate and
+# up, the residual projections (whose sums must not be split over K: K below 2048 or few columns)
+@pytest.mark.parametrize("name,over", [("t_mid_bf16", dict(n_layers=1, d_model=128, n_q_heads=28, n_kv_heads=4, d_ffn=512)),
+                                       ("t_mid_f16", dict(n_layers=2, d_model=128, n_q_heads=2, n_kv_heads=2, d_ffn=2176)),
+                                       ("t_mid_f16", dict(n_layers=2, d_model=4344, n_q_heads=2, n_kv_heads=2, d_ffn=520))])
+def test_two_tile_shapes_in_one_launch_give_the_bits_of_one(name, over):
+    """Keys and values of a prompt's first 600 rows: 4096 rows take both tile shapes in one launch, 600 rows one; the same bits."""
+    print(f"mixed tiles {name} {over}", flush=True)
+    pair = Pair(name, head_dim=128, vocab=300, n_specialists=1, positions_per_specialist=6, max_seq=4224, **over)
+    prompt = np.random.default_rng(7).integers(0, 300, 4096).astype(np.int32)
+    got = []
+    for n in (600, 4096):
+        pair.ctx.reset()
+        pair.ctx.prefill(prompt[:n])
+        got.append([pair.ctx.debug_read_kv(-1, layer, 0, 600) for layer in range(pair.cfg.n_layers)])
+    for few, many in zip(*got):
+        assert np.abs(few[0]).max() > 0 and np.array_equal(few[0], many[0]) and np.array_equal(few[1], many[1])
+    pair.close()
