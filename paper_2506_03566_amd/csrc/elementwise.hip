@@ -304,11 +304,11 @@ bool launch_sample(const float *logits, int ld, int rows, int vocab, float tempe
 // so all that follows keeps it: block sums by wave_sum; a scan over the shares of 1024 "threads" (ceil(blocks / 1024) blocks each),
 // 64 at a time, the sixteen totals added one after the other; the drafter's total over its row by the same 1024 threads.
 // Two launches over the whole chip (draw_max_kernel, draw_mass_kernel) leave, per row, the maximum, the masses and the block
-// sums; a draw is one wave's work, with the sixteen scans in registers: no barriers, one trip to memory, and a drawn id changes
-// one scan.  Ten children of ten rows of 128256: 79.5 -> 41.6 us, the two launches of 10 us included (before: one workgroup per row made every pass over it and
-// every step of a draw was a workgroup's).
+// sums; a draw is one wave's work: no barriers, one trip to memory for all draws as a rule, and a drawn id changes
+// one scan.  Ten children of ten rows of 128256: 21.8 us (31 with scans and shares in registers, a trip to memory a draw and scans
+// by shuffles), and 10 for the two launches.  It is a serial chain: about 3500 cycles a draw, of which the two scans are 800.
 constexpr int DRAW_THREADS = 1024, DRAW_BLOCK = 256, DRAW_MAX_BLOCKS = 8192, DRAW_SEG = 4096;
-constexpr int DRAW_UNROLL = 4, DRAW_WAVES = DRAW_THREADS / 64;
+constexpr int DRAW_UNROLL = 4, DRAW_WAVES = DRAW_THREADS / 64, DRAW_MAX_K = 16;
 typedef float f32x4e __attribute__((ext_vector_type(4)));
 
 static inline int draw_blocks(int vocab) { return (vocab + DRAW_BLOCK - 1) / DRAW_BLOCK; }
@@ -432,17 +432,34 @@ __device__ __forceinline__ int find_block(DrawLds &L, int nblk, float u, float *
     return L.i[1] < 0 ? 0 : L.i[1];
 }
 
+// Inclusive scan of non-negative values over a wave: for o = 1, 2, .. 32, v[l] += v[l - o] where there is such a lane (0 elsewhere, which
+// adds nothing).  Up to 8 lanes by DPP (wave_shr:1, o times), 16 and 32 by the row swaps: about 350 cycles; six shuffles through the LDS
+// crossbar took 1000 in these kernels.
+__device__ __forceinline__ float wave_shr1(float x) { return dpp<0x138>(0.f, x); }
+__device__ __forceinline__ float wave_scan(float v) {
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        float t = v;
+#pragma unroll
+        for (int i = 0; i < o; ++i) t = wave_shr1(t);
+        v += t;
+    }
+    float lo, hi, lo2, hi2;
+    swap16(v, lo, hi);                                    // rows (0 0 2 2) and (1 1 3 3)
+    swap32(hi, lo2, hi2);                                 // lo2: row 1 everywhere
+    v += lane < 16 ? 0.f : (lane >> 4) == 2 ? lo2 : lo;
+    swap32(v, lo, hi);
+    v += lane < 32 ? 0.f : lo;
+    return v;
+}
+
 // By one wave: the id inside block b at which the cumulative mass (m: the lane's four ids, in id order) exceeds `rest`; with
 // take_last or nothing crossing, the last id with mass (the block's first if none has any).
 __device__ __forceinline__ int pick_in_block(int b, float rest, bool take_last, f32x4e m) {
     const int lane = threadIdx.x & 63;
     const float ls = ((m[0] + m[1]) + m[2]) + m[3];
-    float incl = ls;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const float t = __shfl_up(incl, o, 64);
-        if (lane >= o) incl += t;
-    }
+    const float incl = wave_scan(ls);
     const float prev = incl - ls;                         // (exclusive prefix of this lane)
     int last = -1;
 #pragma unroll
@@ -484,61 +501,105 @@ __device__ __forceinline__ f32x4e load_masses(const float *mass, int ld, int b, 
 __global__ __launch_bounds__(DRAW_THREADS) void sample_children_kernel(const float *__restrict__ logits, int ld, int vocab, int nblk, int k,
                                                                        float inv_t, DrawMasses dm, const float *__restrict__ u,
                                                                        int32_t *__restrict__ out_id, float *__restrict__ out_logp) {
+    typedef __attribute__((address_space(3))) void *LdsPtr;
     __shared__ float bsum[DRAW_MAX_BLOCKS];
     __shared__ float red[17];
+    __shared__ float scans[DRAW_THREADS];
+    __shared__ __attribute__((aligned(1024))) float fetched[DRAW_MAX_K][DRAW_BLOCK];
     const int rowi = blockIdx.x, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const float *mass = dm.mass + (size_t)rowi * ld;
     const int per = (nblk + DRAW_THREADS - 1) / DRAW_THREADS;
     if (wave == 0) {
         const float uu = lane < k ? u[rowi * k + lane] : 0.f, mx = dm.mx[rowi];
-        for (int b = lane; b < nblk; b += 64) bsum[b] = dm.bsum[(size_t)rowi * nblk + b];
+        for (int b0 = lane; b0 < nblk; b0 += 64 * 8) {    // (eight at a time on their way)
+            float t[8];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) t[x] = dm.bsum[(size_t)rowi * nblk + min(b0 + 64 * x, nblk - 1)];
+#pragma unroll
+            for (int x = 0; x < 8; ++x) if (b0 + 64 * x < nblk) bsum[b0 + 64 * x] = t[x];
+        }
         wave_lds_sync();
-        // share t = blocks [t per, (t + 1) per); lane l of scan w has share 64 w + l: sh its sum, sc the inclusive scan over the 64
+        // share t = blocks [t per, (t + 1) per); scan w is over the shares 64 w ..: scans[] holds them, lane w of `totals` the total of
+        // scan w, lane w of `ends` the sum of the totals up to and with it.  (Scans behind the last block hold nothing.  Scans and
+        // shares in registers, sixteen of each, meant sixteen copies of the code of every step, the sixteen scans of the start 22 K cycles
+        // of 65 K, mostly for fetching it.)
+        const int n_w = (nblk + per * 64 - 1) / (per * 64);
         auto share = [&](int t) {
+            if (per == 1) return t < nblk ? bsum[t] : 0.f;
             float s = 0.f;
             for (int b = t * per; b < min(nblk, (t + 1) * per); ++b) s += bsum[b];
             return s;
         };
-        auto scan = [&](float v) {
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const float t = __shfl_up(v, o, 64);
-                if (lane >= o) v += t;
-            }
-            return v;
+        float totals = 0.f, ends = 0.f;
+        auto scan_shares = [&](int w) {
+            const float sc = wave_scan(share(w * 64 + lane));
+            scans[w * 64 + lane] = sc;
+            const float all = lane_value(sc, 63);
+            if (lane == w) totals = all;
         };
-        float sh[DRAW_WAVES], sc[DRAW_WAVES];
+        auto add_totals = [&]() {                         // one after the other
+            float sum = 0.f;
+            for (int w0 = 0; w0 < n_w; w0 += 4)
 #pragma unroll
-        for (int w = 0; w < DRAW_WAVES; ++w) { sh[w] = share(w * 64 + lane); sc[w] = scan(sh[w]); }
+                for (int w = 0; w < 4; ++w) {
+                    sum += lane_value(totals, w0 + w);
+                    if (lane == w0 + w) ends = sum;
+                }
+            return sum;
+        };
+        for (int w = 0; w < n_w; ++w) scan_shares(w);
+        wave_lds_sync();
+        float total = add_totals();
+        const float log_z = logf(total);                  // the normaliser of the full distribution
+        // The blocks that the draws would come from if none took anything out, fetched in one trip (a draw from elsewhere makes a trip of
+        // its own): of the first share whose inclusive prefix exceeds lane j's target; one block per share up to DRAW_THREADS blocks.
+        int guess = 0;
+        {
+            const float aim = uu * total;
+            float before = 0.f;
+            int w = 0;
+            for (int x = 0; x < n_w - 1; ++x) {
+                const float end = lane_value(ends, x);
+                if (end <= aim) { w = x + 1; before = end; }
+            }
+            guess = w * 64;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) if (scans[guess + o - 1] + before <= aim) guess += o;
+            guess = min(guess * per, nblk - 1);
+        }
+        const unsigned lds0 = (unsigned)(uintptr_t)(LdsPtr)&fetched[0][0];
+        for (int j = 0; j < k; ++j) {
+            const int id0 = __builtin_amdgcn_readlane(guess, j) * DRAW_BLOCK + lane * 4;
+            lds_dma16(lds0 + j * (DRAW_BLOCK * 4), mass + (id0 + 3 < ld ? id0 : 0));
+        }
+        dma_wait<0>();
+        wave_lds_sync();
         int mine = 0;                                     // lane j < k: the j-th id drawn
-        float log_z = 0.f;
         for (int d = 0; d < k; ++d) {
-            float off[DRAW_WAVES + 1];
-            off[0] = 0.f;
-#pragma unroll
-            for (int w = 0; w < DRAW_WAVES; ++w) off[w + 1] = off[w] + lane_value(sc[w], 63);
-            const float total = off[DRAW_WAVES], target = lane_value(uu, d) * total;
-            if (d == 0) log_z = logf(total);              // the normaliser of the full distribution
+            if (d > 0) total = add_totals();
+            const float target = lane_value(uu, d) * total;
             // the scan that holds the target, the share inside it, the block inside the share
-            int b = -1, w_hit = -1;
+            int b = -1;
             float before = -INFINITY;
-#pragma unroll
-            for (int w = 0; w < DRAW_WAVES; ++w) {
-                if (w_hit >= 0 || !(off[w] <= target && target < off[w + 1])) continue;      // (wave-uniform)
-                const float incl = sc[w] + off[w];
-                float prev = __shfl_up(incl, 1, 64);
-                if (lane == 0) prev = off[w];
-                const unsigned long long hit = __ballot(sh[w] > 0.f && prev <= target && target < incl);
-                if (!hit) continue;
-                w_hit = w;
-                const int l = __ffsll((long long)hit) - 1, t = w * 64 + l;
-                before = lane_value(prev, l);
-                int last_mass = -1;
-                for (int x = t * per; x < min(nblk, (t + 1) * per); ++x) if (bsum[x] > 0.f) last_mass = x;
-                for (int x = t * per; x < min(nblk, (t + 1) * per); ++x) {
-                    const float m = bsum[x];
-                    if (m > 0.f && (before + m > target || x == last_mass)) { b = x; break; }
-                    before += m;
+            const int w = __popcll(__ballot(lane < n_w && ends <= target));
+            if (w < n_w) {
+                const float start = w ? lane_value(ends, w - 1) : 0.f;
+                const float incl = scans[w * 64 + lane] + start, prev = lane ? scans[w * 64 + max(lane, 1) - 1] + start : start;
+                const unsigned long long hit = __ballot(share(w * 64 + lane) > 0.f && prev <= target && target < incl);
+                if (hit) {
+                    const int l = __ffsll((long long)hit) - 1, t = w * 64 + l;
+                    before = lane_value(prev, l);
+                    if (per == 1) {                       // its mass is above 0
+                        b = t;
+                    } else {
+                        int last_mass = -1;
+                        for (int x = t * per; x < min(nblk, (t + 1) * per); ++x) if (bsum[x] > 0.f) last_mass = x;
+                        for (int x = t * per; x < min(nblk, (t + 1) * per); ++x) {
+                            const float m = bsum[x];
+                            if (m > 0.f && (before + m > target || x == last_mass)) { b = x; break; }
+                            before += m;
+                        }
+                    }
                 }
             }
             if (b < 0) {                                  // rounding pushed the target past the total: the last block with mass
@@ -549,27 +610,35 @@ __global__ __launch_bounds__(DRAW_THREADS) void sample_children_kernel(const flo
                 for (int o = 32; o > 0; o >>= 1) last = max(last, __shfl_xor(last, o, 64));
                 b = last;
             }
-            f32x4e m = load_masses(mass, ld, b, lane);    // without the ids already drawn
+            b = __builtin_amdgcn_readfirstlane(b);
+            // its masses without the ids already drawn: they are taken out of the fetched copy as they are drawn
+            const unsigned long long at = __ballot(lane < k && guess == b);
+            const int slot = at ? __ffsll((long long)at) - 1 : -1;
+            f32x4e m;
             const int id0 = b * DRAW_BLOCK + lane * 4;
-            for (int j = 0; j < d; ++j) {
-                const int r = __builtin_amdgcn_readlane(mine, j) - id0;
+            if (slot >= 0) {
+                m = *reinterpret_cast<const f32x4e *>(&fetched[slot][lane * 4]);
+                if (id0 + 3 >= ld) m = f32x4e{0.f, 0.f, 0.f, 0.f};
+            } else {
+                m = load_masses(mass, ld, b, lane);
+                for (int j = 0; j < d; ++j) {
+                    const int r = __builtin_amdgcn_readlane(mine, j) - id0;
 #pragma unroll
-                for (int x = 0; x < 4; ++x) if (r == x) m[x] = 0.f;
+                    for (int x = 0; x < 4; ++x) if (r == x) m[x] = 0.f;
+                }
             }
             const int c = pick_in_block(b, target - before, before == -INFINITY, m);
             if (lane == d) mine = c;
 #pragma unroll
             for (int x = 0; x < 4; ++x) if (c - id0 == x) m[x] = 0.f;
             const float s = wave_sum(((m[0] + m[1]) + m[2]) + m[3]);      // the block's mass without the id just drawn, formed afresh
-            if (lane == 0) bsum[b] = s;
+            if (lane == 0) {
+                bsum[b] = s;
+                if (slot >= 0) fetched[slot][c - b * DRAW_BLOCK] = 0.f;      // (c lies in block b)
+            }
             wave_lds_sync();
-            const int t = b / per;
-#pragma unroll
-            for (int w = 0; w < DRAW_WAVES; ++w)
-                if (t >> 6 == w) {                        // (wave-uniform)
-                    if (lane == (t & 63)) sh[w] = share(t);
-                    sc[w] = scan(sh[w]);
-                }
+            scan_shares((per == 1 ? b : b / per) >> 6);
+            wave_lds_sync();
         }
         if (lane < k) {
             out_id[rowi * k + lane] = mine;

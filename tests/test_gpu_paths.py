@@ -157,3 +157,35 @@ def test_projection_with_its_epilogue_inside_gives_the_streaming_kernels_bits(na
         k, v = pair.ctx.debug_read_kv(-1, 0, 0, n)
         assert np.array_equal(k, want_k[:n]) and np.array_equal(v, want_v[:n]), n
     pair.close()
+
+
+# equal numbers land in one block until its ids are gone; sharp distributions move every later target to a block that was not fetched ahead;
+# the last two: one id holds nearly all the mass, and two blocks per share of the scan
+@pytest.mark.parametrize("vocab,temperature,number", [(4100, 0.8, 0.5), (4100, 0.05, None), (70001, 0.1, 0.3), (128256, 0.02, None), (262401, 0.1, None)])
+def test_draws_from_blocks_that_were_not_expected(vocab, temperature, number):
+    """Children of the root against the float64 inverse CDF of what the earlier draws left (3e-5 of the interval, as above)."""
+    print(f"draws from {vocab} ids at {temperature}", flush=True)
+    pair = Pair("c0_tiny_f32", vocab=vocab, d_model=64, n_q_heads=1, n_kv_heads=1, d_ffn=64, n_layers=1, n_specialists=1,
+                positions_per_specialist=1, depth=1, top_k=7, total_tokens=7)       # (every child is in the tree, in the order of the draws)
+    cfg, ctx, k = pair.cfg, pair.ctx, pair.cfg.top_k
+    ctx.prefill(make_prompt(cfg, n=12))
+    ctx.set_sampling(temperature, np.zeros(cfg.depth + 1, np.float32))
+    for seed in range(4):
+        rng = np.random.default_rng(seed)
+        UD = (rng.random((cfg.depth, k, k)) * 0.999).astype(np.float32)
+        if number is not None:
+            UD[:] = number
+        ctx.set_draft_sampling(UD, (rng.random((cfg.depth + 1, k + 1)) * 0.999).astype(np.float32))
+        d = ctx.draft_tree().as_dict()
+        root = [i for i in range(1, d["n"]) if d["parent"][i] == 0]
+        left = softmax_t(ctx.debug_draft_logits(0, 1)[0].cpu().numpy().astype(np.float64), temperature)
+        for j, node in enumerate(root):
+            c = d["token"][node]
+            if left.sum() < 1e-6:                          # what is left is the rounding of a float32 sum
+                break
+            cdf = np.cumsum(left) / left.sum()
+            lo, hi = (cdf[c - 1] if c else 0.0), cdf[c]
+            assert lo - 3e-5 <= float(UD[0, 0, j]) < hi + 3e-5, (seed, j, c, lo, hi)
+            left[c] = 0.0
+        assert len(root) == k
+    pair.close()
