@@ -119,7 +119,7 @@ def test_many_rows_are_the_streaming_kernels_whatever_the_matrix_size(dtype, N, 
 
 @pytest.mark.parametrize("name", ["t_mid_bf16", "t_mid_f16"])
 def test_keys_do_not_hang_on_how_many_rows_share_the_projection(name):
-    """d_model 2048: up to 32 rows take the QKV kernel with the rotary embedding inside, more take the streaming kernel and its
+    """d_model 2048: up to 64 rows take the QKV kernel with the rotary embedding inside, more take the streaming kernel and its
     epilogue.  The first 30 tokens' keys and values of the first layer are the same bits either way (31 thousand keys a prompt: a
     rotation that one of them rounds once and the other twice, in fp16, shows in a few of them)."""
     pair = Pair(name, n_layers=1, d_model=2048, n_q_heads=8, n_kv_heads=8, head_dim=128, d_ffn=256, vocab=1000, n_specialists=1,
