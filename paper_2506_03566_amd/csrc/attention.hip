@@ -15,6 +15,7 @@
 // into LDS (LDS-direct loads), swizzled so that operand reads run at the full LDS rate.
 // Softmax is online (running max / sum per query row, float32); partial (max, sum, O) per split
 // are merged by a second kernel in fixed order.
+#include "attn_split.h"
 #include "device_utils.h"
 
 #include <type_traits>
@@ -988,7 +989,7 @@ __global__ __launch_bounds__(WALK_THREADS) void attn_walk_batch_kernel(AttnSeqs 
 // the (max, sum) pairs.  Four times 61 rows of the 8B shape, four
 // splits: 9.5 -> 5.9 us; 61 rows: 4.6 -> 4.5 (before: a workgroup per (row, head),
 // a column per lane).
-constexpr int ATTN_MAX_SPLITS = 256, MERGE_THREADS = 256;
+constexpr int MERGE_THREADS = 256;
 template <typename T, int NR>
 __global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(AttnSeqs seqs, int hq, int hkv, int dh, T *__restrict__ out) {
     struct __attribute__((aligned(8))) Quad { T t[4]; };
@@ -1124,27 +1125,6 @@ __global__ __launch_bounds__(AF32_THREADS) void attn_f32_kernel(const float *__r
     }
 }
 
-// Blocks of 32 keys per split.  A workgroup walks its blocks one after the other, each a dependent trip
-// to memory, so a short context is still cut into about four pieces of >= 4 blocks (the merge kernel
-// costs less than the serial walk it replaces); long contexts walk 32 blocks per workgroup.  The rule looks at the committed
-// prefix only, never at the number of rows or the size of the tree region: a row's arithmetic (which keys
-// meet in which split, in which order) is then the same whether it is verified alone or among 60 others,
-// which is what makes the speculative stream reproduce the one-token-at-a-time stream bit for bit as long
-// as only bonus tokens are committed.  keys_per_split > 0 overrides.
-// keys_per_split < 0: the rule above with splits of at most -keys_per_split keys (the specialists' passes carry few
-// rows, so that only a few dozen workgroups exist per split level: at long contexts they want shorter walks than the
-// target's passes; the drafter's caches are its own, so its rule need not match the target's).
-constexpr int ATTN_MAX_BPS = 64;                         // blocks per split the kernel can address (one page-table entry per lane)
-static int blocks_per_split(int n_prefix, int keys_per_split) {
-    if (keys_per_split > 0) return keys_per_split >= 32 ? (keys_per_split / 32 < ATTN_MAX_BPS ? keys_per_split / 32 : ATTN_MAX_BPS) : 1;
-    const int prefix_blocks = (n_prefix + 31) / 32;
-    int bps = (prefix_blocks + 3) / 4;
-    if (bps < 4) bps = 4;
-    const int cap = keys_per_split < 0 && -keys_per_split >= 128 ? -keys_per_split / 32 : 32;
-    if (bps > cap) bps = cap;
-    return bps;
-}
-
 // Launch shape of one sequence's attention: the split rule, key-ways and row tiles per wave.
 // Key-ways follow the split size (so, like it, the committed prefix only); the number of row tiles per wave may follow
 // the row count: it does not change any row's arithmetic.
@@ -1156,8 +1136,7 @@ static AttnShape attention_shape(const ModelDims &md, int rows, int n_prefix, in
     const int tiles = (rows * G + 15) / 16;
     a.rho_pad = tiles * 16;
     const int n_blocks = (n_prefix + region_len + 31) / 32;
-    a.bps = blocks_per_split(n_prefix, keys_per_split);
-    while ((n_blocks + a.bps - 1) / a.bps > ATTN_MAX_SPLITS) a.bps *= 2;     // only with a tiny split override on a very long context
+    a.bps = attn_blocks_per_split(n_prefix, n_blocks, keys_per_split);
     a.n_splits = (n_blocks + a.bps - 1) / a.bps;
     a.kw = a.bps >= 4 ? 2 : 1;
     a.walk = md.dt == DT_BF16 && a.bps >= WALK_MIN_BPS;

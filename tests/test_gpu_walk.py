@@ -82,3 +82,23 @@ def test_long_walk_is_the_short_one(name, prompts, rows, over):
 ])
 def test_prompts_of_other_head_groups(name, n_prompt, over):
     check_prompt(name, n_prompt, over)
+
+
+def test_splits_of_a_very_long_context_stay_within_what_a_wave_can_address():
+    """271000 tokens in splits of 1056 keys would be 257 splits: they become splits of 2048 keys (64 blocks, a page-table entry per lane),
+    not of 2112.  The same bits as 2048 keys asked for; one KV head, reversed pages."""
+    over = dict(n_layers=1, n_q_heads=2, n_kv_heads=1, d_model=128, d_ffn=64, vocab=300, max_seq=271360, kv_page_order=1, n_specialists=1,
+                positions_per_specialist=6)
+    print("walk over 271000 tokens", flush=True)
+    pair = Pair("t_mid_bf16", **over)
+    tree = _tree(9, 300, 0)
+    out = []
+    for keys in (2048, 1056):
+        pair.ctx.reset()
+        pair.ctx.prefill(np.random.default_rng(3).integers(0, 300, 271000).astype(np.int32))
+        pair.ctx.set_tuning(0, keys)
+        feats = torch.zeros(9, 128, dtype=torch.float32, device="cuda")
+        pair.ctx.verify_tree(tree, feat_out=feats)
+        out.append(feats.cpu().numpy())
+    pair.close()
+    assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
