@@ -22,6 +22,8 @@
 
 namespace poss {
 
+static_assert(ATTN_MAX_REGION == MAX_ROWS, "a region's slots are the rows of one sequence in a pass");
+
 typedef float  f32x4 __attribute__((ext_vector_type(4)));
 typedef float  f32x16 __attribute__((ext_vector_type(16)));
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
@@ -1136,7 +1138,7 @@ static AttnShape attention_shape(const ModelDims &md, int rows, int n_prefix, in
     const int tiles = (rows * G + 15) / 16;
     a.rho_pad = tiles * 16;
     const int n_blocks = (n_prefix + region_len + 31) / 32;
-    a.bps = attn_blocks_per_split(n_prefix, n_blocks, keys_per_split);
+    a.bps = attn_blocks_per_split(n_prefix, keys_per_split);
     a.n_splits = (n_blocks + a.bps - 1) / a.bps;
     a.kw = a.bps >= 4 ? 2 : 1;
     a.walk = md.dt == DT_BF16 && a.bps >= WALK_MIN_BPS;

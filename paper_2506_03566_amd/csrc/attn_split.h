@@ -5,6 +5,7 @@ namespace poss {
 
 constexpr int ATTN_MAX_BPS = 64;                         // blocks per split the kernels can address (one page-table entry per lane)
 constexpr int ATTN_MAX_SPLITS = 256;
+constexpr int ATTN_MAX_REGION = 128;                     // slots behind the prefix that a pass sees at most (a row's mask)
 
 // Blocks of 32 keys per split.  A workgroup walks its blocks one after the other, each a dependent trip
 // to memory, so a short context is still cut into about four pieces of >= 4 blocks (the merge kernel
@@ -16,9 +17,10 @@ constexpr int ATTN_MAX_SPLITS = 256;
 // keys_per_split < 0: the rule above with splits of at most -keys_per_split keys (the specialists' passes carry few
 // rows, so that only a few dozen workgroups exist per split level: at long contexts they want shorter walks than the
 // target's passes; the drafter's caches are its own, so its rule need not match the target's).
-// At most ATTN_MAX_SPLITS splits over n_blocks blocks (small splits on a very long context are doubled until they are that few);
+// At most ATTN_MAX_SPLITS splits, whatever the region (small splits on a very long context are doubled until they are that few);
 // ATTN_MAX_SPLITS of ATTN_MAX_BPS blocks are 524288 keys, more than a context can hold.
-static inline int attn_blocks_per_split(int n_prefix, int n_blocks, int keys_per_split) {
+static inline int attn_blocks_per_split(int n_prefix, int keys_per_split) {
+    const int n_blocks = (n_prefix + ATTN_MAX_REGION + 31) / 32;
     int bps;
     if (keys_per_split > 0) {
         bps = keys_per_split >= 32 ? keys_per_split / 32 : 1;
