@@ -160,17 +160,20 @@ __global__ __launch_bounds__(256) void topk_seg_kernel(const float *__restrict__
     }
 }
 
-// Both stages of a row that 256 threads can hold, NV values each: one launch, no records (4 rows of 4096 logits: 12.1 us for the
-// two stages and the boundary between them, 6.1 so).
-template <int NV>
+// Both stages of a row that 256 threads can hold, 2 NH values each: one launch, no records (4 rows of 4096 logits: 12.1 us for the
+// two stages and the boundary between them, 6.0 so).  The exponentials are summed per TOPK_SEG ids, against those ids' maximum,
+// and the two sums merged, in the operations and the order of the two stages: a score is the same bits either way.
+template <int NH>
 __global__ __launch_bounds__(256) void topk_row_kernel(const float *__restrict__ logits, int ld, int vocab, int k,
                                                        int32_t *__restrict__ out_id, float *__restrict__ out_logp) {
+    static_assert(NH * 256 == TOPK_SEG, "a half is a segment");
+    constexpr int NV = 2 * NH;
     __shared__ TopkLds lds;
-    __shared__ float red[17];
-    const int row = blockIdx.x;
+    __shared__ float red[2][4];
+    const int row = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float *src = logits + (size_t)row * ld;
     float v[NV]; int id[NV];
-    float mx = -INFINITY;
+    float mx[2] = {-INFINITY, -INFINITY};
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
         const int i = threadIdx.x + j * 256;
@@ -178,16 +181,31 @@ __global__ __launch_bounds__(256) void topk_row_kernel(const float *__restrict__
         const float x = src[ok ? i : 0];
         v[j] = ok ? x : -INFINITY;
         id[j] = ok ? i : 0x7fffffff - j;                  // distinct dummies keep "indices are unique" true
-        mx = fmaxf(mx, v[j]);
+        mx[j / NH] = fmaxf(mx[j / NH], v[j]);
     }
-    mx = wave_max(mx);
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mx;
-    __syncthreads();
-    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    float se = 0.f;
+    auto exchange = [&](float (&a)[2], auto combine) {    // of the four waves' values, in wave order
+        __syncthreads();                                  // (red may still be read)
+        if (lane == 0) { red[0][wave] = a[0]; red[1][wave] = a[1]; }
+        __syncthreads();
 #pragma unroll
-    for (int j = 0; j < NV; ++j) se += v[j] > -INFINITY ? expf(v[j] - mx) : 0.f;
-    const float lse = mx + logf(block_sum(se, red));
+        for (int s = 0; s < 2; ++s) a[s] = combine(combine(combine(red[s][0], red[s][1]), red[s][2]), red[s][3]);
+    };
+    mx[0] = wave_max(mx[0]); mx[1] = wave_max(mx[1]);
+    exchange(mx, [](float a, float b) { return fmaxf(a, b); });
+    float se[2] = {0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < NV; ++j) se[j / NH] += v[j] > -INFINITY ? expf(v[j] - mx[j / NH]) : 0.f;
+    se[0] = wave_sum(se[0]); se[1] = wave_sum(se[1]);
+    exchange(se, [](float a, float b) { return a + b; });
+    const float m = fmaxf(mx[0], mx[1]);
+    float all = 0.f;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        float w = mx[s] > -INFINITY ? se[s] * expf(mx[s] - m) : 0.f;
+        asm("" : "+v"(w));                                // (rounded before it is added)
+        all += w;
+    }
+    const float lse = m + logf(all);
     float ov; int oi;
     block_topk<NV>(v, id, k, lds, ov, oi);
     if ((int)threadIdx.x < k) {
@@ -341,8 +359,8 @@ void launch_topk_merge(const float *seg_records, int n_seg, int rows, int k, int
 
 void launch_topk_logsoftmax(const float *logits, int ld, int rows, int vocab, int k, float *seg_scratch,
                             int32_t *out_id, float *out_logp, hipStream_t st) {
-    if (vocab <= 256 * 16) {
-        hipLaunchKernelGGL((topk_row_kernel<16>), dim3(rows), dim3(256), 0, st, logits, ld, vocab, k, out_id, out_logp);
+    if (vocab <= 2 * TOPK_SEG) {
+        hipLaunchKernelGGL((topk_row_kernel<TOPK_SEG / 256>), dim3(rows), dim3(256), 0, st, logits, ld, vocab, k, out_id, out_logp);
         return;
     }
     const int n_seg = (vocab + TOPK_SEG - 1) / TOPK_SEG;

@@ -92,3 +92,34 @@ def test_f32_children_with_equal_logits(vocab, k):
     assert got["token"] == want.token and got["parent"] == want.parent
     assert np.abs(np.array(got["score"]) - np.array(want.score)).max() <= 1e-4
     pair.close()
+
+
+# one id beyond the first half of a row, in between, and the most that one launch takes
+@pytest.mark.parametrize("vocab", [2049, 3000, 4096])
+def test_f32_scores_are_those_of_the_two_launches(vocab):
+    """Children's scores are bit for bit what they are with ids that have no mass behind the vocabulary: 4200 ids take two launches, which
+    sum 2048 ids each and merge the sums.  Feature 0 is about 8 in every row; ids without mass have logits of about -1600."""
+    print(f"f32 scores vocab={vocab}", flush=True)
+    over = dict(top_k=16, depth=1, total_tokens=16, n_layers=1, n_specialists=1, positions_per_specialist=1, d_model=64, n_q_heads=1,
+                n_kv_heads=1, d_ffn=64)
+    st = make_weights(get_config("c0_tiny_f32", vocab=4200, **over))
+    st["embed"][:, 0] = 1
+    st["spec0.fc_w"][0, 0] = 1
+    st["lm_head"] *= 100
+    st["lm_head"][:, 0] = -1.2                             # (log-sum-exp near 0, where its unit in the last place is small)
+    st["lm_head"][vocab:] = 0
+    st["lm_head"][vocab:, 0] = -200
+    got = []
+    for v in (vocab, 4200):
+        pair = Pair("c0_tiny_f32", storage=dict(st, embed=st["embed"][:v].copy(), lm_head=st["lm_head"][:v].copy()), vocab=v, **over)
+        out = []
+        for seed in range(64):
+            pair.ctx.reset()
+            pair.ctx.prefill(np.random.default_rng(seed).integers(0, vocab, 20).astype(np.int32))
+            d = pair.ctx.draft_tree().as_dict()
+            out.append((d["token"], d["score"]))
+        got.append(out)
+        pair.close()
+    differ = [seed for seed, (a, b) in enumerate(zip(*got)) if a[0] != b[0] or not np.array_equal(a[1], b[1])]
+    print(f"  scores {got[0][0][1][1]:.3f} .. {got[0][0][1][-1]:.3f}, {len(differ)} of 64 prompts differ", flush=True)
+    assert max(max(t) for t, _ in got[1]) < vocab and not differ
