@@ -68,7 +68,7 @@ typedef struct poss_ctx poss_ctx;           /* opaque; created by poss_load, hos
  * dtype is the storage type of weights, GEMM operands and KV caches; accumulation,
  * the residual stream, softmax, norms and logits are float32. */
 typedef struct poss_config {
-    int32_t n_layers, d_model, n_q_heads, n_kv_heads, head_dim, d_ffn, vocab;
+    int32_t n_layers, d_model, n_q_heads, n_kv_heads, head_dim, d_ffn, vocab;   /* head_dim: 64 or 128; float32: multiples of 32 up to 256 */
     float   rms_eps, rope_theta;
     int32_t dtype;                           /* POSS_DTYPE_*                               */
     int32_t n_specialists, positions_per_specialist, fc_bias;

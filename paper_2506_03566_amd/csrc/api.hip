@@ -143,7 +143,8 @@ const char *check_config(const poss_config &c) {
     if (c.n_q_heads % c.n_kv_heads) return "n_q_heads must be a multiple of n_kv_heads";
     if (c.dtype != POSS_DTYPE_F32 && c.head_dim != 64 && c.head_dim != 128)
         return "16-bit kernels support head_dim 64 or 128";
-    if (c.head_dim < 2 || c.head_dim > 256 || (c.head_dim & 1)) return "head_dim must be even and <= 256";
+    if (c.dtype == POSS_DTYPE_F32 && (c.head_dim < 32 || c.head_dim > 256 || c.head_dim % 32))
+        return "float32 kernels support head_dim in multiples of 32 up to 256";
     if (c.dtype != POSS_DTYPE_F32 && ((c.d_model % 8) || (c.d_ffn % 8))) return "16-bit kernels need d_model, d_ffn multiples of 8";
     if (c.n_specialists < 1 || c.positions_per_specialist < 1) return "need at least one specialist and one position each";
     if (c.top_k < 1 || c.top_k > 16 || c.top_k >= c.vocab) return "top_k must be in 1..16 and below vocab";

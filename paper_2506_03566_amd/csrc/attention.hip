@@ -1062,7 +1062,6 @@ static void launch_merge_t(const ModelDims &md, const AttnSeqs &seqs, int n_rows
 // whose partial sums are added in group order.  4 rows of four heads over 89 keys: 19.3 -> 6.5 us (before: one wave, dh
 // scalar loads per key and one dependent load per key in P V).
 constexpr int AF32_THREADS = 256;
-template <bool VEC>
 __global__ __launch_bounds__(AF32_THREADS) void attn_f32_kernel(const float *__restrict__ q, int hq, int hkv, int dh, int dh2,
                                                                 const uint64_t *__restrict__ mask, int n_prefix, int region_len,
                                                                 KVCache kv, float scale, float *__restrict__ out) {
@@ -1079,15 +1078,11 @@ __global__ __launch_bounds__(AF32_THREADS) void attn_f32_kernel(const float *__r
         if (slot_visible(sl, n_prefix, region_len, m0, m1)) {
             const float *kr = kc + k_offset(kv, sl, kvh, hkv, dh);
             float a = 0.f;
-            if constexpr (VEC) {
 #pragma unroll 8
-                for (int i = 0; i < dh; i += 4) {
-                    const f32x4 k4 = *reinterpret_cast<const f32x4 *>(kr + i), q4 = *reinterpret_cast<const f32x4 *>(qr + i);
+            for (int i = 0; i < dh; i += 4) {             // (dh is a multiple of 32)
+                const f32x4 k4 = *reinterpret_cast<const f32x4 *>(kr + i), q4 = *reinterpret_cast<const f32x4 *>(qr + i);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) a = fmaf(q4[j], k4[j], a);
-                }
-            } else {
-                for (int i = 0; i < dh; ++i) a = fmaf(qr[i], kr[i], a);
+                for (int j = 0; j < 4; ++j) a = fmaf(q4[j], k4[j], a);
             }
             x = a * scale;
         }
@@ -1305,12 +1300,8 @@ void launch_attention(const ModelDims &md, const void *q, int rows, const RowMet
         const float scale = 1.0f / sqrtf((float)md.dh);
         const float *qf = static_cast<const float *>(q);
         float *of = static_cast<float *>(out);
-        if (md.dh % 4 == 0)
-            hipLaunchKernelGGL((attn_f32_kernel<true>), dim3(rows, md.hq), dim3(AF32_THREADS), lds, st, qf, md.hq, md.hkv, md.dh, dh2,
-                               rm.mask, n_prefix, region_len, kv, scale, of);
-        else
-            hipLaunchKernelGGL((attn_f32_kernel<false>), dim3(rows, md.hq), dim3(AF32_THREADS), lds, st, qf, md.hq, md.hkv, md.dh, dh2,
-                               rm.mask, n_prefix, region_len, kv, scale, of);
+        hipLaunchKernelGGL(attn_f32_kernel, dim3(rows, md.hq), dim3(AF32_THREADS), lds, st, qf, md.hq, md.hkv, md.dh, dh2, rm.mask, n_prefix,
+                           region_len, kv, scale, of);
     } else if (md.dt == DT_BF16) {
         launch_attention_t<bf16_t>(md, q, rows, rm, n_prefix, region_len, kv, keys_per_split, sc, out, st);
     } else {

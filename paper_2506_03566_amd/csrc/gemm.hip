@@ -1486,11 +1486,12 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
 }
 
 // Refuse, on the host, argument sets that would make a kernel write through a null pointer.
-static bool gemm_args_ok(const GemmShape &g, const void *Wp, const void *X, const float *part, const EpiArgs &e) {
+static bool gemm_args_ok(int dt, const GemmShape &g, const void *Wp, const void *X, const float *part, const EpiArgs &e) {
     if (!Wp || !X || !part || g.M < 1 || g.M > LAUNCH_ROWS || g.S < 1) return false;
     switch (e.mode) {
         case EPI_PLAIN: return e.out || g.S == 1;          // unsplit: plane 0 is the result
-        case EPI_ROPE_KV: return e.q && e.cs && e.slot && (e.dh == 64 || e.dh == 128);   // caches: checked per range
+        case EPI_ROPE_KV:                                  // caches: checked per range
+            return e.q && e.cs && e.slot && (dt == DT_F32 ? e.dh >= 32 && e.dh % 32 == 0 : e.dh == 64 || e.dh == 128);
         case EPI_RESIDUAL: return e.h && (!e.gain || e.u);
         case EPI_SILU: return e.act != nullptr;
         case EPI_HEAD:
@@ -1516,7 +1517,7 @@ static bool ranges_ok(const GemmShape &g, RopeRanges &rr) {
 
 bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int ldx, float *part,
                  const EpiArgs &epi, float eps, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop, const RopeRanges *ranges) {
-    if (!gemm_args_ok(g, Wp, X, part, epi)) return false;
+    if (!gemm_args_ok(dt, g, Wp, X, part, epi)) return false;
     if (ranges && epi.mode != EPI_ROPE_KV) return false;               // only that epilogue works by row range
     RopeRanges rr;
     if (epi.mode == EPI_ROPE_KV) {

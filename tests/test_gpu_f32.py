@@ -123,3 +123,28 @@ def test_f32_scores_are_those_of_the_two_launches(vocab):
     differ = [seed for seed, (a, b) in enumerate(zip(*got)) if a[0] != b[0] or not np.array_equal(a[1], b[1])]
     print(f"  scores {got[0][0][1][1]:.3f} .. {got[0][0][1][-1]:.3f}, {len(differ)} of 64 prompts differ", flush=True)
     assert max(max(t) for t, _ in got[1]) < vocab and not differ
+
+
+# half a head in one group of 16 pairs, an odd number of groups (and of 16-byte pieces a thread group), the widest; K of 72 and heads that
+# share keys
+@pytest.mark.parametrize("head_dim,n_prompt,over", [(32, 100, {}), (96, 17, dict(d_model=72)), (160, 70, dict(n_kv_heads=1)), (256, 33, {})])
+def test_f32_head_sizes_other_than_the_16_bit_types(head_dim, n_prompt, over):
+    """A whole round: prompt, draft (the keys and values of the specialists), verification against the oracle."""
+    print(f"f32 head_dim={head_dim} prompt={n_prompt} {over}", flush=True)
+    pair = Pair("c0_tiny_f32", head_dim=head_dim, **dict(dict(n_kv_heads=2), **over))
+    cfg, prompt = pair.cfg, make_prompt(pair.cfg, n=n_prompt)
+    o = pair.oracle()
+    o.prefill(prompt)
+    assert pair.ctx.prefill(prompt) == o.tokens[-1]
+    for layer in range(cfg.n_layers):
+        for got, want in zip(pair.ctx.debug_read_kv(-1, layer, 0, n_prompt), o.kv[layer]):
+            assert np.abs(got - want).max() <= tol_for(cfg)
+    tr = pair.ctx.draft_tree()
+    from oracle.tree import Tree
+    d, want = tr.as_dict(), o.draft_tree()
+    assert np.abs(np.sort(np.array(d["score"])) - np.sort(np.array(want.score))).max() <= tol_for(cfg)
+    logits = torch.zeros(tr.n, cfg.vocab, device="cuda")
+    pair.ctx.verify_tree(logits_out=logits)
+    assert np.abs(logits.cpu().numpy() - o.verify_tree(Tree(d["token"], d["parent"]))[1]).max() <= tol_for(cfg)
+    assert len(pair.ctx.accept_and_commit()[2]) >= 1
+    pair.close()

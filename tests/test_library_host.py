@@ -78,3 +78,12 @@ def test_null_arguments_are_rejected_before_any_gpu_work():
     assert lib.poss_debug_gemm_scratch_bytes(1, 0, 10, 10) == 0
     assert lib.poss_debug_gemm_scratch_bytes(1, 257, 10, 16) == 0
     lib.poss_free(None)
+
+
+def test_float32_head_sizes():
+    """The float32 products write rotary pairs in groups of 16: multiples of 32, up to the 256 threads of the attention's last sum.  What
+    cannot run is refused when a context is configured."""
+    lib, base = _lib(), get_config("c0_tiny_f32")
+    for dh in range(0, 300):
+        need = lib.poss_workspace_bytes(ctypes.byref(P.make_config(base.with_(head_dim=dh))))
+        assert (need > 0) == (dh > 0 and dh % 32 == 0 and dh <= 256), dh
