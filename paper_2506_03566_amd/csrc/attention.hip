@@ -512,6 +512,11 @@ __device__ __forceinline__ float max3(float a, float b, float c) {         // (a
 }
 template <int BYTES> __device__ __forceinline__ int walk_swizzle(int r) { return BYTES == 256 ? r & 15 : BYTES == 128 ? (r >> 1) & 7 : (r >> 2) & 3; }
 
+// Which 32 query rows of its workgroup's 128 a wave takes.  A SIMD holds waves w and w + 4, one of each key-way: two groups apart, so that
+// up to two groups' worth of rows have a SIMD per wave.  One apart, the second group shared a SIMD with the first: a pass of four layers,
+// 4000 keys, us, 10 rows of the 8B shape 545 / 528, 40 rows of 640 wide (bf16) 337 / 325; 8 and 24 rows of the 8B shape the same.
+__device__ __forceinline__ int walk_rows_of(int wave) { return (wave + 2 * (wave >> 2)) & 3; }
+
 // The wave's rows: row0 .. row0 + rows - 1 of the pass see the n_prefix slots before them and, of their own region_len slots, those in
 // their masks; lane's row m = row0 + rho / G, rho = rho0 + lane % 32.  The walk: blocks [b0, b1).
 template <typename T, int DH, bool PROMPT>
@@ -531,8 +536,7 @@ __device__ __forceinline__ void attn_walk_body(
     T *ks_lds = lds_all, *vs_lds = lds_all + NST * KW * BLK;
 
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, h = lane >> 5, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    // (a SIMD holds a wave of each key-way, of different row groups: with few rows only group 0 has work)
-    const int kway = wave >> 2, wq = (wave + kway) & 3;
+    const int kway = wave >> 2, wq = walk_rows_of(wave);
     const int stid = wq * 64 + lane, G = hq / hkv;
     const int rho = rho0 + l32;
     const bool valid = rho < rows * G, active = rho0 < rows * G;   // (active: wave-uniform)
@@ -874,7 +878,7 @@ template <typename T, int DH>
 __device__ __forceinline__ void attn_walk_split(T *lds, int row_group, int kvh, int split, const T *q, int rows, int hq, int hkv, const uint64_t *mask,
                                                 int n_prefix, int region_len, KVCache kv, int blocks_per_split, float scale, float *o_part,
                                                 float *ml_part, int rho_pad, T *out_direct) {
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wq = (wave + (wave >> 2)) & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wq = walk_rows_of(wave);
     const int b0 = split * blocks_per_split, b1 = min((n_prefix + region_len + 31) >> 5, b0 + blocks_per_split);
     attn_walk_body<T, DH, false>(lds, kvh, split, q, 0, rows, (row_group * 4 + wq) * 32, hq, hkv, mask, n_prefix, region_len, kv, b0, b1, scale, o_part,
                                  ml_part, rho_pad, out_direct);
@@ -938,7 +942,7 @@ __global__ __launch_bounds__(WALK_THREADS) void attn_prompt_kernel(const T *__re
                                     nullptr, nullptr, 0, out + off);
         return;
     }
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wq = (wave + (wave >> 2)) & 3;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wq = walk_rows_of(wave);
     attn_walk_body<T, DH, true>(lds, pair % hkv, 0, q, r0, n, (row_group * 4 + wq) * 32, hq, hkv, mask, c0 + r0, n, kv, 0, b1, scale,
                                 nullptr, nullptr, 0, out);
 }
