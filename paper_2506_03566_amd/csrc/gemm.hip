@@ -1351,9 +1351,15 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
 //   5120 -> 15360 (2 splits)  1 row (79 MB) 28.3 / 26.6, 10 rows 28.4 / 26.7, 31 rows (157 MB) 30.0 / 32.0, 61 rows (315 MB) 32.1 / 42.0
 //   640 -> 1920 (1 split)     1 row 8.3 / 5.8, 10 rows 8.9 / 6.2, 31 rows 9.3 / 7.4, 61 rows (5 MB) 10.4 / 9.3
 //   512 -> 768 (1 split)      1 row 7.0 / 5.0, 10 rows 7.4 / 5.4, 31 rows 7.7 / 6.0, 61 rows (2 MB) 8.6 / 8.1
-constexpr size_t QKV_FUSED_BYTES = (size_t)80 << 20;
+// Nor with more tiles than CUs and a last round that leaves many of them without one: what they could have streamed meanwhile counts
+// (idle CUs x a tile's weights).  The same figures (bf16, a layer's share of a pass, 1 row; up to 31 rows alike):
+//   1024 -> 12288 (384 tiles, 8 MB) -2, 13B above (480, 10 MB) -1.7, 1024 -> 9216 (288, 15 MB) 0, 2048 -> 12288 (17 MB) -1.2;
+//   2048 -> 10240 (320, 25 MB) +1.4, 4096 -> 12288 (34 MB) +3, 3072 -> 9216 (44 MB) +4.4, 4096 -> 10240 (50 MB) +5.7, 8192 -> 10240 (101 MB) +9.
+constexpr size_t QKV_FUSED_BYTES = (size_t)80 << 20, QKV_IDLE_BYTES = (size_t)20 << 20;
 static bool qkv_fused(const GemmShape &g) {
-    return g.Mpad <= 64 && g.S <= QKV_MAX_SPLITS && (size_t)(g.Npad / (GEMM_NT * 16)) * g.Mpad * g.K * 2 <= QKV_FUSED_BYTES;
+    const size_t tiles = g.Npad / (GEMM_NT * 16), idle = tiles > 256 ? (256 - tiles % 256) % 256 : 0;
+    return g.Mpad <= 64 && g.S <= QKV_MAX_SPLITS && tiles * g.Mpad * g.K * 2 <= QKV_FUSED_BYTES &&
+           idle * (GEMM_NT * 16) * g.K * 2 <= QKV_IDLE_BYTES;
 }
 
 // The QKV projection of 16-bit types: one kernel, rotary embedding and cache writes included.
