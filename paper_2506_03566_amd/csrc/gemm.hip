@@ -1355,10 +1355,12 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
 // (idle CUs x a tile's weights).  The same figures (bf16, a layer's share of a pass, 1 row; up to 31 rows alike):
 //   1024 -> 12288 (384 tiles, 8 MB) -2, 13B above (480, 10 MB) -1.7, 1024 -> 9216 (288, 15 MB) 0, 2048 -> 12288 (17 MB) -1.2;
 //   2048 -> 10240 (320, 25 MB) +1.4, 4096 -> 12288 (34 MB) +3, 3072 -> 9216 (44 MB) +4.4, 4096 -> 10240 (50 MB) +5.7, 8192 -> 10240 (101 MB) +9.
-constexpr size_t QKV_FUSED_BYTES = (size_t)80 << 20, QKV_IDLE_BYTES = (size_t)20 << 20;
+// Two row tiles pay up to 100 MiB (four layers, us, stream / one kernel): 6144 -> 8192 (96 MiB) 17 rows 558 / 548, 31 rows 585 / 575; 7168 ->
+// 7168 (98 MiB) 24 rows 613 / 610; 8192 -> 7168 (112 MiB) 17 rows 671 / 678, 31 rows 674 / 686.  Four do not: the 47 rows above.
+constexpr size_t QKV_FUSED_BYTES = (size_t)80 << 20, QKV_FUSED_BYTES_32 = (size_t)100 << 20, QKV_IDLE_BYTES = (size_t)20 << 20;
 static bool qkv_fused(const GemmShape &g) {
     const size_t tiles = g.Npad / (GEMM_NT * 16), idle = tiles > 256 ? (256 - tiles % 256) % 256 : 0;
-    return g.Mpad <= 64 && g.S <= QKV_MAX_SPLITS && tiles * g.Mpad * g.K * 2 <= QKV_FUSED_BYTES &&
+    return g.Mpad <= 64 && g.S <= QKV_MAX_SPLITS && tiles * g.Mpad * g.K * 2 <= (g.Mpad == 32 ? QKV_FUSED_BYTES_32 : QKV_FUSED_BYTES) &&
            idle * (GEMM_NT * 16) * g.K * 2 <= QKV_IDLE_BYTES;
 }
 
