@@ -102,3 +102,97 @@ def test_splits_of_a_very_long_context_stay_within_what_a_wave_can_address():
         out.append(feats.cpu().numpy())
     pair.close()
     assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1])
+
+
+def _round(x, cfg):
+    return to_float64(to_storage(x, cfg.dtype), cfg.dtype)
+
+
+def _attention_scales(q, k, seen, s, cfg):
+    """Rows (q: [rows, heads, dh]) over keys k [keys, KV heads, dh] that they see, values s[key] c[dim]: the float64 output as a multiple of c per
+    row and head, and that multiple as it is read from rounded outputs (the mean over the dims) when the probabilities enter P V as hi + lo,
+    as hi alone, and as hi + the low halves of the keys 8 further."""
+    dh, group = cfg.head_dim, cfg.n_q_heads // cfg.n_kv_heads
+    c = (128 + np.arange(dh) * (128 // dh)) / 128
+    score = np.stack([q[:, h] @ k[:, h // group].T for h in range(cfg.n_q_heads)], 1) / np.sqrt(dh)
+    score = np.where(seen[:, None], score, -np.inf)
+    p = np.exp(score - score.max(-1, keepdims=True))
+    hi = _round(p, cfg)
+    lo = _round(p - hi, cfg)
+    z = p.sum(-1)
+    return p @ s / z, [(_round((x @ s / z)[..., None] * c, cfg) / c).mean(-1) for x in (hi + lo, hi, hi + np.roll(lo, 8, -1))]
+
+
+# Both head widths (8 and 16 fragments of keys in a step), rows that leave a workgroup's last wave partly empty, a last split of one block;
+# splits of 2048 keys use all 64 page-table entries that a wave holds
+@pytest.mark.parametrize("n_prompt,rows,over", [(4000, 61, dict(kv_page_tokens=32, kv_page_order=1)), (4064, 100, dict(n_q_heads=4, n_kv_heads=2, head_dim=128))])
+def test_low_halves_of_the_probabilities_count(n_prompt, rows, over):
+    """bf16 probabilities enter P V as the sum of two bf16 numbers, in walks and prompts.  One layer without an MLP whose values are s c[dim] with s
+    1 or 2 per token (exact), output projection the identity: an output is a multiple of c, rounded, and the mean over the dims reads the multiple
+    to 4e-5 to 7e-5, where one bf16 number per probability is off by 2e-4.  The median error over rows and heads against float64
+    (keys from the cache; queries formed here, whose rounding a float32 sum flips in a few rows) is held to what the float64 model
+    of hi + lo shows, output rounding included, and a quarter; models without the low halves, or with another key's, are off by more."""
+    over = dict(dict(n_layers=1, max_seq=4480, n_specialists=1, positions_per_specialist=6, total_tokens=100, norm_gain_jitter=0.0), **over)
+    cfg = get_config("t_mid_bf16", **over)
+    print(f"low halves prompt={n_prompt} rows={rows} {over}", flush=True)
+    rng, d, dh = np.random.default_rng(5), cfg.d_model, cfg.head_dim
+    qd, kd = cfg.n_q_heads * dh, cfg.n_kv_heads * dh
+    assert qd == d
+    c = (128 + np.arange(dh) * (128 // dh)) / 128
+    embed = rng.choice([-1.0, 1.0], (cfg.vocab, d))        # RMSNorm leaves them as they are
+    embed[:, :2] = 1
+    wq, wk = rng.normal(0, 2 / np.sqrt(d), (qd, d)), rng.normal(0, 2 / np.sqrt(d), (kd, d))     # scores of standard deviation 4
+    wv = np.zeros((kd, d))
+    wv[:, 0], wv[:, 1], wv[:, 2] = np.tile(c, cfg.n_kv_heads), np.tile(c / 2, cfg.n_kv_heads), np.tile(c / 2, cfg.n_kv_heads)
+    storage = make_weights(cfg)
+    for name, w in (("embed", embed), ("layer0.wq", wq), ("layer0.wk", wk), ("layer0.wv", wv), ("layer0.wo", np.eye(d)),
+                    ("layer0.w_down", np.zeros((d, cfg.d_ffn)))):
+        storage[name] = to_storage(w, cfg.dtype)
+    pair = Pair("t_mid_bf16", storage=storage, **over)
+    wq = _round(wq, cfg)
+
+    def queries(ids, pos):
+        x = (embed[ids] @ wq.T).reshape(-1, cfg.n_q_heads, dh)
+        ang = np.asarray(pos)[:, None, None] * cfg.rope_theta ** (-2.0 * np.arange(dh // 2) / dh)
+        a, b = x[..., :dh // 2], x[..., dh // 2:]
+        return _round(np.concatenate([a * np.cos(ang) - b * np.sin(ang), b * np.cos(ang) + a * np.sin(ang)], -1), cfg)
+
+    def check(what, out, ids, pos, k, seen, s):
+        want, (both, one, other) = _attention_scales(queries(ids, pos), k, seen, s, cfg)
+        got = (out.reshape(-1, cfg.n_q_heads, dh) / c).mean(-1)
+        err, both, one, other = [float(np.median(np.abs(x / want - 1))) for x in (got, both, one, other)]
+        print(f"  {what}: {err:.2e}; model {both:.2e}, high halves alone {one:.2e}, other low halves {other:.2e}", flush=True)
+        assert 1.25 * both < min(one, other)
+        assert err <= 1.25 * both, what
+
+    prompt = rng.integers(0, cfg.vocab, n_prompt).astype(np.int32)
+    last = (n_prompt - 1) % 256 + 1
+    taps = torch.zeros(2, last, d, dtype=torch.float32, device="cuda")
+    tree = _tree(rows, cfg.vocab, 1)
+    for keys in (0, 512, 1024, 2048):
+        pair.ctx.reset()
+        pair.ctx.set_tuning(0, keys)
+        pair.ctx.debug_set_taps(taps if keys == 0 else None)
+        pair.ctx.prefill(prompt)
+        pair.ctx.debug_set_taps(None)
+        ids = np.array([pair.ctx.tokens()[-1]] + [int(t) for t in tree.token[1:rows]])
+        s = 1.5 + 0.5 * embed[np.concatenate([prompt, ids]), 2]
+        if keys == 0:
+            pos = np.arange(n_prompt - last, n_prompt)
+            k = pair.ctx.debug_read_kv(-1, 0, 0, n_prompt)[0].astype(np.float64)
+            seen = np.arange(n_prompt)[None] <= pos[:, None]
+            check("prompt", (taps[1] - taps[0]).cpu().numpy().astype(np.float64), prompt[pos], pos, k, seen, s[:n_prompt])
+        feats = torch.zeros(rows, d, dtype=torch.float32, device="cuda")
+        pair.ctx.verify_tree(tree, feat_out=feats)
+        k, v = pair.ctx.debug_read_kv(-1, 0, 0, n_prompt + rows)
+        assert np.array_equal(v[:, 0], (s[:, None] * c).astype(np.float32))
+        seen, depth = np.zeros((rows, n_prompt + rows), bool), np.zeros(rows, int)
+        seen[:, :n_prompt] = True
+        for i in range(rows):
+            p = int(tree.parent[i])
+            if p >= 0:
+                seen[i] |= seen[p]
+                depth[i] = depth[p] + 1
+            seen[i, n_prompt + i] = True
+        check(f"{keys or 'usual'} keys a split", feats.cpu().numpy().astype(np.float64) - embed[ids], ids, n_prompt + depth, k.astype(np.float64), seen, s)
+    pair.close()
