@@ -97,7 +97,6 @@ struct EpiArgs {
     // EPI_ROPE_KV: columns are [q heads | k heads | v heads]; rows < rows_q get a rotated query,
     // every row its rotated key and its value written to cache slot slot[m]
     int rows_q; const float2 *cs; const int32_t *slot; void *q; KVCache kv; int hq, hkv, dh;
-    int rope_packed;   // set by the launcher: the columns of a head are in the packed order of PackSrc::rope_dh
     // EPI_RESIDUAL: h[m][n] = sum + bias[n] + (residual ? h[m][n] : 0); h_copy likewise, and rows below h_user_rows of h_user;
     // h_stash (16-bit types): the same in the storage type; then, if
     // gain != nullptr, u[m][n] = T(rmsnorm(h[m]) * gain[n]) - the operand of the next GEMM
@@ -114,8 +113,8 @@ struct EpiArgs {
 // part must hold S * Mpad * Npad floats.  X row-major [M][ldx] of dtype dt.  ev_start / ev_stop, if both
 // given, receive the begin and end timestamps of the weight-streaming kernel itself (per-launch timing).
 // Returns false, launching nothing, if a pointer the chosen epilogue writes through is null.
-// EPI_ROPE_KV (the QKV projection; 16-bit types: one kernel that needs no partial planes, weights packed with
-// PackSrc::rope_dh): `ranges`, if given, sends row ranges [r0, r1) each into its own cache with its own query limit
+// EPI_ROPE_KV (the QKV projection; 16-bit types: weights packed with PackSrc::rope_dh; float32 and, with few rows or small
+// matrices, 16-bit types: one kernel, which leaves part alone): `ranges`, if given, sends row ranges [r0, r1) each into its own cache with its own query limit
 // (rows below rows_q get a rotated query) - several sequences batched into one launch; row indices stay those of the
 // launch (epi.cs, epi.slot, epi.q are indexed by them), epi.kv and epi.rows_q are ignored, blk0 is filled in here.
 constexpr int ROPE_MAX_RANGES = 16;

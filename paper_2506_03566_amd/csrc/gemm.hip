@@ -759,35 +759,27 @@ __global__ __launch_bounds__(QKV_MAX_SPLITS * 128) void gemm_qkv_rope_kernel(con
 // registers, PF k-steps in flight (an A fragment of v_mfma 16x16x32 is 16 contiguous bytes of one activation row, and with K split
 // among the waves no two of them want the same fragment): no LDS hop, no barrier in the loop.  4096 -> 6144, us with the boundary to
 // the next launch, this kernel / the one above: 1 row 10.1 / 11.2, 10 rows 11.7 / 12.2; two row tiles of it, 20 rows 13.8 / 13.1,
-// 31 rows 16.1 / 14.0 (64-byte pieces of the rows).
+// 31 rows 16.1 / 14.0 (64-byte pieces of the rows).  Other widths, passes of four layers, 1 and 8 rows: 2048 -> 3072 241 / 250 and 249 / 256,
+// 2048 -> 6144 242 / 246 and 248 / 254, 6144 -> 8192 529 / 528 and 538 / 541; 16 rows within 1 %.
 template <typename T, int PF>
 __global__ __launch_bounds__(256) void gemm_qkv_row_kernel(const u32x4 *__restrict__ Wp, const T *__restrict__ X, int ldx,
                                                            int M, int K, int ksteps_total, QkvEpi e) {
-    constexpr int MT = 1, NTILE = GEMM_NT;
-    __shared__ f32x4 red[4 * NTILE * 64];
+    __shared__ f32x4 red[4 * GEMM_NT * 64];
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, tile = blockIdx.x;
     const int w0 = wave * ksteps_total / 4, w1 = (wave + 1) * ksteps_total / 4, n_w = w1 - w0;
     const u32x4 *wp = Wp + ((size_t)tile * ksteps_total + w0) * (GEMM_NT * 64) + lane;      // this wave's first k-step
-    const T *xp[MT];
+    const T *xp = X + (size_t)min(lane & 15, M - 1) * ldx + (size_t)w0 * GEMM_KSTEP + (lane >> 4) * 8;   // rows beyond M repeat the last row
+    f32x4 acc[GEMM_NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        const int m = mt * 16 + (lane & 15);
-        xp[mt] = X + (size_t)(m < M ? m : M - 1) * ldx + (size_t)w0 * GEMM_KSTEP + (lane >> 4) * 8;   // rows beyond M repeat the last row
-    }
-    f32x4 acc[MT][GEMM_NT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < GEMM_NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < GEMM_NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     int done = 0;
     if (w1 * GEMM_KSTEP <= K && n_w >= PF) {             // no k-step of this wave reaches beyond K: loads need no mask
-        u32x4 wr[PF][GEMM_NT], ar[PF][MT];
+        u32x4 wr[PF][GEMM_NT], ar[PF];
         auto load_step = [&](int p, int i) {             // k-step w0 + i into ring slot p (p static after unrolling)
 #pragma unroll
             for (int nt = 0; nt < GEMM_NT; ++nt) wr[p][nt] = __builtin_nontemporal_load(wp + (size_t)i * (GEMM_NT * 64) + nt * 64);
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) ar[p][mt] = *reinterpret_cast<const u32x4 *>(xp[mt] + (size_t)i * GEMM_KSTEP);
+            ar[p] = *reinterpret_cast<const u32x4 *>(xp + (size_t)i * GEMM_KSTEP);
         };
 #pragma unroll
         for (int p = 0; p < PF; ++p) load_step(p, p);
@@ -796,16 +788,13 @@ __global__ __launch_bounds__(256) void gemm_qkv_row_kernel(const u32x4 *__restri
             constexpr bool MORE = decltype(more_tag)::value;
 #pragma unroll
             for (int p = 0; p < PF; ++p) {
-                u32x4 w[GEMM_NT], a[MT];
+                u32x4 w[GEMM_NT];
+                const u32x4 a = ar[p];
 #pragma unroll
                 for (int nt = 0; nt < GEMM_NT; ++nt) w[nt] = wr[p][nt];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) a[mt] = ar[p][mt];
                 if constexpr (MORE) load_step(p, (g + 1) * PF + p);
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int nt = 0; nt < GEMM_NT; ++nt) acc[mt][nt] = Mfma<T>::run(a[mt], w[nt], acc[mt][nt]);
+                for (int nt = 0; nt < GEMM_NT; ++nt) acc[nt] = Mfma<T>::run(a, w[nt], acc[nt]);
                 __builtin_amdgcn_sched_barrier(0);       // one k-step at a time: loads stay in ring order
             }
         };
@@ -815,32 +804,25 @@ __global__ __launch_bounds__(256) void gemm_qkv_row_kernel(const u32x4 *__restri
     }
     for (int i = done; i < n_w; ++i) {                   // what the ring did not cover; fragments beyond K are zero
         const bool ok = (w0 + i) * GEMM_KSTEP + (lane >> 4) * 8 < K;
-        u32x4 w[GEMM_NT], a[MT];
+        u32x4 w[GEMM_NT];
 #pragma unroll
         for (int nt = 0; nt < GEMM_NT; ++nt) w[nt] = wp[(size_t)i * (GEMM_NT * 64) + nt * 64];
+        const u32x4 v = *reinterpret_cast<const u32x4 *>(ok ? xp + (size_t)i * GEMM_KSTEP : xp - (size_t)w0 * GEMM_KSTEP - (lane >> 4) * 8);
+        const u32x4 a = ok ? v : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const u32x4 v = *reinterpret_cast<const u32x4 *>(ok ? xp[mt] + (size_t)i * GEMM_KSTEP : xp[mt] - (size_t)w0 * GEMM_KSTEP - (lane >> 4) * 8);
-            a[mt] = ok ? v : u32x4{0u, 0u, 0u, 0u};
-        }
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int nt = 0; nt < GEMM_NT; ++nt) acc[mt][nt] = Mfma<T>::run(a[mt], w[nt], acc[mt][nt]);
+        for (int nt = 0; nt < GEMM_NT; ++nt) acc[nt] = Mfma<T>::run(a, w[nt], acc[nt]);
     }
 
     const int tph = e.dh >> 5, gh = tile / tph, pi = (tile % tph) * 16 + (lane & 15);   // 32-column tiles per head; the lane's pair
     QkvRows rows;
-    if (wave < MT) {
-        qkv_rows(e, gh, pi, wave, M, lane, rows);
+    if (wave == 0) {
+        qkv_rows(e, gh, pi, 0, M, lane, rows);
         qkv_pages(e, gh, rows);
     }
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < GEMM_NT; ++nt) red[(wave * NTILE + mt * GEMM_NT + nt) * 64 + lane] = acc[mt][nt];
+    for (int nt = 0; nt < GEMM_NT; ++nt) red[(wave * GEMM_NT + nt) * 64 + lane] = acc[nt];
     __syncthreads();
-    qkv_epilogue<T, MT>(red, 4, gh, pi, M, wave, 4, lane, e, rows);
+    qkv_epilogue<T, 1>(red, 4, gh, pi, M, wave, 4, lane, e, rows);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1230,9 +1212,8 @@ __global__ __launch_bounds__(ROPE_THREADS) void epilogue_rope_ranges_kernel(cons
     const int half = e.dh >> 1, c = ((int)threadIdx.x & 15) * 4;
     const int hb = (int)blockIdx.x * GEMM_BLOCK_N + (c / half) * e.dh, i = c % half, gh = hb / e.dh;
     if (r >= rr.r1[jr] || gh >= e.hq + 2 * e.hkv || (gh < e.hq && r >= rr.rows_q[jr])) return;
-    // columns of the pairs: natural order (i, i + dh/2), or the packed order of PackSrc::rope_dh, in which a 32-column
-    // group holds dims [16j, 16j+16) followed by their partners
-    const int c1 = e.rope_packed ? hb + (i >> 4) * 32 + (i & 15) : hb + i, c2 = e.rope_packed ? c1 + 16 : c1 + half;
+    // columns of the pairs: in the packed order of PackSrc::rope_dh a 32-column group holds dims [16j, 16j+16) followed by their partners
+    const int c1 = hb + (i >> 4) * 32 + (i & 15), c2 = c1 + 16;
     float2 cs[4];                                          // requested together with the planes
 #pragma unroll
     for (int j = 0; j < 4; ++j) cs[j] = e.cs[r * half + i + j];
@@ -1334,8 +1315,9 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
         }
         case EPI_HEAD: break;           // reduced inside the stream kernel
         case EPI_SILU:
-            if (silu_done) break;       // applied inside the stream kernel
-            hipLaunchKernelGGL((epilogue_kernel<T, EPI_SILU>), pair_grid, eb, 0, st, part, plane, g.S, g.Npad, g.N, 0, g.M, epi);
+            if constexpr (!std::is_same<T, float>::value)               // (float32: inside gemm_f32_kernel)
+                if (!silu_done)         // otherwise applied inside the stream kernel
+                    hipLaunchKernelGGL((epilogue_kernel<T, EPI_SILU>), pair_grid, eb, 0, st, part, plane, g.S, g.Npad, g.N, 0, g.M, epi);
             break;
         default:
             if (g.S > 1 || epi.out)     // S == 1 without an output buffer: plane 0 is the result
@@ -1430,12 +1412,10 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
 #undef POSS_TALL_LAUNCH_MT
 #undef POSS_TALL_LAUNCH
         if (epi.mode == EPI_ROPE_KV) {
-            EpiArgs pe = epi;
-            pe.rope_packed = 1;
             const size_t plane = (size_t)g.Mpad * g.Npad;
             const int blocks = rr->blk0[rr->n - 1] + (rr->r1[rr->n - 1] - rr->r0[rr->n - 1] + EPI_ROWS_PAIR - 1) / EPI_ROWS_PAIR;
             hipLaunchKernelGGL((epilogue_rope_ranges_kernel<T>), dim3(g.Npad / GEMM_BLOCK_N, blocks), dim3(ROPE_THREADS), 0, st, part, plane, g.S,
-                               g.Npad, *rr, pe);
+                               g.Npad, *rr, epi);
             return;
         }
         launch_epilogue_t<T>(g, part, epi, eps, fuse_silu, st);
@@ -1482,12 +1462,10 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
 #undef POSS_GEMM_CASE
 #undef POSS_GEMM_LAUNCH
     if (epi.mode == EPI_ROPE_KV) {                       // rotary + cache writes per row range, one launch
-        EpiArgs pe = epi;
-        pe.rope_packed = 1;
         const size_t plane = (size_t)g.Mpad * g.Npad;
         const int blocks = rr->blk0[rr->n - 1] + (rr->r1[rr->n - 1] - rr->r0[rr->n - 1] + EPI_ROWS_PAIR - 1) / EPI_ROWS_PAIR;
         hipLaunchKernelGGL((epilogue_rope_ranges_kernel<T>), dim3(g.Npad / GEMM_BLOCK_N, blocks), dim3(ROPE_THREADS), 0, st, part, plane, g.S,
-                           g.Npad, *rr, pe);
+                           g.Npad, *rr, epi);
         return;
     }
     launch_epilogue_t<T>(g, part, epi, eps, fuse_silu, st);
