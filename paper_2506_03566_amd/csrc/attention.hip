@@ -497,7 +497,9 @@ __device__ __forceinline__ void attn_mfma_body(
 // Which splits are long (bf16): with few rows a wave of 32 has little to do but wait for its own chain, and 16-row tiles are through
 // sooner; fp16, without the low halves, gains nothing before they are.  8B shape, us a pass of four target layers, 16-row tiles / these: 1000
 // keys (9 blocks a split) 61 rows 583 / 602; 2000 keys 599 / 617; 3000 keys 608 / 630; 4000 keys (32 blocks) 1 row 529 / 520, 61 rows
-// 664 / 644; 8192 keys 530 / 523, 81 rows 716 / 700.  640 wide, fp16, 8000 keys 278 / 278, 61 rows 330 / 346.
+// 664 / 644; 8192 keys 530 / 523, 81 rows 716 / 700.  fp16, 8000 keys: 640 wide (5 heads) 1 row 275 / 272, 61 rows 333 / 334, 100 rows 398 / 421;
+// 13B (40 heads) 759 / 754, 871 / 871, 81 rows 1001 / 966, 100 rows 1088 / 1052; 4000 keys 641 / 640, 767 / 766, 871 / 850, 957 / 940: with
+// many heads it would gain from 65 rows on, and a rule for fp16 would have to go by heads x splits, not by rows (a row's bits).
 constexpr int WALK_MIN_BPS = 32, WALK_THREADS = 512;
 constexpr int PROMPT_SHORT_BLOCKS = 8;                    // a prompt's first range (4 blocks) is computed as a short context is
 template <typename T> __device__ __forceinline__ unsigned pack2(float a, float b) {   // two values rounded to T, a in the low half
@@ -1143,7 +1145,9 @@ static AttnShape attention_shape(const ModelDims &md, int rows, int n_prefix, in
     a.walk = md.dt == DT_BF16 && a.bps >= WALK_MIN_BPS;
     // Two row tiles a wave where one would put more workgroups in the launch than the chip has CUs (a workgroup fills a CU's LDS: the
     // surplus would run as a second round).  Otherwise the keys are staged twice as often, by twice as many CUs: 61 rows of the 8B
-    // shape, us a pass of four layers, two tiles / one: 1000 keys 600 / 583, 2000 623 / 599, 3000 648 / 608.
+    // shape, us a pass of four layers, two tiles / one: 1000 keys 600 / 583, 2000 623 / 599, 3000 648 / 608; 100 rows of 640 wide, fp16, 1000
+    // keys 379 / 358, 4000 435 / 398, 8000 437 / 397.  At the line, 280 workgroups of 5 blocks (100 rows of the 8B shape, 600 keys), a launch
+    // takes 14.3 / 14.1.
     const int pairs = 8 * ((md.hkv * a.n_splits + 7) / 8);
     a.rt = a.walk || (tiles > 4 && (crowded || (tiles + 3) / 4 * pairs > 256)) ? 2 : 1;
     a.n_row_groups = (tiles + 4 * a.rt - 1) / (4 * a.rt);
