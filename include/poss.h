@@ -240,8 +240,9 @@ void poss_free(poss_ctx *ctx);
 int poss_profile_gemm(poss_ctx *ctx, int32_t enable);
 int poss_gemm_profile(poss_ctx *ctx, int64_t *launches, double *ms, double *weight_bytes);
 
-/* Tuning knobs for sweeps: target number of workgroups per GEMM launch (0 = default).  Prompts of more than 512 tokens
- * (16-bit types) do not use them. */
+/* Tuning knobs for sweeps: target number of workgroups per GEMM launch (0 = default); keys per attention split, a multiple of 32,
+ * at least 64 (0 = default; at most 2048 are taken, and small splits are doubled where a context would be cut into more than 256).
+ * Prompts of more than 512 tokens (16-bit types) do not use them. */
 int poss_set_tuning(poss_ctx *ctx, int32_t gemm_target_workgroups, int32_t attn_keys_per_split);
 
 /* Rows that one launch of a batch's pass carries at most (POSS_MAX_ROWS .. POSS_LAUNCH_ROWS, default the latter): the
