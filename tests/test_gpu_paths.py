@@ -189,3 +189,22 @@ def test_draws_from_blocks_that_were_not_expected(vocab, temperature, number):
             left[c] = 0.0
         assert len(root) == k
     pair.close()
+
+
+# 48 and 96 MiB of activation reads with one and two row tiles, the streaming kernel from 33 rows on; 320 column tiles on 256 CUs: always
+@pytest.mark.parametrize("d_model,heads,rows", [(6144, (48, 8), (16, 17, 32, 33)), (2048, (48, 16), (1, 16, 33))])
+def test_projections_at_the_line_between_the_two_kernels(d_model, heads, rows):
+    """Keys and values of a prompt's first rows: the same bits on either side of where the one-kernel form stops."""
+    print(f"qkv line d_model={d_model} heads={heads}", flush=True)
+    pair = Pair("t_mid_bf16", n_layers=1, d_model=d_model, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, d_ffn=64, vocab=300,
+                n_specialists=1, positions_per_specialist=6)
+    prompt = np.random.default_rng(d_model).integers(0, pair.cfg.vocab, 120).astype(np.int32)
+    pair.ctx.prefill(prompt)
+    want_k, want_v = pair.ctx.debug_read_kv(-1, 0, 0, 64)
+    assert np.abs(want_k).max() > 0 and np.abs(want_v).max() > 0
+    for n in rows:
+        pair.ctx.reset()
+        pair.ctx.prefill(prompt[:n])
+        k, v = pair.ctx.debug_read_kv(-1, 0, 0, n)
+        assert np.array_equal(k, want_k[:n]) and np.array_equal(v, want_v[:n]), n
+    pair.close()
