@@ -139,6 +139,13 @@ __device__ __forceinline__ float half_max(float v) {
     v = fmaxf(v, xor8(v)); v = fmaxf(v, xor4(v)); v = fmaxf(v, xor2(v)); v = fmaxf(v, xor1(v));
     return v;
 }
+__device__ __forceinline__ int half_min(int x) {
+    float a, b;
+    swap16(as_float(x), a, b); x = min(as_int(a), as_int(b));
+    x = min(x, as_int(xor8(as_float(x)))); x = min(x, as_int(xor4(as_float(x))));
+    x = min(x, as_int(xor2(as_float(x)))); x = min(x, as_int(xor1(as_float(x))));
+    return x;
+}
 __device__ __forceinline__ float half_sum(float v) {
     float a, b;
     swap16(v, a, b); v = a + b;

@@ -150,51 +150,105 @@ __device__ __forceinline__ void silu_tile_store(const T *tile, T *__restrict__ a
 }
 
 // The Head's reduction of a tile of logits in LDS, tile[row][TW] = columns [col0, col0 + TW): one half wave per row (NHW
-// of them; the exchanges stay inside a half and in the vector ALU: by shuffles, about 100 cycles each, the ten rounds of a
-// drafted row cost 4 us of the Head's 167).  HEAD_ARGMAX: the best (value, index) of the row's segment; HEAD_TOPK: maximum,
-// sum of exp(l - max) in a fixed order, and the k best by k rounds of (argmax, remove).
+// of them; the exchanges stay inside a half and in the vector ALU).  HEAD_ARGMAX: the best (value, index) of the row's segment;
+// HEAD_TOPK: maximum, sum of exp(l - max) in a fixed order, and the k best, sorted.
+// Every workgroup of a Head launch arrives here at the same time, so nothing streams meanwhile and what it costs is instructions
+// (four waves to a SIMD).  The k best: the k-th largest of the 32 lanes' maxima is a lower bound of the k-th largest value, so
+// the winners are among the values that reach it, a dozen, and those are ranked by counting.  10 rows of 256 columns, k = 10:
+// 14.0 thousand cycles by k rounds of (argmax, remove), which remain for rows with more than HEAD_CAND values at the bound, 5.6
+// thousand so; the argmax of 61 rows 7.0 -> 3.8 thousand (value first, then the lowest index that holds it).
+constexpr int HEAD_CAND = 32;
+template <int NVH>
+__device__ __forceinline__ void head_topk_rounds(float (&v)[NVH], int hl, int col0, int k, float *rec) {
+    float my_v = -INFINITY; int my_i = 0x7fffffff;
+    for (int r = 0; r < k; ++r) {
+        float wv = -INFINITY; int wi = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < NVH; ++j)
+            if (better(v[j], col0 + hl + 32 * j, wv, wi)) { wv = v[j]; wi = col0 + hl + 32 * j; }
+        half_argmax(wv, wi);
+        if (hl == r) { my_v = wv; my_i = wi; }
+#pragma unroll
+        for (int j = 0; j < NVH; ++j)
+            if (col0 + hl + 32 * j == wi) v[j] = -INFINITY;   // indices are unique: removes exactly the winner
+    }
+    if (hl < k) {
+        rec[2 + hl] = my_v;
+        reinterpret_cast<int *>(rec)[2 + TOPK_MAXK + hl] = my_v > -INFINITY ? my_i : 0x7fffffff;
+    }
+}
+
 template <int TW, int NHW>
-__device__ __forceinline__ void head_tile_reduce(const float *tile, int M, const HeadEpi &he, int seg, int n_seg, int tid) {
+__device__ __forceinline__ void head_tile_reduce(float *tile, int M, const HeadEpi &he, int seg, int n_seg, int tid) {
     constexpr int NVH = TW / 32;
+    static_assert(TW >= 2 * HEAD_CAND + 32, "a row's candidates and its lanes' maxima take the place of its logits");
     const int hw = tid >> 5, hl = tid & 31, col0 = seg * TW;
     for (int row = hw; row < M; row += NHW) {
-        float v[NVH]; int id[NVH];
-        float bv = -INFINITY; int bi = 0x7fffffff;
+        float v[NVH], lane_max = -INFINITY;
 #pragma unroll
-        for (int j = 0; j < NVH; ++j) {
-            const int c = hl + 32 * j, n = col0 + c;
-            const bool ok = n < he.vocab;
-            v[j] = ok ? tile[row * TW + c] : -INFINITY;
-            id[j] = ok ? n : 0x7fffffff - j;         // dummies stay below every real entry
-            if (better(v[j], id[j], bv, bi)) { bv = v[j]; bi = id[j]; }
+        for (int j = 0; j < NVH; ++j) {                   // columns beyond the vocabulary: -inf, with indices above every real one
+            const float x = tile[row * TW + hl + 32 * j];
+            v[j] = col0 + hl + 32 * j < he.vocab ? x : -INFINITY;
+            lane_max = fmaxf(lane_max, v[j]);
         }
+        const float mx = half_max(lane_max);
         if (he.mode == HEAD_ARGMAX) {
-            half_argmax(bv, bi);
-            if (hl == 0) { he.pv[(size_t)row * n_seg + seg] = bv; he.pi[(size_t)row * n_seg + seg] = bi; }
+            int bi = 0x7fffffff;                          // the lowest index that holds the maximum (none: a row of NaN)
+#pragma unroll
+            for (int j = NVH - 1; j >= 0; --j)
+                if (v[j] == mx && col0 + hl + 32 * j < he.vocab) bi = col0 + hl + 32 * j;
+            bi = half_min(bi);
+            if (hl == 0) { he.pv[(size_t)row * n_seg + seg] = mx; he.pi[(size_t)row * n_seg + seg] = bi; }
             continue;
         }
-        const float mx = half_max(bv);
         float se = 0.f;
 #pragma unroll
         for (int j = 0; j < NVH; ++j) se += v[j] > -INFINITY ? expf(v[j] - mx) : 0.f;
         se = half_sum(se);
         float *rec = he.seg_out + ((size_t)row * n_seg + seg) * TOPK_REC;
         if (hl == 0) { rec[0] = mx; rec[1] = se; }
-        float my_v = -INFINITY; int my_i = 0x7fffffff;
-        for (int r = 0; r < he.k; ++r) {
-            float wv = -INFINITY; int wi = 0x7fffffff;
+        float *cand_v = tile + row * TW, *maxima = cand_v + 2 * HEAD_CAND;
+        int *cand_i = reinterpret_cast<int *>(cand_v + HEAD_CAND);
+        wave_lds_sync();                                  // (the row has been read)
+        maxima[hl] = lane_max;
+        wave_lds_sync();
+        int above = 0;                                    // lanes with a larger maximum
 #pragma unroll
-            for (int j = 0; j < NVH; ++j)
-                if (better(v[j], id[j], wv, wi)) { wv = v[j]; wi = id[j]; }
-            half_argmax(wv, wi);
-            if (hl == r) { my_v = wv; my_i = wi; }
+        for (int j = 0; j < 32; j += 4) {
+            const f32x4 o = *reinterpret_cast<const f32x4 *>(maxima + j);
 #pragma unroll
-            for (int j = 0; j < NVH; ++j)
-                if (id[j] == wi) v[j] = -INFINITY;   // real indices are unique: removes exactly the winner
+            for (int q = 0; q < 4; ++q) above += o[q] > lane_max;
         }
-        if (hl < he.k) {
-            rec[2 + hl] = my_v;
-            reinterpret_cast<int *>(rec)[2 + TOPK_MAXK + hl] = my_v > -INFINITY ? my_i : 0x7fffffff;
+        const float thr = -half_max(above < he.k ? -lane_max : -INFINITY);   // (of equal maxima all count, k or more)
+        int cnt = 0;
+#pragma unroll
+        for (int j = 0; j < NVH; ++j) {
+            const bool in = v[j] > -INFINITY && v[j] >= thr;
+            const unsigned who = (unsigned)(__ballot(in) >> (tid & 32));
+            const int p = cnt + __popc(who & ((1u << hl) - 1u));
+            if (in && p < HEAD_CAND) { cand_v[p] = v[j]; cand_i[p] = col0 + hl + 32 * j; }
+            cnt += __popc(who);
+        }
+        wave_lds_sync();
+        if (cnt > HEAD_CAND) {
+            head_topk_rounds<NVH>(v, hl, col0, he.k, rec);
+            continue;
+        }
+        const float cv = cand_v[hl]; const int ci = cand_i[hl];
+        int rank = 0;
+        for (int j = 0; j < cnt; j += 4) {
+            const f32x4 ov = *reinterpret_cast<const f32x4 *>(cand_v + j);
+            const u32x4 oi = *reinterpret_cast<const u32x4 *>(cand_i + j);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) rank += j + q < cnt && better(ov[q], (int)oi[q], cv, ci);
+        }
+        if (hl < cnt && rank < he.k) {
+            rec[2 + rank] = cv;
+            reinterpret_cast<int *>(rec)[2 + TOPK_MAXK + rank] = ci;
+        }
+        if (hl >= cnt && hl < he.k) {                     // fewer than k values: no entry
+            rec[2 + hl] = -INFINITY;
+            reinterpret_cast<int *>(rec)[2 + TOPK_MAXK + hl] = 0x7fffffff;
         }
     }
 }

@@ -214,6 +214,33 @@ def test_all_equal_logits_pick_lowest_ids():
     pair.close()
 
 
+@pytest.mark.parametrize("run,vocab", [(1, 8192), (1, 131), (5, 1000), (24, 1000), (33, 1000), (128, 1000), (1000, 1000)])
+def test_children_are_the_best_logits_of_the_head(run, vocab):
+    """16-bit Head, whose column tiles select their k best themselves: the root's children against a sort of the very logits (the
+    same product, written by a context that draws).  Runs of identical Head rows: up to 32 values at a tile's bound are ranked by
+    counting, more go through rounds; vocabularies that end inside a tile, or leave one with fewer than k columns.  Scores: the
+    float32 log-sum-exp of at most 8192 logits below 64 in size is within 1e-4 of float64's."""
+    over = dict(vocab=vocab, depth=1, total_tokens=10)
+    st = make_weights(get_config("t_mid_bf16", **over))
+    head = st["lm_head"].copy()
+    st["lm_head"] = head[np.arange(vocab) // run * run].copy()
+    prompt = make_prompt(get_config("t_mid_bf16", **over), n=30)
+    draws, pair = (Pair("t_mid_bf16", storage=st, **over) for _ in range(2))
+    k = pair.cfg.top_k
+    assert draws.ctx.prefill(prompt) == pair.ctx.prefill(prompt)
+    draws.ctx.set_sampling(1.0, np.zeros(2, np.float32))
+    draws.ctx.set_draft_sampling(np.zeros((1, k, k), np.float32), np.zeros((2, k + 1), np.float32))
+    draws.ctx.draft_tree()
+    lg = draws.ctx.debug_draft_logits(0, 1)[0].cpu().numpy()
+    d = pair.ctx.draft_tree().as_dict()
+    want = np.lexsort((np.arange(vocab), -lg))[:k]
+    assert d["token"][1:k + 1] == want.tolist() and d["parent"][1:] == [0] * k
+    lse = np.log(np.exp(lg.astype(np.float64)).sum())
+    assert np.abs(lg).max() < 64 and np.abs(np.array(d["score"][1:]) - (lg[want] - lse)).max() < 1e-4
+    draws.close()
+    pair.close()
+
+
 def test_duplicated_head_rows_order_equal_logits_by_id():
     """LM-head rows 2i and 2i+1 made identical: their logits are bitwise equal, so wherever the
     odd token appears among a node's children the even one must be there too, ranked just before
