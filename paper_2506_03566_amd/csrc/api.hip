@@ -78,7 +78,7 @@ struct poss_ctx {
     std::vector<Seq> seq;
     // activations
     size_t part_floats;                // what part holds
-    float *h, *part, *logits, *feats, *fhat[2], *topk_scratch, *taps_user;
+    float *h, *h_other, *part, *logits, *feats, *fhat[2], *topk_scratch, *taps_user;
     float2 *cs;
     void *u, *xin, *q, *attn_out, *act;
     AttnScratch attn_sc;
@@ -244,7 +244,7 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
     }
     const int QR = B * 16 < R ? B * 16 : R;                  // full rows of a draft pass: at most k <= 16 per sequence
     const int PR = prefill_rows(c);                          // rows of the passes over a prompt
-    float *h = a.take_n<float>((size_t)PR * d);
+    float *h = a.take_n<float>((size_t)PR * d), *h_other = a.take_n<float>(d);
     float2 *cs = a.take_n<float2>((size_t)PR * (c.head_dim / 2));
     float *part = a.take_n<float>(part_floats);
     float *logits = a.take_n<float>((size_t)R * gemm_npad(V));
@@ -320,7 +320,7 @@ size_t carve(const poss_config &c, Arena &a, poss_ctx *ctx, WeightSlots *ws) {
         ctx->seq = seqs;
         ctx->cs = cs;
         ctx->part_floats = part_floats;
-        ctx->h = h; ctx->part = part; ctx->logits = logits; ctx->feats = feats; ctx->fhat[0] = fhat0; ctx->fhat[1] = fhat1;
+        ctx->h = h; ctx->h_other = h_other; ctx->part = part; ctx->logits = logits; ctx->feats = feats; ctx->fhat[0] = fhat0; ctx->fhat[1] = fhat1;
         ctx->topk_scratch = topk_scr; ctx->u = u; ctx->xin = xin; ctx->q = q; ctx->attn_out = ao; ctx->act = act;
         ctx->attn_sc = AttnScratch{ao_part, ml_part};
         ctx->row_pos = row_pos; ctx->row_slot = row_slot; ctx->row_mask = row_mask;
@@ -365,19 +365,46 @@ EpiArgs epi_residual(poss_ctx *c, bool residual, const void *bias, float *h_copy
 // key/value-only rows [x0, x0 + nx); its cache, committed prefix and region length.
 struct Seg { int b; const KVCache *kv; int q0, nq, x0, nx, n_prefix, region_len; };
 
+// A pass of one row (plain decoding, the first drafting pass without catch-up), 16-bit types: between two products there is no kernel
+// for the residual addition and the norm; the product that reads the normed row forms it from the planes of the one before
+// (launch_gemm_row).  h: the buffer that holds the residual stream; pending: what the next product has to add up first.
+struct RowFlow {
+    bool on, pending; RowNorm norm; float *h;
+    float *other(poss_ctx *c) const { return h == c->h ? c->h_other : c->h; }
+};
+
+// The planes of a product of a row flow's row, as the next product adds them to the stream and norms them; whether that product (of
+// next_cols columns, K = d) takes them; the product itself.
+RowNorm row_norm_of(poss_ctx *c, const RowFlow &rf, const GemmShape &g, bool residual, const void *bias, const void *gain) {
+    return RowNorm{c->part, (size_t)g.Mpad * g.Npad, g.S, c->md.d, bias, residual ? 1 : 0, residual ? rf.h : nullptr, rf.other(c), gain, c->md.eps};
+}
+bool row_next_ok(poss_ctx *c, const RowNorm &n, int next_cols, int mode) {
+    return gemm_row_ok(c->md.dt, gemm_plan(c->md.dt, 1, next_cols, c->md.d, mode == EPI_SILU ? 1 : c->gemm_target_wgs), n, mode);
+}
+void run_gemm_row(poss_ctx *c, RowFlow &rf, const void *Wp, int N, const RowNorm &n, const EpiArgs &e) {
+    const GemmShape g = gemm_plan(c->md.dt, 1, N, c->md.d, e.mode == EPI_SILU ? 1 : c->gemm_target_wgs);
+    const ProfileSlot p = profile_slot(c, N, c->md.d);
+    if (!launch_gemm_row(c->md.dt, g, Wp, n, e, c->st, p.start, p.stop)) c->launch_refused = true;
+    rf.h = n.h_out;
+    rf.pending = false;
+}
+
 // One decoder layer on rows_all rows (all produce K/V) of which the first rows_q go through
 // attention and the MLP; the full rows of every sequence come first, each sequence attends to its
 // own cache.  On entry c->u holds T(rmsnorm(h) * attn_norm) and c->cs the rotary table of the rows;
-// on exit c->h is updated and c->u holds T(rmsnorm(h) * next_gain).
+// on exit c->h is updated and c->u holds T(rmsnorm(h) * next_gain).  In a row flow (rf.on) the residual stream is rf.h instead, and
+// what is pending on entry takes the place of c->u; with `more` (another layer follows) the same may be left on exit.
 void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int rows_all, int rows_q, const RowMeta &rm,
-               const void *next_gain, float *h_copy, bool drafter = false, float *h_user = nullptr, int h_user_rows = 0) {
+               const void *next_gain, float *h_copy, RowFlow &rf, bool more, bool drafter = false, float *h_user = nullptr, int h_user_rows = 0) {
     const ModelDims &md = c->md;
     const int qd = md.hq * md.dh, kd = md.hkv * md.dh;
     EpiArgs e{};
     e.mode = EPI_ROPE_KV; e.rows_q = rows_q; e.cs = c->cs; e.slot = rm.slot; e.q = c->q; e.kv = *segs[0].kv;
     e.hq = md.hq; e.hkv = md.hkv; e.dh = md.dh;
     const bool one = segs.size() == 1 && segs[0].q0 == 0 && segs[0].x0 == segs[0].nq;
-    if (one) {
+    if (rf.pending) {
+        run_gemm_row(c, rf, w.wqkv, qd + 2 * kd, rf.norm, e);
+    } else if (one) {
         run_gemm(c, w.wqkv, qd + 2 * kd, md.d, c->u, md.d, rows_all, c->part, false, e);
     } else {
         // one weight stream for every sequence, each sequence's rows into its own cache
@@ -390,22 +417,44 @@ void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int r
         run_gemm(c, w.wqkv, qd + 2 * kd, md.d, c->u, md.d, rows_all, c->part, false, e, &rr);
     }
     if (rows_q == 0) return;
-    {
-        AttnSeg as[8];
-        int na = 0;
-        for (const Seg &sg : segs)
-            if (sg.nq > 0) as[na++] = AttnSeg{sg.q0, sg.nq, sg.n_prefix, sg.region_len, sg.kv};
-        // a specialist's pass: splits of at most 512 keys (few rows, its own cache); a tuning override applies to both
-        const int kps = c->attn_keys_per_split ? c->attn_keys_per_split : (drafter ? -512 : 0);
-        launch_attention_batch(md, c->q, rm, as, na, kps, c->attn_sc, c->attn_out, c->st);
+    AttnSeg as[8];
+    int na = 0;
+    for (const Seg &sg : segs)
+        if (sg.nq > 0) as[na++] = AttnSeg{sg.q0, sg.nq, sg.n_prefix, sg.region_len, sg.kv};
+    // a specialist's pass: splits of at most 512 keys (few rows, its own cache); a tuning override applies to both
+    const int kps = c->attn_keys_per_split ? c->attn_keys_per_split : (drafter ? -512 : 0);
+    EpiArgs eo = epi_residual(c, true, nullptr, nullptr, w.mlp_norm);
+    const GemmShape go = gemm_plan(md.dt, rows_q, md.d, qd, c->gemm_target_wgs);
+    RowNorm mlp{};
+    bool mlp_row = false;
+    if (rf.on) {
+        eo.h = rf.h;
+        mlp = row_norm_of(c, rf, go, true, nullptr, w.mlp_norm);
+        mlp_row = row_next_ok(c, mlp, gate_up_rows(md.ffn), EPI_SILU);
+        if (mlp_row) eo.mode = EPI_PLANES;
     }
-    run_gemm(c, w.wo, md.d, qd, c->attn_out, qd, rows_q, c->part, false, epi_residual(c, true, nullptr, nullptr, w.mlp_norm));
+    const AttnMerge am = attention_partials(md, as[0].rows, as[0].n_prefix, as[0].region_len, kps, c->attn_sc);
+    if (na == 1 && as[0].row0 == 0 && gemm_merged_ok(md.dt, go, am)) {           // few rows: the output projection merges the splits itself
+        launch_attention(md, c->q, rows_q, rm, as[0].n_prefix, as[0].region_len, *as[0].kv, kps, c->attn_sc, c->attn_out, c->st, false);
+        const ProfileSlot p = profile_slot(c, md.d, qd);
+        if (!launch_gemm_merged(md.dt, go, w.wo, am, c->part, eo, md.eps, c->st, p.start, p.stop)) c->launch_refused = true;
+    } else {
+        launch_attention_batch(md, c->q, rm, as, na, kps, c->attn_sc, c->attn_out, c->st);
+        run_gemm(c, w.wo, md.d, qd, c->attn_out, qd, rows_q, c->part, false, eo);
+    }
     EpiArgs es{};
     es.mode = EPI_SILU; es.act = c->act; es.F = md.ffn;
     // K unsplit: the stream kernel then applies SiLU * up itself (one tile per workgroup already fills most CUs)
-    run_gemm(c, w.wgu, gate_up_rows(md.ffn), md.d, c->u, md.d, rows_q, c->part, true, es);
+    if (mlp_row) run_gemm_row(c, rf, w.wgu, gate_up_rows(md.ffn), mlp, es);
+    else run_gemm(c, w.wgu, gate_up_rows(md.ffn), md.d, c->u, md.d, rows_q, c->part, true, es);
     EpiArgs ed = epi_residual(c, true, nullptr, h_copy, next_gain);
     ed.h_user = h_user; ed.h_user_rows = h_user_rows;
+    if (rf.on) {
+        ed.h = rf.h;
+        rf.norm = row_norm_of(c, rf, gemm_plan(md.dt, 1, md.d, md.ffn, c->gemm_target_wgs), true, nullptr, next_gain);
+        rf.pending = more && row_next_ok(c, rf.norm, qd + 2 * kd, EPI_ROPE_KV);
+        if (rf.pending) ed.mode = EPI_PLANES;
+    }
     run_gemm(c, w.wdown, md.d, md.ffn, c->act, md.ffn, rows_q, c->part, false, ed);
 }
 
@@ -418,13 +467,14 @@ void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowM
     const ModelDims &md = c->md;
     launch_embed_norm(md, c->embed, tokens_dev, rows, c->layers[0].attn_norm, c->h, c->u, rm.pos, c->inv_freq, c->cs, c->st);
     const int nl = c->cfg.n_layers;
+    RowFlow rf{rows == 1 && md.dt != DT_F32 && !c->taps_user, false, RowNorm{}, c->h};   // (taps read the stream between the layers)
     for (int l = 0; l < nl; ++l) {
         if (c->taps_user)
             launch_copy_rows_f32(c->h, md.d, c->taps_user + (size_t)l * rows * md.d, md.d, rows, md.d, c->st);
         const void *next_gain = l + 1 < nl ? c->layers[l + 1].attn_norm : c->final_norm;
         for (Seg &sg : segs) sg.kv = &c->seq[sg.b].target_kv[l];
-        run_layer(c, c->layers[l], segs, rows, rows, rm, next_gain, l + 1 == nl ? feats_out : nullptr, false, l + 1 == nl ? feat_user : nullptr,
-                  feat_user_rows);
+        run_layer(c, c->layers[l], segs, rows, rows, rm, next_gain, l + 1 == nl ? feats_out : nullptr, rf, l + 1 < nl, false,
+                  l + 1 == nl ? feat_user : nullptr, feat_user_rows);
     }
     if (c->taps_user)
         launch_copy_rows_f32(c->h, md.d, c->taps_user + (size_t)nl * rows * md.d, md.d, rows, md.d, c->st);
@@ -539,10 +589,17 @@ void spec_pass(poss_ctx *c, int s, std::vector<SeqPlan> &plans, int depth_index,
         if (q0_out) q0_out->push_back(q0);
         q0 += p.nq; x0 += nx;
     }
-    run_gemm(c, w.fc_w, md.d, 2 * md.d, c->xin, 2 * md.d, rows_all, c->part, false,
-             epi_residual(c, false, c->cfg.fc_bias ? w.fc_b : nullptr, nullptr, w.layer.attn_norm));
+    const void *bias = c->cfg.fc_bias ? w.fc_b : nullptr;
+    EpiArgs ef = epi_residual(c, false, bias, nullptr, w.layer.attn_norm);
+    RowFlow rf{rows_all == 1 && rows_q == 1 && md.dt != DT_F32, false, RowNorm{}, c->h};
+    if (rf.on) {
+        rf.norm = row_norm_of(c, rf, gemm_plan(md.dt, 1, md.d, 2 * md.d, c->gemm_target_wgs), false, bias, w.layer.attn_norm);
+        rf.pending = row_next_ok(c, rf.norm, (md.hq + 2 * md.hkv) * md.dh, EPI_ROPE_KV);
+        if (rf.pending) ef.mode = EPI_PLANES;
+    }
+    run_gemm(c, w.fc_w, md.d, 2 * md.d, c->xin, 2 * md.d, rows_all, c->part, false, ef);
     RowMeta rm{c->row_pos, c->row_slot, c->row_mask};
-    run_layer(c, w.layer, segs, rows_all, rows_q, rm, c->final_norm, fhat_out, true);
+    run_layer(c, w.layer, segs, rows_all, rows_q, rm, c->final_norm, fhat_out, rf, false, true);
 }
 
 void run_block(poss_ctx *c, const void *Wp, int N, int K, int col0, const void *X, int M, const EpiArgs &e) {

@@ -16,7 +16,7 @@
 // Softmax is online (running max / sum per query row, float32); partial (max, sum, O) per split
 // are merged by a second kernel in fixed order.
 #include "attn_split.h"
-#include "device_utils.h"
+#include "attn_merge.h"
 
 #include <type_traits>
 
@@ -1013,29 +1013,14 @@ __global__ __launch_bounds__(MERGE_THREADS) void attn_merge_kernel(AttnSeqs seqs
     const size_t stride = (size_t)hkv * a.rho_pad;        // rows between consecutive splits
     const size_t row0 = (size_t)kvh * a.rho_pad + rho;
     const float *src = a.o_part + row0 * dh + i, *ml = a.ml_part + row0 * 2;
-    float M = -INFINITY, den = 0.f;
+    float den = 0.f;
     f32x4 num = f32x4{0.f, 0.f, 0.f, 0.f};
-    // a split without visible keys has weight 0 and O = 0; maxima are in the log2 domain
     if constexpr (NR > 0) {
-        float ms[NR], ls[NR];
-        f32x4 v[NR];
-#pragma unroll
-        for (int s = 0; s < NR; ++s) {
-            const int sc = s < n_splits ? s : n_splits - 1;
-            const float2 x = *reinterpret_cast<const float2 *>(ml + (size_t)sc * stride * 2);
-            ms[s] = x.x; ls[s] = x.y;
-            v[s] = *reinterpret_cast<const f32x4 *>(src + (size_t)sc * stride * dh);
-        }
-#pragma unroll
-        for (int s = 0; s < NR; ++s) if (s < n_splits) M = fmaxf(M, ms[s]);
-#pragma unroll
-        for (int s = 0; s < NR; ++s)
-            if (s < n_splits) {
-                const float w = ms[s] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms[s] - M);
-                den += w * ls[s];
-                num += w * v[s];
-            }
+        MergeQuad<NR> mq;
+        mq.load(src, ml, stride, dh, n_splits);
+        mq.merge(n_splits, num, den);
     } else {
+        float M = -INFINITY;
         for (int s = 0; s < n_splits; ++s) M = fmaxf(M, ml[(size_t)s * stride * 2]);
 #pragma unroll 4
         for (int s = 0; s < n_splits; ++s) {
@@ -1158,7 +1143,7 @@ static AttnShape attention_shape(const ModelDims &md, int rows, int n_prefix, in
 template <typename T>
 static void launch_attention_t(const ModelDims &md, const void *q, int rows, const RowMeta &rm, int n_prefix,
                                int region_len, const KVCache &kv, int keys_per_split, const AttnScratch &sc,
-                               void *out, hipStream_t st) {
+                               void *out, hipStream_t st, bool merge) {
     const AttnShape a = attention_shape(md, rows, n_prefix, region_len, keys_per_split);
     const float scale = 1.4426950408889634f / sqrtf((float)md.dh);     // log2(e) / sqrt(dh): scores in the log2 domain
     T *direct = a.n_splits == 1 ? static_cast<T *>(out) : nullptr;
@@ -1180,7 +1165,7 @@ static void launch_attention_t(const ModelDims &md, const void *q, int rows, con
     if (md.dh == 128) POSS_ATTN_DH(128); else POSS_ATTN_DH(64);
 #undef POSS_ATTN_DH
 #undef POSS_ATTN
-    if (a.n_splits > 1) {
+    if (a.n_splits > 1 && merge) {
         AttnSeqs one;
         one.n = 1;
         one.s[0] = AttnSeq{q, rm.mask, direct, sc.o, sc.ml, kv, rows, n_prefix, region_len, a.bps, a.n_splits, a.n_row_groups, a.rho_pad, 0, 0};
@@ -1292,6 +1277,12 @@ void launch_attention_prompt(const ModelDims &md, const void *q, int rows, const
     else launch_attention_prompt_t<f16_t>(md, q, rows, mask, c0, kv, out, st);
 }
 
+AttnMerge attention_partials(const ModelDims &md, int rows, int n_prefix, int region_len, int keys_per_split, const AttnScratch &sc) {
+    if (md.dt == DT_F32) return AttnMerge{nullptr, nullptr, 1, 0, md.hq, md.hkv, md.dh};
+    const AttnShape a = attention_shape(md, rows, n_prefix, region_len, keys_per_split);
+    return AttnMerge{sc.o, sc.ml, a.n_splits, a.rho_pad, md.hq, md.hkv, md.dh};
+}
+
 int attention_splits(int total_keys, int keys_per_split) {
     int bps = keys_per_split / 32; if (bps < 1) bps = 1;
     return ((total_keys + 31) / 32 + bps - 1) / bps;
@@ -1299,7 +1290,7 @@ int attention_splits(int total_keys, int keys_per_split) {
 
 void launch_attention(const ModelDims &md, const void *q, int rows, const RowMeta &rm, int n_prefix,
                       int region_len, const KVCache &kv, int keys_per_split, const AttnScratch &sc,
-                      void *out, hipStream_t st) {
+                      void *out, hipStream_t st, bool merge) {
     if (md.dt == DT_F32) {
         const int keys = n_prefix + region_len;
         const size_t lds = (size_t)(keys < AF32_THREADS ? AF32_THREADS : keys) * sizeof(float);
@@ -1311,9 +1302,9 @@ void launch_attention(const ModelDims &md, const void *q, int rows, const RowMet
         hipLaunchKernelGGL(attn_f32_kernel, dim3(rows, md.hq), dim3(AF32_THREADS), lds, st, qf, md.hq, md.hkv, md.dh, dh2, rm.mask, n_prefix,
                            region_len, kv, scale, of);
     } else if (md.dt == DT_BF16) {
-        launch_attention_t<bf16_t>(md, q, rows, rm, n_prefix, region_len, kv, keys_per_split, sc, out, st);
+        launch_attention_t<bf16_t>(md, q, rows, rm, n_prefix, region_len, kv, keys_per_split, sc, out, st, merge);
     } else {
-        launch_attention_t<f16_t>(md, q, rows, rm, n_prefix, region_len, kv, keys_per_split, sc, out, st);
+        launch_attention_t<f16_t>(md, q, rows, rm, n_prefix, region_len, kv, keys_per_split, sc, out, st, merge);
     }
 }
 

@@ -84,7 +84,7 @@ struct RowMeta {
 // ---------------------------------------------------------------- GEMM with fused epilogue
 // The stream kernel writes split-K partial planes; an epilogue kernel with one workgroup per
 // 128-column tile sums them in split order and applies the fused operation.
-enum { EPI_PLAIN = 0, EPI_ROPE_KV = 1, EPI_RESIDUAL = 2, EPI_SILU = 3, EPI_HEAD = 4 };
+enum { EPI_PLAIN = 0, EPI_ROPE_KV = 1, EPI_RESIDUAL = 2, EPI_SILU = 3, EPI_HEAD = 4, EPI_PLANES = 5 };
 // What the Head GEMM reduces in its own epilogue (EPI_HEAD, 16-bit types, K unsplit): every workgroup owns whole
 // columns of every row, so it leaves, per row, the winner or the k best of its columns instead of (or besides) logits.
 enum { HEAD_ARGMAX = 1, HEAD_TOPK = 2 };
@@ -92,6 +92,7 @@ constexpr int TOPK_MAXK = 16;
 constexpr int TOPK_REC = 2 + 2 * TOPK_MAXK;    // segment record: [max, sum exp(l - max), k values, k indices (as bits)]
 struct EpiArgs {
     int mode;
+    // EPI_PLANES: the partial planes and nothing behind them (16-bit types)
     // EPI_PLAIN: out[m][n] = sum (with out == nullptr and S == 1 plane 0 is the result, row stride Npad)
     float *out; int ld_out;
     // EPI_ROPE_KV: columns are [q heads | k heads | v heads]; rows < rows_q get a rotated query,
@@ -125,6 +126,20 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
 // The same product (EPI_PLAIN, y[m * N + n]) from a row-major matrix of a 16-bit type, at most 128 rows and 16 splits, in one
 // launch: bit for bit what packing it and launch_gemm give.  Returns false, launching nothing, for what it does not take.
 bool launch_gemm_direct(int dt, const GemmShape &g, const void *W, const void *X, float *y, hipStream_t st);
+// One row (plain decoding, the first drafting pass): the residual addition and the RMSNorm that EPI_RESIDUAL describes, formed by every
+// workgroup of the product that reads the normed row, from the planes of the product before.  h_out must not be h.
+struct RowNorm {
+    const float *part; size_t plane; int S;       // planes of the row's sums (a GemmShape's: plane = Mpad * Npad)
+    int d;
+    const void *bias; int residual;
+    const float *h; float *h_out;
+    const void *gain; float eps;
+};
+// The QKV projection (EPI_ROPE_KV) or gate/up (EPI_SILU, K unsplit) of that row: bit for bit launch_residual_norm and launch_gemm.
+// gemm_row_ok: whether this build takes the shape.
+bool gemm_row_ok(int dt, const GemmShape &g, const RowNorm &norm, int mode);
+bool launch_gemm_row(int dt, const GemmShape &g, const void *Wp, const RowNorm &norm, const EpiArgs &epi, hipStream_t st,
+                     hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 // Column tiles ("segments") of an unsplit launch of this shape, i.e. records per row an EPI_HEAD launch writes;
 // head_segments_max bounds it for any row count.
 int gemm_head_segments(const GemmShape &g);
@@ -167,7 +182,16 @@ void launch_copy_rows_f32(const float *src, int ld_src, float *dst, int ld_dst, 
 struct AttnScratch { float *o; float *ml; };  // partial outputs [split][Hq][rows][dh], (m, l) pairs
 void launch_attention(const ModelDims &md, const void *q, int rows, const RowMeta &rm, int n_prefix,
                       int region_len, const KVCache &kv, int keys_per_split, const AttnScratch &sc,
-                      void *out, hipStream_t st);
+                      void *out, hipStream_t st, bool merge = true);
+// Where such a launch with merge == false leaves the rows' splits, for a kernel that merges them itself (n_splits == 1: the rows are
+// in out already).
+struct AttnMerge { const float *o, *ml; int n_splits, rho_pad, hq, hkv, dh; };
+AttnMerge attention_partials(const ModelDims &md, int rows, int n_prefix, int region_len, int keys_per_split, const AttnScratch &sc);
+// The output projection of up to 16 rows straight from their attention splits (16-bit types), then the epilogue EPI_RESIDUAL: bit for bit
+// the merge and launch_gemm (EPI_PLANES: without an epilogue).  Returns false, launching nothing, where the two kernels are the better way (gemm.hip) or not possible.
+bool launch_gemm_merged(int dt, const GemmShape &g, const void *Wp, const AttnMerge &src, float *part, const EpiArgs &epi, float rms_eps,
+                        hipStream_t st, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+bool gemm_merged_ok(int dt, const GemmShape &g, const AttnMerge &src);
 // The same for several sequences whose rows [row0, row0 + rows) share the q / mask / out buffers (segs in row
 // order): one launch for all of them (and one merge), each sequence against its own cache with its own split count.
 // The partial buffers must hold every sequence's slices: row tiles padded per sequence.

@@ -25,7 +25,7 @@
 //     memory, 42 without LDS operand reads as well, of which 31 are the MFMAs at the clock that they then hold, 2.1 GHz; the kernel
 //     itself runs at 1.9, the matrix pipe busy 55 % of its workgroups' time) and the QKV kernels with the epilogue inside (few rows or
 //     small matrices).
-#include "device_utils.h"
+#include "attn_merge.h"
 
 #include <hip/hip_ext.h>
 
@@ -33,7 +33,6 @@
 
 namespace poss {
 
-typedef float  f32x4 __attribute__((ext_vector_type(4)));
 typedef bf16_t bf16x8 __attribute__((ext_vector_type(8)));
 typedef f16_t  f16x8 __attribute__((ext_vector_type(8)));
 
@@ -429,8 +428,98 @@ __global__ __launch_bounds__(WPB * 64) void gemm_stream_kernel(
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int m = mt * 16 + 4 * (lane >> 4) + r;
-                out[(size_t)m * Npad + n0 + nt * 16] = acc[mt][nt][r];
+                if (MT > 1 || m < M) out[(size_t)m * Npad + n0 + nt * 16] = acc[mt][nt][r];   // (rows beyond M are never read)
             }
+}
+
+// ------------------------------------------------------------------------------------------
+// The output projection of up to 16 rows, whose attention splits every workgroup merges for itself: the heads its K split covers, all
+// rows, into LDS in A-operand order, ahead of a loop that has no barrier.  Splits of K, order of the sums and planes are the
+// streaming kernel's, the merge is attn_merge_kernel's: the same bits.  What it saves is a launch (4.8 us); what it costs is that the
+// column tiles of a split repeat the merge (rows x K of the split x splits x 4 bytes a workgroup), which is why it is for few rows.
+// us, product + merge / so: 13B, 1 row of 1024 keys (20 KB) 9.6 + 4.8 / 10.2, 8B, 10 rows of 512 keys (82 KB) 9.0 + 4.9 / 10.9: two of
+// the five for 82 KB, hence the line at 96.  A thread's first quads are asked for ahead of the weights.
+constexpr size_t MERGED_BYTES = (size_t)96 << 10;
+template <typename T, int NR, int QB>                     // QB: quads of a thread at a time
+__global__ __launch_bounds__(256) void gemm_merged_kernel(const u32x4 *__restrict__ Wp, AttnMerge src, float *__restrict__ part, int M, int K,
+                                                          int Npad, int ksteps_total) {
+    constexpr int PF = KCS;                               // weight k-steps in flight
+    struct __attribute__((aligned(8))) Quad { T t[4]; };
+    extern __shared__ __attribute__((aligned(16))) u32x4 xm[];          // [k-step of the split][64]
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int n_chunks_total = ksteps_total / KCS;
+    const int ks0 = (int)blockIdx.y * n_chunks_total / (int)gridDim.y * KCS;
+    const int n_ks = ((int)blockIdx.y + 1) * n_chunks_total / (int)gridDim.y * KCS - ks0;
+    const int ngroup = blockIdx.x * 4 + wave, quads = n_ks * 8, G = src.hq / src.hkv;
+    const size_t stride = (size_t)src.hkv * src.rho_pad;
+    MergeQuad<NR> mq[QB];
+    auto request = [&](int i0) {                          // quads i0 + tid, i0 + 256 + tid, ..: an index beyond the last re-reads it
+#pragma unroll
+        for (int j = 0; j < QB; ++j) {
+            const int i = min(i0 + j * 256 + tid, M * quads - 1), m = i / quads, k = min(ks0 * GEMM_KSTEP + (i % quads) * 4, K - 4);
+            const int qh = k / src.dh;
+            const size_t row = (size_t)(qh / G) * src.rho_pad + m * G + qh % G;
+            mq[j].load(src.o + row * src.dh + k % src.dh, src.ml + row * 2, stride, src.dh, src.n_splits);
+        }
+    };
+    auto finish = [&](int i0) {
+#pragma unroll
+        for (int j = 0; j < QB; ++j) {
+            const int i = i0 + j * 256 + tid, m = i / quads, kq = i % quads, ks = kq >> 3, g = (kq >> 1) & 3;
+            if (i >= M * quads) continue;
+            f32x4 num; float den;
+            mq[j].merge(src.n_splits, num, den);
+            const bool in = ks0 * GEMM_KSTEP + kq * 4 < K;               // (beyond K the weights are zero)
+            Quad o;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o.t[r] = in ? from_f<T>(num[r] / den) : from_f<T>(0.f);
+            *reinterpret_cast<Quad *>(reinterpret_cast<char *>(&xm[ks * 64 + g * 16 + (m ^ xs_swizzle(g))]) + (kq & 1) * 8) = o;
+        }
+    };
+    request(0);
+    __builtin_amdgcn_sched_barrier(0);                    // these loads ahead of the weights
+    const u32x4 *wp = Wp + ((size_t)ngroup * ksteps_total + ks0) * (GEMM_NT * 64) + lane;
+    u32x4 wr[PF][GEMM_NT];
+#pragma unroll
+    for (int p = 0; p < PF; ++p)
+#pragma unroll
+        for (int nt = 0; nt < GEMM_NT; ++nt) wr[p][nt] = __builtin_nontemporal_load(wp + (size_t)p * (GEMM_NT * 64) + nt * 64);
+    __builtin_amdgcn_sched_barrier(0);
+    finish(0);
+    for (int i0 = QB * 256; i0 < M * quads; i0 += QB * 256) { request(i0); finish(i0); }
+    __syncthreads();
+
+    f32x4 acc[GEMM_NT];
+#pragma unroll
+    for (int nt = 0; nt < GEMM_NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const int lane_sw = (lane & 48) + ((lane & 15) ^ xs_swizzle(lane >> 4));
+    auto group = [&](auto more_tag, int g) {              // PF k-steps; the ring is refilled for the next PF
+        constexpr bool MORE = decltype(more_tag)::value;
+        u32x4 a[PF];
+#pragma unroll
+        for (int p = 0; p < PF; ++p) a[p] = xm[(g + p) * 64 + lane_sw];
+#pragma unroll
+        for (int p = 0; p < PF; ++p) {
+#pragma unroll
+            for (int nt = 0; nt < GEMM_NT; ++nt) acc[nt] = Mfma<T>::run(a[p], wr[p][nt], acc[nt]);
+            if constexpr (MORE) {
+#pragma unroll
+                for (int nt = 0; nt < GEMM_NT; ++nt) wr[p][nt] = __builtin_nontemporal_load(wp + (size_t)(g + PF + p) * (GEMM_NT * 64) + nt * 64);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    for (int g = 0; g + PF < n_ks; g += PF) group(std::true_type{}, g);
+    group(std::false_type{}, n_ks - PF);
+    float *out = part + (size_t)blockIdx.y * 16 * Npad;
+    const int n0 = ngroup * (GEMM_NT * 16) + (lane & 15);
+#pragma unroll
+    for (int nt = 0; nt < GEMM_NT; ++nt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int m = 4 * (lane >> 4) + r;
+            if (m < M) out[(size_t)m * Npad + n0 + nt * 16] = acc[nt][r];
+        }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -878,6 +967,183 @@ __global__ __launch_bounds__(256) void gemm_qkv_row_kernel(const u32x4 *__restri
     for (int nt = 0; nt < GEMM_NT; ++nt) red[(wave * GEMM_NT + nt) * 64 + lane] = acc[nt];
     __syncthreads();
     qkv_epilogue<T, 1>(red, 4, gh, pi, M, wave, 4, lane, e, rows);
+}
+
+// ------------------------------------------------------------------------------------------
+// One row: the residual addition and the norm in the product that follows (RowNorm).  As a kernel of its own a row's norm is one
+// workgroup and 5.2 us, half of it the boundary between two launches; here every workgroup adds the planes up for itself (S x d x 4
+// bytes, 100 to 130 KB at the 8B and 13B shapes, out of the L2s) while its first weights are on their way, and keeps the normed row in
+// LDS, where an A fragment of all sixteen rows is one broadcast read: the loop has no staging and no barrier, and 128 KB of weights a CU
+// are in flight.  For two rows the planes would be twice as much and the saving the same.  us, stream + norm / so: 13B gate/up 41.9 + 5.2 /
+// 44.3, QKV 27.7 + 5.2 / 27.3, 8B gate/up 37.7 + 4.5 / 37.0; a pass of one row of the 13B shape through four layers, 1024 keys, with
+// the merge above 631 -> 587.  Groups of four columns, partial sums of squares and their order are epilogue_residual_norm_kernel's
+// (wave v of that kernel is a virtual wave here): the same bits.
+// The groups are dealt out to W waves: slot s < NV of a wave is virtual wave wave + W s (NV = 16 / W), the slots behind those the same
+// virtual waves' second turn (d > 4096); NSL slots are formed, every plane of theirs requested at once (NP planes: slots beyond S re-read
+// the last), ahead of the weights, which `ahead` asks for.
+static __host__ __device__ __forceinline__ int norm_threads(int d) { return min(1024, (d / 4 + 63) / 64 * 64); }
+constexpr int row_slots(int d, int W) { return d <= 4096 ? 16 / W : 16 / W + (d - 4096 + 256 * W - 1) / (256 * W); }
+
+template <typename T, int NP, int NSL, int W, typename Ahead>
+__device__ __forceinline__ void row_norm(const RowNorm &p, T *urow, int Kpad, float *red, int tid, bool writer, Ahead ahead) {
+    struct __attribute__((aligned(4 * sizeof(T)))) Quad { T t[4]; };
+    constexpr int NV = 16 / W;
+    static_assert(NV * W == 16 && NSL >= NV && NSL <= 2 * NV, "slots of one or two turns");
+    const int wave = tid >> 6, lane = tid & 63, threads = norm_threads(p.d), nvw = threads >> 6;
+    const T *bias = static_cast<const T *>(p.bias), *gain = static_cast<const T *>(p.gain);
+    auto column = [&](int s) {
+        const int vw = wave + W * (s % NV), n = ((s / NV) * threads + vw * 64 + lane) * 4;
+        return vw < nvw && n < p.d ? n : -1;
+    };
+    f32x4 v[NSL][NP], add[NSL];
+    Quad bq[NSL], gq[NSL];
+#pragma unroll
+    for (int j = 0; j < NSL; ++j) {
+        const int n = max(column(j), 0);                  // (a slot without columns reads the first ones and drops them)
+#pragma unroll
+        for (int s = 0; s < NP; ++s) v[j][s] = *reinterpret_cast<const f32x4 *>(p.part + (size_t)min(s, p.S - 1) * p.plane + n);
+        add[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if (p.residual) add[j] = *reinterpret_cast<const f32x4 *>(p.h + n);
+        if (bias) bq[j] = *reinterpret_cast<const Quad *>(bias + n);
+        gq[j] = *reinterpret_cast<const Quad *>(gain + n);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    ahead();
+    __builtin_amdgcn_sched_barrier(0);
+    f32x4 x[NSL];
+#pragma unroll
+    for (int j = 0; j < NSL; ++j) {
+        f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < NP; ++s) if (s < p.S) a += v[j][s];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) if (bias) add[j][r] += to_f(bq[j].t[r]);
+        x[j] = a + add[j];
+        const int n = column(j);
+        if (writer && n >= 0) *reinterpret_cast<f32x4 *>(p.h_out + n) = x[j];
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        float ss = 0.f;
+#pragma unroll
+        for (int s = j; s < NSL; s += NV)
+            if (column(s) >= 0)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) ss = fmaf(x[s][r], x[s][r], ss);
+        ss = wave_sum(ss);
+        if (lane == 0 && wave + W * j < nvw) red[wave + W * j] = ss;
+    }
+    for (int k = p.d + tid; k < Kpad; k += W * 64) urow[k] = from_f<T>(0.f);    // beyond K the weights are zero
+    __syncthreads();
+    float sum = 0.f;
+    for (int i = 0; i < nvw; ++i) sum += red[i];
+    const float rs = 1.0f / sqrtf(sum / (float)p.d + p.eps);
+#pragma unroll
+    for (int j = 0; j < NSL; ++j) {
+        const int n = column(j);
+        if (n < 0) continue;
+        Quad o;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o.t[r] = mul_round<T>(x[j][r] * rs, to_f(gq[j].t[r]));
+        *reinterpret_cast<Quad *>(urow + n) = o;
+    }
+    __syncthreads();
+}
+
+// The products of a wave: its NTW column tiles, k-steps [0, n_w) of its stream (whole groups of 8), the row's fragments from LDS.  16 / NTW
+// k-steps are in flight, the first of them asked for ahead; k-steps beyond the last repeat it.
+constexpr int ROW_PF(int ntw) { return 16 / ntw; }
+template <int NTW>
+__device__ __forceinline__ void row_fetch(const u32x4 *__restrict__ wp, int ks, int n_w, u32x4 (&w)[NTW]) {
+    const u32x4 *src = wp + (size_t)min(ks, n_w - 1) * (GEMM_NT * 64);
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt) w[nt] = __builtin_nontemporal_load(src + nt * 64);
+}
+template <typename T, int NTW>
+__device__ __forceinline__ void row_products(const u32x4 *__restrict__ wp, int n_w, const u32x4 *frag, u32x4 (&wr)[ROW_PF(NTW)][NTW], f32x4 (&acc)[NTW]) {
+    constexpr int PF = ROW_PF(NTW);
+    auto group = [&](auto more_tag, auto steps_tag, int g) {
+        constexpr bool MORE = decltype(more_tag)::value;
+        constexpr int STEPS = decltype(steps_tag)::value;
+        u32x4 a[STEPS];
+#pragma unroll
+        for (int p = 0; p < STEPS; ++p) a[p] = frag[(g + p) * 4];
+#pragma unroll
+        for (int p = 0; p < STEPS; ++p) {
+#pragma unroll
+            for (int nt = 0; nt < NTW; ++nt) acc[nt] = Mfma<T>::run(a[p], wr[p][nt], acc[nt]);
+            if constexpr (MORE) row_fetch<NTW>(wp, g + PF + p, n_w, wr[p]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int g = 0;
+    for (; g + PF < n_w; g += PF) group(std::true_type{}, std::integral_constant<int, PF>{}, g);
+    if (n_w - g == PF) group(std::false_type{}, std::integral_constant<int, PF>{}, g);
+    else group(std::false_type{}, std::integral_constant<int, KCS>{}, g);       // (PF = 16 and 8 k-steps left)
+}
+
+// gate/up, K unsplit: a 128-column tile per workgroup, a 16-column tile per wave.  The gate and the up of a unit then lie in two waves
+// and meet in LDS.
+constexpr int ROW_SILU_WAVES = 8, ROW_QKV_WAVES = 4;
+template <typename T, int NP, int NSL>
+__global__ __launch_bounds__(ROW_SILU_WAVES * 64) void gemm_row_silu_kernel(const u32x4 *__restrict__ Wp, RowNorm norm, int ksteps_total,
+                                                                            T *__restrict__ act, int F) {
+    constexpr int PF = ROW_PF(1);
+    extern __shared__ __attribute__((aligned(16))) u32x4 rlds[];        // the row
+    __shared__ float red[17], ups[64];
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, ngroup = blockIdx.x * 4 + (wave >> 1), nt = wave & 1;
+    const u32x4 *wp = Wp + (size_t)ngroup * ksteps_total * (GEMM_NT * 64) + nt * 64 + lane;
+    u32x4 wr[PF][1];
+    row_norm<T, NP, NSL, ROW_SILU_WAVES>(norm, reinterpret_cast<T *>(rlds), ksteps_total * GEMM_KSTEP, red, tid, blockIdx.x == 0, [&] {
+#pragma unroll
+        for (int p = 0; p < PF; ++p) row_fetch<1>(wp, p, ksteps_total, wr[p]);
+    });
+    f32x4 acc[1] = {f32x4{0.f, 0.f, 0.f, 0.f}};
+    row_products<T, 1>(wp, ksteps_total, rlds + (lane >> 4), wr, acc);
+    if (nt == 1 && lane < 16) ups[(wave >> 1) * 16 + lane] = acc[0][0];        // D tile: row 0 is register 0 of lanes 0 .. 15
+    __syncthreads();
+    const int f = ngroup * 16 + lane;
+    if (nt == 0 && lane < 16 && f < F) {
+        const float g = acc[0][0];
+        act[f] = mul_round<T>(g / (1.0f + expf(-g)), ups[(wave >> 1) * 16 + lane]);
+    }
+}
+
+// The QKV projection, a 32-column tile per workgroup, K split inside it: four splits, a wave each, or (NTW = 1) one or two, a pair of
+// waves each, which take a 16-column tile (one split: the other pair only norms).
+template <typename T, int NP, int NSL, int NTW>
+__global__ __launch_bounds__(ROW_QKV_WAVES * 64, 2) void gemm_row_qkv_kernel(const u32x4 *__restrict__ Wp, RowNorm norm, int ksteps_total, QkvEpi e, int S) {
+    constexpr int PF = ROW_PF(NTW);
+    extern __shared__ __attribute__((aligned(16))) u32x4 rlds[];        // the row; at the end [split][GEMM_NT][64] partial tiles
+    __shared__ float red[17];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, tile = blockIdx.x;
+    const int split = min(NTW == GEMM_NT ? wave : wave >> 1, S - 1), nt0 = NTW == GEMM_NT ? 0 : wave & 1;
+    const bool multiplies = NTW == GEMM_NT || (wave >> 1) < S;          // (wave-uniform)
+    const int n_chunks = ksteps_total / KCS, k0 = split * n_chunks / S * KCS, n_w = (split + 1) * n_chunks / S * KCS - k0;
+    const u32x4 *wp = Wp + ((size_t)tile * ksteps_total + k0) * (GEMM_NT * 64) + nt0 * 64 + lane;
+    u32x4 wr[PF][NTW];
+    row_norm<T, NP, NSL, ROW_QKV_WAVES>(norm, reinterpret_cast<T *>(rlds), ksteps_total * GEMM_KSTEP, red, tid, blockIdx.x == 0, [&] {
+#pragma unroll
+        for (int p = 0; p < PF; ++p) row_fetch<NTW>(wp, p, n_w, wr[p]);
+    });
+    f32x4 acc[NTW];
+#pragma unroll
+    for (int nt = 0; nt < NTW; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (multiplies) row_products<T, NTW>(wp, n_w, rlds + k0 * 4 + (lane >> 4), wr, acc);
+    const int tph = e.dh >> 5, gh = tile / tph, pi = (tile % tph) * 16 + (lane & 15);
+    QkvRows rows;
+    if (wave == 0) {
+        qkv_rows(e, gh, pi, 0, 1, lane, rows);
+        qkv_pages(e, gh, rows);
+    }
+    __syncthreads();                                      // every wave has read its fragments
+    f32x4 *tiles = reinterpret_cast<f32x4 *>(rlds);
+    if (multiplies) {
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt) tiles[(split * GEMM_NT + nt0 + nt) * 64 + lane] = acc[nt];
+    }
+    __syncthreads();
+    qkv_epilogue<T, 1>(tiles, S, gh, pi, 1, wave, ROW_QKV_WAVES, lane, e, rows);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1369,6 +1635,7 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
             break;
         }
         case EPI_HEAD: break;           // reduced inside the stream kernel
+        case EPI_PLANES: break;
         case EPI_SILU:
             if constexpr (!std::is_same<T, float>::value)               // (float32: inside gemm_f32_kernel)
                 if (!silu_done)         // otherwise applied inside the stream kernel
@@ -1534,6 +1801,7 @@ static bool gemm_args_ok(int dt, const GemmShape &g, const void *Wp, const void 
         case EPI_ROPE_KV:                                  // caches: checked per range
             return e.q && e.cs && e.slot && (dt == DT_F32 ? e.dh >= 32 && e.dh % 32 == 0 : e.dh == 64 || e.dh == 128);
         case EPI_RESIDUAL: return e.h && (!e.gain || e.u);
+        case EPI_PLANES: return dt != DT_F32;
         case EPI_SILU: return e.act != nullptr;
         case EPI_HEAD:
             if (g.S != 1 || g.N < 1) return false;
@@ -1591,6 +1859,99 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
     } else {
         launch_gemm_t<f16_t>(g, Wp, X, ldx, part, epi, eps, st, ev_start, ev_stop, epi.mode == EPI_ROPE_KV ? &rr : nullptr);
     }
+    return true;
+}
+
+static int longest_split(const GemmShape &g) { return (g.Kpad / GEMM_KCHUNK + g.S - 1) / g.S * GEMM_KCHUNK; }
+
+bool gemm_merged_ok(int dt, const GemmShape &g, const AttnMerge &src) {
+    const int k = longest_split(g);
+    return dt != DT_F32 && g.M >= 1 && g.M <= 16 && src.n_splits >= 2 && src.n_splits <= 12 && k <= 4096 && g.K == src.hq * src.dh &&
+           (size_t)g.M * k * src.n_splits * 4 <= MERGED_BYTES;
+}
+
+bool launch_gemm_merged(int dt, const GemmShape &g, const void *Wp, const AttnMerge &src, float *part, const EpiArgs &epi, float eps,
+                        hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
+    if (!gemm_merged_ok(dt, g, src) || !src.o || !src.ml || (epi.mode != EPI_RESIDUAL && epi.mode != EPI_PLANES) ||
+        !gemm_args_ok(dt, g, Wp, src.o, part, epi)) return false;
+    dim3 grid(g.Npad / GEMM_BLOCK_N, g.S);
+    const size_t lds = (size_t)longest_split(g) / GEMM_KSTEP * 1024;
+    const int ksteps = g.Kpad / GEMM_KSTEP;
+    const u32x4 *w = static_cast<const u32x4 *>(Wp);
+#define POSS_MERGED(T, NR, QB)                                                                                               \
+    do {                                                                                                                     \
+        if (ev_start && ev_stop)                                                                                             \
+            hipExtLaunchKernelGGL((gemm_merged_kernel<T, NR, QB>), grid, dim3(256), lds, st, ev_start, ev_stop, 0, w, src, part, g.M, g.K, g.Npad, ksteps); \
+        else                                                                                                                 \
+            hipLaunchKernelGGL((gemm_merged_kernel<T, NR, QB>), grid, dim3(256), lds, st, w, src, part, g.M, g.K, g.Npad, ksteps); \
+    } while (0)
+#define POSS_MERGED_T(T)                                                                                                     \
+    do {                                                                                                                     \
+        if (src.n_splits <= 4) { if (one) POSS_MERGED(T, 4, 1); else POSS_MERGED(T, 4, 4); }                                 \
+        else if (src.n_splits <= 8) { if (one) POSS_MERGED(T, 8, 1); else POSS_MERGED(T, 8, 2); }                            \
+        else POSS_MERGED(T, 12, 1);                                                                                          \
+    } while (0)
+    const bool one = g.M * longest_split(g) <= 4 * 256;   // a quad per thread
+    if (dt == DT_BF16) { POSS_MERGED_T(bf16_t); launch_epilogue_t<bf16_t>(g, part, epi, eps, false, st); }
+    else { POSS_MERGED_T(f16_t); launch_epilogue_t<f16_t>(g, part, epi, eps, false, st); }
+#undef POSS_MERGED_T
+#undef POSS_MERGED
+    return true;
+}
+
+// d up to 5120 (QKV) and 6144 (gate/up): a wave's slots times its planes have to fit its registers.
+bool gemm_row_ok(int dt, const GemmShape &g, const RowNorm &norm, int mode) {
+    if (dt == DT_F32 || g.M != 1 || g.K != norm.d || norm.d % 4 || norm.S < 1 || norm.S > (norm.d <= 4096 ? 8 : 6)) return false;
+    if (mode == EPI_SILU) return norm.d <= 6144 && g.S == 1;
+    return mode == EPI_ROPE_KV && norm.d <= 5120 && qkv_fused(g) && g.S != 3;
+}
+
+bool launch_gemm_row(int dt, const GemmShape &g, const void *Wp, const RowNorm &norm, const EpiArgs &epi, hipStream_t st,
+                     hipEvent_t ev_start, hipEvent_t ev_stop) {
+    if (!gemm_row_ok(dt, g, norm, epi.mode) || !norm.part || !norm.h_out || norm.h_out == norm.h || !norm.gain || (norm.residual && !norm.h) ||
+        !gemm_args_ok(dt, g, Wp, norm.part, const_cast<float *>(norm.part), epi)) return false;
+    const int ksteps = g.Kpad / GEMM_KSTEP;
+    const u32x4 *w = static_cast<const u32x4 *>(Wp);
+    size_t lds = (size_t)ksteps * GEMM_KSTEP * 2;
+    QkvEpi qe{};
+    if (epi.mode == EPI_ROPE_KV) {
+        qe = QkvEpi{epi.cs, epi.slot, epi.q, epi.hq, epi.hkv, epi.dh, RopeRanges{}};
+        qe.rr.n = 1; qe.rr.r0[0] = 0; qe.rr.r1[0] = 1; qe.rr.rows_q[0] = epi.rows_q; qe.rr.kv[0] = epi.kv;
+        if (!ranges_ok(g, qe.rr)) return false;
+        lds = max(lds, (size_t)g.S * GEMM_NT * 64 * sizeof(f32x4));
+    }
+#define POSS_ROW(KERNEL, GRID, THREADS, ...)                                                                                 \
+    do {                                                                                                                     \
+        if (ev_start && ev_stop) hipExtLaunchKernelGGL(KERNEL, dim3(GRID), dim3(THREADS), lds, st, ev_start, ev_stop, 0, w, norm, ksteps, __VA_ARGS__); \
+        else hipLaunchKernelGGL(KERNEL, dim3(GRID), dim3(THREADS), lds, st, w, norm, ksteps, __VA_ARGS__);                   \
+    } while (0)
+#define POSS_ROW_SILU(T, NP, NSL) POSS_ROW((gemm_row_silu_kernel<T, NP, NSL>), g.Npad / GEMM_BLOCK_N, ROW_SILU_WAVES * 64, static_cast<T *>(epi.act), epi.F)
+#define POSS_ROW_QKV(T, NP, NSL)                                                                                             \
+    do {                                                                                                                     \
+        if (g.S == QKV_MAX_SPLITS) POSS_ROW((gemm_row_qkv_kernel<T, NP, NSL, GEMM_NT>), g.Npad / (GEMM_NT * 16), ROW_QKV_WAVES * 64, qe, g.S); \
+        else POSS_ROW((gemm_row_qkv_kernel<T, NP, NSL, 1>), g.Npad / (GEMM_NT * 16), ROW_QKV_WAVES * 64, qe, g.S);           \
+    } while (0)
+#define POSS_ROW_T(T)                                                                                                        \
+    do {                                                                                                                     \
+        if (epi.mode == EPI_SILU) {                                                                                          \
+            static_assert(row_slots(4096, ROW_SILU_WAVES) == 2 && row_slots(6144, ROW_SILU_WAVES) == 3, "");                 \
+            if (norm.d > 4096) { if (norm.S <= 4) POSS_ROW_SILU(T, 4, 3); else POSS_ROW_SILU(T, 6, 3); }                     \
+            else if (norm.S <= 2) POSS_ROW_SILU(T, 2, 2);                                                                    \
+            else if (norm.S <= 4) POSS_ROW_SILU(T, 4, 2);                                                                    \
+            else POSS_ROW_SILU(T, 8, 2);                                                                                     \
+        } else {                                                                                                             \
+            static_assert(row_slots(4096, ROW_QKV_WAVES) == 4 && row_slots(5120, ROW_QKV_WAVES) == 5, ""); \
+            if (norm.d > 4096) { if (norm.S <= 4) POSS_ROW_QKV(T, 4, 5); else POSS_ROW_QKV(T, 6, 5); }                  \
+            else if (norm.S <= 2) POSS_ROW_QKV(T, 2, 4);                                                                     \
+            else if (norm.S <= 4) POSS_ROW_QKV(T, 4, 4);                                                                     \
+            else POSS_ROW_QKV(T, 8, 4);                                                                                      \
+        }                                                                                                                    \
+    } while (0)
+    if (dt == DT_BF16) POSS_ROW_T(bf16_t); else POSS_ROW_T(f16_t);
+#undef POSS_ROW_T
+#undef POSS_ROW_QKV
+#undef POSS_ROW_SILU
+#undef POSS_ROW
     return true;
 }
 

@@ -208,3 +208,36 @@ def test_projections_at_the_line_between_the_two_kernels(d_model, heads, rows):
         k, v = pair.ctx.debug_read_kv(-1, 0, 0, n)
         assert np.array_equal(k, want_k[:n]) and np.array_equal(v, want_v[:n]), n
     pair.close()
+
+
+@pytest.mark.parametrize("name,over", [
+    ("t_mid_bf16", dict()),                                                                   # one K split of QKV
+    ("t_mid_f16", dict()),                                                                    # K padded to whole chunks
+    ("t_mid_bf16", dict(d_model=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, d_ffn=1000)),  # two splits, units that end inside a tile
+    ("t_mid_f16", dict(d_model=1536, n_q_heads=12, n_kv_heads=4, d_ffn=1544)),                # three: the norm stays a kernel
+    ("t_mid_bf16", dict(d_model=2048, n_q_heads=16, n_kv_heads=2, head_dim=128)),             # four, a wave each
+    ("t_mid_f16", dict(d_model=4224, n_q_heads=4, n_kv_heads=1, d_ffn=4000)),                 # a second turn of the norm's groups
+])
+def test_one_row_has_the_bits_of_a_tree_row(name, over):
+    """A pass of one row forms its norms and merges its attention splits inside the products; a row of a wider tree (17 rows and more:
+    neither) goes through kernels of their own.  Same logits and features, bit for bit, from one attention split to more than the
+    merge inside takes; 2 and 16 rows (merge inside, norms not) as well."""
+    over = dict(over, n_layers=2, vocab=1000, max_seq=4096, n_specialists=1)
+    pair = Pair(name, **over)
+    cfg, ctx = pair.cfg, pair.ctx
+    rs = np.random.RandomState(5)
+    wide = [0] + [int(x) for x in rs.permutation(1000)[:16]]
+    for n_prompt in (20, 300, 600, 1300, 2500):
+        prompt, got = rs.randint(0, 1000, n_prompt).astype(np.int32), []
+        for rows in (17, 1, 2, 16):
+            ctx.reset()
+            ctx.prefill(prompt)
+            logits, feats = torch.zeros(rows, 1000, device="cuda"), torch.zeros(rows, cfg.d_model, device="cuda")
+            ctx.verify_tree(P.TreeArrays.from_lists(wide[:rows], [-1] + [0] * (rows - 1)), logits_out=logits, feat_out=feats)
+            got.append((logits, feats))
+        torch.cuda.synchronize()
+        for logits, feats in got[1:]:
+            n = logits.shape[0]
+            assert torch.equal(logits, got[0][0][:n]) and torch.equal(feats, got[0][1][:n]), (n_prompt, n)
+        assert torch.isfinite(got[0][0]).all()
+    pair.close()
