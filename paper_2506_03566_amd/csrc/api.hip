@@ -353,12 +353,18 @@ GemmShape run_gemm(poss_ctx *c, const void *Wp, int N, int K, const void *X, int
     return g;
 }
 
-// h (+)= GEMM (+ bias), then u = T(rmsnorm(h) * gain) for the next GEMM
+// h (+)= GEMM (+ bias), then u = T(rmsnorm(h) * gain) for the next GEMM (float32 storage: the next GEMM does that, normed_input)
 EpiArgs epi_residual(poss_ctx *c, bool residual, const void *bias, float *h_copy, const void *gain) {
     EpiArgs e{};
     e.mode = EPI_RESIDUAL; e.h = c->h; e.bias = bias; e.residual = residual ? 1 : 0; e.h_copy = h_copy;
-    e.gain = gain; e.u = c->u;
+    e.gain = c->md.dt == DT_F32 ? nullptr : gain; e.u = c->u;
     return e;
+}
+// The operand of a product that reads T(rmsnorm(h) * gain): c->u, or in float32 storage the residual stream itself, which the product norms.
+const void *normed_input(poss_ctx *c, const void *gain, EpiArgs *e) {
+    if (c->md.dt != DT_F32) return c->u;
+    e->x_gain = gain;
+    return c->h;
 }
 
 // The rows of one sequence inside a pass: full rows [q0, q0 + nq) (query, attention, MLP) and
@@ -405,7 +411,8 @@ void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int r
     if (rf.pending) {
         run_gemm_row(c, rf, w.wqkv, qd + 2 * kd, rf.norm, e);
     } else if (one) {
-        run_gemm(c, w.wqkv, qd + 2 * kd, md.d, c->u, md.d, rows_all, c->part, false, e);
+        const void *x = normed_input(c, w.attn_norm, &e);
+        run_gemm(c, w.wqkv, qd + 2 * kd, md.d, x, md.d, rows_all, c->part, false, e);
     } else {
         // one weight stream for every sequence, each sequence's rows into its own cache
         RopeRanges rr;
@@ -414,7 +421,8 @@ void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int r
             if (sg.nq > 0) { rr.r0[rr.n] = sg.q0; rr.r1[rr.n] = sg.q0 + sg.nq; rr.rows_q[rr.n] = sg.q0 + sg.nq; rr.kv[rr.n] = *sg.kv; ++rr.n; }
             if (sg.nx > 0) { rr.r0[rr.n] = sg.x0; rr.r1[rr.n] = sg.x0 + sg.nx; rr.rows_q[rr.n] = 0; rr.kv[rr.n] = *sg.kv; ++rr.n; }
         }
-        run_gemm(c, w.wqkv, qd + 2 * kd, md.d, c->u, md.d, rows_all, c->part, false, e, &rr);
+        const void *x = normed_input(c, w.attn_norm, &e);
+        run_gemm(c, w.wqkv, qd + 2 * kd, md.d, x, md.d, rows_all, c->part, false, e, &rr);
     }
     if (rows_q == 0) return;
     AttnSeg as[8];
@@ -445,8 +453,12 @@ void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int r
     EpiArgs es{};
     es.mode = EPI_SILU; es.act = c->act; es.F = md.ffn;
     // K unsplit: the stream kernel then applies SiLU * up itself (one tile per workgroup already fills most CUs)
-    if (mlp_row) run_gemm_row(c, rf, w.wgu, gate_up_rows(md.ffn), mlp, es);
-    else run_gemm(c, w.wgu, gate_up_rows(md.ffn), md.d, c->u, md.d, rows_q, c->part, true, es);
+    if (mlp_row) {
+        run_gemm_row(c, rf, w.wgu, gate_up_rows(md.ffn), mlp, es);
+    } else {
+        const void *x = normed_input(c, w.mlp_norm, &es);
+        run_gemm(c, w.wgu, gate_up_rows(md.ffn), md.d, x, md.d, rows_q, c->part, true, es);
+    }
     EpiArgs ed = epi_residual(c, true, nullptr, h_copy, next_gain);
     ed.h_user = h_user; ed.h_user_rows = h_user_rows;
     if (rf.on) {
@@ -480,16 +492,19 @@ void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowM
         launch_copy_rows_f32(c->h, md.d, c->taps_user + (size_t)nl * rows * md.d, md.d, rows, md.d, c->st);
 }
 
-// Head(features) for the rows whose final-normed activations start at x (default: c->u).  head_mode 0: the logits,
+// Head(features) for the rows of c->u (float32 storage: c->h, which the product norms) from row0 on.  head_mode 0: the logits,
 // c->logits[rows][Npad].  HEAD_ARGMAX / HEAD_TOPK (16-bit storage): the GEMM reduces its own column tiles into
 // c->topk_scratch - per row and tile the best (value, index), or the record of the k best with the tile's maximum and
 // sum of exponentials - and writes logits only where asked, those of the first user_rows rows to user_logits[row][vocab];
-// *n_seg_out receives the number of tiles.  Float32 storage has no such epilogue: it always writes c->logits and reports 0 tiles.
-GemmShape run_head(poss_ctx *c, int rows, int head_mode, float *user_logits, int user_rows, int *n_seg_out, const void *x = nullptr,
+// *n_seg_out receives the number of tiles.  Float32 storage has no such epilogue: it writes c->logits, or user_logits where that takes
+// every row, and reports 0 tiles.
+GemmShape run_head(poss_ctx *c, int rows, int head_mode, float *user_logits, int user_rows, int *n_seg_out, int row0 = 0,
                    float *logits_dst = nullptr) {
     EpiArgs e{};
     e.mode = EPI_PLAIN;
+    const char *x = static_cast<const char *>(normed_input(c, c->final_norm, &e)) + (size_t)row0 * c->md.d * dtype_size(c->md.dt);
     if (n_seg_out) *n_seg_out = 0;
+    if (c->md.dt == DT_F32 && user_logits && user_rows >= rows) { e.out = user_logits; e.ld_out = c->md.vocab; }
     if (head_mode && c->md.dt != DT_F32) {
         const GemmShape g0 = gemm_plan(c->md.dt, rows, c->md.vocab, c->md.d, 1);
         const int n_seg = gemm_head_segments(g0);
@@ -498,7 +513,7 @@ GemmShape run_head(poss_ctx *c, int rows, int head_mode, float *user_logits, int
         e.pv = c->topk_scratch; e.pi = reinterpret_cast<int *>(c->topk_scratch + (size_t)rows * n_seg);
         if (n_seg_out) *n_seg_out = n_seg;
     }
-    return run_gemm(c, c->lm_head, c->md.vocab, c->md.d, x ? x : c->u, c->md.d, rows, logits_dst ? logits_dst : c->logits, true, e);
+    return run_gemm(c, c->lm_head, c->md.vocab, c->md.d, x, c->md.d, rows, logits_dst ? logits_dst : c->logits, true, e);
 }
 
 // The drafter's k best next tokens and their log-probabilities for `rows` rows of final-normed activations in c->u.
@@ -510,7 +525,7 @@ void run_head_topk(poss_ctx *c, int rows, int depth) {
         const int V = c->cfg.vocab;
         const size_t row0 = depth == 1 ? 0 : 1 + (size_t)(depth - 2) * k;
         float *dst = c->dlogits + row0 * gemm_npad(V);
-        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, nullptr, dst);
+        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, 0, dst);
         const DrawMasses m{c->draft_m.mass + row0 * gemm_npad(V), c->draft_m.bsum + row0 * draw_bsum_floats(1, V), c->draft_m.mx + row0,
                            c->draft_m.pm + row0 * draw_pm_floats(1, V), c->draft_m.z + row0};
         c->draft_m_temperature = c->temperature;
@@ -937,7 +952,7 @@ void poss_free(poss_ctx *c) {
 
 const char *poss_last_error(poss_ctx *c) { return c ? c->err : g_load_error; }
 
-static int head_and_choose(poss_ctx *c, const void *x, int rows, float *user_logits, int user_rows, const int32_t *depth,
+static int head_and_choose(poss_ctx *c, int x_row0, int rows, float *user_logits, int user_rows, const int32_t *depth,
                            const int *seq_ids, int n_seq, const int *row0, const int *n_rows, int base, int *ld_out, bool drafted_tree = false);
 
 int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_prompt, int32_t *first_token_out) {
@@ -973,9 +988,8 @@ int poss_prefill_seq(poss_ctx *c, int32_t seq, const int32_t *prompt, int32_t n_
             stash_rows(c, sq, rows, c0);
         }
         if (c0 + rows == n_prompt) {
-            // Head on the last row only: its normed activations sit at row rows-1 of c->u
-            const char *last = static_cast<const char *>(c->u) + (size_t)(rows - 1) * md.d * dtype_size(md.dt);
-            { const int zero = 0, one = 1, id = seq; int rc = head_and_choose(c, last, 1, nullptr, 0, nullptr, &id, 1, &zero, &one, 0, nullptr); if (rc) return rc; }
+            // Head on the last row only
+            { const int zero = 0, one = 1, id = seq; int rc = head_and_choose(c, rows - 1, 1, nullptr, 0, nullptr, &id, 1, &zero, &one, 0, nullptr); if (rc) return rc; }
             HIP_TRY(c, hipMemcpyAsync(sq.tokens_dev + n_prompt, c->argmax_dev, sizeof(int32_t), hipMemcpyDeviceToDevice, c->st));
         }
         HIP_TRY(c, hipStreamSynchronize(c->st));          // the staging buffer is reused by the next chunk
@@ -999,19 +1013,19 @@ int poss_prefill(poss_ctx *c, const int32_t *prompt, int32_t n_prompt, int32_t *
     return poss_prefill_seq(c, 0, prompt, n_prompt, first_token_out);
 }
 
-// Head over `rows` rows of final-normed activations at x (nullptr: c->u), then the token the target chooses after
+// Head over `rows` rows of the pass from x_row0 on, then the token the target chooses after
 // each: the argmax - reduced per column tile inside the Head GEMM, logits written only for the first user_rows rows, to
 // user_logits if that is given - or at
 // temperature > 0 a draw by inverse CDF with the uniform number of the row's depth (depth == nullptr: all rows use u[0]).
 // Sequence seq_ids[i] owns rows [row0[i], row0[i] + n_rows[i]) and has its own numbers; the rows' depths and results
 // sit `base` rows further on in the batch-wide arrays (the rows of earlier groups).  *ld_out: row stride of c->logits, 0 where
 // the logits asked for are at user_logits already.
-static int head_and_choose(poss_ctx *c, const void *x, int rows, float *user_logits, int user_rows, const int32_t *depth,
+static int head_and_choose(poss_ctx *c, int x_row0, int rows, float *user_logits, int user_rows, const int32_t *depth,
                            const int *seq_ids, int n_seq, const int *row0, const int *n_rows, int base, int *ld_out, bool drafted_tree) {
     if (c->temperature > 0.f && c->draft_sampling && drafted_tree) {
         // drawn children: the rejection walk over the target's and the drafter's logits writes the path as the g[] of a
         // greedy walk (g[node] = next token on the path), which is what the commit kernel follows
-        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, x);
+        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, x_row0);
         if (ld_out) *ld_out = g.Npad;
         const poss_config &cf = c->cfg;
         HIP_TRY(c, hipMemcpyAsync(c->ua_dev, c->ua_pinned, (size_t)(cf.depth + 1) * (cf.top_k + 1) * sizeof(float), hipMemcpyHostToDevice, c->st));
@@ -1025,7 +1039,7 @@ static int head_and_choose(poss_ctx *c, const void *x, int rows, float *user_log
         return POSS_OK;
     }
     if (c->temperature > 0.f) {
-        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, x);
+        const GemmShape g = run_head(c, rows, 0, nullptr, 0, nullptr, x_row0);
         if (ld_out) *ld_out = g.Npad;
         const int nu = POSS_MAX_DEPTH + 1, ld = g.Npad;
         HIP_TRY(c, hipMemcpyAsync(c->u_dev, c->u_pinned, (size_t)c->B * nu * sizeof(float), hipMemcpyHostToDevice, c->st));
@@ -1037,14 +1051,16 @@ static int head_and_choose(poss_ctx *c, const void *x, int rows, float *user_log
         return POSS_OK;
     }
     int n_seg = 0;
-    const GemmShape g = run_head(c, rows, HEAD_ARGMAX, user_logits, user_rows, &n_seg, x);
-    if (ld_out) *ld_out = n_seg ? 0 : g.Npad;
+    const GemmShape g = run_head(c, rows, HEAD_ARGMAX, user_logits, user_rows, &n_seg, x_row0);
+    const bool direct = c->md.dt == DT_F32 && user_logits && user_rows >= rows;  // the caller's array holds them already
+    if (ld_out) *ld_out = n_seg || direct ? 0 : g.Npad;
     int32_t *host = base == 0 ? c->argmax_host_dev : nullptr;     // (at most LAUNCH_ROWS rows)
     if (n_seg)
         launch_argmax_merge(c->topk_scratch, reinterpret_cast<const int *>(c->topk_scratch + (size_t)rows * n_seg), n_seg, rows,
                             c->argmax_dev + base, host, c->st);
     else
-        launch_argmax(c->logits, g.Npad, rows, c->cfg.vocab, c->topk_scratch, c->argmax_dev + base, host, c->st);
+        launch_argmax(direct ? user_logits : c->logits, direct ? c->cfg.vocab : g.Npad, rows, c->cfg.vocab, c->topk_scratch, c->argmax_dev + base, host,
+                      c->st);
     return POSS_OK;
 }
 
@@ -1325,7 +1341,7 @@ int poss_verify_tree(poss_ctx *c, const poss_tree *tree, int32_t *argmax_out, vo
         float *lg = i0 == 0 ? static_cast<float *>(logits_out) : nullptr;
         target_forward(c, grows, c->tree_token_all + base, rm, segs, c->feats + (size_t)base * cf.d_model, i0 == 0 && feat_direct ? static_cast<float *>(feat_out) : nullptr, n);
         int ld = 0;
-        { int rc = head_and_choose(c, nullptr, grows, lg, n, c->tree_depth_all, act.data() + i0, i1 - i0, rel0, n_rows + i0, base, &ld, tree == nullptr); if (rc) return rc; }
+        { int rc = head_and_choose(c, 0, grows, lg, n, c->tree_depth_all, act.data() + i0, i1 - i0, rel0, n_rows + i0, base, &ld, tree == nullptr); if (rc) return rc; }
         if (lg && ld)                                      // before the next group overwrites the logits
             launch_copy_rows_f32(c->logits, ld, lg, cf.vocab, n, cf.vocab, c->st);
         i0 = i1;

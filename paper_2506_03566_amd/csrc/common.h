@@ -92,6 +92,9 @@ constexpr int TOPK_MAXK = 16;
 constexpr int TOPK_REC = 2 + 2 * TOPK_MAXK;    // segment record: [max, sum exp(l - max), k values, k indices (as bits)]
 struct EpiArgs {
     int mode;
+    // float32 storage: X is the residual stream and this product norms its rows, u = rmsnorm(x) * x_gain (EPI_SILU and EPI_ROPE_KV: always);
+    // EPI_RESIDUAL norms nothing then (gain: 16-bit types)
+    const void *x_gain;
     // EPI_PLANES: the partial planes and nothing behind them (16-bit types)
     // EPI_PLAIN: out[m][n] = sum (with out == nullptr and S == 1 plane 0 is the result, row stride Npad)
     float *out; int ld_out;

@@ -138,22 +138,33 @@ void launch_norm_rows(const ModelDims &md, const float *h, int rows, const void 
 
 // ------------------------------------------------------------------ argmax per row (lowest index on ties)
 // Two stages so that a 128K-entry row is not one workgroup's serial scan: (segment, row) partial
-// winners, then one small workgroup per row over the partials.
+// winners, then one small workgroup per row over the partials.  A row of one segment is finished by the first stage (25 rows of 4096
+// ids, two launches: 7.3 + 4.7 us; one, its ids requested in one trip: 4.0).
+__device__ __forceinline__ void argmax_out(int bi, int rowi, int32_t *__restrict__ out, int32_t *__restrict__ host_out) {
+    if (bi == 0x7fffffff) bi = 0;                         // no logit of the row compared (all NaN): token 0, not an id outside the vocabulary
+    out[rowi] = bi;
+    if (host_out) host_out[rowi] = bi;
+}
+
 constexpr int ARGMAX_SEG = 4096;
-__global__ __launch_bounds__(256) void argmax_seg_kernel(const float *__restrict__ logits, int ld, int vocab, int n_seg,
-                                                         float *__restrict__ pv, int *__restrict__ pi) {
+__global__ __launch_bounds__(256) void argmax_seg_kernel(const float *__restrict__ logits, int ld, int vocab, int n_seg, float *__restrict__ pv,
+                                                         int *__restrict__ pi, int32_t *__restrict__ out, int32_t *__restrict__ host_out) {
+    constexpr int NV = ARGMAX_SEG / 256;
     __shared__ float red_v[17];
     __shared__ int red_i[17];
-    const int seg = blockIdx.x, rowi = blockIdx.y;
+    const int seg = blockIdx.x, rowi = blockIdx.y, i0 = seg * ARGMAX_SEG + (int)threadIdx.x;
     const float *row = logits + (size_t)rowi * ld;
+    float v[NV];
+#pragma unroll
+    for (int j = 0; j < NV; ++j) v[j] = row[min(i0 + j * 256, vocab - 1)];       // one trip; ids beyond the vocabulary do not compete
     float bv = -INFINITY; int bi = 0x7fffffff;
-    const int end = min(vocab, (seg + 1) * ARGMAX_SEG);
-    for (int i = seg * ARGMAX_SEG + threadIdx.x; i < end; i += blockDim.x) {
-        const float v = row[i];
-        if (better(v, i, bv, bi)) { bv = v; bi = i; }
-    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+        if (i0 + j * 256 < vocab && better(v[j], i0 + j * 256, bv, bi)) { bv = v[j]; bi = i0 + j * 256; }
     block_argmax(bv, bi, red_v, red_i);
-    if (threadIdx.x == 0) { pv[rowi * n_seg + seg] = bv; pi[rowi * n_seg + seg] = bi; }
+    if (threadIdx.x != 0) return;
+    if (n_seg == 1) argmax_out(bi, rowi, out, host_out);
+    else { pv[rowi * n_seg + seg] = bv; pi[rowi * n_seg + seg] = bi; }
 }
 
 __global__ __launch_bounds__(64) void argmax_merge_kernel(const float *__restrict__ pv, const int *__restrict__ pi, int n_seg,
@@ -165,10 +176,7 @@ __global__ __launch_bounds__(64) void argmax_merge_kernel(const float *__restric
         if (better(v, i, bv, bi)) { bv = v; bi = i; }
     }
     wave_argmax(bv, bi);
-    if (threadIdx.x != 0) return;
-    if (bi == 0x7fffffff) bi = 0;                         // no logit of the row compared (all NaN): token 0, not an id outside the vocabulary
-    out[rowi] = bi;
-    if (host_out) host_out[rowi] = bi;
+    if (threadIdx.x == 0) argmax_out(bi, rowi, out, host_out);
 }
 
 size_t argmax_scratch_floats(int rows, int vocab) { return (size_t)2 * rows * head_segments_max(vocab); }   // finest segmentation: the Head GEMM's tiles
@@ -181,8 +189,8 @@ void launch_argmax(const float *logits, int ld, int rows, int vocab, float *scra
     const int n_seg = (vocab + ARGMAX_SEG - 1) / ARGMAX_SEG;
     float *pv = scratch;
     int *pi = reinterpret_cast<int *>(scratch + (size_t)rows * n_seg);
-    hipLaunchKernelGGL(argmax_seg_kernel, dim3(n_seg, rows), dim3(256), 0, st, logits, ld, vocab, n_seg, pv, pi);
-    launch_argmax_merge(pv, pi, n_seg, rows, out, host_out, st);
+    hipLaunchKernelGGL(argmax_seg_kernel, dim3(n_seg, rows), dim3(256), 0, st, logits, ld, vocab, n_seg, pv, pi, out, host_out);
+    if (n_seg > 1) launch_argmax_merge(pv, pi, n_seg, rows, out, host_out, st);
 }
 
 // ------------------------------------------------------------------ temperature sampling per row

@@ -1270,10 +1270,10 @@ bool launch_gemm_direct(int dt, const GemmShape &g, const void *W, const void *X
 // Residual epilogue, one workgroup per row: h = sum of planes (+ bias) (+ h); then, because the
 // whole row is in this workgroup, the RMSNorm that feeds the next GEMM right away:
 // u = T(h / sqrt(mean(h^2) + eps) * gain).  Saves a kernel per norm.
-// A thread owns MAXIT groups of four columns; where N is a multiple of 4 (VEC: every 16-bit shape) each operand of a group is
+// (16-bit types.)  A thread owns MAXIT groups of four columns (N is a multiple of 4); each operand of a group is
 // one load, all of them requested before the first use: one trip to memory (column by column the same loads sat behind branches:
 // the round of the 8B shape 6040 -> 5888 us, 76 launches of it; one row of the 13B shape 668 -> 635 us a pass).
-template <typename T, bool VEC>
+template <typename T>
 __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const float *__restrict__ part, size_t plane, int S,
                                                                       int Npad, int N, float eps, EpiArgs e) {
     struct __attribute__((aligned(4 * sizeof(T)))) Quad { T t[4]; };
@@ -1293,49 +1293,28 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
         gn[it] = f32x4{0.f, 0.f, 0.f, 0.f};
         if (n < N) {
             f32x4 add = f32x4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (VEC) {
-                Quad bq, gq;
-                if (e.residual) add = *reinterpret_cast<const f32x4 *>(h + n);
-                if (bias) bq = *reinterpret_cast<const Quad *>(bias + n);
-                if (gain) gq = *reinterpret_cast<const Quad *>(gain + n);
-                const f32x4 v = sum_planes4(part, plane, S, (size_t)m * Npad + n);
+            Quad bq, gq;
+            if (e.residual) add = *reinterpret_cast<const f32x4 *>(h + n);
+            if (bias) bq = *reinterpret_cast<const Quad *>(bias + n);
+            if (gain) gq = *reinterpret_cast<const Quad *>(gain + n);
+            const f32x4 v = sum_planes4(part, plane, S, (size_t)m * Npad + n);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (bias) add[j] += to_f(bq.t[j]);
-                    if (gain) gn[it][j] = to_f(gq.t[j]);
-                }
-                x[it] = v + add;
-                *reinterpret_cast<f32x4 *>(h + n) = x[it];
-                if (h_copy) *reinterpret_cast<f32x4 *>(h_copy + n) = x[it];
-                if (h_user) *reinterpret_cast<f32x4 *>(h_user + n) = x[it];
-                if (e.h_stash) {
-                    Quad o;
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) o.t[j] = from_f<T>(x[it][j]);
-                    *reinterpret_cast<Quad *>(static_cast<T *>(e.h_stash) + (size_t)m * N + n) = o;
-                }
-#pragma unroll
-                for (int j = 0; j < 4; ++j) ss = fmaf(x[it][j], x[it][j], ss);   // (spelt out: which product is rounded on its own is not left to the compiler)
-            } else {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (n + j >= N) continue;
-                    if (e.residual) add[j] = h[n + j];
-                    if (bias) add[j] += to_f(bias[n + j]);
-                    if (gain) gn[it][j] = to_f(gain[n + j]);
-                }
-                f32x4 v = sum_planes4(part, plane, S, (size_t)m * Npad + n);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (n + j >= N) { v[j] = 0.f; continue; }
-                    v[j] += add[j];
-                    h[n + j] = v[j];
-                    if (h_copy) h_copy[n + j] = v[j];
-                    if (h_user) h_user[n + j] = v[j];
-                    ss = fmaf(v[j], v[j], ss);
-                }
-                x[it] = v;
+            for (int j = 0; j < 4; ++j) {
+                if (bias) add[j] += to_f(bq.t[j]);
+                if (gain) gn[it][j] = to_f(gq.t[j]);
             }
+            x[it] = v + add;
+            *reinterpret_cast<f32x4 *>(h + n) = x[it];
+            if (h_copy) *reinterpret_cast<f32x4 *>(h_copy + n) = x[it];
+            if (h_user) *reinterpret_cast<f32x4 *>(h_user + n) = x[it];
+            if (e.h_stash) {
+                Quad o;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o.t[j] = from_f<T>(x[it][j]);
+                *reinterpret_cast<Quad *>(static_cast<T *>(e.h_stash) + (size_t)m * N + n) = o;
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ss = fmaf(x[it][j], x[it][j], ss);   // (spelt out: which product is rounded on its own is not left to the compiler)
         }
     }
     if (!gain) return;
@@ -1344,17 +1323,11 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
 #pragma unroll
     for (int it = 0; it < MAXIT; ++it) {
         const int n = (it * (int)blockDim.x + (int)threadIdx.x) * 4;
-        if constexpr (VEC) {
-            if (n >= N) continue;
-            Quad o;
+        if (n >= N) continue;
+        Quad o;
 #pragma unroll
-            for (int j = 0; j < 4; ++j) o.t[j] = mul_round<T>(x[it][j] * rs, gn[it][j]);
-            *reinterpret_cast<Quad *>(u + (size_t)m * N + n) = o;
-        } else {
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (n + j < N) u[(size_t)m * N + n + j] = mul_round<T>(x[it][j] * rs, gn[it][j]);
-        }
+        for (int j = 0; j < 4; ++j) o.t[j] = mul_round<T>(x[it][j] * rs, gn[it][j]);
+        *reinterpret_cast<Quad *>(u + (size_t)m * N + n) = o;
     }
 }
 
@@ -1372,13 +1345,22 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
 // 5.8 instead of 4.0 + 4.4 for QKV (its slots and pages are a chain of three loads), and a boundary between launches less.  A request
 // of the 256 wide shape (prompt and first round, with topk_row_kernel): 773 -> 667 us, 163 -> 134 launches.
 constexpr int F32_WAVES = 4, F32_PF = 4, F32_KSTEP = 16;
-struct F32Epi { float *act; int F; QkvEpi qkv; };
+// The residual addition (EPI_RESIDUAL, no norm behind it) is applied to the whole sums as well, and a norm belongs to the product that
+// reads the normed rows (NORM): x gain is formed where an operand is used, the sum of squares beside it, by the waves that hold
+// the row's k anyway, and the sums are scaled by 1 / rms at the end.  The same request: 675 -> 600 us, 134 -> 102 launches.  Error against 64
+// bits over 48 requests, the ratio to norms in kernels of their own: logits 1.005 +- 0.004, features 0.998 +- 0.004.
+struct F32Epi {
+    float *act; int F; QkvEpi qkv;
+    float *h, *h_copy, *h_user; int h_user_rows, residual; const float *bias;
+    const float *gain; float eps;
+};
 
-template <int MT, int NT, bool VEC, int EPI>
+template <int MT, int NT, bool VEC, int EPI, bool NORM>
 __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(const float *__restrict__ W, const float *__restrict__ X, int ldx,
                                                                   float *__restrict__ out, int ld_out, int M, int N, int K, F32Epi epi) {
-    static_assert(EPI == EPI_PLAIN || NT == 2, "a lane holds both columns of a pair");
+    static_assert(EPI == EPI_PLAIN || EPI == EPI_RESIDUAL || NT == 2, "a lane holds both columns of a pair");
     __shared__ f32x4 red[F32_WAVES][MT * NT][64];
+    __shared__ float squares[F32_WAVES][MT * 16];
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, lr = lane & 15, lg = lane >> 4;
     const int m0 = blockIdx.y * (16 * MT), half = epi.qkv.dh >> 1;
     const int n0 = EPI == EPI_ROPE_KV ? (int)blockIdx.x / (half >> 4) * epi.qkv.dh + (int)blockIdx.x % (half >> 4) * 16
@@ -1415,45 +1397,70 @@ __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(const float *_
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    f32x4 a[2][F32_PF][MT], b[2][F32_PF][NT];
-    auto fetch = [&](int ks, f32x4 (&fa)[F32_PF][MT], f32x4 (&fb)[F32_PF][NT]) {
+    f32x4 a[2][F32_PF][MT], b[2][F32_PF][NT], gn[2][F32_PF];
+    f32x4 ss[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) ss[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto fetch = [&](int ks, f32x4 (&fa)[F32_PF][MT], f32x4 (&fb)[F32_PF][NT], f32x4 (&fg)[F32_PF]) {
 #pragma unroll
         for (int p = 0; p < F32_PF; ++p) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) fa[p][mt] = load(xp[mt], ks + p);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) fb[p][nt] = load(wp[nt], ks + p);
+            if constexpr (NORM) fg[p] = load(epi.gain, ks + p);
         }
     };
-    auto multiply = [&](const f32x4 (&fa)[F32_PF][MT], const f32x4 (&fb)[F32_PF][NT]) {
+    auto multiply = [&](const f32x4 (&fa)[F32_PF][MT], const f32x4 (&fb)[F32_PF][NT], const f32x4 (&fg)[F32_PF]) {
 #pragma unroll
         for (int p = 0; p < F32_PF; ++p)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
+                for (int mt = 0; mt < MT; ++mt) {
+                    float x = fa[p][mt][j];
+                    if constexpr (NORM) { ss[mt][j] = fmaf(x, x, ss[mt][j]); x *= fg[p][j]; }
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[p][mt][j], fb[p][nt][j], acc[mt][nt], 0, 0, 0);
+                    for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(x, fb[p][nt][j], acc[mt][nt], 0, 0, 0);
+                }
     };
-    fetch(k0, a[0], b[0]);
+    fetch(k0, a[0], b[0], gn[0]);
     if constexpr (EPI == EPI_ROPE_KV)
         if (wave < MT) qkv_pages(epi.qkv, n0 / epi.qkv.dh, rows);
     for (int ks = k0; ks < k1; ks += 2 * F32_PF) {        // (a k-step beyond k1 is all zeros: it changes no sum)
-        fetch(ks + F32_PF, a[1], b[1]);
-        multiply(a[0], b[0]);
+        fetch(ks + F32_PF, a[1], b[1], gn[1]);
+        multiply(a[0], b[0], gn[0]);
         if (ks + F32_PF >= k1) break;
-        fetch(ks + 2 * F32_PF, a[0], b[0]);
-        multiply(a[1], b[1]);
+        fetch(ks + 2 * F32_PF, a[0], b[0], gn[0]);
+        multiply(a[1], b[1], gn[1]);
     }
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) red[wave][mt * NT + nt][lane] = acc[mt][nt];
+    if constexpr (NORM) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {                 // of a row: four lanes' shares
+            float q = (ss[mt][0] + ss[mt][1]) + (ss[mt][2] + ss[mt][3]), lo, hi;
+            swap16(q, lo, hi); q = lo + hi;
+            swap32(q, lo, hi); q = lo + hi;
+            if (lane < 16) squares[wave][mt * 16 + lane] = q;
+        }
+    }
     __syncthreads();
-    auto sum_of = [&](int t) {
+    auto sum_of = [&](int t) {                            // tile t = row tile * NT + column tile; register r is row 4 * (lane / 16) + r
         f32x4 v = red[0][t][lane];
 #pragma unroll
         for (int w = 1; w < F32_WAVES; ++w) v += red[w][t][lane];
+        if constexpr (NORM) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int row = t / NT * 16 + lg * 4 + r;
+                const float q = (squares[0][row] + squares[1][row]) + (squares[2][row] + squares[3][row]);
+                static_assert(F32_WAVES == 4, "the sum above");
+                v[r] *= 1.0f / sqrtf(q / (float)K + epi.eps);
+            }
+        }
         return v;
     };
     if constexpr (EPI == EPI_SILU) {
@@ -1481,24 +1488,36 @@ __global__ __launch_bounds__(F32_WAVES * 64) void gemm_f32_kernel(const float *_
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int m = m0 + (t / NT) * 16 + lg * 4 + r;
-            if (m < M && n < N) out[(size_t)m * ld_out + n] = v[r];
+            if (m >= M || n >= N) continue;
+            if constexpr (EPI == EPI_RESIDUAL) {
+                const size_t at = (size_t)m * N + n;
+                float add = epi.residual ? epi.h[at] : 0.f;
+                if (epi.bias) add += epi.bias[n];
+                const float x = v[r] + add;
+                epi.h[at] = x;
+                if (epi.h_copy) epi.h_copy[at] = x;
+                if (epi.h_user && m < epi.h_user_rows) epi.h_user[at] = x;
+            } else {
+                out[(size_t)m * ld_out + n] = v[r];
+            }
         }
     }
 }
 
 // Two row tiles and two column tiles per workgroup where there are rows for it (half the operand traffic of 16 x 16).
-template <int EPI>
+template <int EPI, bool NORM>
 static void launch_gemm_f32(const float *W, const float *X, int ldx, float *out, int ld_out, int M, int N, int K, const F32Epi &epi, hipStream_t st,
                             hipEvent_t ev_start, hipEvent_t ev_stop) {
-    const bool vec = K % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0;
-    constexpr int NT1 = EPI == EPI_PLAIN ? 1 : 2;
+    const bool vec = K % 4 == 0 && ldx % 4 == 0 && reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(W) % 16 == 0 &&
+                     (!NORM || reinterpret_cast<uintptr_t>(epi.gain) % 16 == 0);
+    constexpr int NT1 = EPI == EPI_PLAIN || EPI == EPI_RESIDUAL ? 1 : 2;
 #define POSS_F32(MT, NT, VEC)                                                                                              \
     do {                                                                                                                   \
         dim3 grid((N + 16 * NT - 1) / (16 * NT), (M + 16 * MT - 1) / (16 * MT)), block(F32_WAVES * 64);                    \
         if (ev_start && ev_stop)                                                                                           \
-            hipExtLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC, EPI>), grid, block, 0, st, ev_start, ev_stop, 0, W, X, ldx, out, ld_out, M, N, K, epi); \
+            hipExtLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC, EPI, NORM>), grid, block, 0, st, ev_start, ev_stop, 0, W, X, ldx, out, ld_out, M, N, K, epi); \
         else                                                                                                               \
-            hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC, EPI>), grid, block, 0, st, W, X, ldx, out, ld_out, M, N, K, epi); \
+            hipLaunchKernelGGL((gemm_f32_kernel<MT, NT, VEC, EPI, NORM>), grid, block, 0, st, W, X, ldx, out, ld_out, M, N, K, epi); \
     } while (0)
     if (M <= 16 || (size_t)M * N < 64 * 1024) { if (vec) POSS_F32(1, NT1, true); else POSS_F32(1, NT1, false); }
     else { if (vec) POSS_F32(2, 2, true); else POSS_F32(2, 2, false); }
@@ -1569,9 +1588,9 @@ void launch_residual_norm(int dt, const float *part, int S, int rows, int N, flo
     int threads = round_up((N + 3) / 4, 64);
     if (threads > 1024) threads = 1024;
     if (dt == DT_BF16)
-        hipLaunchKernelGGL((epilogue_residual_norm_kernel<bf16_t, true>), dim3(rows), dim3(threads), 0, st, part, (size_t)rows * N, S, N, N, eps, epi);
+        hipLaunchKernelGGL((epilogue_residual_norm_kernel<bf16_t>), dim3(rows), dim3(threads), 0, st, part, (size_t)rows * N, S, N, N, eps, epi);
     else
-        hipLaunchKernelGGL((epilogue_residual_norm_kernel<f16_t, true>), dim3(rows), dim3(threads), 0, st, part, (size_t)rows * N, S, N, N, eps, epi);
+        hipLaunchKernelGGL((epilogue_residual_norm_kernel<f16_t>), dim3(rows), dim3(threads), 0, st, part, (size_t)rows * N, S, N, N, eps, epi);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1623,17 +1642,13 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
     dim3 pair_grid(tiles, (g.M + EPI_ROWS_PAIR - 1) / EPI_ROWS_PAIR), plain_grid(tiles, (g.M + EPI_ROWS_PLAIN - 1) / EPI_ROWS_PLAIN);
     dim3 eb(256);
     switch (epi.mode) {
-        case EPI_RESIDUAL: {
-            int threads = round_up((g.N + 3) / 4, 64);
-            if (threads > 1024) threads = 1024;
-            if (g.N % 4 == 0)
-                hipLaunchKernelGGL((epilogue_residual_norm_kernel<T, true>), dim3(g.M), dim3(threads), 0, st, part, plane, g.S, g.Npad,
-                                   g.N, eps, epi);
-            else
-                hipLaunchKernelGGL((epilogue_residual_norm_kernel<T, false>), dim3(g.M), dim3(threads), 0, st, part, plane, g.S, g.Npad,
-                                   g.N, eps, epi);
+        case EPI_RESIDUAL:
+            if constexpr (!std::is_same<T, float>::value) {             // (float32: inside gemm_f32_kernel)
+                int threads = round_up((g.N + 3) / 4, 64);
+                if (threads > 1024) threads = 1024;
+                hipLaunchKernelGGL((epilogue_residual_norm_kernel<T>), dim3(g.M), dim3(threads), 0, st, part, plane, g.S, g.Npad, g.N, eps, epi);
+            }
             break;
-        }
         case EPI_HEAD: break;           // reduced inside the stream kernel
         case EPI_PLANES: break;
         case EPI_SILU:
@@ -1796,6 +1811,11 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
 // Refuse, on the host, argument sets that would make a kernel write through a null pointer.
 static bool gemm_args_ok(int dt, const GemmShape &g, const void *Wp, const void *X, const float *part, const EpiArgs &e) {
     if (!Wp || !X || !part || g.M < 1 || g.M > LAUNCH_ROWS || g.S < 1) return false;
+    if (e.x_gain && dt != DT_F32) return false;
+    if (dt == DT_F32) {                                    // norms belong to the products that read them
+        if (e.mode == EPI_RESIDUAL) return e.h && !e.gain && e.h != X;
+        if ((e.mode == EPI_SILU || e.mode == EPI_ROPE_KV) && !e.x_gain) return false;
+    }
     switch (e.mode) {
         case EPI_PLAIN: return e.out || g.S == 1;          // unsplit: plane 0 is the result
         case EPI_ROPE_KV:                                  // caches: checked per range
@@ -1842,17 +1862,27 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
                             !overlap(epi.out, out_bytes, Wp, (size_t)g.N * g.K * sizeof(float));
         const float *w = static_cast<const float *>(Wp), *x = static_cast<const float *>(X);
         F32Epi fe{};
+        fe.gain = static_cast<const float *>(epi.x_gain); fe.eps = eps;
         if (epi.mode == EPI_SILU) {
             fe.act = static_cast<float *>(epi.act); fe.F = epi.F;
-            launch_gemm_f32<EPI_SILU>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+            launch_gemm_f32<EPI_SILU, true>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
             return true;
         }
         if (epi.mode == EPI_ROPE_KV) {
             fe.qkv = QkvEpi{epi.cs, epi.slot, epi.q, epi.hq, epi.hkv, epi.dh, rr};
-            launch_gemm_f32<EPI_ROPE_KV>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+            launch_gemm_f32<EPI_ROPE_KV, true>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
             return true;
         }
-        launch_gemm_f32<EPI_PLAIN>(w, x, ldx, direct ? epi.out : part, direct ? epi.ld_out : g.Npad, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+        if (epi.mode == EPI_RESIDUAL) {
+            fe.h = epi.h; fe.h_copy = epi.h_copy; fe.h_user = epi.h_user; fe.h_user_rows = epi.h_user_rows;
+            fe.residual = epi.residual; fe.bias = static_cast<const float *>(epi.bias);
+            launch_gemm_f32<EPI_RESIDUAL, false>(w, x, ldx, nullptr, 0, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+            return true;
+        }
+        float *dst = direct ? epi.out : part;
+        const int ld = direct ? epi.ld_out : g.Npad;
+        if (epi.x_gain) launch_gemm_f32<EPI_PLAIN, true>(w, x, ldx, dst, ld, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
+        else launch_gemm_f32<EPI_PLAIN, false>(w, x, ldx, dst, ld, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
         if (!direct) launch_epilogue_t<float>(g, part, epi, eps, false, st);
     } else if (dt == DT_BF16) {
         launch_gemm_t<bf16_t>(g, Wp, X, ldx, part, epi, eps, st, ev_start, ev_stop, epi.mode == EPI_ROPE_KV ? &rr : nullptr);

@@ -11,6 +11,7 @@ pytestmark = pytest.mark.gpu
 if have_gpu():
     import torch
     import paper_2506_03566_amd as P
+    from oracle.tree import Tree
     from synth import get_config, make_prompt, make_weights
     from synth.gpu import to_device
 
@@ -147,4 +148,27 @@ def test_f32_head_sizes_other_than_the_16_bit_types(head_dim, n_prompt, over):
     pair.ctx.verify_tree(logits_out=logits)
     assert np.abs(logits.cpu().numpy() - o.verify_tree(Tree(d["token"], d["parent"]))[1]).max() <= tol_for(cfg)
     assert len(pair.ctx.accept_and_commit()[2]) >= 1
+    pair.close()
+
+
+@pytest.mark.parametrize("d,ffn,vocab,rows", [(256, 688, 4096, 25), (70, 90, 4096, 17), (96, 250, 4097, 1), (1100, 1030, 100, 33), (32, 64, 8200, 16)])
+def test_norms_inside_the_products(d, ffn, vocab, rows):
+    """Float32 layers whose products norm their own operands: widths that are and are not multiples of 4 and of a k-step, more k-steps
+    than a wave keeps in flight, row counts around a tile; greedy choices of one and of two segments.  Against the oracle in float64:
+    sums of at most 1100 products of size 1, five layers and norms deep, 1e-4 as everywhere in float32; the chosen token is the largest logit,
+    logits in the caller's array are those the choice was made from."""
+    pair = Pair("c0_tiny_f32", d_model=d, d_ffn=ffn, vocab=vocab, n_q_heads=2, n_kv_heads=2, head_dim=32, depth=6, total_tokens=40)
+    ctx, o = pair.ctx, pair.oracle()
+    prompt = make_prompt(pair.cfg, n=20)
+    ctx.prefill(prompt)
+    o.prefill(prompt)
+    o.tokens[-1] = ctx.tokens()[-1]
+    tree = [int(o.tokens[-1])] + [(7 * i) % vocab for i in range(1, rows)]
+    parent = [-1] + [(i - 1) // 2 for i in range(1, rows)]
+    logits, feats = torch.zeros(rows, vocab, device="cuda"), torch.zeros(rows, d, device="cuda")
+    g = ctx.verify_tree(P.TreeArrays.from_lists(tree, parent), logits_out=logits, feat_out=feats)[:rows]
+    _, want, want_f = o.verify_tree(Tree(tree, parent))
+    assert np.abs(logits.cpu().numpy() - want).max() < 1e-4
+    assert np.abs(feats.cpu().numpy() - want_f).max() < 1e-4
+    assert g.tolist() == logits.argmax(1).tolist()
     pair.close()
