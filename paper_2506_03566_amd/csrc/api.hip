@@ -577,7 +577,8 @@ uint64_t ones(int bits) { return bits <= 0 ? 0ull : bits >= 64 ? ~0ull : ((1ull 
 
 // Rows of sequence b in one specialist pass: plan rows [0, nq) are its full rows, the rest produce
 // keys and values only.
-struct SeqPlan { int b; DraftRowPlan plan; int nq, n_prefix, region_len; };
+// td: with the rows of the top-k that belong to the sequence; expand: they are not in the tree yet.
+struct SeqPlan { int b; DraftRowPlan plan; int nq, n_prefix, region_len; TreeDev td; bool expand; };
 
 // One pass of specialist s over the rows of every plan.  Full rows of all sequences first (sequence
 // order), then the key/value-only rows: the GEMMs after attention run on the leading rows.
@@ -597,7 +598,7 @@ void spec_pass(poss_ctx *c, int s, std::vector<SeqPlan> &plans, int depth_index,
         const int nx = p.plan.n_rows - p.nq;
         for (int r = 0; r < p.nq; ++r) p.plan.dst[r] = (int16_t)(q0 + r);
         for (int r = 0; r < nx; ++r) p.plan.dst[p.nq + r] = (int16_t)(x0 + r);
-        launch_draft_assemble(md, p.plan, depth_index, c->cfg.top_k, c->embed, sq.tokens_dev, sq.feat_stash, sq.td,
+        launch_draft_assemble(md, p.plan, depth_index, p.expand, c->cfg.top_k, c->embed, sq.tokens_dev, sq.feat_stash, p.td,
                               fhat_prev ? fhat_prev + (size_t)i * prev_rows_each * md.d : nullptr, sq.xin_tmp, c->xin,
                               c->row_pos, c->row_slot, c->row_mask, c->inv_freq, c->cs, c->st);
         segs.push_back(Seg{p.b, &sq.spec_kv[s], q0, p.nq, x0, nx, p.n_prefix, p.region_len});
@@ -701,7 +702,7 @@ void spec_catchup(poss_ctx *c, int b, int s, int upto) {
         const int i0 = sq.spec_len[s], n = upto - i0 < MAX_ROWS ? upto - i0 : MAX_ROWS;
         std::vector<SeqPlan> plans(1);
         SeqPlan &p = plans[0];
-        p.b = b; p.nq = 0; p.n_prefix = 0; p.region_len = 0;
+        p.b = b; p.nq = 0; p.n_prefix = 0; p.region_len = 0; p.td = sq.td; p.expand = false;
         p.plan.n_rows = n; p.plan.mask0[0] = p.plan.mask0[1] = 0;
         for (int r = 0; r < n; ++r) { p.plan.kind[r] = 0; p.plan.idx[r] = i0 + r; p.plan.slot[r] = i0 + r; p.plan.pos[r] = i0 + r; }
         spec_pass(c, s, plans, 0, nullptr, 0, nullptr, nullptr);
@@ -1144,6 +1145,9 @@ int poss_draft_tree(poss_ctx *c, poss_tree *out) {
     }
     const std::vector<int> &act = all;
     const int B = (int)act.size();                         // sequences in this round
+    // The children of the depth before, where every sequence's are there at once: the next kernel that reads the tree forms them.
+    std::vector<TreeDev> etd(B);
+    bool pending = false;
     for (int d = 1; d <= L; ++d) {
         int s = (d - 1) / cf.positions_per_specialist;
         if (s > cf.n_specialists - 1) s = cf.n_specialists - 1;
@@ -1157,6 +1161,7 @@ int poss_draft_tree(poss_ctx *c, poss_tree *out) {
             const int t = sq.t;
             int n = 0;
             sp.b = b; sp.nq = rows_q_each;
+            sp.td = pending ? etd[i] : sq.td; sp.expand = pending;
             if (d == 1) {
                 // root pair [x_t ; f_{t-1}] first (the only row whose output is used), then the other
                 // pairs this specialist has not seen; all of them become committed cache entries
@@ -1179,6 +1184,13 @@ int poss_draft_tree(poss_ctx *c, poss_tree *out) {
         // large: then group by group, each depth by the rows it brings).  The drafted features of the
         // frontier rows sit at the sequence's place in the batch (i * rows_q_each), whatever the grouping.
         const int prev_each = d - 1 == 1 ? 1 : k;
+        int rows_d = 0;
+        for (const SeqPlan &sp : plans) rows_d += sp.plan.n_rows;
+        if (pending && rows_d > c->launch_rows) {          // several groups: the first one's top-k would take the others' place
+            launch_tree_expand(etd.data(), B, d - 1, k, L, prev_each, cf.vocab, c->st);
+            for (SeqPlan &sp : plans) sp.expand = false;
+        }
+        pending = false;
         for (int i0 = 0; i0 < B;) {
             int i1 = i0, grows = 0;
             while (i1 < B && grows + plans[i1].plan.n_rows <= c->launch_rows) grows += plans[i1++].plan.n_rows;
@@ -1189,15 +1201,16 @@ int poss_draft_tree(poss_ctx *c, poss_tree *out) {
                       c->fhat[d & 1] + (size_t)i0 * rows_q_each * c->md.d, &q0);
             const int rows_q = nb * rows_q_each;
             run_head_topk(c, rows_q, d);
-            TreeDev tds[8];
             for (int i = 0; i < nb; ++i) {
                 Seq &sq = c->seq[act[i0 + i]];
-                tds[i] = sq.td;                              // with this sequence's rows of the top-k
-                tds[i].topk_id = c->topk_id_all + (size_t)q0[i] * k; tds[i].topk_logp = c->topk_logp_all + (size_t)q0[i] * k;
+                TreeDev &td = etd[i0 + i];
+                td = sq.td;                                  // with this sequence's rows of the top-k
+                td.topk_id = c->topk_id_all + (size_t)q0[i] * k; td.topk_logp = c->topk_logp_all + (size_t)q0[i] * k;
                 sq.spec_len[s] = sq.t;
                 sq.spec_tmp_depth[s] = d - 1;
             }
-            launch_tree_expand(tds, nb, d, k, L, rows_q_each, cf.vocab, c->st);   // one launch, a workgroup per sequence
+            pending = nb == B;
+            if (!pending) launch_tree_expand(etd.data() + i0, nb, d, k, L, rows_q_each, cf.vocab, c->st);   // one launch, a workgroup per sequence
             i0 = i1;
         }
     }
@@ -1210,12 +1223,12 @@ int poss_draft_tree(poss_ctx *c, poss_tree *out) {
         TreeHost *hosts[8];
         for (int i = 0; i < B; ++i) {
             Seq &sq = c->seq[act[i]];
-            tds[i] = sq.td; ts[i] = sq.t; toks[i] = sq.tokens_dev; slots[i] = sq.tree_slot;
+            tds[i] = pending ? etd[i] : sq.td; ts[i] = sq.t; toks[i] = sq.tokens_dev; slots[i] = sq.tree_slot;
             hosts[i] = sq.tree_host_dev; sq.tree_on_host = 1;
             sq.tree_n = (cf.total_tokens < pool ? cf.total_tokens : pool) + 1;
             sq.tree_ready = 1;
         }
-        launch_tree_finalize(tds, B, k, L, cf.total_tokens, ts, toks, slots, hosts, c->st);
+        launch_tree_finalize(tds, B, k, L, cf.total_tokens, ts, toks, slots, hosts, cf.vocab, pending, c->st);
     }
     (void)hipEventRecord(c->ev[1], c->st);
     c->ev_pending[0] = true;
@@ -1250,7 +1263,7 @@ int poss_debug_build_tree(poss_ctx *c, const int32_t *ids, const float *logp, po
     }
     {
         const int32_t *toks = sq.tokens_dev;
-        launch_tree_finalize(&sq.td, 1, k, L, cf.total_tokens, &sq.t, &toks, &sq.tree_slot, &sq.tree_host_dev, c->st);
+        launch_tree_finalize(&sq.td, 1, k, L, cf.total_tokens, &sq.t, &toks, &sq.tree_slot, &sq.tree_host_dev, cf.vocab, false, c->st);
         sq.tree_on_host = 1;
     }
     const int pool = k + (L - 1) * k * k;

@@ -254,9 +254,11 @@ void launch_topk_logsoftmax(const float *logits, int ld, int rows, int vocab, in
 constexpr int TREE_BATCH_MAX = 8;
 void launch_tree_expand(const TreeDev *tds, int n_seq, int d, int k, int L, int rows, int vocab, hipStream_t st);
 // also writes the KV slot of every node (slot_out[s][i] = t[s] + i), which the verification pass reads, and the tree into host
-// memory mapped into the device (host[s], laid out as TreeHost): the host reads it there, no copy follows
+// memory mapped into the device (host[s], laid out as TreeHost): the host reads it there, no copy follows.  expand: forms the candidates
+// of depth L itself (their launch_tree_expand has not run)
 void launch_tree_finalize(const TreeDev *tds, int n_seq, int k, int L, int n_keep, const int *t,
-                          const int32_t *const *tokens_dev, int32_t *const *slot_out, struct TreeHost *const *host, hipStream_t st);
+                          const int32_t *const *tokens_dev, int32_t *const *slot_out, struct TreeHost *const *host, int vocab, bool expand,
+                          hipStream_t st);
 struct TreeHost { int32_t token[MAX_ROWS], parent[MAX_ROWS], depth[MAX_ROWS], pos[MAX_ROWS]; float score[MAX_ROWS]; uint64_t mask[MAX_ROWS * MASK_WORDS]; };
 // rows of [embedding ; feature] pairs for one specialist pass
 struct DraftRowPlan {
@@ -269,7 +271,8 @@ struct DraftRowPlan {
     int32_t pos[MAX_ROWS];
     int16_t dst[MAX_ROWS];        // row of the pass this plan row is written to (several sequences share a pass)
 };
-void launch_draft_assemble(const ModelDims &md, const DraftRowPlan &plan, int depth_index, int k,
+// expand: forms the frontier of depth depth_index itself, from td's top-k (its launch_tree_expand has not run; the plan holds every rank)
+void launch_draft_assemble(const ModelDims &md, const DraftRowPlan &plan, int depth_index, bool expand, int k,
                            const void *embed, const int32_t *tokens_dev, const void *feat_stash,
                            const TreeDev &td, const float *fhat_prev, void *xin_tmp, void *x_out,
                            int32_t *pos_out, int32_t *slot_out, uint64_t *mask_out, const double *inv_freq,

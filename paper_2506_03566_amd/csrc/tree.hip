@@ -376,7 +376,10 @@ size_t topk_scratch_floats(int rows, int vocab) {      // the Head GEMM's column
 // Children of the frontier of depth d-1 (the root for d = 1) join the candidate pool; unless d = L,
 // the k best of them become the frontier of depth d.  A frontier node's drafter row lives in temp
 // slot (d-1)*k + rank; fr_mask collects the temp slots of the node and its drafted ancestors.
-// One workgroup per sequence of the batch.
+// The next pass's row assembly (or, at d = L, the kernel that finishes the tree) does this by itself, every workgroup that needs it for
+// itself: a launch of 5 us less per depth (drafting six levels of the 8B shape 2166 -> 2143 us, where assembly makes the trip to the top-k
+// instead of the one to the frontier).  tree_expand_kernel, one workgroup per sequence, is for groups of sequences that share the
+// top-k's rows.
 struct TreeBatch {
     TreeDev td[TREE_BATCH_MAX];
     int t[TREE_BATCH_MAX];
@@ -384,63 +387,77 @@ struct TreeBatch {
     int32_t *slot_out[TREE_BATCH_MAX];
     TreeHost *host[TREE_BATCH_MAX];
 };
+constexpr int CHILDREN_MAX = TOPK_MAXK * TOPK_MAXK;       // = threads of the workgroups that expand
 
-__global__ __launch_bounds__(256) void tree_expand_kernel(TreeBatch tb, int d, int k, int L, int rows, int vocab) {
-    __shared__ __attribute__((aligned(16))) float sc[256];
-    const TreeDev &td = tb.td[blockIdx.x];
-    const int n_child = rows * k;
-    const int base = d == 1 ? 0 : k + (d - 2) * k * k;
-    const int tid = threadIdx.x;
-    sc[tid] = -INFINITY;                                  // (the ranking reads the scores four at a time)
-    uint64_t pw0 = 0ull, pw1 = 0ull;                      // the parent's ancestor mask, asked for with the rest
-    if (tid < n_child) {
-        const int r = tid / k;
-        const float ps = d == 1 ? 0.f : td.fr_score[(d - 1) * k + r];
-        if (d > 1 && d < L) { pw0 = td.fr_mask[((d - 1) * k + r) * MASK_WORDS]; pw1 = td.fr_mask[((d - 1) * k + r) * MASK_WORDS + 1]; }
-        // A score that is not a number (a drafter fed NaN) would compare false with everything: every child would rank
-        // first here and every candidate be kept by the final ranking, beyond the tree's arrays.  It counts as -inf
-        // (ties go by index), and an id that is no vocabulary entry as token 0.
-        float s = ps + td.topk_logp[tid];
-        if (!(s == s)) s = -INFINITY;
-        sc[tid] = s;
-        const int tok = embedding_row(td.topk_id[tid], vocab);
-        td.pool_token[base + tid] = tok;
-        td.pool_parent[base + tid] = d == 1 ? -1 : td.fr_pool[(d - 1) * k + r];
-        td.pool_depth[base + tid] = d;
-        td.pool_score[base + tid] = s;
-    }
+// Child c of depth d: what a candidate consists of, and the ancestor mask of its parent (asked for where a frontier follows).
+struct Child { float score; int token, parent, row; uint64_t w0, w1; };
+__device__ __forceinline__ int first_child(int d, int k) { return d == 1 ? 0 : k + (d - 2) * k * k; }     // in the pool
+__device__ __forceinline__ Child child_of(const TreeDev &td, int d, int k, int vocab, int c, bool frontier) {
+    Child ch;
+    ch.row = c / k;
+    const int o = (d - 1) * k + ch.row;
+    const float ps = d == 1 ? 0.f : td.fr_score[o];
+    ch.parent = d == 1 ? -1 : td.fr_pool[o];
+    ch.w0 = d > 1 && frontier ? td.fr_mask[o * MASK_WORDS] : 0ull;
+    ch.w1 = d > 1 && frontier ? td.fr_mask[o * MASK_WORDS + 1] : 0ull;
+    // A score that is not a number (a drafter fed NaN) would compare false with everything: every child would rank
+    // first here and every candidate be kept by the final ranking, beyond the tree's arrays.  It counts as -inf
+    // (ties go by index), and an id that is no vocabulary entry as token 0.
+    const float s = ps + td.topk_logp[c];
+    ch.score = s == s ? s : -INFINITY;
+    ch.token = embedding_row(td.topk_id[c], vocab);
+    return ch;
+}
+__device__ __forceinline__ void pool_write(const TreeDev &td, int i, int d, const Child &ch) {
+    td.pool_token[i] = ch.token; td.pool_parent[i] = ch.parent; td.pool_depth[i] = d; td.pool_score[i] = ch.score;
+}
+// The rank of child tid among all n_child, by a workgroup of CHILDREN_MAX threads; sc: as many floats of LDS.
+__device__ __forceinline__ int child_rank(float score, int tid, int n_child, float *sc) {
+    sc[tid] = tid < n_child ? score : -INFINITY;          // (read four at a time)
     __syncthreads();
-    if (d < L && tid < n_child) {
-        const float s = sc[tid];
-        int rank = 0;
+    int rank = 0;
+    if (tid < n_child) {
 #pragma unroll 4
         for (int j = 0; j < n_child; j += 4) {
             const float4 o = *reinterpret_cast<const float4 *>(&sc[j]);
-            rank += (o.x > s) || (o.x == s && j < tid);
-            rank += (o.y > s) || (o.y == s && j + 1 < tid);
-            rank += (o.z > s) || (o.z == s && j + 2 < tid);
-            rank += (o.w > s) || (o.w == s && j + 3 < tid);
-        }
-        if (rank < k) {
-            const int r = tid / k, o = d * k + rank;
-            td.fr_pool[o] = base + tid;
-            td.fr_token[o] = embedding_row(td.topk_id[tid], vocab);
-            td.fr_parent_rank[o] = r;
-            td.fr_score[o] = s;
-            const int bit = (d - 1) * k + rank;
-            uint64_t w0 = pw0, w1 = pw1;
-            if (bit < 64) w0 |= 1ull << bit; else w1 |= 1ull << (bit - 64);
-            td.fr_mask[o * MASK_WORDS] = w0;
-            td.fr_mask[o * MASK_WORDS + 1] = w1;
+            rank += (o.x > score) || (o.x == score && j < tid);
+            rank += (o.y > score) || (o.y == score && j + 1 < tid);
+            rank += (o.z > score) || (o.z == score && j + 2 < tid);
+            rank += (o.w > score) || (o.w == score && j + 3 < tid);
         }
     }
+    return rank;
+}
+__device__ __forceinline__ void frontier_bit(int d, int k, int rank, uint64_t &w0, uint64_t &w1) {
+    const int bit = (d - 1) * k + rank;
+    if (bit < 64) w0 |= 1ull << bit; else w1 |= 1ull << (bit - 64);
+}
+__device__ __forceinline__ void frontier_write(const TreeDev &td, int d, int k, int pool, int rank, Child ch) {
+    const int o = d * k + rank;
+    td.fr_pool[o] = pool; td.fr_token[o] = ch.token; td.fr_parent_rank[o] = ch.row; td.fr_score[o] = ch.score;
+    frontier_bit(d, k, rank, ch.w0, ch.w1);
+    td.fr_mask[o * MASK_WORDS] = ch.w0; td.fr_mask[o * MASK_WORDS + 1] = ch.w1;
+}
+
+__global__ __launch_bounds__(CHILDREN_MAX) void tree_expand_kernel(TreeBatch tb, int d, int k, int L, int rows, int vocab) {
+    __shared__ __attribute__((aligned(16))) float sc[CHILDREN_MAX];
+    const TreeDev &td = tb.td[blockIdx.x];
+    const int n_child = rows * k, tid = threadIdx.x;
+    Child ch{-INFINITY, 0, 0, 0, 0, 0};
+    if (tid < n_child) {
+        ch = child_of(td, d, k, vocab, tid, d < L);
+        pool_write(td, first_child(d, k) + tid, d, ch);
+    }
+    if (d == L) return;
+    const int rank = child_rank(ch.score, tid, n_child, sc);
+    if (tid < n_child && rank < k) frontier_write(td, d, k, first_child(d, k) + tid, rank, ch);
 }
 
 void launch_tree_expand(const TreeDev *tds, int n_seq, int d, int k, int L, int rows, int vocab, hipStream_t st) {
     if (n_seq < 1 || n_seq > TREE_BATCH_MAX) return;
     TreeBatch tb{};
     for (int i = 0; i < n_seq; ++i) tb.td[i] = tds[i];
-    hipLaunchKernelGGL(tree_expand_kernel, dim3(n_seq), dim3(256), 0, st, tb, d, k, L, rows, vocab);
+    hipLaunchKernelGGL(tree_expand_kernel, dim3(n_seq), dim3(CHILDREN_MAX), 0, st, tb, d, k, L, rows, vocab);
 }
 
 // ------------------------------------------------------------------ rerank + emit
@@ -448,7 +465,8 @@ void launch_tree_expand(const TreeDev *tds, int n_seq, int d, int k, int L, int 
 // the root x_t.  pos = t + depth; mask = node and its ancestors; slot = t + node index.
 constexpr int POOL_MAX = 2048;
 constexpr int POSS_TREE_MAX_DEPTH = 16;              // the deepest tree a context can be configured for
-__global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int pool_n, int n_keep) {
+// expand > 0: the children of that depth, the deepest, are not in the pool yet (k rows of them, the root's alone at depth 1).
+__global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int pool_n, int n_keep, int expand, int k, int vocab) {
     const TreeDev &td = tb.td[blockIdx.x];
     const int t = tb.t[blockIdx.x];
     const int32_t *__restrict__ tokens_dev = tb.tokens_dev[blockIdx.x];
@@ -464,7 +482,12 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int p
     for (int p = 0; p < 2; ++p) {
         const int i = tid + p * 1024;
         my_token[p] = 0; my_depth[p] = 0;
-        if (i < pool_n) {
+        if (expand && i >= first_child(expand, k) && i < pool_n) {
+            const Child ch = child_of(td, expand, k, vocab, i - first_child(expand, k), false);
+            pool_write(td, i, expand, ch);
+            sc[i] = ch.score; par[i] = (int16_t)ch.parent;
+            my_token[p] = ch.token; my_depth[p] = expand;
+        } else if (i < pool_n) {
             sc[i] = td.pool_score[i]; par[i] = (int16_t)td.pool_parent[i];
             my_token[p] = td.pool_token[i]; my_depth[p] = td.pool_depth[i];
         } else if (i < ((pool_n + 3) & ~3)) {
@@ -562,18 +585,21 @@ __global__ __launch_bounds__(1024) void tree_finalize_kernel(TreeBatch tb, int p
 }
 
 void launch_tree_finalize(const TreeDev *tds, int n_seq, int k, int L, int n_keep, const int *t,
-                          const int32_t *const *tokens_dev, int32_t *const *slot_out, TreeHost *const *host, hipStream_t st) {
+                          const int32_t *const *tokens_dev, int32_t *const *slot_out, TreeHost *const *host, int vocab, bool expand, hipStream_t st) {
     if (n_seq < 1 || n_seq > TREE_BATCH_MAX) return;
     const int pool_n = k + (L - 1) * k * k;
     TreeBatch tb{};
     for (int i = 0; i < n_seq; ++i) { tb.td[i] = tds[i]; tb.t[i] = t[i]; tb.tokens_dev[i] = tokens_dev[i]; tb.slot_out[i] = slot_out[i]; tb.host[i] = host[i]; }
-    hipLaunchKernelGGL(tree_finalize_kernel, dim3(n_seq), dim3(1024), 0, st, tb, pool_n, n_keep < pool_n ? n_keep : pool_n);
+    hipLaunchKernelGGL(tree_finalize_kernel, dim3(n_seq), dim3(1024), 0, st, tb, pool_n, n_keep < pool_n ? n_keep : pool_n, expand ? L : 0, k,
+                       vocab);
 }
 
 // ------------------------------------------------------------------ rows of one specialist pass
+// expand: the frontier of depth depth_index is still to be formed from the top-k of the pass before.  A workgroup whose row is a node
+// of it does so for itself; the first of them writes pool and frontier (nothing of depth depth_index is read in this launch).
 template <typename T>
-__global__ __launch_bounds__(256) void draft_assemble_kernel(
-    DraftRowPlan plan, int depth_index, int k, int d_model, int vocab, const T *__restrict__ embed,
+__global__ __launch_bounds__(CHILDREN_MAX) void draft_assemble_kernel(
+    DraftRowPlan plan, int depth_index, int expand, int k, int d_model, int vocab, const T *__restrict__ embed,
     const int32_t *__restrict__ tokens_dev, const T *__restrict__ feat_stash, TreeDev td,
     const float *__restrict__ fhat_prev, T *__restrict__ xin_tmp, T *__restrict__ x_out,
     int32_t *__restrict__ pos_out, int32_t *__restrict__ slot_out, uint64_t *__restrict__ mask_out,
@@ -606,8 +632,28 @@ __global__ __launch_bounds__(256) void draft_assemble_kernel(
         }
     } else {                            // new frontier row: [emb(token_v) ; drafted feature of parent(v)]
         const int o = depth_index * k + idx;
-        const T *e = embed + (size_t)embedding_row(td.fr_token[o], vocab) * d_model;
-        const float *f = fhat_prev + (size_t)td.fr_parent_rank[o] * d_model;
+        int token, parent_row;
+        if (expand) {                   // (workgroup-uniform)
+            __shared__ __attribute__((aligned(16))) float sc[CHILDREN_MAX];
+            __shared__ Child mine;
+            const int tid = threadIdx.x, n_child = depth_index == 1 ? k : k * k, pool = first_child(depth_index, k) + tid;
+            Child ch{-INFINITY, 0, 0, 0, 0, 0};
+            if (tid < n_child) ch = child_of(td, depth_index, k, vocab, tid, true);
+            const int rank = child_rank(ch.score, tid, n_child, sc);
+            if (tid < n_child && rank == idx) mine = ch;
+            if (idx == 0 && tid < n_child) {
+                pool_write(td, pool, depth_index, ch);
+                if (rank < k) frontier_write(td, depth_index, k, pool, rank, ch);
+            }
+            __syncthreads();
+            token = mine.token; parent_row = mine.row; w0 = mine.w0; w1 = mine.w1;
+            frontier_bit(depth_index, k, idx, w0, w1);
+        } else {
+            token = td.fr_token[o]; parent_row = td.fr_parent_rank[o];
+            w0 = td.fr_mask[o * MASK_WORDS]; w1 = td.fr_mask[o * MASK_WORDS + 1];
+        }
+        const T *e = embed + (size_t)embedding_row(token, vocab) * d_model;
+        const float *f = fhat_prev + (size_t)parent_row * d_model;
         T *keep = xin_tmp + (size_t)((depth_index - 1) * k + idx) * 2 * d_model;
         if (vec) {
             const uint4 *e4 = reinterpret_cast<const uint4 *>(e);
@@ -630,7 +676,6 @@ __global__ __launch_bounds__(256) void draft_assemble_kernel(
                 keep[i] = ev; keep[d_model + i] = fv;
             }
         }
-        w0 = td.fr_mask[o * MASK_WORDS]; w1 = td.fr_mask[o * MASK_WORDS + 1];
     }
     if (threadIdx.x == 0) {
         pos_out[row] = plan.pos[prow];
@@ -640,13 +685,13 @@ __global__ __launch_bounds__(256) void draft_assemble_kernel(
     }
 }
 
-void launch_draft_assemble(const ModelDims &md, const DraftRowPlan &plan, int depth_index, int k,
+void launch_draft_assemble(const ModelDims &md, const DraftRowPlan &plan, int depth_index, bool expand, int k,
                            const void *embed, const int32_t *tokens_dev, const void *feat_stash,
                            const TreeDev &td, const float *fhat_prev, void *xin_tmp, void *x_out,
                            int32_t *pos_out, int32_t *slot_out, uint64_t *mask_out, const double *inv_freq,
                            float2 *cs, hipStream_t st) {
 #define POSS_ASM(T)                                                                                          \
-    hipLaunchKernelGGL((draft_assemble_kernel<T>), dim3(plan.n_rows), dim3(256), 0, st, plan, depth_index, k,   \
+    hipLaunchKernelGGL((draft_assemble_kernel<T>), dim3(plan.n_rows), dim3(CHILDREN_MAX), 0, st, plan, depth_index, expand ? 1 : 0, k, \
                        md.d, md.vocab, static_cast<const T *>(embed), tokens_dev, static_cast<const T *>(feat_stash), td, \
                        fhat_prev, static_cast<T *>(xin_tmp), static_cast<T *>(x_out), pos_out, slot_out, mask_out, \
                        inv_freq, md.dh / 2, cs)
