@@ -241,3 +241,25 @@ def test_one_row_has_the_bits_of_a_tree_row(name, over):
             assert torch.equal(logits, got[0][0][:n]) and torch.equal(feats, got[0][1][:n]), (n_prompt, n)
         assert torch.isfinite(got[0][0]).all()
     pair.close()
+
+
+@pytest.mark.parametrize("vocab,rows,shift", [(1000, 17, 0), (1001, 5, 0), (131, 40, 0), (1000, 9, 1), (8192, 1, 0)])
+def test_logits_of_a_head_tile_in_the_callers_array(vocab, rows, shift):
+    """Verified rows' logits leave the Head's tiles in pieces of four: vocabularies that are and are not multiples of 4 and end inside a
+    tile, an array that is not aligned to 16 bytes.  The greedy choice is their argmax; nothing beyond the array's rows is written; the
+    values are the oracle's within the storage type's tolerance."""
+    pair = Pair("t_mid_bf16", vocab=vocab)
+    ctx, o = pair.ctx, pair.oracle()
+    prompt = make_prompt(pair.cfg, n=20)
+    ctx.prefill(prompt)
+    o.prefill(prompt)
+    o.tokens[-1] = ctx.tokens()[-1]
+    token, parent = [int(o.tokens[-1])] + list(range(1, rows)), [-1] + [0] * (rows - 1)
+    buf = torch.full((rows * vocab + 8,), -7.0, device="cuda")
+    logits = buf[shift:shift + rows * vocab].view(rows, vocab)
+    g = ctx.verify_tree(P.TreeArrays.from_lists(token, parent), logits_out=logits)[:rows]
+    assert g.tolist() == logits.argmax(1).tolist()
+    assert (buf[:shift] == -7.0).all() and (buf[shift + rows * vocab:] == -7.0).all()
+    _, want, _ = o.verify_tree(Tree(token, parent))
+    assert np.abs(logits.cpu().numpy() - want).max() < tol_for(pair.cfg)
+    pair.close()
