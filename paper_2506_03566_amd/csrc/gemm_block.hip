@@ -331,15 +331,18 @@ static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, 
 
 // K splits of a product whose sums a kernel of its own adds up (the residual + norm epilogue): with few tiles for the chip
 // 256 x 256 tiles over a part of K each are faster than small tiles over all of it, the planes included - in us, 109 for a round
-// of K = 4096 and 3.5 TB/s for the planes' way out and back, against the same per-K time of the tile chosen without splits.
-// Measured at 1001 rows: (request of 1001 tokens at the 13B shape, weights cold): products with
-// N = 5120, K = 13824 and 10240, 175 us on average over all of K, 125 us in three splits and 14 us more in the epilogue; the
-// request 6.45 -> 5.95 ms.
+// of K = 4096 and 3.5 TB/s for the planes' way out and back, against the same per-K time of the tile chosen without splits.  That
+// time is of weights just touched.  A model's come from memory, and the small tiles, whose k-steps are short, feel it: 1001 x 5120 x 5120
+// by 160 tiles of 256 x 128 72 us warm, 97 cold, 2048 x 4096 x 4096 71 / 80, 1001 x 4096 x 4096 by 128 x 128 42 / 49; 256 x 256 the same
+// either way.  Hence the factors, 0.9 where it is whole rounds of large tiles.
+// Measured at 1001 rows of the 13B shape: N = 5120, K = 13824 and 10240 175 us on average over all of K, 125 us in three splits and 14 us more in
+// the epilogue; K = 5120 104 + 7 for its norm, in three splits 61 + 25.  Prompt and catch-up through four layers, us, all at 0.9 / so: 8B 1700
+// tokens 4161 / 4047, 2048 tokens 4596 / 4436, 13B 1001 tokens 3828 / 3758, 8B 1001 2616 / 2594; others within 1 %.
 int gemm_block_splits(int M, int N, int K, size_t part_floats) {
     int cost;
-    (void)block_tile(M, N, &cost);
+    const int tile = block_tile(M, N, &cost);
     const double per_k = 1.09 * K / 4096.0, t0 = block_tiles(M, N, 256, 256);
-    double best = 0.9 * cost * per_k;
+    double best = (tile == 1 ? 1.25 : tile == 2 ? 1.15 : 0.9) * cost * per_k;
     int S = 1;
     for (int s = 2; s <= 8 && K / s >= 1024 && (size_t)s * M * N <= part_floats; ++s) {
         const double rounds = (double)(((long long)t0 * s + 255) / 256);
