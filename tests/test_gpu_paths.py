@@ -243,6 +243,25 @@ def test_one_row_has_the_bits_of_a_tree_row(name, over):
     pair.close()
 
 
+@pytest.mark.parametrize("name,n_prompt", [("t_mid_bf16", 257), ("t_mid_f16", 257), ("t_mid_bf16", 2)])
+def test_prompt_whose_last_launch_is_one_row(name, n_prompt):
+    """A streamed prompt's launches of 256 tokens can leave one row, whose norms are formed inside the products like a decoded row's: its keys,
+    values and features against the oracle, through the logits and features of the row behind it (the storage type's tolerance)."""
+    pair = Pair(name)
+    ctx, o = pair.ctx, pair.oracle()
+    prompt = make_prompt(pair.cfg, n=n_prompt)
+    ctx.prefill(prompt)
+    o.prefill(prompt)
+    o.tokens[-1] = ctx.tokens()[-1]
+    logits, feats = torch.zeros(1, pair.cfg.vocab, device="cuda"), torch.zeros(1, pair.cfg.d_model, device="cuda")
+    ctx.verify_tree(P.TreeArrays.from_lists([int(o.tokens[-1])], [-1]), logits_out=logits, feat_out=feats)
+    _, want, want_f = o.verify_tree(Tree([int(o.tokens[-1])], [-1]))
+    tol = tol_for(pair.cfg)
+    assert np.abs(logits.cpu().numpy() - want).max() < tol
+    assert np.abs(feats.cpu().numpy() - want_f).max() < tol * np.abs(want_f).max()
+    pair.close()
+
+
 @pytest.mark.parametrize("vocab,rows,shift", [(1000, 17, 0), (1001, 5, 0), (131, 40, 0), (1000, 9, 1), (8192, 1, 0)])
 def test_logits_of_a_head_tile_in_the_callers_array(vocab, rows, shift):
     """Verified rows' logits leave the Head's tiles in pieces of four: vocabularies that are and are not multiples of 4 and end inside a
