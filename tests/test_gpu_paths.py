@@ -12,7 +12,8 @@ if have_gpu():
     import paper_2506_03566_amd as P
     from oracle.sampling import softmax_t
     from oracle.tree import Tree
-    from synth import make_prompt
+    from synth import get_config, make_prompt
+    from synth.gpu import make_weights_on_device
 
 
 # a block and one id less and more; segments of 4096; 1025 blocks: two blocks per share of the scan
@@ -216,7 +217,7 @@ def test_projections_at_the_line_between_the_two_kernels(d_model, heads, rows):
     ("t_mid_bf16", dict(d_model=1024, n_q_heads=8, n_kv_heads=8, head_dim=128, d_ffn=1000)),  # two splits, units that end inside a tile
     ("t_mid_f16", dict(d_model=1536, n_q_heads=12, n_kv_heads=4, d_ffn=1544)),                # three: the norm stays a kernel
     ("t_mid_bf16", dict(d_model=2048, n_q_heads=16, n_kv_heads=2, head_dim=128)),             # four, a wave each
-    ("t_mid_f16", dict(d_model=4224, n_q_heads=4, n_kv_heads=1, d_ffn=4000)),                 # a second turn of the norm's groups
+    ("t_mid_f16", dict(d_model=4224, n_q_heads=4, n_kv_heads=1, d_ffn=4000)),                 # a second turn of the norm's groups, in gate/up alone (six)
 ])
 def test_one_row_has_the_bits_of_a_tree_row(name, over):
     """A pass of one row forms its norms and merges its attention splits inside the products; a row of a wider tree (17 rows and more:
@@ -224,10 +225,33 @@ def test_one_row_has_the_bits_of_a_tree_row(name, over):
     merge inside takes; 2 and 16 rows (merge inside, norms not) as well."""
     over = dict(over, n_layers=2, vocab=1000, max_seq=4096, n_specialists=1)
     pair = Pair(name, **over)
-    cfg, ctx = pair.cfg, pair.ctx
+    one_row_against_tree_rows(pair.cfg, pair.ctx, (20, 300, 600, 1300, 2500))
+    pair.close()
+
+
+# gemm_row_qkv_kernel<T, NP, NSL, NTW>: planes read at once, slots a wave forms, column tiles of a wave (2: four QKV splits, 1: fewer); its
+# planes are the down projection's.  gemm_row_silu_kernel<T, NP, NSL>: its planes are the output projection's.
+@pytest.mark.parametrize("name,over", [
+    ("t_mid_f16", dict(d_model=2048, n_q_heads=16, n_kv_heads=2, head_dim=128, d_ffn=1024)),    # qkv <2, 4, 2> (2 planes), silu <4, 2> (4)
+    ("t_mid_bf16", dict(d_ffn=4096)),                                                           # qkv <8, 4, 1> (8 planes), silu <2, 2> (1)
+    ("t_mid_bf16", dict(d_model=4096, n_q_heads=32, n_kv_heads=8, head_dim=128, d_ffn=4096)),   # qkv <8, 4, 2>, silu <8, 2> (8 planes each): the 8B shape
+    ("t_mid_f16", dict(d_model=5120, n_q_heads=40, n_kv_heads=40, head_dim=128, d_ffn=4096)),   # qkv <6, 5, 1> (6), silu <6, 3> (5): the 13B shape
+    ("t_mid_bf16", dict(d_model=5120, n_q_heads=40, n_kv_heads=8, head_dim=128, d_ffn=4096)),   # qkv <6, 5, 2>, the same with grouped heads
+    ("t_mid_f16", dict(d_model=5120, n_q_heads=40, n_kv_heads=40, head_dim=128, d_ffn=2048)),   # qkv <4, 5, 1> (4)
+    ("t_mid_bf16", dict(d_model=4616, n_q_heads=40, n_kv_heads=8, head_dim=128, d_ffn=2048)),   # qkv <4, 5, 2>; a second turn of 130 groups, K padded
+])
+def test_one_row_at_every_number_of_planes_and_turns(name, over):
+    """The same at plane counts, widths and QKV splits that lead to the other instantiations of the two kernels."""
+    cfg = get_config(name, **dict(over, n_layers=2, vocab=1000, max_seq=2048, n_specialists=1))
+    ctx = P.Poss(cfg, make_weights_on_device(cfg))
+    one_row_against_tree_rows(cfg, ctx, (20, 1300))
+    ctx.close()
+
+
+def one_row_against_tree_rows(cfg, ctx, prompts):
     rs = np.random.RandomState(5)
     wide = [0] + [int(x) for x in rs.permutation(1000)[:16]]
-    for n_prompt in (20, 300, 600, 1300, 2500):
+    for n_prompt in prompts:
         prompt, got = rs.randint(0, 1000, n_prompt).astype(np.int32), []
         for rows in (17, 1, 2, 16):
             ctx.reset()
@@ -240,7 +264,6 @@ def test_one_row_has_the_bits_of_a_tree_row(name, over):
             n = logits.shape[0]
             assert torch.equal(logits, got[0][0][:n]) and torch.equal(feats, got[0][1][:n]), (n_prompt, n)
         assert torch.isfinite(got[0][0]).all()
-    pair.close()
 
 
 @pytest.mark.parametrize("name,n_prompt", [("t_mid_bf16", 257), ("t_mid_f16", 257), ("t_mid_bf16", 2)])
