@@ -266,16 +266,25 @@ def one_row_against_tree_rows(cfg, ctx, prompts):
         assert torch.isfinite(got[0][0]).all()
 
 
-@pytest.mark.parametrize("name,n_prompt", [("t_mid_bf16", 257), ("t_mid_f16", 257), ("t_mid_bf16", 2)])
+@pytest.mark.parametrize("name,n_prompt", [("t_mid_bf16", 257), ("t_mid_f16", 257), ("t_mid_bf16", 1), ("t_mid_f16", 1)])
 def test_prompt_whose_last_launch_is_one_row(name, n_prompt):
-    """A streamed prompt's launches of 256 tokens can leave one row, whose norms are formed inside the products like a decoded row's: its keys,
-    values and features against the oracle, through the logits and features of the row behind it (the storage type's tolerance)."""
+    """A streamed prompt's launches of 256 tokens can leave one row (a prompt of one token is one), whose norms are formed inside the products
+    like a decoded row's.  Its keys and values in every layer are, bit for bit, those of a prompt of nine tokens more, where it shares a launch
+    and the norms are kernels; its greedy token is the oracle's where two tolerances part the two best logits; the row behind it, which
+    attends to it, has the oracle's logits and features (the storage type's tolerance)."""
     pair = Pair(name)
-    ctx, o = pair.ctx, pair.oracle()
-    prompt = make_prompt(pair.cfg, n=n_prompt)
-    ctx.prefill(prompt)
-    o.prefill(prompt)
-    o.tokens[-1] = ctx.tokens()[-1]
+    ctx, o, layers = pair.ctx, pair.oracle(), range(pair.cfg.n_layers)
+    longer = make_prompt(pair.cfg, n=n_prompt + 9)
+    prompt = longer[:n_prompt]
+    ctx.prefill(longer)
+    shared = [ctx.debug_read_kv(-1, layer, 0, n_prompt) for layer in layers]
+    ctx.reset()
+    first = ctx.prefill(prompt)
+    for layer, (k, v) in zip(layers, shared):
+        alone_k, alone_v = ctx.debug_read_kv(-1, layer, 0, n_prompt)
+        assert np.abs(k[-1]).max() > 0 and np.array_equal(alone_k, k) and np.array_equal(alone_v, v), layer
+    assert o.prefill(prompt) == first or o.margins[-1] <= 2 * tol_for(pair.cfg)
+    o.tokens[-1] = first
     logits, feats = torch.zeros(1, pair.cfg.vocab, device="cuda"), torch.zeros(1, pair.cfg.d_model, device="cuda")
     ctx.verify_tree(P.TreeArrays.from_lists([int(o.tokens[-1])], [-1]), logits_out=logits, feat_out=feats)
     _, want, want_f = o.verify_tree(Tree([int(o.tokens[-1])], [-1]))
