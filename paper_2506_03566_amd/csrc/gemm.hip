@@ -1125,6 +1125,7 @@ __global__ __launch_bounds__(ROW_QKV_WAVES * 64, 2) void gemm_row_qkv_kernel(con
     const u32x4 *wp = Wp + ((size_t)tile * ksteps_total + k0) * (GEMM_NT * 64) + nt0 * 64 + lane;
     u32x4 wr[PF][NTW];
     row_norm<T, NP, NSL, ROW_QKV_WAVES>(norm, reinterpret_cast<T *>(rlds), ksteps_total * GEMM_KSTEP, red, tid, blockIdx.x == 0, [&] {
+        if (!multiplies) return;
 #pragma unroll
         for (int p = 0; p < PF; ++p) row_fetch<NTW>(wp, p, n_w, wr[p]);
     });
