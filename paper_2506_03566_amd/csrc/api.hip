@@ -398,7 +398,7 @@ void run_gemm_row(poss_ctx *c, RowFlow &rf, const void *Wp, int N, const RowNorm
 // One decoder layer on rows_all rows (all produce K/V) of which the first rows_q go through
 // attention and the MLP; the full rows of every sequence come first, each sequence attends to its
 // own cache.  On entry c->u holds T(rmsnorm(h) * attn_norm) and c->cs the rotary table of the rows;
-// on exit c->h is updated and c->u holds T(rmsnorm(h) * next_gain).  In a row flow (rf.on) the residual stream is rf.h instead, and
+// on exit c->h is updated and c->u holds T(rmsnorm(h) * next_gain) (float32 storage: c->h alone, its products norm it).  In a row flow (rf.on) the residual stream is rf.h instead, and
 // what is pending on entry takes the place of c->u; with `more` (another layer follows) the same may be left on exit.
 void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int rows_all, int rows_q, const RowMeta &rm,
                const void *next_gain, float *h_copy, RowFlow &rf, bool more, bool drafter = false, float *h_user = nullptr, int h_user_rows = 0) {
@@ -472,7 +472,7 @@ void run_layer(poss_ctx *c, const LayerW &w, const std::vector<Seg> &segs, int r
 
 // Target pass over `rows` rows (all of them full rows; segs says which belong to which sequence)
 // whose tokens / metadata are on the device.  Leaves features in c->feats and
-// T(rmsnorm_final(features)) in c->u.
+// T(rmsnorm_final(features)) in c->u (float32 storage: c->h, which the Head norms).
 // feat_user (16-byte aligned): the features of the first feat_user_rows rows go there as well.
 void target_forward(poss_ctx *c, int rows, const int32_t *tokens_dev, const RowMeta &rm, std::vector<Seg> segs, float *feats_out,
                     float *feat_user = nullptr, int feat_user_rows = 0) {
@@ -516,7 +516,7 @@ GemmShape run_head(poss_ctx *c, int rows, int head_mode, float *user_logits, int
     return run_gemm(c, c->lm_head, c->md.vocab, c->md.d, x, c->md.d, rows, logits_dst ? logits_dst : c->logits, true, e);
 }
 
-// The drafter's k best next tokens and their log-probabilities for `rows` rows of final-normed activations in c->u.
+// The drafter's k best next tokens and their log-probabilities for the first `rows` rows of the pass (run_head).
 void run_head_topk(poss_ctx *c, int rows, int depth) {
     if (c->draft_sampling) {
         // drawn children: the logits of the pass's rows are kept (the walk needs the distribution each child came from),

@@ -163,7 +163,7 @@ void launch_residual_norm(int dt, const float *part, int S, int rows, int N, flo
 // ---------------------------------------------------------------- launchers: elementwise
 // u[m] = T(rmsnorm(h[m]) * gain) and, if stash != nullptr, stash[m] = T(h[m]); d a multiple of 4, at most 16384
 void launch_norm_rows(const ModelDims &md, const float *h, int rows, const void *gain, void *u, void *stash, hipStream_t st);
-// also writes the rotary table of the rows: cs[m][i] = (cos, sin)(pos[m] * theta^(-2i/dh)), angle formed in float64
+// h[m] = embedding, u[m] = T(rmsnorm(h[m]) * gain) (16-bit types); also writes the rotary table of the rows: cs[m][i] = (cos, sin)(pos[m] * theta^(-2i/dh)), angle formed in float64
 void launch_embed_norm(const ModelDims &md, const void *embed, const int32_t *tokens, int rows,
                        const void *gain, float *h, void *u, const int32_t *pos, const double *inv_freq,
                        float2 *cs, hipStream_t st);

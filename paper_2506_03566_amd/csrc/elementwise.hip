@@ -3,6 +3,8 @@
 #include "device_utils.h"
 #include "quotient.h"
 
+#include <type_traits>
+
 namespace poss {
 
 #define POSS_DISPATCH(dt, ...)                                               \
@@ -13,7 +15,7 @@ namespace poss {
     }
 
 // ------------------------------------------------------------------ h = emb[token]; u = T(rmsnorm(h) g)
-// (and the row's rotary table, which every layer of the pass uses)
+// (and the row's rotary table, which every layer of the pass uses; no u in float32 storage, whose products norm the rows they read)
 template <typename T>
 __global__ __launch_bounds__(256) void embed_norm_kernel(const T *__restrict__ embed, const int32_t *__restrict__ tokens,
                                                          int vocab, int d, float eps, const T *__restrict__ gain,
@@ -21,6 +23,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const T *__restrict__ e
                                                          const int32_t *__restrict__ pos,
                                                          const double *__restrict__ inv_freq, int half,
                                                          float2 *__restrict__ cs) {
+    constexpr bool NORM = !std::is_same<T, float>::value;
     __shared__ float red[17];
     const int row = blockIdx.x;
     // the rotary table by the last wave, so that the first ones start on the embedding row at once
@@ -38,7 +41,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const T *__restrict__ e
             const int p = threadIdx.x + j * 256;
             if (p < nv) {
                 ev[j].q = reinterpret_cast<const uint4 *>(e)[p];
-                gv[j].q = reinterpret_cast<const uint4 *>(gain)[p];
+                if constexpr (NORM) gv[j].q = reinterpret_cast<const uint4 *>(gain)[p];
             }
         }
         float ss = 0.f;                                    // fixed order: a thread's pieces one after the other, element by element
@@ -54,6 +57,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const T *__restrict__ e
                 }
             }
         }
+        if constexpr (!NORM) return;
         ss = block_sum(ss, red);
         const float rs = 1.0f / sqrtf(ss / (float)d + eps);
 #pragma unroll
@@ -74,6 +78,7 @@ __global__ __launch_bounds__(256) void embed_norm_kernel(const T *__restrict__ e
         h[(size_t)row * d + i] = v;
         ss += v * v;
     }
+    if constexpr (!NORM) return;
     ss = block_sum(ss, red);
     const float rs = 1.0f / sqrtf(ss / (float)d + eps);
     for (int i = threadIdx.x; i < d; i += blockDim.x)
