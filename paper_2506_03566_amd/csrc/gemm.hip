@@ -55,28 +55,9 @@ constexpr int KCS = GEMM_KCHUNK / GEMM_KSTEP;   // k-steps per LDS chunk (8)
 // with fewer workgroups than CUs, where each CU has to keep more bytes in flight to fill the memory system.
 
 // ------------------------------------------------------------------------------------------
-// Epilogue of one output tile (columns [tile*128, tile*128+128)) for rows [r_begin, r_end), run by
-// 256 threads.  Split-K planes are added in split order; loads are issued eight at a time.
-constexpr int EPI_ROWS_PLAIN = 16;  // rows per epilogue workgroup: plain sums sweep 8 rows at a time,
-constexpr int EPI_ROWS_PAIR = 4;    // rotary / SiLU epilogues give every 64-thread group one row
-
-__device__ __forceinline__ float sum_planes(const float *part, size_t plane, int S, size_t idx) {
-    float a = 0.f;
-    int s = 0;
-    for (; s + 8 <= S; s += 8) {
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = part[(size_t)(s + j) * plane + idx];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) a += v[j];
-    }
-    for (; s + 2 <= S; s += 2) {
-        const float v0 = part[(size_t)s * plane + idx], v1 = part[(size_t)(s + 1) * plane + idx];
-        a = (a + v0) + v1;
-    }
-    for (; s < S; ++s) a += part[(size_t)s * plane + idx];
-    return a;
-}
+// Epilogues of split products: the planes are added in split order, loads issued eight at a time.
+constexpr int EPI_ROWS_PLAIN = 16;  // rows per workgroup of the plain epilogue,
+constexpr int EPI_ROWS_PAIR = 4;    // of the rotary epilogue
 
 __device__ __forceinline__ f32x4 sum_planes4(const float *part, size_t plane, int S, size_t idx) {
     f32x4 a = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -95,33 +76,6 @@ __device__ __forceinline__ f32x4 sum_planes4(const float *part, size_t plane, in
     }
     for (; s < S; ++s) a += *reinterpret_cast<const f32x4 *>(part + (size_t)s * plane + idx);
     return a;
-}
-
-template <typename T, int EPI>
-__device__ __forceinline__ void tile_epilogue(const float *__restrict__ part, size_t plane, int S, int Npad,
-                                              int N, int r_begin, int r_end, int tile, const EpiArgs &e) {
-    const int t = threadIdx.x, n0 = tile * GEMM_BLOCK_N;
-    if constexpr (EPI == EPI_SILU) {
-        const int c = t & 63, f = tile * 64 + c, cg = n0 + (c >> 4) * 32 + (c & 15);   // gate column; up is 16 further
-        if (f >= e.F) return;
-        T *act = static_cast<T *>(e.act);
-        for (int r = r_begin + (t >> 6); r < r_end; r += 4) {
-            const float g = sum_planes(part, plane, S, (size_t)r * Npad + cg);
-            const float up = sum_planes(part, plane, S, (size_t)r * Npad + cg + 16);
-            act[(size_t)r * e.F + f] = mul_round<T>(g / (1.0f + expf(-g)), up);
-        }
-    } else {    // EPI_PLAIN: 32 threads x 4 columns per row, 8 rows per sweep
-        const int c4 = (t & 31) * 4, n = n0 + c4;
-        for (int rb = r_begin; rb < r_end; rb += 8) {
-            const int r = rb + (t >> 5);
-            if (r < r_end && n < N) {
-                const f32x4 v = sum_planes4(part, plane, S, (size_t)r * Npad + n);
-#pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (n + j < N) e.out[(size_t)r * e.ld_out + n + j] = v[j];
-            }
-        }
-    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1527,14 +1481,18 @@ static void launch_gemm_f32(const float *W, const float *X, int ldx, float *out,
 #undef POSS_F32
 }
 
-// The epilogue of every (128-column tile, 16-row block), one workgroup each: sums the split-K planes in split
-// order (bitwise repeatable) and applies the fused operation.
-template <typename T, int EPI>
-__global__ __launch_bounds__(256) void epilogue_kernel(const float *__restrict__ part, size_t plane, int S, int Npad,
-                                                       int N, int row0, int M, EpiArgs epi) {   // rows [row0, M)
-    constexpr int ROWS = EPI == EPI_PLAIN ? EPI_ROWS_PLAIN : EPI_ROWS_PAIR;
-    const int r0 = row0 + blockIdx.y * ROWS;
-    tile_epilogue<T, EPI>(part, plane, S, Npad, N, r0, min(M, r0 + ROWS), blockIdx.x, epi);
+// The plain epilogue of every (128-column tile, 16-row block), one workgroup each: sums the split-K planes in split
+// order (bitwise repeatable).  32 threads x 4 columns per row, 8 rows per sweep.
+__global__ __launch_bounds__(256) void epilogue_kernel(const float *__restrict__ part, size_t plane, int S, int Npad, int N, int M,
+                                                       float *out, int ld_out) {
+    const int t = threadIdx.x, n = blockIdx.x * GEMM_BLOCK_N + (t & 31) * 4, r0 = blockIdx.y * EPI_ROWS_PLAIN, r1 = min(M, r0 + EPI_ROWS_PLAIN);
+    if (n >= N) return;
+    for (int r = r0 + (t >> 5); r < r1; r += 8) {
+        const f32x4 v = sum_planes4(part, plane, S, (size_t)r * Npad + n);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (n + j < N) out[(size_t)r * ld_out + n + j] = v[j];
+    }
 }
 
 // The RoPE + KV-write epilogue over several row ranges in one launch, each range into its own cache
@@ -1638,12 +1596,8 @@ static bool gemm_wide(const GemmShape &g) {
 int gemm_head_segments(const GemmShape &g) { return g.Npad / (GEMM_BLOCK_N * (gemm_wide(g) ? 2 : 1)); }
 
 template <typename T>
-static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiArgs &epi, float eps, bool silu_done,
-                              hipStream_t st) {
+static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiArgs &epi, float eps, hipStream_t st) {
     const size_t plane = (size_t)g.Mpad * g.Npad;
-    const int tiles = g.Npad / GEMM_BLOCK_N;
-    dim3 pair_grid(tiles, (g.M + EPI_ROWS_PAIR - 1) / EPI_ROWS_PAIR), plain_grid(tiles, (g.M + EPI_ROWS_PLAIN - 1) / EPI_ROWS_PLAIN);
-    dim3 eb(256);
     switch (epi.mode) {
         case EPI_RESIDUAL:
             if constexpr (!std::is_same<T, float>::value) {             // (float32: inside gemm_f32_kernel)
@@ -1654,14 +1608,11 @@ static void launch_epilogue_t(const GemmShape &g, const float *part, const EpiAr
             break;
         case EPI_HEAD: break;           // reduced inside the stream kernel
         case EPI_PLANES: break;
-        case EPI_SILU:
-            if constexpr (!std::is_same<T, float>::value)               // (float32: inside gemm_f32_kernel)
-                if (!silu_done)         // otherwise applied inside the stream kernel
-                    hipLaunchKernelGGL((epilogue_kernel<T, EPI_SILU>), pair_grid, eb, 0, st, part, plane, g.S, g.Npad, g.N, 0, g.M, epi);
-            break;
+        case EPI_SILU: break;           // applied inside the stream kernel
         default:
             if (g.S > 1 || epi.out)     // S == 1 without an output buffer: plane 0 is the result
-                hipLaunchKernelGGL((epilogue_kernel<T, EPI_PLAIN>), plain_grid, eb, 0, st, part, plane, g.S, g.Npad, g.N, 0, g.M, epi);
+                hipLaunchKernelGGL(epilogue_kernel, dim3(g.Npad / GEMM_BLOCK_N, (g.M + EPI_ROWS_PLAIN - 1) / EPI_ROWS_PLAIN), dim3(256), 0, st, part,
+                                   plane, g.S, g.Npad, g.N, g.M, epi.out, epi.ld_out);
             break;
     }
 }
@@ -1724,7 +1675,7 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
         launch_qkv_rope_t<T>(g, Wp, X, ldx, epi, *rr, st, ev_start, ev_stop);
         return;
     }
-    const bool fuse_silu = epi.mode == EPI_SILU && g.S == 1;
+    const bool fuse_silu = epi.mode == EPI_SILU;
     const bool head = epi.mode == EPI_HEAD;
     if (g.Mpad > 128) {                                  // the tall kernel: one 128-column tile of 192 or 256 rows
         HeadEpi he{};
@@ -1758,7 +1709,7 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
                                g.Npad, *rr, epi);
             return;
         }
-        launch_epilogue_t<T>(g, part, epi, eps, fuse_silu, st);
+        launch_epilogue_t<T>(g, part, epi, eps, st);
         return;
     }
     // Two tiles per workgroup when the column count alone gives every CU work and K is not split.
@@ -1808,7 +1759,7 @@ static void launch_gemm_t(const GemmShape &g, const void *Wp, const void *X, int
                            g.Npad, *rr, epi);
         return;
     }
-    launch_epilogue_t<T>(g, part, epi, eps, fuse_silu, st);
+    launch_epilogue_t<T>(g, part, epi, eps, st);
 }
 
 // Refuse, on the host, argument sets that would make a kernel write through a null pointer.
@@ -1825,7 +1776,7 @@ static bool gemm_args_ok(int dt, const GemmShape &g, const void *Wp, const void 
             return e.q && e.cs && e.slot && (dt == DT_F32 ? e.dh >= 32 && e.dh % 32 == 0 : e.dh == 64 || e.dh == 128);
         case EPI_RESIDUAL: return e.h && (!e.gain || e.u);
         case EPI_PLANES: return dt != DT_F32;
-        case EPI_SILU: return e.act != nullptr;
+        case EPI_SILU: return e.act && g.S == 1;           // applied to whole sums
         case EPI_HEAD:
             if (g.S != 1 || g.N < 1) return false;
             if (e.head_mode == HEAD_ARGMAX) return e.pv && e.pi;
@@ -1886,7 +1837,7 @@ bool launch_gemm(int dt, const GemmShape &g, const void *Wp, const void *X, int 
         const int ld = direct ? epi.ld_out : g.Npad;
         if (epi.x_gain) launch_gemm_f32<EPI_PLAIN, true>(w, x, ldx, dst, ld, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
         else launch_gemm_f32<EPI_PLAIN, false>(w, x, ldx, dst, ld, g.M, g.N, g.K, fe, st, ev_start, ev_stop);
-        if (!direct) launch_epilogue_t<float>(g, part, epi, eps, false, st);
+        if (!direct) launch_epilogue_t<float>(g, part, epi, eps, st);
     } else if (dt == DT_BF16) {
         launch_gemm_t<bf16_t>(g, Wp, X, ldx, part, epi, eps, st, ev_start, ev_stop, epi.mode == EPI_ROPE_KV ? &rr : nullptr);
     } else {
@@ -1925,8 +1876,8 @@ bool launch_gemm_merged(int dt, const GemmShape &g, const void *Wp, const AttnMe
         else POSS_MERGED(T, 12, 1);                                                                                          \
     } while (0)
     const bool one = g.M * longest_split(g) <= 4 * 256;   // a quad per thread
-    if (dt == DT_BF16) { POSS_MERGED_T(bf16_t); launch_epilogue_t<bf16_t>(g, part, epi, eps, false, st); }
-    else { POSS_MERGED_T(f16_t); launch_epilogue_t<f16_t>(g, part, epi, eps, false, st); }
+    if (dt == DT_BF16) { POSS_MERGED_T(bf16_t); launch_epilogue_t<bf16_t>(g, part, epi, eps, st); }
+    else { POSS_MERGED_T(f16_t); launch_epilogue_t<f16_t>(g, part, epi, eps, st); }
 #undef POSS_MERGED_T
 #undef POSS_MERGED
     return true;
