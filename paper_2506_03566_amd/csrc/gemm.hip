@@ -1304,8 +1304,14 @@ __global__ __launch_bounds__(1024) void epilogue_residual_norm_kernel(const floa
 constexpr int F32_WAVES = 4, F32_PF = 4, F32_KSTEP = 16;
 // The residual addition (EPI_RESIDUAL, no norm behind it) is applied to the whole sums as well, and a norm belongs to the product that
 // reads the normed rows (NORM): x gain is formed where an operand is used, the sum of squares beside it, by the waves that hold
-// the row's k anyway, and the sums are scaled by 1 / rms at the end.  The same request: 675 -> 600 us, 134 -> 102 launches.  Error against 64
-// bits over 48 requests, the ratio to norms in kernels of their own: logits 1.005 +- 0.004, features 0.998 +- 0.004.
+// the row's k anyway, and the sums are scaled by 1 / rms at the end.  The same request: 134 -> 96 launches, 675 -> 621 and 668 -> 606 us in
+// two comparisons (runs of one side differ by 12 and 18 %).  Error against 64 bits over 160 requests, the ratio to norms and
+// additions in kernels of their own: logits 0.998 +- 0.002, features 0.999 +- 0.002.
+// Every column tile sums the squares again, which wide layers with few rows notice and wide layers with many do not.  Two layers, us, norms in
+// kernels of their own / so: drafting six levels, 4 rows 256 wide 325 / 295, 512 389 / 364, 1024 491 / 482, 2048 848 / 865, 4096 1901 / 1940;
+// verifying 61 rows 256 130 / 123, 1024 227 / 232, 2048 542 / 536, 4096 1282 / 1260; a prompt of 256 tokens 256 218 / 199, 1024 590 / 582, 2048
+// 1536 / 1483, 4096 5411 / 5144, of 1000 tokens 4096 25136 / 24077.  So at every width: a line would have to lie at a number of
+// rows, and a row's bits must not hang on how many rows share a pass.
 struct F32Epi {
     float *act; int F; QkvEpi qkv;
     float *h, *h_copy, *h_user; int h_user_rows, residual; const float *bias;

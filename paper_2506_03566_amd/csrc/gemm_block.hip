@@ -332,12 +332,14 @@ static void launch_block_e(BlockGeom g, const void *Wp, const void *X, int ldx, 
 // K splits of a product whose sums a kernel of its own adds up (the residual + norm epilogue): with few tiles for the chip
 // 256 x 256 tiles over a part of K each are faster than small tiles over all of it, the planes included - in us, 109 for a round
 // of K = 4096 and 3.5 TB/s for the planes' way out and back, against the same per-K time of the tile chosen without splits.  That
-// time is of weights just touched.  A model's come from memory, and the small tiles, whose k-steps are short, feel it: 1001 x 5120 x 5120
-// by 160 tiles of 256 x 128 72 us warm, 97 cold, 2048 x 4096 x 4096 71 / 80, 1001 x 4096 x 4096 by 128 x 128 42 / 49; 256 x 256 the same
-// either way.  Hence the factors, 0.9 where it is whole rounds of large tiles.
-// Measured at 1001 rows of the 13B shape: N = 5120, K = 13824 and 10240 175 us on average over all of K, 125 us in three splits and 14 us more in
-// the epilogue; K = 5120 104 + 7 for its norm, in three splits 61 + 25.  Prompt and catch-up through four layers, us, all at 0.9 / so: 8B 1700
-// tokens 4161 / 4047, 2048 tokens 4596 / 4436, 13B 1001 tokens 3828 / 3758, 8B 1001 2616 / 2594; others within 1 %.
+// time is of weights just touched.  A model's come from memory, and the small tiles, whose k-steps are short, feel it.  A product alone, us,
+// repeated on one matrix / on matrices that no cache holds: 1001 x 5120 x 5120 by 160 tiles of 256 x 128 72 / 97, 2048 x 4096 x 4096 71 / 80,
+// 1001 x 4096 x 4096 by 128 x 128 42 / 49; 256 x 256 the same either way.  Hence the factors, 0.9 where it is whole rounds of large tiles.
+// In the trace of a request of 1001 tokens at the 13B shape: N = 5120, K = 5120 103 us and 7 for its norm, in three splits 61 + 25; K = 13824 and 10240
+// 114 on average in three splits + 25 and 22 (over all of K 175, with an earlier build).  Prompt and catch-up through four layers, us, all at
+// 0.9 / so: 8B 1500 tokens 3880 / 3539, 1700 4021 / 3859, 2048 4464 / 4256, 13B 1001 3696 / 3581, 1280 5129 / 4759, 1536 5421 / 5130; of 47 lengths
+// from 513 to 2100 tokens none is slower by more than its runs differ (2 % at most, 3 at 900 of the 8B shape).  Error against 64 bits over 56
+// requests whose splits are others, the ratio: logits 0.9998 +- 0.0004, features 0.9999 +- 0.0003.
 int gemm_block_splits(int M, int N, int K, size_t part_floats) {
     int cost;
     const int tile = block_tile(M, N, &cost);
