@@ -23,15 +23,20 @@ PAPER_TAU = {"c1_llama3_8b_3x2": 4.55, "c2_llama3_8b_6x1": 4.54, "c3_llama2_13b_
 # HBM bytes per gemm_stream_kernel launch (average over the launches of a round) from rocprofv3 TCC
 # counters, scaled by the reading of a plain 1 GiB copy (FETCH_SIZE x2.000, WRITE_SIZE x1.000);
 # commands and raw sums: profiles/gemm_stream_kernel_c1_hbm_traffic.md.  The figures belong to one state of
-# the kernel's source: they are quoted only while csrc/gemm.hip still hashes to the value recorded with them.
+# the sources that decide what the counted launches read and which launches there are - the products, the attention splits that
+# some of them merge, the choice among them: they are quoted only while these still hash to the value recorded with them.
+TRAFFIC_SOURCES = ("gemm.hip", "attn_merge.h", "attn_split.h", "attention.hip", "api.hip", "common.h", "device_utils.h")
 MEASURED_TRAFFIC = {"c1_llama3_8b_3x2": dict(fetch_bytes=153.1e6, write_bytes=5.08e6,
-                                             gemm_hip_sha256="102ee59ed216d8657a0d15077777879f78c1fd90d4e9211543c55a3f4011c1ed")}
+                                             sources_sha256="92c2d862511fb1b8fa699347a4177b6b0865b79657bda854d8686993c5abf5ab")}
 
 
-def gemm_source_hash():
+def traffic_source_hash(csrc=os.path.join(ROOT, "paper_2506_03566_amd", "csrc")):
     import hashlib
-    with open(os.path.join(ROOT, "paper_2506_03566_amd", "csrc", "gemm.hip"), "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()
+    h = hashlib.sha256()
+    for name in TRAFFIC_SOURCES:
+        with open(os.path.join(csrc, name), "rb") as f:
+            h.update(name.encode() + b"\0" + hashlib.sha256(f.read()).digest())
+    return h.hexdigest()
 
 
 def measured_traffic(cfg_name):
@@ -39,8 +44,8 @@ def measured_traffic(cfg_name):
     m = MEASURED_TRAFFIC.get(cfg_name)
     if not m:
         return None, "no counter run recorded for this workload"
-    if m["gemm_hip_sha256"] != gemm_source_hash():
-        return None, "counter run predates the current csrc/gemm.hip (recorded for %s...)" % m["gemm_hip_sha256"][:12]
+    if m["sources_sha256"] != traffic_source_hash():
+        return None, "counter run predates the current sources of the counted launches (recorded for %s...)" % m["sources_sha256"][:12]
     return m["fetch_bytes"] + m["write_bytes"], None
 
 

@@ -87,3 +87,21 @@ def test_float32_head_sizes():
     for dh in range(0, 300):
         need = lib.poss_workspace_bytes(ctypes.byref(P.make_config(base.with_(head_dim=dh))))
         assert (need > 0) == (dh > 0 and dh % 32 == 0 and dh <= 256), dh
+
+
+def test_quoted_traffic_belongs_to_every_source_that_decides_it(tmp_path):
+    """bench.py quotes counted HBM bytes only for the sources they were counted with: a change to any file that decides which products a
+    round launches and what they read (among them the merge and the splits that gemm.hip only includes or is told of) has to end it."""
+    import shutil
+    import bench
+    csrc = os.path.join(ROOT, "paper_2506_03566_amd", "csrc")
+    for f in os.listdir(csrc):
+        shutil.copy(os.path.join(csrc, f), tmp_path / f)
+    now = bench.traffic_source_hash()
+    assert bench.traffic_source_hash(str(tmp_path)) == now
+    for f in ("gemm.hip", "attn_merge.h", "attn_split.h", "attention.hip", "api.hip", "common.h"):
+        text = (tmp_path / f).read_bytes()
+        (tmp_path / f).write_bytes(text + b"\n")
+        assert bench.traffic_source_hash(str(tmp_path)) != now, f
+        (tmp_path / f).write_bytes(text)
+    assert bench.traffic_source_hash(str(tmp_path)) == now
